@@ -14,57 +14,77 @@
 //           hp [block][f/32] for the second GEMM
 //   down  : per (token tile of 256 rows, 256 output features): yg = h.w2, fp32
 //
-// GEMM kernel (measured figures behind it: one 256 x 256 x 32 step = 1024 matrix-core
-// clocks per SIMD; four waves read ~140 B/clk from LDS and pull ~60 B/clk of L2-resident
-// data per CU, more with more waves; the operand stream of this tile is 31 B/clk at the
-// full matrix rate, 29 % of which misses L2):
-//   * workgroup tile 256 tokens x 16 weight fragment rows, 4 waves, one per
-//     SIMD; wave w owns fragment rows 4w..4w+3 for ALL 16 token blocks:
-//     64 MFMA tiles = 256 accumulator registers (pinned to the accumulation
-//     register file through the inline-asm constraint).
-//   * weights (A) never touch LDS: each wave streams its own 4 fragments per
-//     step straight from global memory into a 4-deep register ring (the
-//     packed layout makes these 1 KiB coalesced loads with no redundancy
-//     between waves).
-//   * token fragments (B) are shared by the 4 waves through an 8-stage LDS ring
-//     filled by direct-to-LDS loads (no staging registers, no LDS stores);
-//     every wave reads the 16 B fragments of the next step while it issues the
-//     64 MFMAs of the current one (single register set, refilled in place right
-//     after its last use).  LDS traffic per step: 64 KiB reads + 16 KiB writes.
-//   * the vector-memory requests (4 direct-to-LDS + 4 weight loads per wave
-//     and step) and the 16 LDS reads are spread between the MFMAs, one barrier
-//     per step publishes the next stage.
-//   * the workgroup is persistent (one per CU) and the load stream runs across
-//     tile boundaries: while the last steps of a tile are multiplied, the first
-//     stages of the next tile are already being requested.
-//   * tiles are walked in an order that keeps a weight tile on one XCD (one L2):
-//     expert, then feature tile, then token tile, one contiguous eighth of that
-//     order per XCD.
+// GEMM kernel (one 256 x 256 x 32 step = 1024 matrix-core clocks per SIMD).  What bounds it at
+// prefill size is the board's power: at 4096 tokens the matrix cores are busy 80 % of the
+// clocks, at 1.55-1.65 GHz; with all-zero tokens the same launch is 1.23 times as fast, and
+// halving the L2 misses or taking out 15 % of the clocks alone changed nothing.  In a loop of
+// matrix instructions alone 16x16x32 sustains 2080 TFLOP/s on random operands, 32x32x16 1830,
+// which decides the instruction.  Below ~200 rows per expert the weight stream bounds it (5.5-6.4
+// TB/s).
+//   * workgroup tile: up to 256 token rows x 16 weight fragment rows, 4 waves, one per
+//     SIMD; wave w owns fragment rows 4w..4w+3 for all token rows: 64 MFMA tiles = 256
+//     accumulator registers (pinned to the accumulation register file through the inline-asm
+//     constraint).
+//   * token rows come in units of 64 (4 blocks of 16).  An expert's units are dealt evenly to
+//     its tiles, and the step loop exists once per number of units (1..4): a tile that is not
+//     full costs only the matrix instructions, LDS reads and token requests of its own units.
+//     Skewed routing leaves every expert's last tile partly filled: with whole tiles of 256
+//     rows 34 % of the matrix work of 3062 rows (8 experts) was padding, with units 7 %.
+//   * weights (A) never touch LDS: each wave streams its own fragments straight from global
+//     memory into a register ring, LA steps ahead (the packed layout makes these 1 KiB
+//     coalesced loads with no redundancy between waves).
+//   * token fragments (B) are shared by the 4 waves through a ring of NS LDS stages filled by
+//     direct-to-LDS loads (no staging registers, no LDS stores); every wave reads the fragments
+//     of the next step while it issues the matrix instructions of the current one (one register
+//     set, refilled in place right after its last use).
+//   * the requests of a step are spread between the matrix instructions, one barrier per two
+//     steps publishes the next stages.  They are buffer loads: an address is a descriptor, the
+//     lane offset and one scalar, where 64-bit pointers per request filled the scalar registers
+//     and put ~100 instructions between the matrix instructions of a step, 60 now.
+//   * the workgroup is persistent (one per CU) and the two load streams run across tile
+//     boundaries: while the last steps of a tile are multiplied, the first stages of the next
+//     one are already being requested.  The last groups of U steps of a tile are their own
+//     copies of the loop body, in which it is a compile-time matter which requests belong to
+//     the next tile.  The stores of a tile's result stay in flight during the next tile's first
+//     steps (loads and stores share one counter, and the first step's operands are older than
+//     the stores); waiting for them cost 3 us of every tile.
+//   * tiles are dealt in rounds of one tile per workgroup, an XCD taking 32 neighbours of the
+//     order expert, group of at most 8 token tiles, feature tile, token tile: about 8 x 4
+//     tiles, which share 12 operand tiles in one L2.  All XCDs work through the same experts at
+//     the same time, so an expert's size does not unbalance them.
+// Measured (start of the kernel with whole 256-row tiles, one tile order per XCD, 64-bit
+// pointers -> this): layer of 4096 tokens, 8 experts, Zipf 2.43 -> 2.30 ms; 1531 tokens 1.145 ->
+// 1.035; 4096 tokens, 16 experts 1.41 -> 1.28; 77 tokens 0.502 -> 0.476; 64 experts of f = 1408,
+// 300 tokens, k = 6 0.276 -> 0.248; 512 tokens, balanced, 0.612 -> 0.613.
 #include <atomic>
 
 #include "moe_internal.h"
 #include "moe_frag_pack.h"
 
-// Tile shapes (token blocks of 16 rows x weight fragment rows of 16 features per workgroup;
-// a wave owns all token blocks x FRW = fragment rows / 4; at most 64 MFMA tiles per wave):
-//   16 x 16 (256 tokens x 256 features): the default;
-//   12 x 16 (192 tokens x 256 features): 97..256 rows per expert on average, where a quarter
-//           of the default tile's matrix work would be padding (measured 2-4 % faster);
-//    8 x 32 (128 tokens x 512 features): experts with up to ~128 rows, where the default
-//           tile is half empty -- twice the weight bytes per step, no padded matrix work.
+// Tile shapes (token rows x weight fragment rows of 16 features per workgroup), by the mean
+// number of rows per expert:
+//   256 x 16 (256 tokens x 256 features): the default;
+//   192 x 16 (192 tokens x 256 features): 97..256 rows;
+//   128 x 32 (128 tokens x 512 features): up to 96 rows -- twice the weight bytes per step,
+//           which is what bounds such experts.
 #define GG_THREADS 256
 #ifndef GG_NS
 #define GG_NS 8            // LDS stages of B fragments (one KiB per token block each)
 #endif
 // The weight fragments of step k are requested GG_LA steps earlier into a register ring that
 // is named statically, so the step loop is unrolled GG_U times (GG_LA < GG_U, reduction %
-// GG_U == 0; GG_LA <= GG_NS - 3, see the waits in the step).  Deeper rings (8 / 5 with 8
-// stages, 8 / 7 with 10 stages on the 192-row tile) measured no faster.
+// GG_U == 0; GG_LA <= GG_NS - 3, see the waits in the step).  The depth itself matters little
+// (2, 3, 4 and 5 steps are within 1 % at every size: what a CU may have in flight is full long
+// before); the 128 x 512 tile, which requests twice as much per step, keeps 2 steps, because a
+// third spills.
 #ifndef GG_U
 #define GG_U 4
 #endif
 #ifndef GG_LA
 #define GG_LA 3
+#endif
+#ifndef GG_WIDE_LA
+#define GG_WIDE_LA 2
 #endif
 #ifndef GG_WIDE_MAX_ROWS
 #define GG_WIDE_MAX_ROWS 96  // mean rows per expert up to which the 128 x 512 tile is used
@@ -72,6 +92,8 @@
 #ifndef GG_R192_MAX_ROWS
 #define GG_R192_MAX_ROWS 256  // ... and up to which the 192 x 256 tile is used
 #endif
+#define GG_GROUP 8         // token tiles that are neighbours of one weight tile, see the tile order
+#define GG_UNIT_BLOCKS 4   // 16-row token blocks per unit
 
 // ------------------------------------------------------------------- GEMM ----
 struct GroupedArgs {
@@ -82,13 +104,13 @@ struct GroupedArgs {
     int E, N;
     int KS;      // reduction steps of 32
     int FR;      // weight fragment rows per expert (up: 2*f/16, down: d/16)
-    int TB;      // token blocks (of 16 rows) per tile: 16 or 8
+    int MU;      // units of 64 token rows per tile, at most
     int FROWS;   // weight fragment rows per tile: 16 or 32
     int NT;      // workgroup tiles along the features = FR / FROWS
     int KS_out;  // up: f/32 (fragment columns of hp); down: unused
     int C;       // down: d (row length of yg)
     int split;   // deal the left-over tiles of each XCD in pieces of their reduction
-    float* part; // split: partial tiles [8 XCDs][workgroups per XCD][2][16*TB][16*FROWS] fp32
+    float* part; // split: partial tiles [8 XCDs][workgroups per XCD][2][256*256] fp32
 };
 
 // s_waitcnt with only one counter constrained (gfx9 encoding: vmcnt = bits 3:0 and
@@ -98,17 +120,17 @@ struct GroupedArgs {
 
 struct TileInfo {
     SegInfo si;
-    int tis;   // token tile inside the segment
-    int nt;    // feature tile
-    int blk0;  // first block of the tile inside the segment
-    int nblk;  // blocks of the tile that exist (1..TB)
+    int nt;     // feature tile
+    int blk0;   // first block of the tile inside the segment
+    int nblk;   // blocks of the tile that exist
+    int units;  // units of 4 blocks (the last one may hold fewer blocks)
     // the part of the tile's reduction this unit of work covers (whole tile: 0, KS)
     int k_lo, klen;
     bool partial;
     int piece;  // 0 or 1: which of this workgroup's two partial-tile slots it writes
 };
 
-// Logical tiles of a launch: NT * sum_e ceil(M_e / (16 * TB)), in the order expert, then
+// Logical tiles of a launch: NT * sum_e ceil(units_e / MU), in the order expert, then
 // feature tile, then token tile (fastest), so that neighbouring indices share a weight tile.
 // The experts' segments are decoded once per workgroup into a table in LDS
 // (entry e: expert e; entries >= E hold no tiles).  A tile index is then decoded with LDS
@@ -123,26 +145,17 @@ struct TileInfo {
 #define GG_SEG_FIELDS 6
 
 // One wave fills the table (lane e: expert e); returns the number of logical tiles.
+// read_once: are the weights of (nearly) every expert read by a single token tile?  Then they
+// are streamed.  The rule: token tiles beyond the first of an expert make up at most 15 % of
+// all token tiles (measured crossover: 11 % wins 8 %, 20 % loses 4 %, 50 % loses 13 %).
 __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets, int E, int N,
-                                            int NT, int TB, int lane, int (*tab)[64], bool write) {
-    // offsets that do not ascend or leave [0, N] are clamped, as in the pack kernel:
-    // lo_e = clamp(offsets[e], lo_{e-1}, N) = min(N, running max of offsets[0..e], at least 0);
-    // hi_e = clamp(offsets[e+1], lo_e, N)
-    const int o0 = (lane < E) ? offsets[lane] : 0, o1 = (lane < E) ? offsets[lane + 1] : 0;
-    int run = o0 < 0 ? 0 : o0;
-#pragma unroll
-    for (int dlt = 1; dlt < 64; dlt <<= 1) {
-        const int v = __shfl_up(run, dlt, 64);
-        if (lane >= dlt) run = run > v ? run : v;
-    }
-    int lo = run > N ? N : run;
-    int hi = o1 < lo ? lo : (o1 > N ? N : o1);
-    if (lane >= E) {
-        lo = 0;
-        hi = 0;
-    }
-    const int rows = hi - lo, nb = (rows + 15) / 16, tiles = (nb + TB - 1) / TB;
-    int inc_t = tiles * NT, inc_b = nb;
+                                            int NT, int MU, int lane, int (*tab)[64], bool write,
+                                            bool& read_once) {
+    int lo, rows;
+    gg_segment_of_lane(offsets, E, N, lane, lo, rows);
+    const int nb = (rows + 15) / 16;
+    const int tiles = (nb + GG_UNIT_BLOCKS * MU - 1) / (GG_UNIT_BLOCKS * MU);
+    int inc_t = tiles, inc_b = nb;
 #pragma unroll
     for (int dlt = 1; dlt < 64; dlt <<= 1) {
         const int vt = __shfl_up(inc_t, dlt, 64), vb = __shfl_up(inc_b, dlt, 64);
@@ -156,14 +169,17 @@ __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets,
         tab[GG_SEG_ROWS][lane] = rows;
         tab[GG_SEG_NB][lane] = nb;
         tab[GG_SEG_TILES][lane] = tiles;
-        tab[GG_SEG_BASE][lane] = inc_t - tiles * NT;
+        tab[GG_SEG_BASE][lane] = (inc_t - tiles) * NT;
         tab[GG_SEG_BB][lane] = inc_b - nb;
     }
-    return __builtin_amdgcn_readlane(inc_t, 63);
+    const int total = __builtin_amdgcn_readlane(inc_t, 63);
+    const int active = __popcll(__ballot(rows > 0));
+    read_once = (total - active) * 100 <= 15 * total;
+    return total * NT;
 }
 
 // Logical tile index -> tile, from the table.
-__device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lane, int NT, int TB,
+__device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lane, int NT,
                                                    int L, TileInfo& ti) {
     const int my_tiles = tab[GG_SEG_TILES][lane], my_base = tab[GG_SEG_BASE][lane];
     const unsigned long long m = __ballot(my_tiles > 0 && L >= my_base && L < my_base + my_tiles * NT);
@@ -172,19 +188,54 @@ __device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lan
     const int tiles = __builtin_amdgcn_readfirstlane(tab[GG_SEG_TILES][e]);
     const int nb = __builtin_amdgcn_readfirstlane(tab[GG_SEG_NB][e]);
     const int r = L - __builtin_amdgcn_readfirstlane(tab[GG_SEG_BASE][e]);
-    ti.nt = r / tiles;
-    ti.tis = r % tiles;
+    // token tiles in groups of at most GG_GROUP, the feature tile next, the token tile fastest
+    const int ng = (tiles + GG_GROUP - 1) / GG_GROUP;
+    const int gq = tiles / ng, gmore = tiles % ng;  // the first gmore groups hold one tile more
+    const int big = gmore * (gq + 1) * NT;
+    const int gw = r < big ? gq + 1 : gq;           // width of the tile's group
+    const int rr = r < big ? r : r - big;
+    const int gi = rr / (gw * NT);                  // group among those of its width
+    const int ro = rr - gi * (gw * NT);
+    ti.nt = ro / gw;
+    const int tis = (r < big ? 0 : gmore * (gq + 1)) + gi * gw + ro % gw;  // token tile inside the segment
     ti.si.e = e;
     ti.si.row0 = __builtin_amdgcn_readfirstlane(tab[GG_SEG_LO][e]);
     ti.si.rows = __builtin_amdgcn_readfirstlane(tab[GG_SEG_ROWS][e]);
     ti.si.bbase = __builtin_amdgcn_readfirstlane(tab[GG_SEG_BB][e]);
-    ti.blk0 = ti.tis * TB;
-    ti.nblk = (nb - ti.blk0) < TB ? (nb - ti.blk0) : TB;
+    // the expert's units, dealt evenly to its tiles
+    const int nu = (nb + GG_UNIT_BLOCKS - 1) / GG_UNIT_BLOCKS;
+    const int per = nu / tiles, more = nu % tiles;  // the first `more` tiles take one more
+    ti.units = per + (tis < more ? 1 : 0);
+    ti.blk0 = GG_UNIT_BLOCKS * (tis * per + (tis < more ? tis : more));
+    ti.nblk = (nb - ti.blk0) < GG_UNIT_BLOCKS * ti.units ? (nb - ti.blk0) : GG_UNIT_BLOCKS * ti.units;
     ti.k_lo = 0;
     ti.klen = 0;  // filled in by the caller
     ti.partial = false;
     ti.piece = 0;
     return true;
+}
+
+// Whole tiles go out in n_full rounds of one tile per workgroup; the tiles of the last,
+// incomplete round are dealt to the XCDs evenly and split there (see the body below).
+struct GgSched {
+    int n_full;   // rounds of whole tiles
+    int left_lo;  // this XCD's left-over tiles: [left_lo, left_lo + R)
+    int R;
+};
+__device__ __forceinline__ GgSched gg_sched(int total, int wgs, int xcd) {
+    GgSched sc;
+    const int W = wgs * 8;
+    sc.n_full = total / W;
+    const int left = total - sc.n_full * W;
+    const int lo = left * xcd / 8, hi = left * (xcd + 1) / 8;
+    sc.left_lo = sc.n_full * W + lo;
+    sc.R = hi - lo;
+    return sc;
+}
+// Workgroup me of an XCD takes a different one of the round's 32 neighbours every round: the
+// token tiles of an expert differ in length, and their period must not pick workgroups.
+__device__ __forceinline__ int gg_round_slot(int n, int wgs, int xcd, int me) {
+    return n * wgs * 8 + xcd * wgs + (int)((unsigned)(me + n) % (unsigned)wgs);
 }
 
 // Cut points of the left-over tiles' joint reduction (S = R tiles x KS steps) for the
@@ -205,13 +256,11 @@ __device__ __forceinline__ int gg_piece_cut(int j, int S, int KS, int wgs, int u
 
 // Weight fragment load.  ANT: non-temporal - when nearly every expert has a single token
 // tile its weights are read once and should not push the token fragments (re-read by every
-// feature tile) out of L2.  Measured, 8 layers of the Mixtral shape, balanced routing:
-// 128 x 512 tile T=256 5.16 -> 4.65 ms, T=384 5.44 -> 4.88; 192 x 256 tile T=512 5.44 -> 5.22
-// but T=1024 8.10 -> 9.17 (experts with two tiles then re-read their weights from HBM
-// instead of L2), hence the rule in gg_weights_read_once.
+// feature tile) out of L2.
 template <bool ANT>
-__device__ __forceinline__ u32x4_t gg_ld_a(const u32x4_t* p) {
-    return ANT ? __builtin_nontemporal_load(p) : *p;
+__device__ __forceinline__ u32x4_t gg_ld_a(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+    // (cache policy 2: nt)
+    return __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, ANT ? 2 : 0));
 }
 
 // The lane number, recomputed where it is used and invisible to the optimiser (which would
@@ -226,76 +275,99 @@ __device__ __forceinline__ int gg_lane_opaque() {
 // MFMA with the accumulator pinned to the accumulation registers: 256 of them
 // are live per wave, and left to itself the register allocator shuffles them
 // through the vector registers inside the loop.
-__device__ __forceinline__ void gg_mfma(f32x4_t& c, const u32x4_t& a, const bf16x8_t& b) {
+__device__ __forceinline__ void gg_mfma(f32x4_t& c, const u32x4_t& a, const u32x4_t& b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
-
-// Global source pointers of one tile for this wave (all wave-uniform).
-template <int FRW, int NBQ>
-struct TileSrc {
-    const u32x4_t* a[FRW];  // this wave's weight fragment rows (start of the reduction)
-    const u32x4_t* b[NBQ];  // the token blocks this wave requests into LDS
-};
-
-template <int FRW, int NBQ>
-__device__ __forceinline__ void gg_tile_src(const GroupedArgs& a, const TileInfo& ti, int wave,
-                                            TileSrc<FRW, NBQ>& ts) {
-#pragma unroll
-    for (int j = 0; j < FRW; j++)
-        ts.a[j] = a.wfrag +
-                  (((size_t)ti.si.e * a.FR + (size_t)ti.nt * (4 * FRW) + FRW * wave + j) * a.KS + ti.k_lo) * 64;
-#pragma unroll
-    for (int i = 0; i < NBQ; i++) {
-        int blk = NBQ * wave + i;
-        blk = blk < ti.nblk ? blk : ti.nblk - 1;  // clamp: every wave always issues NBQ requests
-        ts.b[i] = a.bfrag + (((size_t)(ti.si.bbase + ti.blk0 + blk)) * a.KS + ti.k_lo) * 64;
-    }
+// ... with a zero accumulator going in (the first step of a tile)
+__device__ __forceinline__ void gg_mfma_first(f32x4_t& c, const u32x4_t& a, const u32x4_t& b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
 }
 
-// MODE: which units of work a launch covers: 0 = whole tiles and pieces (second projection:
-// one epilogue serves both), 1 = whole tiles only, 2 = pieces only (the first projection
-// takes two launches, because an epilogue with both the SiLU*mul body and the raw store of
-// partial sums makes the compiler spill ~150 accumulators per tile).
-// NBW x FRW: token blocks of the tile x fragment rows of a wave (16 x 4 or 8 x 8).
+// Buffer descriptor over the 2 GiB of addresses from p on (p is wave-uniform, which the compiler does not
+// know: without the readfirstlanes it would loop over the lanes at every use).  Operand
+// requests then take one scalar add for their address: descriptor + lane offset + scalar
+// offset + immediate.  An offset of GG_RSRC_BYTES is out of its range (and 16 bytes further does
+// not wrap): a store there is dropped.  Offsets inside a tile stay below 1.1 GiB: 32 fragment
+// rows, or 16 token blocks, of at most 32768 fragments; 256 rows of at most 2^20 floats.
+#define GG_RSRC_BYTES 0x80000000u
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t gg_rsrc(const char* p) {
+    const unsigned long long v = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)v);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+    return __builtin_amdgcn_make_buffer_rsrc((void*)(((unsigned long long)hi << 32) | lo), 0, (int)GG_RSRC_BYTES,
+                                             0x00027000);
+}
+
+template <int V>
+struct GgInt {
+    static constexpr int value = V;
+};
+
+// First projection: h = silu(x.w1) * (x.w3) of two neighbouring 16-column blocks (a0, b0: the
+// w1 and w3 tiles of the even block; a1, b1: of the odd one), rounded to bf16, as B fragments of
+// the second GEMM.  Lane l of a tile holds token l % 16 and columns 4*(l/16) .. +3; after
+// exchanging the odd 16-lane rows of the even block with the even rows of the odd block every
+// lane holds eight columns, and the wave writes the token block's whole 1 KiB fragment.
+// (sigmoid by v_rcp_f32, 1 ulp: h is rounded to 8 bits of mantissa next.)
+__device__ __forceinline__ u32x4_t gg_make_h(const f32x4_t& a0, const f32x4_t& b0, const f32x4_t& a1,
+                                             const f32x4_t& b1) {
+    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    unsigned pk[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        f2 hv;
+#pragma unroll
+        for (int r = 0; r < 2; r++) {
+            const float av = (q < 2 ? a0 : a1)[2 * (q & 1) + r], bv = (q < 2 ? b0 : b1)[2 * (q & 1) + r];
+            hv[r] = av * __builtin_amdgcn_rcpf(1.0f + __expf(-av)) * bv;
+        }
+        pk[q] = __builtin_bit_cast(unsigned, __builtin_convertvector(hv, bf2));
+    }
+    const auto s0 = __builtin_amdgcn_permlane16_swap(pk[0], pk[2], false, false);
+    const auto s1 = __builtin_amdgcn_permlane16_swap(pk[1], pk[3], false, false);
+    return u32x4_t{s0[0], s1[0], s0[1], s1[1]};
+}
+// Byte offset of gg_make_h's value for this lane inside the fragment: lanes 16..31 and 48..63
+// hold the odd column block, lanes 32..63 its columns 8..15.
+__device__ __forceinline__ unsigned gg_h_off(int lane) {
+    return (unsigned)(((((lane >> 4) & 1) * 2 + (lane >> 5)) * 16 + (lane & 15)) * 16);
+}
+
+// MODE: which units of work a launch covers: 0 = whole tiles and pieces, 1 = whole tiles only,
+// 2 = pieces only.
+// NBW x FRW: token blocks of the tile, at most, x fragment rows of a wave.
 template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS, bool ANT>
-__device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a) {
-    static_assert(NBW * FRW <= 64 && NBW % 4 == 0, "at most 64 MFMA tiles (256 accumulators) per wave");
+__device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, const int (*s_seg)[64]) {
+    static_assert(NBW * FRW <= 64 && NBW % 4 == 0 && FRW % 4 == 0, "at most 64 MFMA tiles (256 accumulators) per wave");
     static_assert(LA < U && LA <= NS - 3, "ring and stage depths, see the waits in the step");
     constexpr int FROWS = 4 * FRW;     // fragment rows of the workgroup tile
-    constexpr int NBQ = NBW / 4;       // token blocks each wave requests into LDS per step
-    constexpr int VREQ = FRW + NBQ;    // vector-memory requests per wave and step
+    constexpr int NBQ = NBW / 4;       // token blocks each wave requests into LDS per step (= units)
+    constexpr int TG = (NS - 1 + U - 1) / U;  // groups at the end of a tile that look into the next
     extern __shared__ __align__(16) unsigned char smem[];
     u32x4_t* lds = (u32x4_t*)smem;  // [NS stages][NBW fragments][64 lanes]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // fragment rows [FRW*wave, +FRW)
-    const unsigned voff = (unsigned)lane * 16u;                  // byte offset inside a fragment
 
-    // This workgroup's units of work.  The logical tiles of XCD x are x*per_xcd ... ; the
-    // 32 workgroups of an XCD take them round-robin (slot = id/8, id/8 + wgs, ...).  When
-    // the tile count is not a multiple of the workgroup count the last round would leave
-    // most CUs idle (576 second-projection tiles over 256 CUs = 2.25 rounds), so the
-    // left-over tiles are cut along the reduction instead, in equal pieces for all
-    // workgroups; every piece stores its partial sums into scratch and gg_fixup_kernel adds
-    // the pieces of a tile in a fixed order (then applies SiLU*mul, first projection).
-    __shared__ int s_seg[GG_SEG_FIELDS][64];
-    const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW, lane, s_seg, wave == 0);
-    __syncthreads();
-    const int per_xcd = (total + 7) / 8;
+    // This workgroup's units of work: whole tiles in rounds, then pieces.  When the tile count
+    // is not a multiple of the workgroup count the last round would leave most CUs idle (576
+    // second-projection tiles over 256 CUs = 2.25 rounds), so the left-over tiles are cut along
+    // the reduction instead, in equal pieces for all workgroups; every piece stores its partial
+    // sums into scratch and gg_fixup_kernel adds the pieces of a tile in a fixed order (then
+    // applies SiLU*mul, first projection).
     const int xcd = blockIdx.x & 7;
     const int wgs = gridDim.x >> 3;
     const int me = blockIdx.x >> 3;
-    int chunk = total - xcd * per_xcd;
-    chunk = chunk < 0 ? 0 : (chunk > per_xcd ? per_xcd : chunk);  // tiles of this XCD
-    const bool split = a.split && (chunk % wgs) != 0;
-    const int n_full = split ? chunk / wgs : (chunk - me + wgs - 1) / wgs;  // whole tiles I own
-    // pieces of the left-over tiles (slots n_full*wgs ... chunk-1) for this workgroup
+    const GgSched sc = gg_sched(total, wgs, xcd);
+    const bool split = a.split != 0;
+    const int n_full = sc.n_full + ((!split && gg_round_slot(sc.n_full, wgs, xcd, me) < total) ? 1 : 0);
+    // pieces of the left-over tiles for this workgroup
     // (plain scalars, no arrays: an array indexed at run time would live in scratch memory, and
     // every read of it would wait on the counter of the operand loads in flight)
     int pc_tile0 = 0, pc_lo0 = 0, pc_len0 = 0, pc_tile1 = 0, pc_len1 = 0, n_pieces = 0;
-    if (split) {
-        const int R = chunk - n_full * wgs;
-        const int S = R * a.KS;
+    if (split && sc.R > 0) {
+        const int S = sc.R * a.KS;
         const int c0 = gg_piece_cut(me, S, a.KS, wgs, U, NS), c1 = gg_piece_cut(me + 1, S, a.KS, wgs, U, NS);
         if (c0 < c1) {
             const int rA = c0 / a.KS;
@@ -319,21 +391,21 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a) {
     const int n_units = (MODE == 1) ? n_full : n_full + n_pieces;
     auto unit_at = [&](int n, TileInfo& ti) -> bool {
         if (n >= n_units) return false;
-        int sl, lo = 0, len = a.KS;
+        int L, lo = 0, len = a.KS;
         if (n < n_full) {
-            sl = me + n * wgs;
+            L = gg_round_slot(n, wgs, xcd, me);
         } else {
             // first or second piece, selected by arithmetic (a two-way choice on n is turned
             // into a table in scratch memory by the compiler)
             const int first = (n == n_full) ? 1 : 0;
-            sl = n_full * wgs + pc_tile1 + first * (pc_tile0 - pc_tile1);
+            L = sc.left_lo + pc_tile1 + first * (pc_tile0 - pc_tile1);
             lo = first * pc_lo0;
             len = pc_len1 + first * (pc_len0 - pc_len1);
         }
         // (the lane number is recomputed here, opaquely, so that no address derived from it
         // has to stay in a register through the main loop; see the epilogue)
         const int lane_d = gg_lane_opaque();
-        if (!gg_decode_tile_tab(s_seg, lane_d, a.NT, NBW, xcd * per_xcd + sl, ti)) return false;
+        if (!gg_decode_tile_tab(s_seg, lane_d, a.NT, L, ti)) return false;
         ti.k_lo = lo;
         ti.klen = len;
         ti.partial = (n >= n_full);  // pieces always go through scratch and the fix-up
@@ -341,197 +413,225 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a) {
         return true;
     };
 
+    // Operand addresses: the tile's base, a scalar offset that walks along the reduction (1 KiB
+    // per step) and the lane's 16 bytes of the fragment.  A: row j of this wave.  B: block 4v + wave
+    // of the tile is request v of this wave; blocks past the tile's last one repeat it (every wave always has its requests, their products are never stored).  (Offsets
+    // inside a tile: at most 32 rows of f/32 <= 32768 fragments, 1 GiB.)
+    const unsigned row_bytes = (unsigned)a.KS * 1024u;  // one fragment row / token block
+    const unsigned voff = (unsigned)lane * 16u;
+    auto a_base = [&](const TileInfo& ti) -> const char* {
+        return (const char*)a.wfrag +
+               (((size_t)ti.si.e * a.FR + (size_t)ti.nt * FROWS + FRW * wave) * a.KS + ti.k_lo) * 1024;
+    };
+    auto b_base = [&](const TileInfo& ti) -> const char* {
+        return (const char*)a.bfrag + ((size_t)(ti.si.bbase + ti.blk0) * a.KS + ti.k_lo) * 1024;
+    };
+    auto b_off = [&](const TileInfo& ti, unsigned (&vo)[NBQ]) {
+#pragma unroll
+        for (int v = 0; v < NBQ; v++) {
+            const int blk = 4 * v + wave;
+            vo[v] = __builtin_amdgcn_readfirstlane((unsigned)(blk < ti.nblk ? blk : ti.nblk - 1) * row_bytes);
+        }
+    };
+    // request v of this wave for stage number `gstage`, `soff` bytes along the reduction
+    auto issue_b = [&](__amdgpu_buffer_rsrc_t r, unsigned soff, unsigned gstage, int v) {
+        unsigned char* dst = smem + ((gstage % NS) * (NBW * 1024) + wave * 1024);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            r, (__attribute__((address_space(3))) void*)(dst + v * 4096), 16, voff, soff, 0, 0);
+    };
+
     int unit = (MODE == 2) ? n_full : 0;
     TileInfo cur, nxt;
     if (!unit_at(unit, cur)) return;
+    nxt = cur;
     bool has_next = unit_at(unit + 1, nxt);
-    TileSrc<FRW, NBQ> scur, snxt;
-    gg_tile_src(a, cur, wave, scur);
-    if (has_next) gg_tile_src(a, nxt, wave, snxt); else snxt = scur;
-    int KT = cur.klen;  // steps of the current unit: a multiple of U, >= NS
+    if (!has_next) nxt = cur;  // behind the last unit: its own first steps again, never used
+    const char *pa = a_base(cur), *pb = b_base(cur);
+    const char *pa_n = a_base(nxt), *pb_n = b_base(nxt);
+    unsigned vo_b[NBQ], vo_bn[NBQ];
+    b_off(cur, vo_b);
+    b_off(nxt, vo_bn);
 
-    // look-ahead sources: reduction step j of the current tile, or j-KT of the next one
-    auto b_src = [&](int i, int j) -> const char* {
-        const u32x4_t* p = (j < KT) ? scur.b[i] + (size_t)j * 64 : snxt.b[i] + (size_t)(j - KT) * 64;
-        return (const char*)p + voff;
-    };
-    auto a_src = [&](int jr, int j) -> const u32x4_t* {
-        const u32x4_t* p = (j < KT) ? scur.a[jr] + (size_t)j * 64 : snxt.a[jr] + (size_t)(j - KT) * 64;
-        return (const u32x4_t*)((const char*)p + voff);
-    };
-    // g = running step count of this workgroup (never reset): LDS stage g % NS
-    auto issue_b = [&](int i, int j, unsigned gstage) {
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void*)b_src(i, j),
-            (__attribute__((address_space(3))) void*)(lds + ((gstage % NS) * NBW + NBQ * wave + i) * 64),
-            16, 0, 0);
-    };
+    u32x4_t areg[U][FRW];  // [ring slot][fragment row]
 
-    f32x4_t acc[NBW][FRW];
-    u32x4_t areg[U][FRW];
-    bf16x8_t breg[NBW];
-
-    // ---- prologue of the first tile: request stages 0..NS-2 and A of steps 0..PA-2 ----
-    for (int j = 0; j < NS - 1; j++)
+    // ---- prologue of the first tile: request stages 0..NS-2 and A of steps 0..LA-1 ----
+    {
+        const __amdgpu_buffer_rsrc_t ra = gg_rsrc(pa), rb = gg_rsrc(pb);
+        for (int j = 0; j < NS - 1; j++)
 #pragma unroll
-        for (int i = 0; i < NBQ; i++) issue_b(i, j, j);
+            for (int v = 0; v < NBQ; v++) issue_b(rb, vo_b[v] + j * 1024, j, v);
 #pragma unroll
-    for (int s = 0; s < LA; s++)
+        for (int s = 0; s < LA; s++)
 #pragma unroll
-        for (int j = 0; j < FRW; j++) areg[s][j] = gg_ld_a<ANT>(a_src(j, s));
+            for (int j = 0; j < FRW; j++) areg[s][j] = gg_ld_a<ANT>(ra, voff, s * 1024 + j * row_bytes);
+    }
     GG_WAIT_VMCNT(0);
     __builtin_amdgcn_s_barrier();
-#pragma unroll
-    for (int i = 0; i < NBW; i++) breg[i] = __builtin_bit_cast(bf16x8_t, lds[i * 64 + lane]);
-    GG_WAIT_LGKM(0);
 
-    unsigned g = 0;  // running step count (unsigned: g % NS is a mask for the 8-stage ring)
-    for (;;) {
-#pragma unroll
-        for (int i = 0; i < NBW; i++)
-#pragma unroll
-            for (int j = 0; j < FRW; j++) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        // the compiler cannot see the MFMAs below: cover the register write -> matrix read hazard
-        asm volatile("s_nop 7" ::: "memory");
+    unsigned g = 0;  // running step count of this workgroup: LDS stage g % NS
 
-        // One reduction step.  Ac: weight fragments of this step; An: ring slot that
-        // receives the fragments of step k+LA.  fast: every look-ahead lies inside
-        // the current tile, so there is nothing to decide (compile-time after inlining).
-        auto step = [&](int k, u32x4_t(&Ac)[FRW], u32x4_t(&An)[FRW], const bool fast) {
-            // The look-ahead requests carry no condition: behind the workgroup's last unit they
-            // re-read the first steps of that unit (snxt == scur then), into stages and
-            // registers that nothing reads any more.  With conditions the compiler cannot
-            // count the loads in flight and waits for all of them before the weights' use.
-            constexpr bool la_b = true, la_a = true, more = true;
-            // The weights of step k were requested LA steps ago, after that step's requests
-            // for stage k+NS-1-LA; requests retire in order, so with at most the last
-            // LA-1 steps' worth still in flight they have arrived, and so have the stages
-            // requested before them (LA <= NS-3: up to stage k+2).
-            GG_WAIT_VMCNT((LA - 1) * VREQ);
-            // One barrier per TWO steps: at an even step every wave has waited for its
-            // shares of stages k+1 and k+2 (see above), so both are published here; and the
-            // buffers refilled during steps k and k+1 (stages k-1 and k) were last read
-            // before this barrier.
-            if (more && (k & 1) == 0) __builtin_amdgcn_s_barrier();
-            const u32x4_t* pb = lds + ((g + 1) % NS) * NBW * 64 + lane;
-            // request number v of this step: 0..NBQ-1 = this wave's blocks of stage k+NS-1
-            // (straight into LDS), NBQ.. = its FRW weight fragments of step k+LA
-            auto issue = [&](const int v) {
-                    if (v < NBQ) {
-                        if (fast) {
-                            __builtin_amdgcn_global_load_lds(
-                                (const __attribute__((address_space(1))) void*)(
-                                    (const char*)(scur.b[v] + (size_t)(k + NS - 1) * 64) + voff),
-                                (__attribute__((address_space(3))) void*)(
-                                    lds + (((g + NS - 1) % NS) * NBW + NBQ * wave + v) * 64),
-                                16, 0, 0);
-                        } else if (la_b) {
-                            issue_b(v, k + NS - 1, g + NS - 1);
-                        }
+    int stores = 0;  // store instructions of the previous tile's epilogue (at least)
+
+    // one tile of B token blocks (B = 4 * units)
+    auto tile = [&](auto blocks) {
+        constexpr int B = decltype(blocks)::value;
+        constexpr int VMIN = FRW + B / 4;  // requests of a step, at least
+        f32x4_t acc[B][FRW];
+        u32x4_t breg[B];
+        g = __builtin_amdgcn_readfirstlane(g);
+        const __amdgpu_buffer_rsrc_t ra = gg_rsrc(pa), rb = gg_rsrc(pb), ra_n = gg_rsrc(pa_n), rb_n = gg_rsrc(pb_n);
+        unsigned kb = 0;  // bytes along the reduction: 1024 * step of the group's first step
+        const int klen = __builtin_amdgcn_readfirstlane(cur.klen);
+        {
+            const u32x4_t* pl = lds + (g % NS) * NBW * 64 + lane;
+#pragma unroll
+            for (int i = 0; i < B; i++) breg[i] = pl[i * 64];
+        }
+        GG_WAIT_LGKM(0);
+
+        // U steps.  Q: how many groups are left in the tile, this one included, or 0: more than
+        // TG.  A request for step u + look-ahead of the group lies in the next tile when that is
+        // beyond the Q groups.  FIRST: the tile's first group.
+        auto group = [&](auto left, auto first) {
+            constexpr int Q = decltype(left)::value;
+            constexpr bool FIRST = decltype(first)::value != 0;
+            constexpr int NB = Q ? NBQ : B / 4;  // token requests per step (the next tile may need all)
+            constexpr int VREQ = FRW + NB;
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                // The weights of step k were requested LA steps ago, after that step's requests
+                // for stage k+NS-1-LA; requests retire in order, so with at most the last
+                // LA-1 steps' worth still in flight they have arrived, and so have the stages
+                // requested before them (LA <= NS-3: up to stage k+2).  (Steps issue VMIN
+                // requests or more.)  In a tile's first LA steps the previous tile's stores lie
+                // between those requests and the younger ones and may stay in flight as well.
+                __builtin_amdgcn_sched_barrier(0);
+                if (FIRST && u < LA) {
+                    constexpr int V0 = (LA - 1) * VMIN;
+                    if (stores >= 32) GG_WAIT_VMCNT(V0 + 32 < 63 ? V0 + 32 : 63);
+                    else if (stores >= 16) GG_WAIT_VMCNT(V0 + 16);
+                    else if (stores >= 8) GG_WAIT_VMCNT(V0 + 8);
+                    else GG_WAIT_VMCNT(V0);
+                } else {
+                    GG_WAIT_VMCNT((LA - 1) * VMIN);
+                }
+                // One barrier per TWO steps: at an even step every wave has waited for its
+                // shares of stages k+1 and k+2 (see above), so both are published here; and the
+                // buffers refilled during steps k and k+1 (stages k-1 and k) were last read
+                // before this barrier.
+                if ((u & 1) == 0) __builtin_amdgcn_s_barrier();
+                const u32x4_t* pl = lds + ((g + u + 1) % NS) * NBW * 64 + lane;
+                auto issue = [&](const int v) {
+                    if (v < NB) {
+                        const int jb = u + NS - 1;  // step of the group
+                        if (Q == 0 || jb < Q * U)
+                            issue_b(rb, vo_b[v] + kb + jb * 1024, g + jb, v);
+                        else
+                            issue_b(rb_n, vo_bn[v] + (jb - Q * U) * 1024, g + jb, v);
                     } else {
-                        if (fast)
-                            An[v - NBQ] = gg_ld_a<ANT>((const u32x4_t*)((const char*)(scur.a[v - NBQ] +
-                                                            (size_t)(k + LA) * 64) + voff));
-                        else if (la_a)
-                            An[v - NBQ] = gg_ld_a<ANT>(a_src(v - NBQ, k + LA));
+                        const int ja = u + LA, j = v - NB;
+                        if (Q == 0 || ja < Q * U)
+                            areg[ja % U][j] = gg_ld_a<ANT>(ra, voff, kb + ja * 1024 + j * row_bytes);
+                        else
+                            areg[ja % U][j] = gg_ld_a<ANT>(ra_n, voff, (ja - Q * U) * 1024 + j * row_bytes);
                     }
-            };
+                };
 #pragma unroll
-            for (int i = 0; i < NBW; i++) {
-                // the vector-memory requests are spread evenly over the blocks (one per
-                // 8 MFMAs for 16 x 4), so that the requests of the four waves never
-                // queue up in front of the matrix instructions
+                for (int i = 0; i < B; i++) {
+                    // the vector-memory requests are spread evenly over the blocks, so that the
+                    // requests of the four waves never queue up in front of the matrix
+                    // instructions
 #pragma unroll
-                for (int v = (i * VREQ + NBW - 1) / NBW; v < ((i + 1) * VREQ + NBW - 1) / NBW; v++)
-                    issue(v);
-                // LDS reads return in order: with at most NBW-2 younger ones in flight,
-                // breg[i] and breg[i+1] (refilled one step ago) have arrived
-                if ((i & 1) == 0) GG_WAIT_LGKM(NBW - 2);
+                    for (int v = (i * VREQ + B - 1) / B; v < ((i + 1) * VREQ + B - 1) / B; v++) issue(v);
+                    // LDS reads return in order: with at most B-2 younger ones in flight,
+                    // breg[i] and breg[i+1] (refilled one step ago) have arrived
+                    if ((i & 1) == 0) GG_WAIT_LGKM(B - 2);
 #pragma unroll
-                for (int j = 0; j < FRW; j++) gg_mfma(acc[i][j], Ac[j], breg[i]);
-                if (more) breg[i] = __builtin_bit_cast(bf16x8_t, pb[i * 64]);
+                    for (int j = 0; j < FRW; j++) {
+                        if (FIRST && u == 0) gg_mfma_first(acc[i][j], areg[u][j], breg[i]);
+                        else gg_mfma(acc[i][j], areg[u][j], breg[i]);
+                    }
+                    breg[i] = pl[i * 64];
+                }
             }
-            g++;
+            g += U;
+            kb += U * 1024;
         };
-        // steps whose look-aheads (k+NS-1 at most) stay inside this tile: no conditions
-        const int k_fast = ((KT - NS + 1) / U) * U;
-        int k = 0;
-        for (; k < k_fast; k += U) {
-#pragma unroll
-            for (int u = 0; u < U; u++) step(k + u, areg[u], areg[(u + LA) % U], true);
+        int k = klen - TG * U;
+        if (k > 0) {
+            group(GgInt<0>{}, GgInt<1>{});
+            for (k -= U; k > 0; k -= U) group(GgInt<0>{}, GgInt<0>{});
+            if constexpr (TG >= 2) group(GgInt<2>{}, GgInt<0>{});
+        } else {
+            if constexpr (TG >= 2) group(GgInt<2>{}, GgInt<1>{});
         }
-        for (; k < KT; k += U) {
-#pragma unroll
-            for (int u = 0; u < U; u++) step(k + u, areg[u], areg[(u + LA) % U], false);
-        }
+        group(GgInt<1>{}, GgInt<0>{});
+        static_assert(TG == 2, "tail groups");
 
-        // ---- epilogue of the current tile (the next tile's loads are in flight) ----
+        // ---- epilogue of the tile (the next tile's loads are in flight) ----
         // the compiler cannot see the MFMAs: cover the matrix-core write -> read hazard
         asm volatile("s_nop 15\n s_nop 15" ::: "memory");
         // The epilogue's per-lane addresses are derived from a copy of the lane number that the
         // compiler cannot trace back to the one above: it would otherwise compute them before
-        // the main loop and keep them in registers through it -- registers the loop does not
-        // have (the reload of a spilled one is a scratch load, and the wait for it also covers
-        // every store of the epilogue and every operand load of the next tile).
+        // the main loop and keep them in registers through it.
         const int lane_e = gg_lane_opaque();
-        const int t = lane_e & 15, fq = lane_e >> 4;  // token in block, feature quad
-        // a piece's partial sums: [16*NBW rows][16*FROWS columns] fp32 in this workgroup's slot
-        float* slot = a.part + (((size_t)xcd * wgs + me) * 2 + cur.piece) * (256 * 256) +
-                      (size_t)t * (16 * FROWS) + (FRW * wave) * 16 + 4 * fq;
-        if (UP && MODE == 2) {
-            // piece of a tile: raw partial sums to scratch; the fix-up kernel adds the
-            // pieces and applies SiLU*mul
+        const int t = lane_e & 15;  // token in block
+        // Every store is issued, so that their number is known (see the waits above): those of
+        // rows or blocks that do not exist lie beyond the descriptor and are dropped.
+        if (MODE == 2 || (MODE == 0 && cur.partial)) {
+            // piece of a tile: raw partial sums to this workgroup's slot, in the order of the
+            // accumulators (whole lines); the fix-up kernel adds the pieces
+            const __amdgpu_buffer_rsrc_t rs = gg_rsrc(
+                (const char*)(a.part + (((size_t)xcd * wgs + me) * 2 + cur.piece) * (256 * 256) + wave * (NBW * FRW * 256)));
 #pragma unroll
-            for (int i = 0; i < NBW; i++) {
-                if (i >= cur.nblk) continue;
+            for (int i = 0; i < B; i++) {
+                const unsigned vo = i < cur.nblk ? (unsigned)lane_e * 16u : GG_RSRC_BYTES;
 #pragma unroll
                 for (int j = 0; j < FRW; j++)
-                    *(float4*)(slot + (size_t)i * 16 * (16 * FROWS) + j * 16) =
-                        make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs, vo,
+                                                           (i * FRW + j) * 1024, 0);
             }
+            stores = B * FRW;
         } else if (UP) {
+            // fragment rows 4jj..4jj+3 of this wave: w1, w3 of an even and of the next column block
+            const int ks_o = cur.nt * (FROWS / 4) + (FRW / 4) * wave;  // h fragment column of jj = 0
+            const __amdgpu_buffer_rsrc_t rs = gg_rsrc(
+                (const char*)a.out + ((size_t)(cur.si.bbase + cur.blk0) * a.KS_out + ks_o) * 1024);
+            const unsigned vo = gg_h_off(lane_e);
 #pragma unroll
-            for (int i = 0; i < NBW; i++) {
-                if (i >= cur.nblk) continue;
-                const int blk = cur.blk0 + i;  // block inside the segment
-                // fragment rows FRW*wave+j: j even = w1 rows, j odd = w3 rows of the same columns
+            for (int i = 0; i < B; i++)
 #pragma unroll
-                for (int jj = 0; jj < FRW / 2; jj++) {
-                    const f32x4_t av = acc[i][2 * jj], bv = acc[i][2 * jj + 1];
-                    float hv[4];
-#pragma unroll
-                    for (int r = 0; r < 4; r++) hv[r] = av[r] / (1.0f + __expf(-av[r])) * bv[r];
-                    const int colblk = cur.nt * (FROWS / 2) + (FRW / 2) * wave + jj;  // 16 h-columns
-                    const int ks_o = colblk >> 1;
-                    const int lane_o = ((colblk & 1) * 2 + (fq >> 1)) * 16 + t;
-                    uint2 pk;
-                    pk.x = moe_pack_bf16x2(hv[0], hv[1]);
-                    pk.y = moe_pack_bf16x2(hv[2], hv[3]);
-                    unsigned char* dst =
-                        (unsigned char*)a.out +
-                        (((size_t)(cur.si.bbase + blk) * a.KS_out + ks_o) * 64 + lane_o) * 16 +
-                        (fq & 1) * 8;
-                    *(uint2*)dst = pk;
+                for (int jj = 0; jj < FRW / 4; jj++) {
+                    const u32x4_t hv = gg_make_h(acc[i][4 * jj], acc[i][4 * jj + 1], acc[i][4 * jj + 2],
+                                                 acc[i][4 * jj + 3]);
+                    const unsigned o = vo + (unsigned)i * (unsigned)a.KS_out * 1024u + jj * 1024u;
+                    __builtin_amdgcn_raw_buffer_store_b128(hv, rs, i < cur.nblk ? o : GG_RSRC_BYTES, 0, 0);
                 }
-            }
+            stores = B * (FRW / 4);
         } else {
+            const int r0 = cur.blk0 * 16;  // first row of the tile inside the segment
+            const __amdgpu_buffer_rsrc_t rs = gg_rsrc(
+                (const char*)((float*)a.out + (size_t)(cur.si.row0 + r0) * a.C + (cur.nt * FROWS + FRW * wave) * 16));
+            const int rows = cur.si.rows - r0;
+            const unsigned vo = (unsigned)t * (unsigned)a.C * 4u + (unsigned)(lane_e >> 4) * 16u;
 #pragma unroll
-            for (int i = 0; i < NBW; i++) {
-                if (i >= cur.nblk) continue;
-                const int blk = cur.blk0 + i;  // block inside the segment
-                // whole tiles go to yg; pieces of a tile to this workgroup's scratch slot
-                // (same code, only the destination differs)
-                const int r_in_seg = blk * 16 + t;
-                if (r_in_seg < cur.si.rows) {
-                    float* row = cur.partial ? slot + (size_t)i * 16 * (16 * FROWS)
-                                             : (float*)a.out + (size_t)(cur.si.row0 + r_in_seg) * a.C +
-                                                   (cur.nt * FROWS + FRW * wave) * 16 + 4 * fq;
+            for (int i = 0; i < B; i++) {
+                const unsigned o = i * 16 + t < rows ? vo + (unsigned)(i * 16) * (unsigned)a.C * 4u : GG_RSRC_BYTES;
 #pragma unroll
-                    for (int j = 0; j < FRW; j++)
-                        *(float4*)(row + j * 16) =
-                            make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
-                }
+                for (int j = 0; j < FRW; j++)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs, o + j * 64, 0, 0);
             }
+            stores = B * FRW;
+        }
+    };
+
+    for (;;) {
+        // by the number of units of the tile, 1 .. NBW / 4
+        if (cur.units == 1) tile(GgInt<4>{});
+        else if (NBW == 8 || cur.units == 2) tile(GgInt<8>{});
+        else if constexpr (NBW >= 12) {
+            if (NBW == 12 || cur.units == 3) tile(GgInt<12>{});
+            else if constexpr (NBW >= 16) tile(GgInt<16>{});
         }
         if (!has_next) {
             // the unconditional look-ahead of the last steps is still in flight (some of it on
@@ -542,183 +642,118 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a) {
         // advance: next becomes current; look one unit further ahead
         unit++;
         cur = nxt;
-        scur = snxt;
-        KT = cur.klen;
+        pa = pa_n;
+        pb = pb_n;
+#pragma unroll
+        for (int v = 0; v < NBQ; v++) vo_b[v] = vo_bn[v];
         has_next = unit_at(unit + 1, nxt);
-        if (has_next) gg_tile_src(a, nxt, wave, snxt);
-        GG_WAIT_LGKM(0);  // scalar loads of the decode must not sit in the LDS read counter
+        if (!has_next) nxt = cur;
+        pa_n = a_base(nxt);
+        pb_n = b_base(nxt);
+        b_off(nxt, vo_bn);
+        GG_WAIT_LGKM(0);  // the decode's reads must not sit in the LDS read counter
     }
-}
-
-// Are the weights of (nearly) every expert read by a single token tile?  Then they are
-// streamed.  The rule: token tiles beyond the first of an expert make up at most 15 % of all
-// token tiles (measured crossover: 11 % wins 8 %, 20 % loses 4 %, 50 % loses 13 %).
-__device__ __forceinline__ bool gg_weights_read_once(const int32_t* __restrict__ offsets, int E,
-                                                     int N, int TB) {
-    int tiles = 0, active = 0, prev = 0;
-    for (int e = 0; e < E; e++) {
-        const int lo = gg_clamp_off(offsets[e], prev, N);
-        const int hi = gg_clamp_off(offsets[e + 1], lo, N);
-        prev = lo;
-        tiles += (hi - lo + 16 * TB - 1) / (16 * TB);
-        active += (hi > lo) ? 1 : 0;
-    }
-    return (tiles - active) * 100 <= 15 * tiles;
 }
 
 // The two load flavours are two copies of the whole persistent loop: nothing is live across
 // the choice (a choice per tile inside one loop made the compiler spill the accumulators).
 template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS>
 __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
-    // (the 256-token tile is chosen above 256 rows per expert, where the rule never holds)
-    if (NBW < 16 && gg_weights_read_once(a.offsets, a.E, a.N, NBW))
-        gg_gemm_body<UP, NBW, FRW, MODE, U, LA, NS, true>(a);
+    __shared__ int s_seg[GG_SEG_FIELDS][64];
+    bool read_once;
+    const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, threadIdx.x & 63, s_seg,
+                                   threadIdx.x < 64, read_once);
+    __syncthreads();
+    if (read_once)
+        gg_gemm_body<UP, NBW, FRW, MODE, U, LA, NS, true>(a, total, s_seg);
     else
-        gg_gemm_body<UP, NBW, FRW, MODE, U, LA, NS, false>(a);
+        gg_gemm_body<UP, NBW, FRW, MODE, U, LA, NS, false>(a, total, s_seg);
 }
 
 // Adds the pieces of every left-over tile in the order of the workgroups that produced them
-// (deterministic), then writes yg (second projection) or applies SiLU*mul and writes the h
-// fragments (first projection).  blockIdx.x = (XCD, left-over tile), blockIdx.y = group of
-// 16 rows of the tile; every workgroup recomputes the cut points the GEMM workgroups used.
-// FROWS = fragment rows of the tile shape (16 or 32); a.TB = its token blocks.
-#define GG_FIX_ROWS 16
-template <bool UP, int FROWS>
+// (deterministic), then does what the GEMM's epilogue does for a whole tile.  Item = (left-over
+// tile, token block); thread = (wave, lane) of the GEMM.  The grid is of a fixed size (the host
+// does not know the number of tiles) and walks the items; every wave finds the pieces of a tile
+// for itself, from the cut points the GEMM workgroups used.  Loads of two pieces are in flight
+// together: one piece at a time, with a workgroup per item of the largest possible number of
+// tiles, took 40 us instead of 17 for the second projection at 8192 rows.
+#define GG_FIX_GRID 1024
+template <bool UP, int NBW, int FRW>
 __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, int unit, int ns) {
-    __shared__ int s_slot[64];
-    __shared__ int s_n;
-    constexpr int RS = 16 * FROWS;  // floats per row of a partial tile
-    const int xcd = blockIdx.x / wgs, r = blockIdx.x % wgs;
+    constexpr int FROWS = 4 * FRW;
     // the segment table as in the GEMM: one parallel read of the offsets and two wave scans
-    // instead of a walk over the experts with one memory round trip each (most workgroups of
-    // this grid find nothing to do and should find out quickly)
+    // instead of a walk over the experts with one memory round trip each
     __shared__ int s_seg[GG_SEG_FIELDS][64];
     const int lane = threadIdx.x & 63;
-    const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, a.TB, lane, s_seg, threadIdx.x < 64);
-    const int per_xcd = (total + 7) / 8;
-    int chunk = total - xcd * per_xcd;
-    chunk = chunk < 0 ? 0 : (chunk > per_xcd ? per_xcd : chunk);
-    if (chunk % wgs == 0) return;   // (uniform over the workgroup, as the returns below)
-    const int n_full = chunk / wgs;
-    const int R = chunk - n_full * wgs;
-    if (r >= R) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    bool read_once;
+    const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, lane, s_seg, threadIdx.x < 64, read_once);
+    const int left = total % (wgs * 8);
     __syncthreads();
-    TileInfo ti;
-    if (!gg_decode_tile_tab(s_seg, lane, a.NT, a.TB, xcd * per_xcd + n_full * wgs + r, ti)) return;
-    // second projection: the tile's real rows; first: every row of its blocks (h is kept in
-    // whole 16-row fragments, padding rows included)
-    const int tile_max = 16 * a.TB;
-    const int tile_rows = UP ? ti.nblk * 16
-                             : ((ti.si.rows - ti.blk0 * 16) < tile_max ? (ti.si.rows - ti.blk0 * 16)
-                                                                       : tile_max);
-    const int row_lo = blockIdx.y * GG_FIX_ROWS;
-    if (row_lo >= tile_rows) return;
-    // lane j of the first wave looks at workgroup j's cut: it holds at most one piece of
-    // this tile; a ballot keeps the pieces in workgroup order (wgs <= 64)
-    if (threadIdx.x < 64) {
-        const int j = threadIdx.x;
-        const int S = R * a.KS;
+    for (int item = blockIdx.x; item < left * NBW; item += gridDim.x) {
+        // (tile fastest: neighbouring workgroups, and not the same ones again, take blocks that exist)
+        const int lt = item % left, i = item / left;
+        // XCD whose left-over tiles hold tile lt (their ranges are cut as in gg_sched)
+        int xcd = (int)((unsigned)lt * 8u / (unsigned)left);
+        while (left * (xcd + 1) / 8 <= lt) xcd++;
+        while (left * xcd / 8 > lt) xcd--;
+        const GgSched sc = gg_sched(total, wgs, xcd);
+        const int r = sc.n_full * wgs * 8 + lt - sc.left_lo;  // tile number among the XCD's
+        TileInfo ti;
+        if (!gg_decode_tile_tab(s_seg, lane, a.NT, sc.left_lo + r, ti)) return;
+        if (i >= ti.nblk) continue;
+        // lane w looks at workgroup w's cut: it holds at most one piece of this tile; a ballot
+        // keeps the pieces in workgroup order (wgs <= 64)
+        const int S = sc.R * a.KS;
         int slot = -1;
-        if (j < wgs) {
-            const int c0 = gg_piece_cut(j, S, a.KS, wgs, unit, ns),
-                      c1 = gg_piece_cut(j + 1, S, a.KS, wgs, unit, ns);
+        if (lane < wgs) {
+            const int c0 = gg_piece_cut(lane, S, a.KS, wgs, unit, ns),
+                      c1 = gg_piece_cut(lane + 1, S, a.KS, wgs, unit, ns);
             if (c0 < c1) {
                 const int rA = c0 / a.KS;
                 const int endA = c1 < (rA + 1) * a.KS ? c1 : (rA + 1) * a.KS;
-                if (rA == r) slot = (xcd * wgs + j) * 2 + 0;
-                else if (c1 > endA && rA + 1 == r) slot = (xcd * wgs + j) * 2 + 1;
+                if (rA == r) slot = (xcd * wgs + lane) * 2 + 0;
+                else if (c1 > endA && rA + 1 == r) slot = (xcd * wgs + lane) * 2 + 1;
             }
         }
-        const unsigned long long m = __ballot(slot >= 0);
-        const unsigned long long below = (j == 0) ? 0ull : (~0ull >> (64 - j));
-        if (slot >= 0) s_slot[__popcll(m & below)] = slot;
-        if (j == 0) s_n = __popcll(m);
-    }
-    __syncthreads();
-    const int n = s_n;
-    const int rows = (tile_rows - row_lo) < GG_FIX_ROWS ? (tile_rows - row_lo) : GG_FIX_ROWS;
-    if (UP) {
-        // item = (row, block of 16 h-columns cb, feature quad fq): a = x.w1 from fragment
-        // row 2cb, b = x.w3 from fragment row 2cb+1, four columns each
-        constexpr int PER_ROW = (FROWS / 2) * 4;
-        constexpr int IT = GG_FIX_ROWS * PER_ROW / 256;
-        float4 sa[IT], sb[IT];
-        const float* src[IT];
+        unsigned long long m = __ballot(slot >= 0);
+        f32x4_t c[FRW];
 #pragma unroll
-        for (int it = 0; it < IT; it++) {
-            const int idx = it * 256 + threadIdx.x;
-            const int rr = (idx / PER_ROW) < rows ? (idx / PER_ROW) : 0;
-            const int cb = (idx >> 2) % (FROWS / 2), fq = idx & 3;
-            src[it] = a.part + (size_t)(row_lo + rr) * RS + (2 * cb) * 16 + 4 * fq;
-            sa[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-            sb[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        for (int p = 0; p < n; p++) {
-            const size_t base = (size_t)s_slot[p] * 256 * 256;
-            float4 va[IT], vb[IT];
+        for (int j = 0; j < FRW; j++) c[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        const float* src = a.part + (size_t)(wave * NBW + i) * (FRW * 256) + lane * 4;
+        while (m) {
+            const float* p0 = src + (size_t)__builtin_amdgcn_readlane(slot, (int)__builtin_ctzll(m)) * (256 * 256);
+            m &= m - 1;
+            const bool two = m != 0ull;
+            const float* p1 = two ? src + (size_t)__builtin_amdgcn_readlane(slot, (int)__builtin_ctzll(m)) * (256 * 256) : p0;
+            m &= m - 1;
+            f32x4_t v0[FRW], v1[FRW];
 #pragma unroll
-            for (int it = 0; it < IT; it++) {
-                va[it] = *(const float4*)(src[it] + base);
-                vb[it] = *(const float4*)(src[it] + base + 16);
-            }
+            for (int j = 0; j < FRW; j++) v0[j] = *(const f32x4_t*)(p0 + j * 256);
 #pragma unroll
-            for (int it = 0; it < IT; it++) {
-                sa[it].x += va[it].x; sa[it].y += va[it].y; sa[it].z += va[it].z; sa[it].w += va[it].w;
-                sb[it].x += vb[it].x; sb[it].y += vb[it].y; sb[it].z += vb[it].z; sb[it].w += vb[it].w;
+            for (int j = 0; j < FRW; j++) v1[j] = *(const f32x4_t*)(p1 + j * 256);
+#pragma unroll
+            for (int j = 0; j < FRW; j++) {
+                c[j] += v0[j];
+                if (two) c[j] += v1[j];
             }
         }
+        const int blk = ti.blk0 + i;  // block inside the segment
+        if (UP) {
+            const int ks_o = ti.nt * (FROWS / 4) + (FRW / 4) * wave;
+            unsigned char* dst = (unsigned char*)a.out + ((size_t)(ti.si.bbase + blk) * a.KS_out + ks_o) * 1024 +
+                                 gg_h_off(lane);
 #pragma unroll
-        for (int it = 0; it < IT; it++) {
-            const int idx = it * 256 + threadIdx.x;
-            if ((idx / PER_ROW) >= rows) continue;
-            const int row = row_lo + idx / PER_ROW, cb = (idx >> 2) % (FROWS / 2), fq = idx & 3;
-            const float av[4] = {sa[it].x, sa[it].y, sa[it].z, sa[it].w};
-            const float bv[4] = {sb[it].x, sb[it].y, sb[it].z, sb[it].w};
-            float hv[4];
+            for (int jj = 0; jj < FRW / 4; jj++)
+                *(u32x4_t*)(dst + jj * 1024) = gg_make_h(c[4 * jj], c[4 * jj + 1], c[4 * jj + 2], c[4 * jj + 3]);
+        } else {
+            const int row = blk * 16 + (lane & 15);
+            if (row < ti.si.rows) {
+                float* dst = (float*)a.out + (size_t)(ti.si.row0 + row) * a.C + (ti.nt * FROWS + FRW * wave) * 16 +
+                             4 * (lane >> 4);
 #pragma unroll
-            for (int q = 0; q < 4; q++) hv[q] = av[q] / (1.0f + __expf(-av[q])) * bv[q];
-            // same fragment address as the first projection's own epilogue
-            const int blk = ti.blk0 + (row >> 4), t = row & 15;
-            const int colblk = ti.nt * (FROWS / 2) + cb;
-            const int ks_o = colblk >> 1;
-            const int lane_o = ((colblk & 1) * 2 + (fq >> 1)) * 16 + t;
-            uint2 pk;
-            pk.x = moe_pack_bf16x2(hv[0], hv[1]);
-            pk.y = moe_pack_bf16x2(hv[2], hv[3]);
-            *(uint2*)((unsigned char*)a.out +
-                      (((size_t)(ti.si.bbase + blk) * a.KS_out + ks_o) * 64 + lane_o) * 16 +
-                      (fq & 1) * 8) = pk;
-        }
-    } else {
-        constexpr int PER_ROW = RS / 4;                      // float4 per row
-        constexpr int IT = GG_FIX_ROWS * PER_ROW / 256;      // float4 per thread
-        float4 sum[IT];
-        const float* src[IT];
-#pragma unroll
-        for (int it = 0; it < IT; it++) {
-            const int idx = it * 256 + threadIdx.x;
-            // rows past the end of the tile read row 0 of the group instead (never stored)
-            const int row = row_lo + ((idx / PER_ROW) < rows ? (idx / PER_ROW) : 0);
-            src[it] = a.part + (size_t)row * RS + (idx % PER_ROW) * 4;
-            sum[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        for (int p = 0; p < n; p++) {
-            const size_t base = (size_t)s_slot[p] * 256 * 256;
-            float4 v[IT];
-#pragma unroll
-            for (int it = 0; it < IT; it++) v[it] = *(const float4*)(src[it] + base);
-#pragma unroll
-            for (int it = 0; it < IT; it++) {
-                sum[it].x += v[it].x; sum[it].y += v[it].y; sum[it].z += v[it].z; sum[it].w += v[it].w;
+                for (int j = 0; j < FRW; j++) *(f32x4_t*)(dst + j * 16) = c[j];
             }
-        }
-#pragma unroll
-        for (int it = 0; it < IT; it++) {
-            const int idx = it * 256 + threadIdx.x;
-            if ((idx / PER_ROW) < rows)
-                *(float4*)((float*)a.out +
-                           (size_t)(ti.si.row0 + ti.blk0 * 16 + row_lo + idx / PER_ROW) * a.C +
-                           ti.nt * FROWS * 16 + (idx % PER_ROW) * 4) = sum[it];
         }
     }
 }
@@ -744,7 +779,7 @@ enum GgVariant { GG_STD = 0, GG_WIDE = 1, GG_R192 = 2, GG_NVARIANTS = 3 };
 struct GgShape { int tb, frows, u, la, ns; };
 static GgShape gg_shape(GgVariant v) {
     switch (v) {
-        case GG_WIDE: return {8, 32, GG_U, GG_LA, GG_NS};
+        case GG_WIDE: return {8, 32, GG_U, GG_WIDE_LA, GG_NS};
         case GG_R192: return {12, 16, GG_U, GG_LA, GG_NS};
         default: return {16, 16, GG_U, GG_LA, GG_NS};
     }
@@ -753,7 +788,7 @@ static GgShape gg_shape(GgVariant v) {
 template <bool UP, int MODE>
 static const void* gg_kernel_ptr(GgVariant v) {
     switch (v) {
-        case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, MODE, GG_U, GG_LA, GG_NS>;
+        case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, MODE, GG_U, GG_WIDE_LA, GG_NS>;
         case GG_R192: return (const void*)gg_gemm_kernel<UP, 12, 4, MODE, GG_U, GG_LA, GG_NS>;
         default: return (const void*)gg_gemm_kernel<UP, 16, 4, MODE, GG_U, GG_LA, GG_NS>;
     }
@@ -764,7 +799,7 @@ static const void* gg_kernel_ptr(GgVariant v) {
 template <bool UP>
 static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hipStream_t s) {
     const GgShape sh = gg_shape(v);
-    a.TB = sh.tb;
+    a.MU = sh.tb / GG_UNIT_BLOCKS;
     a.FROWS = sh.frows;
     if (a.FR % a.FROWS != 0) return MOE_ERR_UNSUPPORTED;
     a.NT = a.FR / a.FROWS;
@@ -772,7 +807,7 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
     // of a tile with one wave, hence at most 64 workgroups per XCD
     a.split = (a.KS >= 64 && pgrid / 8 <= 64) ? 1 : 0;
     void* params[1] = {(void*)&a};
-    const size_t lds_bytes = (size_t)sh.ns * a.TB * MOE_FRAG_BYTES;
+    const size_t lds_bytes = (size_t)sh.ns * sh.tb * MOE_FRAG_BYTES;
     if (UP) {
         MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<true, 1>(v), dim3(pgrid), dim3(GG_THREADS), params,
                                     lds_bytes, s));
@@ -784,13 +819,14 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
                                     lds_bytes, s));
     }
     if (a.split) {
-        const dim3 fgrid(pgrid, (unsigned)a.TB);
-        if (a.FROWS == 32)
-            hipLaunchKernelGGL((gg_fixup_kernel<UP, 32>), fgrid, dim3(256), 0, s, a, (int)(pgrid / 8),
-                               sh.u, sh.ns);
+        const dim3 fgrid(GG_FIX_GRID);
+        const int wgs = (int)(pgrid / 8);
+        if (v == GG_WIDE)
+            hipLaunchKernelGGL((gg_fixup_kernel<UP, 8, 8>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns);
+        else if (v == GG_R192)
+            hipLaunchKernelGGL((gg_fixup_kernel<UP, 12, 4>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns);
         else
-            hipLaunchKernelGGL((gg_fixup_kernel<UP, 16>), fgrid, dim3(256), 0, s, a, (int)(pgrid / 8),
-                               sh.u, sh.ns);
+            hipLaunchKernelGGL((gg_fixup_kernel<UP, 16, 4>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns);
     }
     return MOE_OK;
 }
