@@ -3,10 +3,10 @@
 // route  : G = next power of two >= E lanes of a wavefront hold one token's
 //          logits; k rounds of a butterfly arg-max (value desc, index asc)
 //          pick the experts; the softmax over the k winners is fp32.
-// permute: a stable counting sort of the T*k slots keyed on the expert.  Ranks
-//          come from wavefront ballots (lanes below me with my expert) plus a
-//          scan over the waves of a 1024-slot chunk, so the order inside an
-//          expert segment is the slot order and the result is unique.
+// permute: a stable counting sort of the T*k slots keyed on the expert.  Every workgroup
+//          counts all slots and places its own (ranks: wavefront ballots, lanes below me
+//          with my expert), so the order inside an expert segment is the slot order and
+//          the result is unique.
 // combine: y[t] = sum_j w[t,j] * yg[inv_perm[t*k+j]], float4 lanes along d.
 #include "moe_internal.h"
 #include "moe_gate_wave.h"
@@ -93,9 +93,8 @@ int moe_route_launch(const float* logits, int T, int E, int k, int32_t* idx, flo
 #define PERM_THREADS 1024
 #define PERM_WAVES (PERM_THREADS / 64)
 
-// Index part of the permute for all N slots, run by ONE workgroup of 1024
-// threads (every workgroup of a launch runs it redundantly when N <= 1024, so
-// that each can then gather its share of rows without a second launch).
+// Index part of the batching for the few slots of the fused front ends (gate_small_kernel), run
+// by every workgroup of 1024 threads for itself, so that each can then gather its share of rows.
 // Outputs are written only when `write` is set.  Returns through LDS: s_off.
 __device__ void permute_indices(const int32_t* __restrict__ idx, int N, int E,
                                 int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
@@ -167,49 +166,137 @@ __device__ void permute_indices(const int32_t* __restrict__ idx, int N, int E,
     }
 }
 
-// N <= 1024: one launch does everything.  Every workgroup computes the slot
-// positions in LDS, workgroup 0 writes the index outputs, and the workgroups
-// share the row gather (16-byte chunks, coalesced along d).
-__global__ __launch_bounds__(PERM_THREADS) void permute_small_kernel(
-    const int32_t* __restrict__ idx, int N, int E, int k, const uint4* __restrict__ x,
+// moe_permute: one launch.  Workgroup b takes the slots of `tpw` consecutive tokens.  It counts
+// the experts of all N slots (LDS histograms, one per wave, slots before its own apart from the
+// rest), which gives it the segment offsets and the positions of its own slots without waiting
+// for another workgroup; ranks inside a group of 64 slots are ballots.  GATHER: then its waves
+// copy their tokens' rows, each row read once and stored at its k positions.
+// Bound: reading idx from L2 in every workgroup (N * 4 bytes each), then the row copy.  One
+// workgroup for all N slots (and a second launch that read every row k times) took 15 + 21 us at
+// 4096 tokens, k = 2, 8 KiB rows, and 14 us for the indices of 300 tokens, k = 6, 64 experts;
+// this one launch 25 and 4 us.  Routing, batching and combine together: 4096 tokens, k = 2 76 ->
+// 62 us; 8192 tokens, k = 6, 64 experts, 4 KiB rows 465 -> 179 us.
+#define PM_THREADS 512
+#define PM_WAVES (PM_THREADS / 64)
+#define PM_MAX_SLOTS 1024  // slots of a workgroup whose positions are kept for the row copy
+
+// One row, copied by a wave to k rows of xg: 8 KiB of loads in flight, the row read once.
+// pos(j): row of copy j.
+template <class POS>
+__device__ __forceinline__ void copy_row_k(const u32x4_t* __restrict__ src, u32x4_t* __restrict__ xg,
+                                           int row_chunks, int k, int lane, POS pos) {
+    for (int c0 = lane; c0 < row_chunks; c0 += 64 * 8) {
+        u32x4_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++)  // past the end of the row: its last chunk, not stored
+            v[u] = src[c0 + u * 64 < row_chunks ? c0 + u * 64 : row_chunks - 1];
+        for (int j = 0; j < k; j++) {
+            u32x4_t* dst = xg + (size_t)pos(j) * row_chunks;
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+                if (c0 + u * 64 < row_chunks) dst[c0 + u * 64] = v[u];
+        }
+    }
+}
+
+template <bool GATHER>
+__global__ __launch_bounds__(PM_THREADS) void permute_kernel(
+    const int32_t* __restrict__ idx, int N, int E, int k, int tpw, const u32x4_t* __restrict__ x,
     int row_chunks /* 16-byte chunks per row */, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
-    uint4* __restrict__ xg) {
-    __shared__ int s_cnt[MOE_MAX_E];
-    __shared__ int s_off[MOE_MAX_E + 1];
-    __shared__ int s_wave[PERM_WAVES * MOE_MAX_E];
-    __shared__ int s_pos[PERM_THREADS];
-    permute_indices(idx, N, E, counts, offsets, perm, inv_perm, blockIdx.x == 0, s_cnt, s_off,
-                    s_wave, s_pos);
-    if (x == nullptr) return;
+    u32x4_t* __restrict__ xg) {
+    __shared__ int s_hist[PM_WAVES][2][MOE_MAX_E];  // [wave][slots before mine, the rest][expert]
+    __shared__ int s_next[MOE_MAX_E];               // next free position per expert
+    __shared__ int s_pos[GATHER ? PM_MAX_SLOTS : 1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < PM_WAVES * 2 * MOE_MAX_E; i += PM_THREADS) (&s_hist[0][0][0])[i] = 0;
     __syncthreads();
-    for (int p = blockIdx.x; p < N; p += gridDim.x) {
-        const uint4* src = x + (size_t)(p / k) * row_chunks;
-        uint4* dst = xg + (size_t)s_pos[p] * row_chunks;
-        for (int c = threadIdx.x; c < row_chunks; c += PERM_THREADS) dst[c] = src[c];
+    const int slot0 = blockIdx.x * tpw * k;  // (grid * tpw tokens: below 2^25 slots)
+    const int slots = (N - slot0) < tpw * k ? (N - slot0) : tpw * k;
+    auto expert = [&](int e) { return e < 0 ? 0 : (e >= E ? E - 1 : e); };
+    for (int p = tid * 4; p < N; p += PM_THREADS * 4) {
+        int e[4];
+        if (p + 4 <= N) {
+            const int4 v = *(const int4*)(idx + p);
+            e[0] = v.x; e[1] = v.y; e[2] = v.z; e[3] = v.w;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; q++) e[q] = p + q < N ? idx[p + q] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            if (p + q < N) atomicAdd(&s_hist[wave][p + q < slot0 ? 0 : 1][expert(e[q])], 1);
     }
+    __syncthreads();
+    if (wave == 0) {
+        int before = 0, rest = 0;
+        for (int w = 0; w < PM_WAVES; w++) {
+            before += s_hist[w][0][lane];
+            rest += s_hist[w][1][lane];
+        }
+        const int cnt = before + rest;  // 0 for lanes >= E
+        int inc = cnt;
+#pragma unroll
+        for (int dlt = 1; dlt < 64; dlt <<= 1) {
+            const int v = __shfl_up(inc, dlt, 64);
+            if (lane >= dlt) inc += v;
+        }
+        if (blockIdx.x == 0) {
+            if (lane < E) {
+                counts[lane] = cnt;
+                offsets[lane] = inc - cnt;
+            }
+            if (lane == E - 1) offsets[E] = inc;
+        }
+        s_next[lane] = inc - cnt + before;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // positions, 64 slots at a time: rank among the group's lower slots of the same expert
+        const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+        for (int g = 0; g < slots; g += 64) {
+            const int p = slot0 + g + lane;
+            const bool live = g + lane < slots;
+            const int e = live ? expert(idx[p]) : 0;
+            unsigned long long same = __ballot(live);
+#pragma unroll
+            for (int b = 0; b < 6; b++) {  // E <= 64
+                const unsigned long long m = __ballot((e >> b) & 1);
+                same &= ((e >> b) & 1) ? m : ~m;
+            }
+            const int rank = __popcll(same & below);
+            int pos = 0;
+            if (live) pos = s_next[e] + rank;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (live) {
+                if (rank == 0) s_next[e] = pos + __popcll(same);
+                perm[pos] = p;
+                inv_perm[p] = pos;
+                if (GATHER) s_pos[g + lane] = pos;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    if (!GATHER) return;
+    __syncthreads();
+    const int tokens = slots / k, t0 = slot0 / k;
+    for (int t = wave; t < tokens; t += PM_WAVES)
+        copy_row_k(x + (size_t)(t0 + t) * row_chunks, xg, row_chunks, k, lane,
+                   [&](int j) { return s_pos[t * k + j]; });
 }
 
-__global__ __launch_bounds__(PERM_THREADS) void permute_index_kernel(
-    const int32_t* __restrict__ idx, int N, int E, int32_t* __restrict__ counts,
-    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
-    __shared__ int s_cnt[MOE_MAX_E];
-    __shared__ int s_off[MOE_MAX_E + 1];
-    __shared__ int s_wave[PERM_WAVES * MOE_MAX_E];
-    permute_indices(idx, N, E, counts, offsets, perm, inv_perm, true, s_cnt, s_off, s_wave,
-                    nullptr);
-}
-
-// xg[i,:] = x[perm[i]/k,:]; one workgroup of 256 threads per group of rows.
-__global__ __launch_bounds__(256) void gather_rows_kernel(const int32_t* __restrict__ perm, int N,
-                                                          int k, const uint4* __restrict__ x,
+// xg[inv_perm[t*k+j],:] = x[t,:]: the row copy on its own, one wave per token (calls whose
+// workgroups hold more slots than PM_MAX_SLOTS).
+__global__ __launch_bounds__(256) void gather_rows_kernel(const int32_t* __restrict__ inv_perm, int T,
+                                                          int k, const u32x4_t* __restrict__ x,
                                                           int row_chunks,
-                                                          uint4* __restrict__ xg) {
-    for (int i = blockIdx.x; i < N; i += gridDim.x) {
-        const uint4* src = x + (size_t)(perm[i] / k) * row_chunks;
-        uint4* dst = xg + (size_t)i * row_chunks;
-        for (int c = threadIdx.x; c < row_chunks; c += 256) dst[c] = src[c];
-    }
+                                                          u32x4_t* __restrict__ xg) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int t = blockIdx.x * 4 + wave; t < T; t += gridDim.x * 4)
+        copy_row_k(x + (size_t)t * row_chunks, xg, row_chunks, k, lane,
+                   [&](int j) { return inv_perm[(size_t)t * k + j]; });
 }
 
 int moe_permute_launch(const int32_t* idx, int T, int E, int k, const void* x, int d,
@@ -217,23 +304,24 @@ int moe_permute_launch(const int32_t* idx, int T, int E, int k, const void* x, i
                        int32_t* inv_perm, void* xg, hipStream_t s) {
     const int N = T * k;
     const int row_chunks = (int)(((size_t)d * (x_dtype == MOE_BF16 ? 2 : 4)) / 16);
-    if (N <= PERM_THREADS) {
-        unsigned grid = 1;
-        if (x != nullptr && N > 0) grid = (unsigned)(N < 64 ? N : 64);
-        hipLaunchKernelGGL(permute_small_kernel, dim3(grid), dim3(PERM_THREADS), 0, s, idx, N, E, k,
-                           (const uint4*)x, row_chunks, counts, offsets, perm, inv_perm,
-                           (uint4*)xg);
+    // one workgroup per CU at most: every one counts all N slots
+    const int cus = moe_num_cus();
+    const int tpw = T > cus ? (T + cus - 1) / cus : 1;
+    const unsigned grid = T > 0 ? (unsigned)((T + tpw - 1) / tpw) : 1u;
+    const bool fused = x != nullptr && (long long)tpw * k <= PM_MAX_SLOTS;
+    if (fused)
+        hipLaunchKernelGGL(permute_kernel<true>, dim3(grid), dim3(PM_THREADS), 0, s, idx, N, E, k, tpw,
+                           (const u32x4_t*)x, row_chunks, counts, offsets, perm, inv_perm, (u32x4_t*)xg);
+    else
+        hipLaunchKernelGGL(permute_kernel<false>, dim3(grid), dim3(PM_THREADS), 0, s, idx, N, E, k, tpw,
+                           (const u32x4_t*)nullptr, 0, counts, offsets, perm, inv_perm, (u32x4_t*)nullptr);
+    if (moe_launch_status() != MOE_OK) return MOE_ERR_HIP;
+    if (x != nullptr && !fused) {
+        hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)(cus * 8)), dim3(256), 0, s, inv_perm, T, k,
+                           (const u32x4_t*)x, row_chunks, (u32x4_t*)xg);
         return moe_launch_status();
     }
-    hipLaunchKernelGGL(permute_index_kernel, dim3(1), dim3(PERM_THREADS), 0, s, idx, N, E, counts,
-                       offsets, perm, inv_perm);
-    if (moe_launch_status() != MOE_OK) return MOE_ERR_HIP;
-    if (x != nullptr) {
-        unsigned grid = (unsigned)(N < 8192 ? N : 8192);
-        hipLaunchKernelGGL(gather_rows_kernel, dim3(grid), dim3(256), 0, s, perm, N, k,
-                           (const uint4*)x, row_chunks, (uint4*)xg);
-    }
-    return moe_launch_status();
+    return MOE_OK;
 }
 
 // ---------------------------------------------------------------- combine ----
