@@ -50,7 +50,7 @@ typedef enum {
     MOE_FFN_AUTO = 0,
     MOE_FFN_STREAM = 1, /* decode: weight-streaming MFMA kernels, <=16 rows per pass */
     MOE_FFN_GROUPED = 2, /* prefill: grouped LDS-tiled MFMA GEMM */
-    MOE_FFN_MID = 3      /* a handful of rows for each of many experts: weight-streaming grouped GEMM */
+    MOE_FFN_MID = 3      /* a handful of rows for each of many experts: grouped GEMM, weight-streaming tile */
 } moe_ffn_path_t;
 
 typedef struct moe_weights moe_weights_t; /* opaque, library-owned */

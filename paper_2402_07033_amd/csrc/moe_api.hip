@@ -25,10 +25,9 @@ static inline bool ranges_overlap(const void* a, size_t an, const void* b, size_
 // limit here):
 //   up to 72 routed rows the decode kernels, which stream each active expert once per
 //   16-row tile at ~6.5 TB/s;
-//   up to MOE_MID_MAX_ROWS rows per expert on average the weight-streaming grouped GEMM
-//   (many experts with a handful of rows each: 11 % ahead at 6 rows per expert, 5 % behind
-//   at 12; with 8 experts the window is 73..80 rows, so this is a path of E >= 16 layers);
-//   above that the LDS-tiled grouped GEMM, whose smaller tiles stream the weights too.
+//   up to MOE_MID_MAX_ROWS rows per expert on average MID, above that GROUPED.  Both are the
+//   grouped GEMM: MID pins its weight-streaming 128 x 512 tile, which GROUPED chooses up to 96
+//   rows per expert as well, and serves f = 128.
 int moe_ffn_auto_path(int N, int E, int d, int f) {
     if (N <= 72 && moe_ffn_stream_supported(d, f)) return MOE_FFN_STREAM;
     if ((long long)N <= (long long)MOE_MID_MAX_ROWS * E && moe_ffn_mid_supported(N, E, d, f))
@@ -128,10 +127,8 @@ size_t moe_expert_ffn_workspace(int N, int E, int d, int f, moe_dtype_t act_dtyp
     size_t need = moe_ffn_f32_workspace(N, E, d, f);
     const size_t s = moe_ffn_stream_workspace(N, E, d, f);
     const size_t g = moe_ffn_grouped_workspace(N, E, d, f);
-    const size_t m = moe_ffn_mid_workspace(N, E, d, f);
     if (s > need) need = s;
     if (g > need) need = g;
-    if (m > need) need = m;
     return align256(need) + 256;
 }
 

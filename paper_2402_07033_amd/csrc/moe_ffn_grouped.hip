@@ -758,6 +758,24 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
     }
 }
 
+// Second projection with fewer reduction steps than the pipelined kernel's stages (f = 128, which
+// MID serves): one wave per (token block, fragment row), straight from the fragments.
+__global__ __launch_bounds__(256) void gg_down_short_kernel(GroupedArgs a) {
+    SegInfo si;
+    const int lane = threadIdx.x & 63;
+    if (!gg_find_block(a.offsets, a.E, a.N, blockIdx.x, lane, si)) return;
+    const int fr = blockIdx.y * 4 + (threadIdx.x >> 6);  // FR is a multiple of 4
+    const u32x4_t* w = a.wfrag + ((size_t)si.e * a.FR + fr) * a.KS * 64 + lane;
+    const u32x4_t* h = a.bfrag + (size_t)blockIdx.x * a.KS * 64 + lane;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int ks = 0; ks < a.KS; ks++)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[ks * 64]),
+                                                      __builtin_bit_cast(bf16x8_t, h[ks * 64]), acc, 0, 0, 0);
+    const int row = ((int)blockIdx.x - si.bbase) * 16 + (lane & 15);
+    if (row < si.rows)
+        *(f32x4_t*)((float*)a.out + (size_t)(si.row0 + row) * a.C + fr * 16 + 4 * (lane >> 4)) = acc;
+}
+
 // ---------------------------------------------------------------- host side ----
 static inline size_t gg_align256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline size_t gg_max_blocks(int N, int E) { return (size_t)N / 16 + E; }
@@ -831,6 +849,12 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
     return MOE_OK;
 }
 
+// The step loop is unrolled u times and looks ns-1 steps ahead.
+static bool gg_fits(GgVariant v, int ks) {
+    const GgShape sh = gg_shape(v);
+    return ks % sh.u == 0 && ks >= sh.ns;
+}
+
 // Variant of each projection by the mean number of rows per expert (the host never sees the
 // real counts): up to GG_WIDE_MAX_ROWS the 128-token x 512-feature tile (needs f % 256 == 0
 // for the first projection, d % 512 == 0 for the second; each falls back on its own), up to
@@ -848,15 +872,10 @@ static bool gg_choose(int N, int E, int d, int f, GgVariant& vu, GgVariant& vd) 
     } else if (mean_rows <= GG_R192_MAX_ROWS) {
         vu = vd = GG_R192;
     }
-    // the step loop is unrolled u times and looks ns-1 steps ahead: a variant whose loop does
-    // not fit a reduction gives way to the standard one
-    auto fits = [&](GgVariant v, int ks) {
-        const GgShape sh = gg_shape(v);
-        return ks % sh.u == 0 && ks >= sh.ns;
-    };
-    if (!fits(vu, d / 32)) vu = GG_STD;
-    if (!fits(vd, f / 32)) vd = GG_STD;
-    return fits(vu, d / 32) && fits(vd, f / 32);
+    // a variant whose loop does not fit a reduction gives way to the standard one
+    if (!gg_fits(vu, d / 32)) vu = GG_STD;
+    if (!gg_fits(vd, f / 32)) vd = GG_STD;
+    return gg_fits(vu, d / 32) && gg_fits(vd, f / 32);
 }
 
 int moe_ffn_grouped_plan(int N, int E, int d, int f, moe_ffn_plan_t* plan) {
@@ -870,12 +889,11 @@ int moe_ffn_grouped_plan(int N, int E, int d, int f, moe_ffn_plan_t* plan) {
     return MOE_OK;
 }
 
-int moe_ffn_grouped_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
-                           const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
-                           float* yg, hipStream_t s) {
+// short_down: the second projection's reduction is too short for the pipelined kernel.
+static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype, const int32_t* perm,
+                     int k, const int32_t* offsets, int N, void* ws, float* yg, GgVariant vu, GgVariant vd,
+                     bool short_down, hipStream_t s) {
     const int d = W->d, f = W->f, E = W->E;
-    GgVariant vu, vd;
-    if (!gg_choose(N, E, d, f, vu, vd)) return MOE_ERR_UNSUPPORTED;
     const size_t nb = gg_max_blocks(N, E);
     u32x4_t* xp = (u32x4_t*)ws;
     u32x4_t* hp = (u32x4_t*)((unsigned char*)ws + gg_align256(nb * 16 * d * 2));
@@ -934,7 +952,38 @@ int moe_ffn_grouped_launch(const moe_weights* W, const void* xg, moe_dtype_t act
     dn.KS_out = 0;
     dn.C = d;
     dn.part = part;
+    if (short_down) {
+        hipLaunchKernelGGL(gg_down_short_kernel, dim3((unsigned)nb, (unsigned)(d / 64)), dim3(256), 0, s, dn);
+        return moe_launch_status();
+    }
     rc = gg_launch_projection<false>(dn, vd, pgrid, s);
     if (rc != MOE_OK) return rc;
     return moe_launch_status();
+}
+
+int moe_ffn_grouped_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
+                           const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
+                           float* yg, hipStream_t s) {
+    GgVariant vu, vd;
+    if (!gg_choose(N, W->E, W->d, W->f, vu, vd)) return MOE_ERR_UNSUPPORTED;
+    return gg_launch(W, xg, act_dtype, perm, k, offsets, N, ws, yg, vu, vd, false, s);
+}
+
+// MID is for a handful of rows for each of many experts; the limit on N is its own (a forced
+// path beyond it stays refused).  It had kernels of its own (a wave streamed two adjacent fragment
+// rows for up to 192 rows); with token units and the 128 x 512 tile the grouped GEMM is ahead at
+// every size of AUTO's window: 8 experts, 80 rows 486 -> 459 us; 16 experts, 96..160 rows, Zipf
+// 322..413 -> 305..368, balanced 444 -> 429; 64 experts of f = 1408, 80..640 rows 122..250 -> 103..173.
+bool moe_ffn_mid_supported(int N, int E, int d, int f) {
+    return f % 128 == 0 && d % 256 == 0 && (size_t)N / 192 + E <= 192;
+}
+
+int moe_ffn_mid_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
+                       const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
+                       float* yg, hipStream_t s) {
+    const int d = W->d, f = W->f;
+    if (!moe_ffn_mid_supported(N, W->E, d, f)) return MOE_ERR_UNSUPPORTED;
+    const GgVariant vu = f % 256 == 0 ? GG_WIDE : GG_STD, vd = d % 512 == 0 ? GG_WIDE : GG_STD;
+    const bool short_down = !gg_fits(vd, f / 32);
+    return gg_launch(W, xg, act_dtype, perm, k, offsets, N, ws, yg, vu, vd, short_down, s);
 }

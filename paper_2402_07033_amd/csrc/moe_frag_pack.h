@@ -1,6 +1,6 @@
-// Shared by the kernels that work on activations re-laid as B-operand fragments
-// (moe_ffn_grouped.hip, moe_ffn_mid.hip): the per-expert block bookkeeping and the pack
-// kernel.  Device code only.
+// Per-expert bookkeeping of the routed rows (for whole waves) and the kernel that re-lays
+// activations as B-operand fragments for the grouped GEMM (moe_ffn_grouped.hip).  Device code
+// only.
 #pragma once
 
 #include "moe_internal.h"
@@ -12,10 +12,6 @@ struct SegInfo {
     int rows;     // rows of the segment
     int bbase;    // first packed block of the segment
 };
-
-__device__ __forceinline__ int gg_clamp_off(int v, int lo, int N) {
-    return v < lo ? lo : (v > N ? N : v);
-}
 
 // Expert `lane`'s rows [lo, lo + rows) of the routed rows (none for lanes >= E), for a whole
 // wave.  Offsets that do not ascend or leave [0, N] are clamped as a walk over the experts

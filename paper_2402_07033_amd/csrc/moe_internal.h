@@ -97,8 +97,9 @@ int moe_ffn_grouped_launch(const moe_weights* W, const void* xg, moe_dtype_t act
                            const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
                            float* yg, hipStream_t s);
 
+// The grouped GEMM with the 128-token x 512-feature tile whatever the number of rows; the same
+// workspace.
 bool moe_ffn_mid_supported(int N, int E, int d, int f);
-size_t moe_ffn_mid_workspace(int N, int E, int d, int f);
 int moe_ffn_mid_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
                        const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
                        float* yg, hipStream_t s);

@@ -47,7 +47,6 @@ int moe_expert_ffn_noalloc(const moe_weights_t* W, const void* xg, moe_dtype_t a
     size_t need;
     if (W->dtype == MOE_F32) need = moe_ffn_f32_workspace(N, W->E, W->d, W->f);
     else if (path == MOE_FFN_STREAM) need = moe_ffn_stream_workspace(N, W->E, W->d, W->f);
-    else if (path == MOE_FFN_MID) need = moe_ffn_mid_workspace(N, W->E, W->d, W->f);
     else need = moe_ffn_grouped_workspace(N, W->E, W->d, W->f);
     if (need > MOE_NOALLOC_SCRATCH_BYTES) return MOE_ERR_WORKSPACE;  // beyond the static scratch
     void* ptr = noalloc_scratch_ptr();

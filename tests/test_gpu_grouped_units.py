@@ -52,3 +52,28 @@ def test_grouped_unit_edges(name, d, f):
     ref = orc.expert_ffn(mi.to_f64(xg), offsets, w1, w3, w2)
     assert np.isfinite(out[0][:N]).all() and max_rel(out[0][:N], ref) <= TOL_BF16
     W.free()
+
+
+# MID pins the 128 x 512 tile (256 x 256 where f % 256 or d % 512 is not 0), whatever the number of
+# rows, and serves f = 128, whose second projection is too short for the pipelined kernel
+@pytest.mark.parametrize("d,f", [(256, 128), (512, 128), (512, 384), (1024, 512)])
+@pytest.mark.parametrize("counts", [[33, 0, 17, 1], [1, 2, 0, 3], [130, 300, 64, 65]])
+def test_mid_path_shapes(d, f, counts):
+    import paper_2402_07033_amd as moe
+    E, N = len(counts), sum(counts)
+    cfg = mi.small_config("mid", 1, d, f, E, 1, 4500 + N + d + f, w_dtype=mi.BF16)
+    w1, w3, w2 = mi.make_weights(cfg, threads=8)
+    xg = mi.normal_f32(cfg.seed, 90, (N, d))
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    W = pack_layer(mi.LayerInputs(cfg, None, None, w1, w3, w2))
+    buf = torch.full((N + 16, d), float("nan"), device="cuda")
+    moe.moe_expert_ffn(W, to_dev(xg), to_dev(offsets), yg=buf[:N], path=moe.MOE_FFN_MID)
+    torch.cuda.synchronize()
+    out = to_host(buf)
+    assert np.isnan(out[N:]).all() and np.isfinite(out[:N]).all()
+    ref = orc.expert_ffn(xg.astype(np.float64), offsets, w1, w3, w2)
+    assert max_rel(out[:N], ref) <= TOL_BF16
+    if f == 128:  # GROUPED has no kernel for this reduction, as before
+        with pytest.raises(moe.MoeError):
+            moe.moe_expert_ffn(W, to_dev(xg), to_dev(offsets), path=moe.MOE_FFN_GROUPED)
+    W.free()
