@@ -157,13 +157,23 @@ def _check(status: int, what: str):
         raise MoeError(status, what)
 
 
+# A call of a few microseconds of GPU work is bound by this file: pointers go to ctypes as plain
+# integers (argtypes make them void*), and the current stream's handle is asked for without a
+# Stream object around it.  The tiny fp32 layer's four calls take 45 us of host time, 54 before.
+_getDevice = getattr(torch._C, "_cuda_getDevice", None)
+_getRawStream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _getRawStream is None or _getDevice is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _getRawStream(_getDevice())
 
 
 def _dev(t: torch.Tensor, dtype, what: str):
@@ -276,7 +286,7 @@ def moe_expert_ffn(W: PackedWeights, xg: torch.Tensor, offsets: torch.Tensor, wo
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=xg.device)
     if yg is None:
         yg = torch.empty((N, W.d), dtype=torch.float32, device=xg.device)
-    _check(lib().moe_expert_ffn_path(C.c_void_p(W.handle), _ptr(xg), adt, _ptr(offsets), N,
+    _check(lib().moe_expert_ffn_path(W.handle, _ptr(xg), adt, _ptr(offsets), N,
                                      _ptr(workspace), workspace.numel(), _ptr(yg), path,
                                      _stream(stream)), "moe_expert_ffn")
     return yg
@@ -303,7 +313,7 @@ def moe_expert_ffn_parts(W: "PackedWeights", xg: torch.Tensor, offsets: torch.Te
         need = moe_expert_ffn_workspace(N, W.E, W.d, W.f, adt)
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=xg.device)
     n = C.c_int(0)
-    _check(lib().moe_expert_ffn_parts(C.c_void_p(W.handle), _ptr(xg), adt, _ptr(offsets), N,
+    _check(lib().moe_expert_ffn_parts(W.handle, _ptr(xg), adt, _ptr(offsets), N,
                                       _ptr(workspace), workspace.numel(), _ptr(yg_parts),
                                       yg_parts.shape[0], C.byref(n), _stream(stream)),
            "moe_expert_ffn_parts")
@@ -325,7 +335,7 @@ def moe_expert_ffn_tokens(W: "PackedWeights", x: torch.Tensor, k: int, perm: tor
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
     if yg is None:
         yg = torch.empty((N, W.d), dtype=torch.float32, device=x.device)
-    _check(lib().moe_expert_ffn_tokens(C.c_void_p(W.handle), _ptr(x), adt, T, k, _ptr(perm),
+    _check(lib().moe_expert_ffn_tokens(W.handle, _ptr(x), adt, T, k, _ptr(perm),
                                        _ptr(offsets), _ptr(workspace), workspace.numel(),
                                        _ptr(yg), _stream(stream)), "moe_expert_ffn_tokens")
     return yg
@@ -339,7 +349,7 @@ def moe_expert_ffn_noalloc(W: "PackedWeights", xg: torch.Tensor, offsets: torch.
     _dev(yg, torch.float32, "yg")
     if not xg.is_cuda or not xg.is_contiguous():
         raise TypeError("xg: expected a contiguous device tensor")
-    _check(lib().moe_expert_ffn_noalloc(C.c_void_p(W.handle), _ptr(xg), _act_dtype(xg),
+    _check(lib().moe_expert_ffn_noalloc(W.handle, _ptr(xg), _act_dtype(xg),
                                         _ptr(offsets), xg.shape[0], _ptr(yg), _stream(stream)),
            "moe_expert_ffn_noalloc")
     return yg
@@ -392,7 +402,7 @@ def moe_decode_layer(W: "PackedWeights", x: torch.Tensor, logits: torch.Tensor, 
                                 dtype=torch.uint8, device=dev)
     if y is None:
         y = torch.empty((T, d), dtype=torch.float32, device=dev)
-    _check(lib().moe_decode_layer(C.c_void_p(W.handle), _ptr(x), _ptr(logits), T, k, _ptr(idx),
+    _check(lib().moe_decode_layer(W.handle, _ptr(x), _ptr(logits), T, k, _ptr(idx),
                                   _ptr(weights), _ptr(counts), _ptr(offsets), _ptr(perm),
                                   _ptr(inv_perm), _ptr(xg), _ptr(workspace), workspace.numel(),
                                   _ptr(yg), _ptr(y), _stream(stream)), "moe_decode_layer")
@@ -466,7 +476,7 @@ def moe_decode_block(W: "PackedWeights", x_in: torch.Tensor, k: int, gate_sums=N
         _dev(w_gate_next, torch.float32, "w_gate_next")
         if gate_sums_next is None:
             gate_sums_next = torch.empty((d // 16, moe_gate_sums_stride(T, E)), **f32)
-    _check(lib().moe_decode_block(C.c_void_p(W.handle), _ptr(x_in), _ptr(gate_sums), n_shares, eps,
+    _check(lib().moe_decode_block(W.handle, _ptr(x_in), _ptr(gate_sums), n_shares, eps,
                                   _ptr(logits), T, k, _ptr(idx), _ptr(weights), _ptr(counts),
                                   _ptr(offsets), _ptr(perm), _ptr(inv_perm), _ptr(workspace),
                                   workspace.numel(), _ptr(x_out), _ptr(w_gate_next),
