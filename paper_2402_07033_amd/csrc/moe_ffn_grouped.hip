@@ -64,7 +64,7 @@
 // Tile shapes (token rows x weight fragment rows of 16 features per workgroup), by the mean
 // number of rows per expert:
 //   256 x 16 (256 tokens x 256 features): the default;
-//   192 x 16 (192 tokens x 256 features): 97..256 rows;
+//   192 x 16 (192 tokens x 256 features): 97..176 and 233..256 rows;
 //   128 x 32 (128 tokens x 512 features): up to 96 rows -- twice the weight bytes per step,
 //           which is what bounds such experts.
 #define GG_THREADS 256
@@ -89,9 +89,13 @@
 #ifndef GG_WIDE_MAX_ROWS
 #define GG_WIDE_MAX_ROWS 96  // mean rows per expert up to which the 128 x 512 tile is used
 #endif
-#ifndef GG_R192_MAX_ROWS
-#define GG_R192_MAX_ROWS 256  // ... and up to which the 192 x 256 tile is used
-#endif
+// ... up to which the 192 x 256 tile is used, and the range above it where the 256 x 256 tile comes
+// first: experts of 177..232 rows on average mostly fit one 256-row tile and need two of 192 (212
+// rows, balanced: 0.77 -> 0.70 ms; 16 experts 0.77 -> 0.63); around 250 rows half of them need two
+// of either, and the smaller tile is 3-5 % ahead.
+#define GG_R192_MAX_ROWS 176
+#define GG_R192_MIN_ROWS2 233
+#define GG_R192_MAX_ROWS2 256
 #define GG_GROUP 8         // token tiles that are neighbours of one weight tile, see the tile order
 #define GG_UNIT_BLOCKS 4   // 16-row token blocks per unit
 
@@ -857,8 +861,8 @@ static bool gg_fits(GgVariant v, int ks) {
 
 // Variant of each projection by the mean number of rows per expert (the host never sees the
 // real counts): up to GG_WIDE_MAX_ROWS the 128-token x 512-feature tile (needs f % 256 == 0
-// for the first projection, d % 512 == 0 for the second; each falls back on its own), up to
-// GG_R192_MAX_ROWS the 192-token x 256-feature one, above that 256 x 256.
+// for the first projection, d % 512 == 0 for the second; each falls back on its own), then the
+// 192-token x 256-feature one in its two ranges, else 256 x 256.
 static bool gg_choose(int N, int E, int d, int f, GgVariant& vu, GgVariant& vd) {
     // up tile = 16 fragment rows = 8 column blocks x (w1,w3): f % 128 == 0;
     // down tile = 256 features: d % 256 == 0; both give reductions of >= 8 steps, step
@@ -869,7 +873,8 @@ static bool gg_choose(int N, int E, int d, int f, GgVariant& vu, GgVariant& vd) 
     if (mean_rows <= GG_WIDE_MAX_ROWS) {
         if (f % 256 == 0) vu = GG_WIDE;
         if (d % 512 == 0) vd = GG_WIDE;
-    } else if (mean_rows <= GG_R192_MAX_ROWS) {
+    } else if (mean_rows <= GG_R192_MAX_ROWS ||
+               (mean_rows >= GG_R192_MIN_ROWS2 && mean_rows <= GG_R192_MAX_ROWS2)) {
         vu = vd = GG_R192;
     }
     // a variant whose loop does not fit a reduction gives way to the standard one
