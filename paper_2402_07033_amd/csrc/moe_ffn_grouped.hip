@@ -151,7 +151,9 @@ struct TileInfo {
 // One wave fills the table (lane e: expert e); returns the number of logical tiles.
 // read_once: are the weights of (nearly) every expert read by a single token tile?  Then they
 // are streamed.  The rule: token tiles beyond the first of an expert make up at most 15 % of
-// all token tiles (measured crossover: 11 % wins 8 %, 20 % loses 4 %, 50 % loses 13 %).
+// all token tiles (measured crossover with the 192-row tile: 11 % wins 8 %, 27 % loses 2.5 %, 50 %
+// loses 13 %; 256-row tile, 50 % and more: loses 4-5 %); with the 128-row x 512-feature tile at most
+// 45 % (20..30 %: wins 2-8 % over 16 and 64 experts, 3 % and -0.6 % over 8).
 __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets, int E, int N,
                                             int NT, int MU, int lane, int (*tab)[64], bool write,
                                             bool& read_once) {
@@ -178,7 +180,7 @@ __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets,
     }
     const int total = __builtin_amdgcn_readlane(inc_t, 63);
     const int active = __popcll(__ballot(rows > 0));
-    read_once = (total - active) * 100 <= 15 * total;
+    read_once = (total - active) * 100 <= (MU <= 2 ? 45 : 15) * total;
     return total * NT;
 }
 
