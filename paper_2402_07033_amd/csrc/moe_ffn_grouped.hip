@@ -15,9 +15,9 @@
 //   down  : per (token tile of 256 rows, 256 output features): yg = h.w2, fp32
 //
 // GEMM kernel (one 256 x 256 x 32 step = 1024 matrix-core clocks per SIMD).  What bounds it at
-// prefill size is the board's power: at 4096 tokens the matrix cores are busy 80 % of the
-// clocks, at 1.55-1.65 GHz; with all-zero tokens the same launch is 1.23 times as fast, and
-// halving the L2 misses or taking out 15 % of the clocks alone changed nothing.  In a loop of
+// prefill size is the board's power: with 32x32x16 the matrix cores were busy 80 % of the clocks
+// at 1.55-1.65 GHz, the same launch with all-zero tokens was 1.23 times as fast, and halving
+// the L2 misses changed nothing; with 16x16x32 they are busy 72 % at 1.85-1.93 GHz.  In a loop of
 // matrix instructions alone 16x16x32 sustains 2080 TFLOP/s on random operands, 32x32x16 1830,
 // which decides the instruction.  Below ~200 rows per expert the weight stream bounds it (5.5-6.4
 // TB/s).
@@ -40,22 +40,24 @@
 //   * the requests of a step are spread between the matrix instructions, one barrier per two
 //     steps publishes the next stages.  They are buffer loads: an address is a descriptor, the
 //     lane offset and one scalar, where 64-bit pointers per request filled the scalar registers
-//     and put ~100 instructions between the matrix instructions of a step, 60 now.
+//     (65..229 spills, 16..92 now); 55 other instructions stand beside the 64 matrix
+//     instructions of a full step, 61 with pointers.
 //   * the workgroup is persistent (one per CU) and the two load streams run across tile
 //     boundaries: while the last steps of a tile are multiplied, the first stages of the next
 //     one are already being requested.  The last groups of U steps of a tile are their own
 //     copies of the loop body, in which it is a compile-time matter which requests belong to
 //     the next tile.  The stores of a tile's result stay in flight during the next tile's first
 //     steps (loads and stores share one counter, and the first step's operands are older than
-//     the stores); waiting for them cost 3 us of every tile.
+//     the stores).
 //   * tiles are dealt in rounds of one tile per workgroup, an XCD taking 32 neighbours of the
 //     order expert, group of at most 8 token tiles, feature tile, token tile: about 8 x 4
 //     tiles, which share 12 operand tiles in one L2.  All XCDs work through the same experts at
 //     the same time, so an expert's size does not unbalance them.
 // Measured (start of the kernel with whole 256-row tiles, one tile order per XCD, 64-bit
-// pointers -> this): layer of 4096 tokens, 8 experts, Zipf 2.43 -> 2.30 ms; 1531 tokens 1.145 ->
-// 1.035; 4096 tokens, 16 experts 1.41 -> 1.28; 77 tokens 0.502 -> 0.476; 64 experts of f = 1408,
-// 300 tokens, k = 6 0.276 -> 0.248; 512 tokens, balanced, 0.612 -> 0.613.
+// pointers -> this): layer of 4096 tokens, 8 experts, Zipf 2.46 -> 2.33 ms; 1531 tokens 1.19 ->
+// 1.10; 4096 tokens, 16 experts 1.46 -> 1.29; 77 tokens 0.503 -> 0.473; 64 experts of f = 1408,
+// 300 tokens, k = 6 0.276 -> 0.237 (10 us of it the one-launch batching); a block of 512 tokens,
+// balanced, 0.625 -> 0.625 (4 us faster RMSNorm included).
 #include <atomic>
 
 #include "moe_internal.h"
