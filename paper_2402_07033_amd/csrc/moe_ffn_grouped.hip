@@ -62,6 +62,7 @@
 
 #include "moe_internal.h"
 #include "moe_frag_pack.h"
+#include "moe_gg_ring.h"
 
 // Tile shapes (token rows x weight fragment rows of 16 features per workgroup), by the mean
 // number of rows per expert:
@@ -70,24 +71,6 @@
 //   128 x 32 (128 tokens x 512 features): up to 96 rows -- twice the weight bytes per step,
 //           which is what bounds such experts.
 #define GG_THREADS 256
-#ifndef GG_NS
-#define GG_NS 8            // LDS stages of B fragments (one KiB per token block each)
-#endif
-// The weight fragments of step k are requested GG_LA steps earlier into a register ring that
-// is named statically, so the step loop is unrolled GG_U times (GG_LA < GG_U, reduction %
-// GG_U == 0; GG_LA <= GG_NS - 3, see the waits in the step).  The depth itself matters little
-// (2, 3, 4 and 5 steps are within 1 % at every size: what a CU may have in flight is full long
-// before); the 128 x 512 tile, which requests twice as much per step, keeps 2 steps, because a
-// third spills.
-#ifndef GG_U
-#define GG_U 4
-#endif
-#ifndef GG_LA
-#define GG_LA 3
-#endif
-#ifndef GG_WIDE_LA
-#define GG_WIDE_LA 2
-#endif
 #ifndef GG_WIDE_MAX_ROWS
 #define GG_WIDE_MAX_ROWS 96  // mean rows per expert up to which the 128 x 512 tile is used
 #endif
@@ -348,10 +331,11 @@ __device__ __forceinline__ unsigned gg_h_off(int lane) {
 template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS, bool ANT>
 __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, const int (*s_seg)[64]) {
     static_assert(NBW * FRW <= 64 && NBW % 4 == 0 && FRW % 4 == 0, "at most 64 MFMA tiles (256 accumulators) per wave");
-    static_assert(LA < U && LA <= NS - 3, "ring and stage depths, see the waits in the step");
+    static_assert(LA < U && U % GG_BARRIER_STEPS == 0, "register ring; a tile starts at a barrier step");
+    static_assert(gg_refill_ordered(NS, GG_AHEAD) && gg_arrival_ordered(GG_AHEAD, LA), "stage ring, see moe_gg_ring.h");
     constexpr int FROWS = 4 * FRW;     // fragment rows of the workgroup tile
     constexpr int NBQ = NBW / 4;       // token blocks each wave requests into LDS per step (= units)
-    constexpr int TG = (NS - 1 + U - 1) / U;  // groups at the end of a tile that look into the next
+    constexpr int TG = (GG_AHEAD + U - 1) / U;  // groups at the end of a tile that look into the next
     extern __shared__ __align__(16) unsigned char smem[];
     u32x4_t* lds = (u32x4_t*)smem;  // [NS stages][NBW fragments][64 lanes]
 
@@ -462,10 +446,10 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
 
     u32x4_t areg[U][FRW];  // [ring slot][fragment row]
 
-    // ---- prologue of the first tile: request stages 0..NS-2 and A of steps 0..LA-1 ----
+    // ---- prologue of the first tile: request stages 0..GG_AHEAD-1 and A of steps 0..LA-1 ----
     {
         const __amdgpu_buffer_rsrc_t ra = gg_rsrc(pa), rb = gg_rsrc(pb);
-        for (int j = 0; j < NS - 1; j++)
+        for (int j = 0; j < GG_AHEAD; j++)
 #pragma unroll
             for (int v = 0; v < NBQ; v++) issue_b(rb, vo_b[v] + j * 1024, j, v);
 #pragma unroll
@@ -508,9 +492,9 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
 #pragma unroll
             for (int u = 0; u < U; u++) {
                 // The weights of step k were requested LA steps ago, after that step's requests
-                // for stage k+NS-1-LA; requests retire in order, so with at most the last
+                // for stage k+GG_AHEAD-LA; requests retire in order, so with at most the last
                 // LA-1 steps' worth still in flight they have arrived, and so have the stages
-                // requested before them (LA <= NS-3: up to stage k+2).  (Steps issue VMIN
+                // requested before them (at least up to stage k+2).  (Steps issue VMIN
                 // requests or more.)  In a tile's first LA steps the previous tile's stores lie
                 // between those requests and the younger ones and may stay in flight as well.
                 __builtin_amdgcn_sched_barrier(0);
@@ -525,13 +509,13 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
                 }
                 // One barrier per TWO steps: at an even step every wave has waited for its
                 // shares of stages k+1 and k+2 (see above), so both are published here; and the
-                // buffers refilled during steps k and k+1 (stages k-1 and k) were last read
-                // before this barrier.
-                if ((u & 1) == 0) __builtin_amdgcn_s_barrier();
+                // slots refilled during steps k and k+1 held stages k-2 and k-1, whose reads
+                // every wave has waited for in its steps k-2 and k-1.
+                if (u % GG_BARRIER_STEPS == 0) __builtin_amdgcn_s_barrier();
                 const u32x4_t* pl = lds + ((g + u + 1) % NS) * NBW * 64 + lane;
                 auto issue = [&](const int v) {
                     if (v < NB) {
-                        const int jb = u + NS - 1;  // step of the group
+                        const int jb = u + GG_AHEAD;  // step of the group
                         if (Q == 0 || jb < Q * U)
                             issue_b(rb, vo_b[v] + kb + jb * 1024, g + jb, v);
                         else
@@ -857,7 +841,7 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
     return MOE_OK;
 }
 
-// The step loop is unrolled u times and looks ns-1 steps ahead.
+// The step loop is unrolled u times and the ring holds ns stages.
 static bool gg_fits(GgVariant v, int ks) {
     const GgShape sh = gg_shape(v);
     return ks % sh.u == 0 && ks >= sh.ns;
