@@ -294,12 +294,25 @@ struct GgInt {
     static constexpr int value = V;
 };
 
+// a / (1 + exp(-a)), to the bits of the fp32 division (16 M values of each of N(0,1), N(0,16) and
+// -90..90, infinities, NaN): the reciprocal estimate, then one correction of the quotient by its
+// exact residual.  The estimate is taken of a quarter of the denominator, because v_rcp_f32 flushes the
+// reciprocals of denominators above 2^126 (a < -87.3) to zero.  The compiler's division takes 11
+// instructions where these are 7: layer of 4096 tokens 2.419 -> 2.409 ms, with the estimate alone
+// (mean error 12 % larger) 2.392.
+__device__ __forceinline__ float gg_silu(float a) {
+    const float e = __expf(-a), den = 1.0f + e;
+    const float r = 0.25f * __builtin_amdgcn_rcpf(__builtin_fmaf(0.25f, e, 0.25f));
+    float q = a * r;
+    q = __builtin_fmaf(__builtin_fmaf(-q, den, a), r, q);
+    return __builtin_amdgcn_div_fixupf(q, den, a);
+}
+
 // First projection: h = silu(x.w1) * (x.w3) of two neighbouring 16-column blocks (a0, b0: the
 // w1 and w3 tiles of the even block; a1, b1: of the odd one), rounded to bf16, as B fragments of
 // the second GEMM.  Lane l of a tile holds token l % 16 and columns 4*(l/16) .. +3; after
 // exchanging the odd 16-lane rows of the even block with the even rows of the odd block every
 // lane holds eight columns, and the wave writes the token block's whole 1 KiB fragment.
-// (sigmoid by v_rcp_f32, 1 ulp: h is rounded to 8 bits of mantissa next.)
 __device__ __forceinline__ u32x4_t gg_make_h(const f32x4_t& a0, const f32x4_t& b0, const f32x4_t& a1,
                                              const f32x4_t& b1) {
     typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
@@ -311,7 +324,7 @@ __device__ __forceinline__ u32x4_t gg_make_h(const f32x4_t& a0, const f32x4_t& b
 #pragma unroll
         for (int r = 0; r < 2; r++) {
             const float av = (q < 2 ? a0 : a1)[2 * (q & 1) + r], bv = (q < 2 ? b0 : b1)[2 * (q & 1) + r];
-            hv[r] = av * __builtin_amdgcn_rcpf(1.0f + __expf(-av)) * bv;
+            hv[r] = gg_silu(av) * bv;
         }
         pk[q] = __builtin_bit_cast(unsigned, __builtin_convertvector(hv, bf2));
     }
