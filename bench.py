@@ -282,8 +282,6 @@ def kernel_label(moe, T, forced_path):
     fam = PATH_NAMES.get(pl["path"], str(pl["path"]))
     if fam == "stream":
         return "stream_kernel, first projection (x.w1, x.w3, silu*mul)", pl
-    if fam == "mid":
-        return "gg_pack + gg_gemm_kernel<UP> 128x512 tile + fix-up (x.w1, x.w3, silu*mul)", pl
     return (f"gg_pack + gg_gemm_kernel<UP> {pl['up_tile_rows']}x{pl['up_tile_features']} tile "
             "+ fix-up (x.w1, x.w3, silu*mul)"), pl
 

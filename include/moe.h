@@ -50,7 +50,7 @@ typedef enum {
     MOE_FFN_AUTO = 0,
     MOE_FFN_STREAM = 1, /* decode: weight-streaming MFMA kernels, <=16 rows per pass */
     MOE_FFN_GROUPED = 2, /* prefill: grouped LDS-tiled MFMA GEMM */
-    MOE_FFN_MID = 3      /* a handful of rows for each of many experts: grouped GEMM, weight-streaming tile */
+    MOE_FFN_MID = 3      /* a handful of rows for each of many experts: GROUPED's kernels, and f = 128 */
 } moe_ffn_path_t;
 
 typedef struct moe_weights moe_weights_t; /* opaque, library-owned */
@@ -125,8 +125,8 @@ size_t moe_expert_ffn_workspace(int N, int E, int d, int f, moe_dtype_t act_dtyp
  *   yg        [N,d] fp32 out
  * bf16-weight kernels multiply on the bf16 matrix cores: fp32 activations are
  * split into bf16 high and low parts (STREAM path, ~2^-16 relative) or rounded
- * to bf16 (GROUPED path); the intermediate silu(a)*b is kept in fp32 (STREAM)
- * or bf16 (GROUPED).  Every path adds its partial sums in a fixed order: the
+ * to bf16 (GROUPED, MID); the intermediate silu(a)*b is kept in fp32 (STREAM)
+ * or bf16 (GROUPED, MID).  Every path adds its partial sums in a fixed order: the
  * same inputs give the same bits on every run.
  */
 int moe_expert_ffn(const moe_weights_t* W, const void* xg, moe_dtype_t act_dtype,
@@ -174,7 +174,7 @@ size_t moe_expert_ffn_noalloc_max_bytes(void);
  *            one kernel pair of their own)
  *   n_parts  reduction parts of the second projection that moe_expert_ffn_parts leaves
  *            unsummed (1 unless STREAM)
- *   up_* / down_*  GROUPED: token rows x output features of the workgroup tile of the
+ *   up_* / down_*  GROUPED, MID: token rows x output features of the workgroup tile of the
  *            first / second projection (0 otherwise).  The first projection's features
  *            count w1 and w3 columns together.
  * Returns MOE_ERR_UNSUPPORTED if a forced family cannot run the shape.

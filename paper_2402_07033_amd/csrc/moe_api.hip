@@ -2,7 +2,8 @@
 // dispatch to the kernel launchers.  Nothing is enqueued when validation fails.
 #include "moe_internal.h"
 
-// mean rows per expert up to which AUTO takes the weight-streaming grouped GEMM
+// mean rows per expert up to which AUTO names MID: no crossover, but the range in which it serves
+// f = 128
 #ifndef MOE_MID_MAX_ROWS
 #define MOE_MID_MAX_ROWS 10
 #endif
@@ -25,9 +26,8 @@ static inline bool ranges_overlap(const void* a, size_t an, const void* b, size_
 // limit here):
 //   up to 72 routed rows the decode kernels, which stream each active expert once per
 //   16-row tile at ~6.5 TB/s;
-//   up to MOE_MID_MAX_ROWS rows per expert on average MID, above that GROUPED.  Both are the
-//   grouped GEMM: MID pins its weight-streaming 128 x 512 tile, which GROUPED chooses up to 96
-//   rows per expert as well, and serves f = 128.
+//   up to MOE_MID_MAX_ROWS rows per expert on average MID, above that GROUPED: the same launches,
+//   except that only MID serves f = 128.
 int moe_ffn_auto_path(int N, int E, int d, int f) {
     if (N <= 72 && moe_ffn_stream_supported(d, f)) return MOE_FFN_STREAM;
     if ((long long)N <= (long long)MOE_MID_MAX_ROWS * E && moe_ffn_mid_supported(N, E, d, f))
@@ -60,9 +60,7 @@ static int ffn_dispatch(const moe_weights_t* W, const void* xg, moe_dtype_t act_
     if (path == MOE_FFN_AUTO) path = moe_ffn_auto_path(N, W->E, W->d, W->f);
     if (path == MOE_FFN_STREAM)
         return moe_ffn_stream_launch(W, xg, act_dtype, perm, k, offsets, N, workspace, yg, nullptr, s);
-    if (path == MOE_FFN_MID)
-        return moe_ffn_mid_launch(W, xg, act_dtype, perm, k, offsets, N, workspace, yg, s);
-    return moe_ffn_grouped_launch(W, xg, act_dtype, perm, k, offsets, N, workspace, yg, s);
+    return moe_ffn_grouped_launch(path == MOE_FFN_MID, W, xg, act_dtype, perm, k, offsets, N, workspace, yg, s);
 }
 
 extern "C" {
@@ -175,10 +173,8 @@ int moe_expert_ffn_plan(int N, int E, int d, int f, moe_dtype_t w_dtype, int pat
     if (path == MOE_FFN_STREAM) {
         if (!moe_ffn_stream_supported(d, f)) return MOE_ERR_UNSUPPORTED;
         plan->n_parts = moe_ffn_stream_parts(N, d, f);
-    } else if (path == MOE_FFN_MID) {
-        if (!moe_ffn_mid_supported(N, E, d, f)) return MOE_ERR_UNSUPPORTED;
     } else {
-        return moe_ffn_grouped_plan(N, E, d, f, plan);
+        return moe_ffn_grouped_plan(path == MOE_FFN_MID, N, E, d, f, plan);
     }
     return MOE_OK;
 }

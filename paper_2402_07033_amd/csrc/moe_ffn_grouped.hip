@@ -765,6 +765,7 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
 
 // Second projection with fewer reduction steps than the pipelined kernel's stages (f = 128, which
 // MID serves): one wave per (token block, fragment row), straight from the fragments.
+#define GG_SHORT_FEATURES 64
 __global__ __launch_bounds__(256) void gg_down_short_kernel(GroupedArgs a) {
     SegInfo si;
     const int lane = threadIdx.x & 63;
@@ -864,7 +865,8 @@ static bool gg_fits(GgVariant v, int ks) {
 // real counts): up to GG_WIDE_MAX_ROWS the 128-token x 512-feature tile (needs f % 256 == 0
 // for the first projection, d % 512 == 0 for the second; each falls back on its own), then the
 // 192-token x 256-feature one in its two ranges, else 256 x 256.
-static bool gg_choose(int N, int E, int d, int f, GgVariant& vu, GgVariant& vd) {
+// short_down: the second projection's reduction is too short for the pipelined kernel (f = 128).
+static bool gg_choose(int N, int E, int d, int f, GgVariant& vu, GgVariant& vd, bool& short_down) {
     // up tile = 16 fragment rows = 8 column blocks x (w1,w3): f % 128 == 0;
     // down tile = 256 features: d % 256 == 0; both give reductions of >= 8 steps, step
     // counts that are multiples of 4.
@@ -881,21 +883,29 @@ static bool gg_choose(int N, int E, int d, int f, GgVariant& vu, GgVariant& vd) 
     // a variant whose loop does not fit a reduction gives way to the standard one
     if (!gg_fits(vu, d / 32)) vu = GG_STD;
     if (!gg_fits(vd, f / 32)) vd = GG_STD;
-    return gg_fits(vu, d / 32) && gg_fits(vd, f / 32);
+    short_down = !gg_fits(vd, f / 32);
+    return gg_fits(vu, d / 32);
 }
 
-int moe_ffn_grouped_plan(int N, int E, int d, int f, moe_ffn_plan_t* plan) {
+// GROUPED refuses f = 128, MID serves it up to a number of rows of its own (a forced path beyond
+// it stays refused); everything else is the same for both.
+static bool gg_path_choose(bool mid, int N, int E, int d, int f, GgVariant& vu, GgVariant& vd, bool& short_down) {
+    if (mid && (size_t)N / 192 + E > 192) return false;
+    return gg_choose(N, E, d, f, vu, vd, short_down) && (mid || !short_down);
+}
+
+int moe_ffn_grouped_plan(bool mid, int N, int E, int d, int f, moe_ffn_plan_t* plan) {
     GgVariant vu, vd;
-    if (!gg_choose(N, E, d, f, vu, vd)) return MOE_ERR_UNSUPPORTED;
+    bool short_down;
+    if (!gg_path_choose(mid, N, E, d, f, vu, vd, short_down)) return MOE_ERR_UNSUPPORTED;
     const GgShape su = gg_shape(vu), sd = gg_shape(vd);
     plan->up_tile_rows = 16 * su.tb;
     plan->up_tile_features = 16 * su.frows;
-    plan->down_tile_rows = 16 * sd.tb;
-    plan->down_tile_features = 16 * sd.frows;
+    plan->down_tile_rows = short_down ? 16 : 16 * sd.tb;
+    plan->down_tile_features = short_down ? GG_SHORT_FEATURES : 16 * sd.frows;
     return MOE_OK;
 }
 
-// short_down: the second projection's reduction is too short for the pipelined kernel.
 static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype, const int32_t* perm,
                      int k, const int32_t* offsets, int N, void* ws, float* yg, GgVariant vu, GgVariant vd,
                      bool short_down, hipStream_t s) {
@@ -959,7 +969,7 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
     dn.C = d;
     dn.part = part;
     if (short_down) {
-        hipLaunchKernelGGL(gg_down_short_kernel, dim3((unsigned)nb, (unsigned)(d / 64)), dim3(256), 0, s, dn);
+        hipLaunchKernelGGL(gg_down_short_kernel, dim3((unsigned)nb, (unsigned)(d / GG_SHORT_FEATURES)), dim3(256), 0, s, dn);
         return moe_launch_status();
     }
     rc = gg_launch_projection<false>(dn, vd, pgrid, s);
@@ -967,29 +977,23 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
     return moe_launch_status();
 }
 
-int moe_ffn_grouped_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
+// MID had kernels of its own (a wave streamed two adjacent fragment rows for up to 192 rows); with
+// token units the grouped GEMM's tiles are ahead at every size.  Up to 96 rows per expert (128 x 512
+// tile): 8 experts, 60..380 tokens, balanced 494..575 -> 468..551 us, Zipf 505..792 -> 464..680; 64
+// experts of f = 1408, 200..1000 tokens 268..489 -> 188..297.  Above, the tiles of GROUPED: 8 experts,
+// 480..800 tokens, balanced 650..1117 -> 575..671, Zipf 939..1119 -> 739..851 (the 128 x 512 tile there,
+// too: 660..773, slower than what it replaced up to 175 rows per expert).
+int moe_ffn_grouped_launch(bool mid, const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
                            const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
                            float* yg, hipStream_t s) {
     GgVariant vu, vd;
-    if (!gg_choose(N, W->E, W->d, W->f, vu, vd)) return MOE_ERR_UNSUPPORTED;
-    return gg_launch(W, xg, act_dtype, perm, k, offsets, N, ws, yg, vu, vd, false, s);
-}
-
-// MID is for a handful of rows for each of many experts; the limit on N is its own (a forced
-// path beyond it stays refused).  It had kernels of its own (a wave streamed two adjacent fragment
-// rows for up to 192 rows); with token units and the 128 x 512 tile the grouped GEMM is ahead at
-// every size of AUTO's window: 8 experts, 80 rows 486 -> 459 us; 16 experts, 96..160 rows, Zipf
-// 322..413 -> 305..368, balanced 444 -> 429; 64 experts of f = 1408, 80..640 rows 122..250 -> 103..173.
-bool moe_ffn_mid_supported(int N, int E, int d, int f) {
-    return f % 128 == 0 && d % 256 == 0 && (size_t)N / 192 + E <= 192;
-}
-
-int moe_ffn_mid_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
-                       const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
-                       float* yg, hipStream_t s) {
-    const int d = W->d, f = W->f;
-    if (!moe_ffn_mid_supported(N, W->E, d, f)) return MOE_ERR_UNSUPPORTED;
-    const GgVariant vu = f % 256 == 0 ? GG_WIDE : GG_STD, vd = d % 512 == 0 ? GG_WIDE : GG_STD;
-    const bool short_down = !gg_fits(vd, f / 32);
+    bool short_down;
+    if (!gg_path_choose(mid, N, W->E, W->d, W->f, vu, vd, short_down)) return MOE_ERR_UNSUPPORTED;
     return gg_launch(W, xg, act_dtype, perm, k, offsets, N, ws, yg, vu, vd, short_down, s);
+}
+
+bool moe_ffn_mid_supported(int N, int E, int d, int f) {
+    GgVariant vu, vd;
+    bool short_down;
+    return gg_path_choose(true, N, E, d, f, vu, vd, short_down);
 }

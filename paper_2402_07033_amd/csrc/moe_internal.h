@@ -92,17 +92,12 @@ int moe_ffn_stream_block_launch(const moe_weights* W, const float* x_in, const f
                                 float* gate_sums_next, hipStream_t s);
 
 size_t moe_ffn_grouped_workspace(int N, int E, int d, int f);
-int moe_ffn_grouped_plan(int N, int E, int d, int f, moe_ffn_plan_t* plan);  // fills the tile fields
-int moe_ffn_grouped_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
+// GROUPED and MID are one GEMM with the same tiles; `mid` serves f = 128 as well, up to a number of rows.
+int moe_ffn_grouped_plan(bool mid, int N, int E, int d, int f, moe_ffn_plan_t* plan);  // fills the tile fields
+int moe_ffn_grouped_launch(bool mid, const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
                            const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
                            float* yg, hipStream_t s);
-
-// The grouped GEMM with the 128-token x 512-feature tile whatever the number of rows; the same
-// workspace.
 bool moe_ffn_mid_supported(int N, int E, int d, int f);
-int moe_ffn_mid_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
-                       const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
-                       float* yg, hipStream_t s);
 
 // ---- small device helpers ------------------------------------------------------
 #ifdef __HIPCC__

@@ -126,6 +126,29 @@ def test_ffn_plan_query(L):
         m.moe_expert_ffn_plan(16, 8, 4096, 100)
 
 
+@pytest.mark.parametrize("E,d,f", [(8, 4096, 14336), (16, 4096, 6400), (64, 2048, 1408)])
+@pytest.mark.parametrize("mean", [4, 10, 60, 96, 97, 150, 176, 177, 232, 233, 256, 257, 380])
+def test_mid_runs_the_grouped_tiles(L, E, d, f, mean):
+    """MID and GROUPED are one GEMM: the same workgroup tiles at every number of rows."""
+    import paper_2402_07033_amd as m
+    mid = m.moe_expert_ffn_plan(mean * E, E, d, f, path=m.MOE_FFN_MID)
+    grouped = m.moe_expert_ffn_plan(mean * E, E, d, f, path=m.MOE_FFN_GROUPED)
+    assert mid.pop("path") == m.MOE_FFN_MID and grouped.pop("path") == m.MOE_FFN_GROUPED
+    assert mid == grouped and mid["up_tile_rows"] > 0
+    # the 512-feature tile needs f % 256 == 0 (first projection), d % 512 == 0 (second)
+    assert mid["up_tile_features"] == (512 if mean <= 96 and f % 256 == 0 else 256)
+
+
+def test_mid_serves_a_reduction_of_four_steps(L):
+    import paper_2402_07033_amd as m
+    pl = m.moe_expert_ffn_plan(80, 8, 512, 128, path=m.MOE_FFN_MID)
+    assert (pl["up_tile_rows"], pl["up_tile_features"]) == (256, 256)
+    assert (pl["down_tile_rows"], pl["down_tile_features"]) == (16, 64)
+    for N, path in ((80, m.MOE_FFN_GROUPED), (192 * 185, m.MOE_FFN_MID)):  # MID: N / 192 + E <= 192
+        with pytest.raises(m.MoeError):
+            m.moe_expert_ffn_plan(N, 8, 512, 128, path=path)
+
+
 def test_workspace_query(L):
     assert L.moe_expert_ffn_workspace(0, 8, 4096, 14336, 1) >= 256
     assert L.moe_expert_ffn_workspace(-1, 8, 4096, 14336, 1) == 0

@@ -54,8 +54,8 @@ def test_grouped_unit_edges(name, d, f):
     W.free()
 
 
-# MID pins the 128 x 512 tile (256 x 256 where f % 256 or d % 512 is not 0), whatever the number of
-# rows, and serves f = 128, whose second projection is too short for the pipelined kernel
+# MID: GROUPED's tiles (here the 128 x 512 one, 256 x 256 where f % 256 or d % 512 is not 0, and 192 x 256 at
+# 140 rows per expert), and f = 128, whose second projection is too short for the pipelined kernel
 @pytest.mark.parametrize("d,f", [(256, 128), (512, 128), (512, 384), (1024, 512)])
 @pytest.mark.parametrize("counts", [[33, 0, 17, 1], [1, 2, 0, 3], [130, 300, 64, 65]])
 def test_mid_path_shapes(d, f, counts):
