@@ -171,7 +171,7 @@ def _tiles_beyond_first(counts, tile_rows):
 # The tile shapes that the 32-layer stack at 512 tokens and the sweeps between decode and
 # prefill run, at the Mixtral shape, with balanced routing so that (nearly) every expert has a
 # single token tile and the kernel streams the weights past L2 (its device-side rule: token
-# tiles beyond an expert's first are at most 15 % of all token tiles).
+# tiles beyond an expert's first are at most 15 % of all token tiles; 45 % with the 128-row tile).
 @pytest.mark.parametrize("T,tile_rows,tile_features", [(512, 192, 256), (256, 128, 512),
                                                        (384, 128, 512)])
 def test_grouped_small_tiles_full_size(moe, mixtral, T, tile_rows, tile_features):
@@ -210,10 +210,11 @@ def test_grouped_small_tile_with_weights_through_l2_full_size(moe, mixtral):
 
 @pytest.mark.parametrize("T", [37, 40])
 def test_mid_kernel_full_size(moe, mixtral, T):
-    """73..80 routed rows at 8 experts: AUTO takes the weight-streaming grouped GEMM."""
+    """73..80 routed rows at 8 experts: AUTO's first calls of the grouped GEMM (named MID there)."""
     cfg = mi.MoEConfig(f"mid_t{T}", T, 4096, 14336, 8, 2, mi.BF16, mi.F32, 1200 + T, 1.2, 1002)
     x, logits, _ = mi.make_activations(cfg)
-    assert moe.moe_expert_ffn_plan(cfg.N, cfg.E, cfg.d, cfg.f)["path"] == moe.MOE_FFN_MID
+    pl = moe.moe_expert_ffn_plan(cfg.N, cfg.E, cfg.d, cfg.f)
+    assert (pl["path"], pl["up_tile_rows"], pl["down_tile_rows"]) == (moe.MOE_FFN_MID, 128, 128)
     out = _layer_with_nan_canary(moe, mixtral["W"], to_dev(x), to_dev(logits), cfg.k)
     rows = np.arange(cfg.N)  # every row
     e_yg, counts, n_tok = _check_sampled(moe, mixtral, cfg, x, logits, out, rows)

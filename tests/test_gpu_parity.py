@@ -160,24 +160,27 @@ def test_layer_bf16_stream_path(moe, T, d, f, E, k, xdt):
         assert e <= 1e-4  # hi/lo split keeps fp32 activations
 
 
-@pytest.mark.parametrize("T,d,f,E,k,xdt", [
-    (1, 256, 512, 8, 2, mi.F32), (100, 256, 512, 8, 2, mi.BF16), (600, 256, 384, 4, 2, mi.BF16),
-    (300, 512, 1024, 8, 2, mi.F32), (1100, 256, 256, 3, 1, mi.BF16),
-    # few rows per expert (tiles mostly padding); f = 2304 cuts left-over tiles along the
-    # reduction
-    (70, 256, 384, 8, 2, mi.F32), (150, 512, 2304, 8, 2, mi.BF16), (9, 256, 2048, 16, 2, mi.BF16),
-    # 41..96 rows per expert: the 128-token x 512-feature tile (first projection needs
-    # f % 256 == 0, second d % 512 == 0, else that projection keeps the default tile);
-    # d = 2048 / f = 2304 also cut left-over tiles along the reduction
-    (380, 1024, 2304, 8, 2, mi.BF16), (300, 256, 512, 8, 2, mi.F32), (330, 512, 384, 4, 1, mi.BF16),
-    (370, 2048, 512, 8, 2, mi.BF16),
-    # 97..256 rows per expert: the 192-token x 256-feature tile (hot experts span several
-    # tiles, the last one ragged); f = 2304 / d = 2048 cut left-over tiles along the reduction
-    (500, 512, 1024, 8, 2, mi.BF16), (900, 1024, 2304, 8, 2, mi.BF16), (1000, 256, 384, 8, 2, mi.F32),
-    (460, 2048, 512, 4, 1, mi.BF16)])
-def test_layer_bf16_grouped_path(moe, T, d, f, E, k, xdt):
+@pytest.mark.parametrize("T,d,f,E,k,xdt,up,down", [
+    # up to 96 rows per expert on average: the 128-token x 512-feature tile (first projection needs
+    # f % 256 == 0, second d % 512 == 0, else that projection has the 256 x 256 tile); d = 2048 /
+    # f = 2304 cut left-over tiles along the reduction
+    (1, 256, 512, 8, 2, mi.F32, 128, 256), (100, 256, 512, 8, 2, mi.BF16, 128, 256),
+    (300, 512, 1024, 8, 2, mi.F32, 128, 128), (70, 256, 384, 8, 2, mi.F32, 256, 256),
+    (150, 512, 2304, 8, 2, mi.BF16, 128, 128), (9, 256, 2048, 16, 2, mi.BF16, 128, 256),
+    (380, 1024, 2304, 8, 2, mi.BF16, 128, 128), (300, 256, 512, 8, 2, mi.F32, 128, 256),
+    (330, 512, 384, 4, 1, mi.BF16, 256, 128), (370, 2048, 512, 8, 2, mi.BF16, 128, 128),
+    # 97..176 and 233..256: the 192-token x 256-feature tile (hot experts span several tiles, the
+    # last one ragged); f = 2304 / d = 2048 cut left-over tiles along the reduction
+    (500, 512, 1024, 8, 2, mi.BF16, 192, 192), (600, 1024, 2304, 8, 2, mi.BF16, 192, 192),
+    (1000, 256, 384, 8, 2, mi.F32, 192, 192), (460, 2048, 512, 4, 1, mi.BF16, 192, 192),
+    # 177..232 and above 256: 256 x 256
+    (900, 1024, 2304, 8, 2, mi.BF16, 256, 256), (600, 256, 384, 4, 2, mi.BF16, 256, 256),
+    (1100, 256, 256, 3, 1, mi.BF16, 256, 256)])
+def test_layer_bf16_grouped_path(moe, T, d, f, E, k, xdt, up, down):
     cfg = mi.small_config("gg", T, d, f, E, k, 600 + T + d, w_dtype=mi.BF16, x_dtype=xdt,
                           zipf_s=1.2)
+    pl = moe.moe_expert_ffn_plan(cfg.N, E, d, f, path=moe.MOE_FFN_GROUPED)
+    assert (pl["up_tile_rows"], pl["down_tile_rows"]) == (up, down)
     _layer_parity(moe, cfg, mi.make_layer(cfg, threads=1), TOL_BF16, path=moe.MOE_FFN_GROUPED)
 
 
@@ -186,8 +189,8 @@ def test_layer_bf16_grouped_path(moe, T, d, f, E, k, xdt):
     (300, 512, 1024, 8, 2, mi.F32), (700, 256, 384, 4, 2, mi.BF16), (260, 1024, 2048, 16, 2, mi.F32),
     (150, 512, 2304, 8, 2, mi.BF16), (500, 256, 4096, 2, 1, mi.BF16)])
 def test_layer_bf16_mid_path(moe, T, d, f, E, k, xdt):
-    """Weight-streaming grouped GEMM: experts of 0 to several hundred rows (several 192-row
-    tiles), 4/8/12-block bodies, one and several reduction parts in the second projection."""
+    """MID, GROUPED's GEMM under its own name: experts of 0 to several hundred rows, all three tiles
+    (2 to 350 rows per expert), whole tiles and pieces in the second projection."""
     cfg = mi.small_config("md", T, d, f, E, k, 700 + T + d, w_dtype=mi.BF16, x_dtype=xdt,
                           zipf_s=1.2)
     _layer_parity(moe, cfg, mi.make_layer(cfg, threads=1), TOL_BF16, path=moe.MOE_FFN_MID)
@@ -289,12 +292,13 @@ def test_all_tokens_to_one_expert_and_k_equals_E(moe, path_name, T, xdt):
 def test_single_expert_layer_and_auto_threshold(moe):
     cfg = mi.small_config("E1", 9, 256, 512, 1, 1, 77, w_dtype=mi.BF16)
     _layer_parity(moe, cfg, mi.make_layer(cfg, threads=1), TOL_BF16)
-    # AUTO on either side of its switches: decode kernels up to 72 routed rows, the
-    # weight-streaming grouped GEMM up to 10 rows per expert (80 rows here), then the
-    # LDS-tiled grouped GEMM (128 x 512 tile up to 96 rows per expert, 192 x 256 up to 256,
-    # 256 x 256 above)
-    for T in (36, 37, 40, 41, 384, 385, 1024, 1025):
+    # AUTO on either side of its switches: decode kernels up to 72 routed rows, the grouped GEMM as
+    # MID up to 10 rows per expert (80 rows here) and as GROUPED above: 128 x 512 tile up to 96
+    # rows per expert, 192 x 256 up to 176 and from 233 to 256, 256 x 256 otherwise
+    for T, tile in ((36, 0), (37, 128), (40, 128), (41, 128), (384, 128), (385, 192), (704, 192),
+                    (705, 256), (928, 256), (929, 192), (1024, 192), (1025, 256)):
         cfg = mi.small_config("thr", T, 256, 512, 8, 2, 80 + T, w_dtype=mi.BF16, zipf_s=1.2)
+        assert moe.moe_expert_ffn_plan(cfg.N, 8, 256, 512)["up_tile_rows"] == tile
         _layer_parity(moe, cfg, mi.make_layer(cfg, threads=1), TOL_BF16)
 
 
