@@ -75,9 +75,14 @@
 #define GG_WIDE_MAX_ROWS 96  // mean rows per expert up to which the 128 x 512 tile is used
 #endif
 // ... up to which the 192 x 256 tile is used, and the range above it where the 256 x 256 tile comes
-// first: experts of 177..232 rows on average mostly fit one 256-row tile and need two of 192 (212
-// rows, balanced: 0.77 -> 0.70 ms; 16 experts 0.77 -> 0.63); around 250 rows half of them need two
-// of either, and the smaller tile is 3-5 % ahead.
+// first: experts of 177..232 rows on average mostly fit one 256-row tile and need two of 192.  At 36
+// sizes and routings there: balanced 2-33 % ahead (200 rows: 877 -> 671 us over 8 experts, 803 -> 604
+// over 16); Zipf 0.6 and 1.2, where the mean describes no expert, from 1 % behind to 8 % ahead at 23 of
+// 24, 4 % behind at one (64 experts, 177 rows).  Around 250 rows
+// half of the experts need two of either, and the smaller tile is 2-17 % ahead, balanced.  (In the 192-row
+// tile's two ranges skewed routing has it from 11 % behind to 3 % ahead of the 256-row one, and
+// the ranges' inner ends are not sharp: balanced, 172 rows 1 % ahead over 8 experts, 9 % behind over
+// 16; 235 rows 2-12 % behind.)
 #define GG_R192_MAX_ROWS 176
 #define GG_R192_MIN_ROWS2 233
 #define GG_R192_MAX_ROWS2 256
@@ -138,7 +143,9 @@ struct TileInfo {
 // are streamed.  The rule: token tiles beyond the first of an expert make up at most 15 % of
 // all token tiles (measured crossover with the 192-row tile: 11 % wins 8 %, 27 % loses 2.5 %, 50 %
 // loses 13 %; 256-row tile, 50 % and more: loses 4-5 %); with the 128-row x 512-feature tile at most
-// 45 % (20..30 %: wins 2-8 % over 16 and 64 experts, 3 % and -0.6 % over 8).
+// 45 %, measured at 32 sizes and routings over 8, 16 and 64 experts: 16..28 % wins 1-9 % at 19 of 24 and
+// loses at most 2 % at the others; 29..40 % is even, from 5 % won (8 experts, one of 640 rows) to 3 % lost
+// (16 experts, one of 1100 rows).
 __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets, int E, int N,
                                             int NT, int MU, int lane, int (*tab)[64], bool write,
                                             bool& read_once) {
@@ -297,12 +304,13 @@ struct GgInt {
 // a / (1 + exp(-a)), to the bits of the fp32 division (16 M values of each of N(0,1), N(0,16) and
 // -90..90, infinities, NaN): the reciprocal estimate, then one correction of the quotient by its
 // exact residual.  The estimate is taken of a quarter of the denominator, because v_rcp_f32 flushes the
-// reciprocals of denominators above 2^126 (a < -87.3) to zero.  The compiler's division takes 11
-// instructions where these are 7: layer of 4096 tokens 2.419 -> 2.409 ms, with the estimate alone
-// (mean error 12 % larger) 2.392.
+// reciprocals of denominators above 2^126 (a < -87.3) to zero.  (ldexp: 0.25 is no inline constant,
+// and a register for it spills in the 256-row tile.)  The compiler's division takes 11 instructions
+// where these are 8: layer of 4096 tokens 2.419 -> 2.409 ms; with the estimate alone (mean error 12 %
+// larger, zero below -87.3) 2.392.
 __device__ __forceinline__ float gg_silu(float a) {
     const float e = __expf(-a), den = 1.0f + e;
-    const float r = 0.25f * __builtin_amdgcn_rcpf(__builtin_fmaf(0.25f, e, 0.25f));
+    const float r = __builtin_ldexpf(__builtin_amdgcn_rcpf(__builtin_ldexpf(den, -2)), -2);
     float q = a * r;
     q = __builtin_fmaf(__builtin_fmaf(-q, den, a), r, q);
     return __builtin_amdgcn_div_fixupf(q, den, a);
