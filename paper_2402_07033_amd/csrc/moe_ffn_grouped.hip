@@ -14,22 +14,24 @@
 //           hp [block][f/32] for the second GEMM
 //   down  : per (token tile of 256 rows, 256 output features): yg = h.w2, fp32
 //
-// GEMM kernel (one 256 x 256 x 32 step = 1024 matrix-core clocks per SIMD).  What bounds it at
-// prefill size is the board's power: with 32x32x16 the matrix cores were busy 80 % of the clocks
-// at 1.55-1.65 GHz, the same launch with all-zero tokens was 1.23 times as fast, and halving
-// the L2 misses changed nothing; with 16x16x32 they are busy 72 % at 1.85-1.93 GHz.  In a loop of
-// matrix instructions alone 16x16x32 sustains 2080 TFLOP/s on random operands, 32x32x16 1830,
-// which decides the instruction.  Below ~200 rows per expert the weight stream bounds it (5.5-6.4
-// TB/s).
+// GEMM kernel (one 256 x 256 x 32 step = 1024 matrix-core clocks per SIMD).  What bounds it: a step
+// takes about 0.75 us whatever its number of matrix instructions.  At 4096 tokens nearly all tiles
+// are full, the matrix cores are busy 69-70 % of the clocks, and the board's power holds these at
+// 1.6-1.85 GHz (an earlier loop on 32x32x16 was 1.23 times as fast on all-zero tokens); at 1531 tokens,
+// or with 16 experts, they are busy 53-57 %.  Below ~200 rows per expert the weight stream bounds it
+// (5.5-6.4 TB/s).
 //   * workgroup tile: up to 256 token rows x 16 weight fragment rows, 4 waves, one per
 //     SIMD; wave w owns fragment rows 4w..4w+3 for all token rows: 64 MFMA tiles = 256
 //     accumulator registers (pinned to the accumulation register file through the inline-asm
-//     constraint).
+//     constraint).  16x16x32 and not 32x32x16: in a loop of this tile's matrix instructions alone,
+//     written for that comparison, the first sustained 2080 TFLOP/s on random operands, the other 1830.
 //   * token rows come in units of 64 (4 blocks of 16).  An expert's units are dealt evenly to
 //     its tiles, and the step loop exists once per number of units (1..4): a tile that is not
-//     full costs only the matrix instructions, LDS reads and token requests of its own units.
+//     full issues only the matrix instructions, LDS reads and token requests of its own units.
 //     Skewed routing leaves every expert's last tile partly filled: with whole tiles of 256
-//     rows 34 % of the matrix work of 3062 rows (8 experts) was padding, with units 7 %.
+//     rows 34 % of the matrix work of 3062 rows (8 experts) was padding, with units 8 %.  The gain
+//     in time is smaller, since a step costs the same: 16 experts, 4096 tokens, first projection
+//     813 -> 771 us.
 //   * weights (A) never touch LDS: each wave streams its own fragments straight from global
 //     memory into a register ring, LA steps ahead (the packed layout makes these 1 KiB
 //     coalesced loads with no redundancy between waves).
@@ -38,10 +40,10 @@
 //     of the next step while it issues the matrix instructions of the current one (one register
 //     set, refilled in place right after its last use).
 //   * the requests of a step are spread between the matrix instructions, one barrier per two
-//     steps publishes the next stages.  They are buffer loads: an address is a descriptor, the
-//     lane offset and one scalar, where 64-bit pointers per request filled the scalar registers
-//     (65..229 spills, 16..92 now); 55 other instructions stand beside the 64 matrix
-//     instructions of a full step, 61 with pointers.
+//     steps publishes the next stages (the order of the ring: moe_gg_ring.h).  They are buffer loads:
+//     an address is a descriptor, the lane offset and one scalar, where 64-bit pointers per request
+//     filled the scalar registers (65..229 spills, 26..88 now); 55 other instructions stand beside the
+//     64 matrix instructions of a full step, 61 with pointers.
 //   * the workgroup is persistent (one per CU) and the two load streams run across tile
 //     boundaries: while the last steps of a tile are multiplied, the first stages of the next
 //     one are already being requested.  The last groups of U steps of a tile are their own
@@ -52,12 +54,13 @@
 //   * tiles are dealt in rounds of one tile per workgroup, an XCD taking 32 neighbours of the
 //     order expert, group of at most 8 token tiles, feature tile, token tile: about 8 x 4
 //     tiles, which share 12 operand tiles in one L2.  All XCDs work through the same experts at
-//     the same time, so an expert's size does not unbalance them.
-// Measured (start of the kernel with whole 256-row tiles, one tile order per XCD, 64-bit
-// pointers -> this): layer of 4096 tokens, 8 experts, Zipf 2.46 -> 2.33 ms; 1531 tokens 1.19 ->
-// 1.10; 4096 tokens, 16 experts 1.46 -> 1.29; 77 tokens 0.503 -> 0.473; 64 experts of f = 1408,
-// 300 tokens, k = 6 0.276 -> 0.237 (10 us of it the one-launch batching); a block of 512 tokens,
-// balanced, 0.625 -> 0.625 (4 us faster RMSNorm included).
+//     the same time, so an expert's size does not unbalance them.  One contiguous range of tiles
+//     per XCD, otherwise the same kernel, hits L2 more often and is slower: 4096 tokens 2.308 ->
+//     2.340 ms, 1531 tokens 1.045 -> 1.056, block of 512 0.608 -> 0.615, 16 experts even.
+// Measured (kernel with whole 256-row tiles, one tile range per XCD, 64-bit pointers -> this): layer
+// of 4096 tokens, 8 experts, Zipf 2.46 -> 2.35 ms; 1531 tokens 1.19 -> 1.07; 4096 tokens, 16 experts
+// 1.46 -> 1.30; 77 tokens 0.518 -> 0.487; 64 experts of f = 1408, 300 tokens, k = 6 0.276 -> 0.238 (10 us of
+// it the one-launch batching); a block of 512 tokens, balanced, 0.63 before and after.
 #include <atomic>
 
 #include "moe_internal.h"

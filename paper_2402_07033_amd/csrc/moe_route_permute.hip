@@ -176,8 +176,9 @@ __device__ void permute_indices(const int32_t* __restrict__ idx, int N, int E,
 // Bound: reading idx from L2 in every workgroup (N * 4 bytes each), then the row copy.  One
 // workgroup for all N slots (and a second launch that read every row k times) took 15 + 21 us at
 // 4096 tokens, k = 2, 8 KiB rows, and 14 us for the indices of 300 tokens, k = 6, 64 experts;
-// this one launch 25 and 4 us.  Routing, batching and combine together: 4096 tokens, k = 2 76 ->
-// 62 us; 8192 tokens, k = 6, 64 experts, 4 KiB rows 465 -> 179 us.
+// this one launch 25 and 5 us.  Routing, batching and combine together, repeated on the same buffers:
+// 4096 tokens, k = 2 75.4 -> 61.7 us (80.7 -> 67.7 with inputs that change); 8192 tokens, k = 6, 64
+// experts, 4 KiB rows 452 -> 173 us.
 #define PM_THREADS 512
 #define PM_WAVES (PM_THREADS / 64)
 #define PM_MAX_SLOTS 1024  // slots of a workgroup whose positions are kept for the row copy
@@ -368,7 +369,8 @@ int moe_combine_launch(const float* yg, const int32_t* inv_perm, const float* we
 // Sum over the wave's 64 lanes, in every lane, without the LDS: inside a row of 16 lanes by DPP
 // (neighbours, pairs, then the mirrored half and the mirrored row), across rows by the two lane
 // swaps.  (__shfl_xor goes through the LDS, 108 times per wave and 16 waves per CU: with it, and with
-// the sums of 16 experts where there are 8, norm_logits_kernel took 18 us at 512 tokens, now 12.)
+// the sums of 16 experts where there are 8, norm_logits_kernel took 13.7 us at 512 tokens in a stack of
+// layers, now 10.6.)
 __device__ __forceinline__ float wave_sum(float v) {
     auto dpp = [](float a, auto ctrl) {
         return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), decltype(ctrl)::value,
