@@ -213,11 +213,16 @@ __global__ __launch_bounds__(PM_THREADS) void permute_kernel(
     __shared__ int s_pos[GATHER ? PM_MAX_SLOTS : 1];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int i = tid; i < PM_WAVES * 2 * MOE_MAX_E; i += PM_THREADS) (&s_hist[0][0][0])[i] = 0;
-    __syncthreads();
+    // (a wave clears and fills its own histogram only: its LDS operations are in order)
+    s_hist[wave][0][lane] = 0;
+    s_hist[wave][1][lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     const int slot0 = blockIdx.x * tpw * k;  // (grid * tpw tokens: below 2^25 slots)
     const int slots = (N - slot0) < tpw * k ? (N - slot0) : tpw * k;
     auto expert = [&](int e) { return e < 0 ? 0 : (e >= E ? E - 1 : e); };
+    // wave 0's first group of its own slots, requested before the count instead of behind it
+    const int own = (wave == 0 && lane < slots) ? idx[slot0 + lane] : 0;
     for (int p = tid * 4; p < N; p += PM_THREADS * 4) {
         int e[4];
         if (p + 4 <= N) {
@@ -260,7 +265,7 @@ __global__ __launch_bounds__(PM_THREADS) void permute_kernel(
         for (int g = 0; g < slots; g += 64) {
             const int p = slot0 + g + lane;
             const bool live = g + lane < slots;
-            const int e = live ? expert(idx[p]) : 0;
+            const int e = live ? expert(g == 0 ? own : idx[p]) : 0;
             unsigned long long same = __ballot(live);
 #pragma unroll
             for (int b = 0; b < 6; b++) {  // E <= 64
