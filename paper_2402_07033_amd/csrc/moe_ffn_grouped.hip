@@ -17,8 +17,8 @@
 // GEMM kernel (one 256 x 256 x 32 step = 1024 matrix-core clocks per SIMD).  What bounds it: a step
 // takes about 0.75 us whatever its number of matrix instructions.  At 4096 tokens nearly all tiles
 // are full, the matrix cores are busy 69-70 % of the clocks, and the board's power holds these at
-// 1.6-1.85 GHz (an earlier loop on 32x32x16 was 1.23 times as fast on all-zero tokens); at 1531 tokens,
-// or with 16 experts, they are busy 53-57 %.  Below ~200 rows per expert the weight stream bounds it
+// 1.6-1.9 GHz (an earlier loop on 32x32x16 was 1.23 times as fast on all-zero tokens); at 1531 tokens,
+// or with 16 experts, they are busy 52-57 %.  Below ~200 rows per expert the weight stream bounds it
 // (5.5-6.4 TB/s).
 //   * workgroup tile: up to 256 token rows x 16 weight fragment rows, 4 waves, one per
 //     SIMD; wave w owns fragment rows 4w..4w+3 for all token rows: 64 MFMA tiles = 256
