@@ -81,11 +81,10 @@
 // first: experts of 177..232 rows on average mostly fit one 256-row tile and need two of 192.  At 36
 // sizes and routings there: balanced 2-33 % ahead (200 rows: 877 -> 671 us over 8 experts, 803 -> 604
 // over 16); Zipf 0.6 and 1.2, where the mean describes no expert, from 1 % behind to 8 % ahead at 23 of
-// 24, 4 % behind at one (64 experts, 177 rows).  Around 250 rows
-// half of the experts need two of either, and the smaller tile is 2-17 % ahead, balanced.  (In the 192-row
-// tile's two ranges skewed routing has it from 11 % behind to 3 % ahead of the 256-row one, and
-// the ranges' inner ends are not sharp: balanced, 172 rows 1 % ahead over 8 experts, 9 % behind over
-// 16; 235 rows 2-12 % behind.)
+// 24, 4 % behind at one (64 experts, 177 rows).  Around 250 rows half of the experts need two of either,
+// and the smaller tile is 2-17 % ahead, balanced.  (In the 192-row tile's two ranges skewed routing has
+// it from 11 % behind to 3 % ahead of the 256-row one, and the ranges' inner ends are not sharp:
+// balanced, 172 rows 1 % ahead over 8 experts, 9 % behind over 16; 235 rows 2-12 % behind.)
 #define GG_R192_MAX_ROWS 176
 #define GG_R192_MIN_ROWS2 233
 #define GG_R192_MAX_ROWS2 256
