@@ -551,23 +551,38 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
                             areg[ja % U][j] = gg_ld_a<ANT>(ra_n, voff, (ja - Q * U) * 1024 + j * row_bytes);
                     }
                 };
+                // One other instruction at most between two matrix instructions where it can be: a
+                // matrix instruction takes 16 clocks and the wave issues one instruction per 4, so
+                // runs of others (they stood behind every eighth, seven in a row) leave the
+                // matrix cores idle.  The order over the tile is a snake: from one matrix instruction to the
+                // next only one of the two operands changes, which costs less power, and power bounds
+                // the clock of full tiles.  (Masks: scalar instructions may move.)  Runs and no snake ->
+                // this, both projections: 4096 tokens Zipf 2187 -> 2130 us, 8 x 1024 rows 2036 -> 1978, 1531
+                // tokens Zipf 995 -> 972; about half of it each.
 #pragma unroll
                 for (int i = 0; i < B; i++) {
-                    // the vector-memory requests are spread evenly over the blocks, so that the
-                    // requests of the four waves never queue up in front of the matrix
-                    // instructions
-#pragma unroll
-                    for (int v = (i * VREQ + B - 1) / B; v < ((i + 1) * VREQ + B - 1) / B; v++) issue(v);
-                    // LDS reads return in order: with at most B-2 younger ones in flight,
+                    // LDS reads return in order: with at most that many younger ones in flight,
                     // breg[i] and breg[i+1] (refilled one step ago) have arrived
-                    if ((i & 1) == 0) GG_WAIT_LGKM(B - 2);
+                    if (i == 0) GG_WAIT_LGKM(B - 2);
+                    else if ((i & 1) == 0) GG_WAIT_LGKM(B - 3);
 #pragma unroll
-                    for (int j = 0; j < FRW; j++) {
+                    for (int jj = 0; jj < FRW; jj++) {
+                        const int j = (i & 1) ? FRW - 1 - jj : jj;
+                        __builtin_amdgcn_sched_barrier(4);
                         if (FIRST && u == 0) gg_mfma_first(acc[i][j], areg[u][j], breg[i]);
                         else gg_mfma(acc[i][j], areg[u][j], breg[i]);
+                        __builtin_amdgcn_sched_barrier(4);
+                        if (jj == 0 && i > 0) breg[i - 1] = pl[(i - 1) * 64];
+                        // the vector-memory requests are spread evenly over the blocks, so that the
+                        // requests of the four waves never queue up in front of the matrix
+                        // instructions
+#pragma unroll
+                        for (int v = 0; v < VREQ; v++)
+                            if ((((2 * v + 1) * B * FRW / (2 * VREQ)) & ~3) + 2 == i * FRW + jj) issue(v);
                     }
-                    breg[i] = pl[i * 64];
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                breg[B - 1] = pl[(B - 1) * 64];
             }
             g += U;
             kb += U * 1024;
