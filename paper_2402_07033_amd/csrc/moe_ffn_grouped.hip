@@ -120,6 +120,7 @@ struct TileInfo {
     int blk0;   // first block of the tile inside the segment
     int nblk;   // blocks of the tile that exist
     int units;  // units of 4 blocks (the last one may hold fewer blocks)
+    int once;   // the expert's only token tile: its weights are read once
     // the part of the tile's reduction this unit of work covers (whole tile: 0, KS)
     int k_lo, klen;
     bool partial;
@@ -141,16 +142,8 @@ struct TileInfo {
 #define GG_SEG_FIELDS 6
 
 // One wave fills the table (lane e: expert e); returns the number of logical tiles.
-// read_once: are the weights of (nearly) every expert read by a single token tile?  Then they
-// are streamed.  The rule: token tiles beyond the first of an expert make up at most 15 % of
-// all token tiles (measured crossover with the 192-row tile: 11 % wins 8 %, 27 % loses 2.5 %, 50 %
-// loses 13 %; 256-row tile, 50 % and more: loses 4-5 %); with the 128-row x 512-feature tile at most
-// 45 %, measured at 32 sizes and routings over 8, 16 and 64 experts: 16..28 % wins 1-9 % at 19 of 24 and
-// loses at most 2 % at the others; 29..40 % is even, from 5 % won (8 experts, one of 640 rows) to 3 % lost
-// (16 experts, one of 1100 rows).
 __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets, int E, int N,
-                                            int NT, int MU, int lane, int (*tab)[64], bool write,
-                                            bool& read_once) {
+                                            int NT, int MU, int lane, int (*tab)[64], bool write) {
     int lo, rows;
     gg_segment_of_lane(offsets, E, N, lane, lo, rows);
     const int nb = (rows + 15) / 16;
@@ -172,10 +165,7 @@ __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets,
         tab[GG_SEG_BASE][lane] = (inc_t - tiles) * NT;
         tab[GG_SEG_BB][lane] = inc_b - nb;
     }
-    const int total = __builtin_amdgcn_readlane(inc_t, 63);
-    const int active = __popcll(__ballot(rows > 0));
-    read_once = (total - active) * 100 <= (MU <= 2 ? 45 : 15) * total;
-    return total * NT;
+    return __builtin_amdgcn_readlane(inc_t, 63) * NT;
 }
 
 // Logical tile index -> tile, from the table.
@@ -202,6 +192,7 @@ __device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lan
     ti.si.row0 = __builtin_amdgcn_readfirstlane(tab[GG_SEG_LO][e]);
     ti.si.rows = __builtin_amdgcn_readfirstlane(tab[GG_SEG_ROWS][e]);
     ti.si.bbase = __builtin_amdgcn_readfirstlane(tab[GG_SEG_BB][e]);
+    ti.once = tiles == 1;
     // the expert's units, dealt evenly to its tiles
     const int nu = (nb + GG_UNIT_BLOCKS - 1) / GG_UNIT_BLOCKS;
     const int per = nu / tiles, more = nu % tiles;  // the first `more` tiles take one more
@@ -254,9 +245,14 @@ __device__ __forceinline__ int gg_piece_cut(int j, int S, int KS, int wgs, int u
     return c;
 }
 
-// Weight fragment load.  ANT: non-temporal - when nearly every expert has a single token
-// tile its weights are read once and should not push the token fragments (re-read by every
-// feature tile) out of L2.
+// Weight fragment load.  ANT: non-temporal, for a tile whose expert has no other token tile: its
+// weights are read once, should not push the token fragments (re-read by every feature tile) out of
+// L2, and a plain read of 1.75 GiB streams at 6.9 TB/s that way, at 6.0 otherwise.  Weights that several
+// token tiles share stay in L2: past it, 27 % second tiles lose 2.5 %, 50 % lose 13 % (192-row tile).
+// Chosen per tile (two more copies of the step loop for each number of units) instead of once for the
+// launch by the share of second tiles, both projections: 8 experts, Zipf, 300 tokens 641 -> 627 us, 600 tokens
+// 795 -> 777, 16 experts, 4096 tokens 1181 -> 1169, 64 experts, 300 tokens 224 -> 220, balanced 512 tokens 603 ->
+// 599; 1531 and 4096 tokens within 0.3 %.
 template <bool ANT>
 __device__ __forceinline__ u32x4_t gg_ld_a(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
     // (cache policy 2: nt)
@@ -351,7 +347,7 @@ __device__ __forceinline__ unsigned gg_h_off(int lane) {
 // MODE: which units of work a launch covers: 0 = whole tiles and pieces, 1 = whole tiles only,
 // 2 = pieces only.
 // NBW x FRW: token blocks of the tile, at most, x fragment rows of a wave.
-template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS, bool ANT>
+template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS>
 __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, const int (*s_seg)[64]) {
     static_assert(NBW * FRW <= 64 && NBW % 4 == 0 && FRW % 4 == 0, "at most 64 MFMA tiles (256 accumulators) per wave");
     static_assert(LA < U && U % GG_BARRIER_STEPS == 0, "register ring; a tile starts at a barrier step");
@@ -478,7 +474,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
 #pragma unroll
         for (int s = 0; s < LA; s++)
 #pragma unroll
-            for (int j = 0; j < FRW; j++) areg[s][j] = gg_ld_a<ANT>(ra, voff, s * 1024 + j * row_bytes);
+            for (int j = 0; j < FRW; j++) areg[s][j] = gg_ld_a<false>(ra, voff, s * 1024 + j * row_bytes);
     }
     GG_WAIT_VMCNT(0);
     __builtin_amdgcn_s_barrier();
@@ -488,8 +484,10 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
     int stores = 0;  // store instructions of the previous tile's epilogue (at least)
 
     // one tile of B token blocks (B = 4 * units)
-    auto tile = [&](auto blocks) {
+    // (its last groups request the next tile's first weights, with this tile's policy)
+    auto tile = [&](auto blocks, auto once) {
         constexpr int B = decltype(blocks)::value;
+        constexpr bool ANT = decltype(once)::value != 0;
         constexpr int VMIN = FRW + B / 4;  // requests of a step, at least
         f32x4_t acc[B][FRW];
         u32x4_t breg[B];
@@ -657,12 +655,16 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
 
     for (;;) {
         // by the number of units of the tile, 1 .. NBW / 4
-        if (cur.units == 1) tile(GgInt<4>{});
-        else if (NBW == 8 || cur.units == 2) tile(GgInt<8>{});
-        else if constexpr (NBW >= 12) {
-            if (NBW == 12 || cur.units == 3) tile(GgInt<12>{});
-            else if constexpr (NBW >= 16) tile(GgInt<16>{});
-        }
+        auto units = [&](auto once) {
+            if (cur.units == 1) tile(GgInt<4>{}, once);
+            else if (NBW == 8 || cur.units == 2) tile(GgInt<8>{}, once);
+            else if constexpr (NBW >= 12) {
+                if (NBW == 12 || cur.units == 3) tile(GgInt<12>{}, once);
+                else if constexpr (NBW >= 16) tile(GgInt<16>{}, once);
+            }
+        };
+        if (cur.once) units(GgInt<1>{});
+        else units(GgInt<0>{});
         if (!has_next) {
             // the unconditional look-ahead of the last steps is still in flight (some of it on
             // its way into LDS): it must land before the workgroup gives its LDS back
@@ -685,19 +687,13 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
     }
 }
 
-// The two load flavours are two copies of the whole persistent loop: nothing is live across
-// the choice (a choice per tile inside one loop made the compiler spill the accumulators).
 template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS>
 __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
     __shared__ int s_seg[GG_SEG_FIELDS][64];
-    bool read_once;
     const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, threadIdx.x & 63, s_seg,
-                                   threadIdx.x < 64, read_once);
+                                   threadIdx.x < 64);
     __syncthreads();
-    if (read_once)
-        gg_gemm_body<UP, NBW, FRW, MODE, U, LA, NS, true>(a, total, s_seg);
-    else
-        gg_gemm_body<UP, NBW, FRW, MODE, U, LA, NS, false>(a, total, s_seg);
+    gg_gemm_body<UP, NBW, FRW, MODE, U, LA, NS>(a, total, s_seg);
 }
 
 // Adds the pieces of every left-over tile in the order of the workgroups that produced them
@@ -716,8 +712,7 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
     __shared__ int s_seg[GG_SEG_FIELDS][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    bool read_once;
-    const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, lane, s_seg, threadIdx.x < 64, read_once);
+    const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, lane, s_seg, threadIdx.x < 64);
     const int left = total % (wgs * 8);
     __syncthreads();
     for (int item = blockIdx.x; item < left * NBW; item += gridDim.x) {
