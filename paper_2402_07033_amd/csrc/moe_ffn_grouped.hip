@@ -105,7 +105,7 @@ struct GroupedArgs {
     int NT;      // workgroup tiles along the features = FR / FROWS
     int KS_out;  // up: f/32 (fragment columns of hp); down: unused
     int C;       // down: d (row length of yg)
-    int split;   // deal the left-over tiles of each XCD in pieces of their reduction
+    int split;   // left-over tiles are cut in pieces if they are at most split/32 of a round (0: never)
     float* part; // split: partial tiles [8 XCDs][workgroups per XCD][2][256*256] fp32
 };
 
@@ -206,14 +206,28 @@ __device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lan
     return true;
 }
 
-// Whole tiles go out in n_full rounds of one tile per workgroup; the tiles of the last,
-// incomplete round are dealt to the XCDs evenly and split there (see the body below).
+// Whole tiles go out in n_full rounds of one tile per workgroup.  The tiles of the last, incomplete
+// round are dealt to the XCDs evenly, and cut there along the reduction so that all workgroups
+// take part (see the body below) -- or left whole, one for each of the first workgroups: pieces store and
+// re-read their partial sums, work at different steps of tiles that would otherwise share operands in L2, and a
+// round that is nearly full saves little; with few workgroups at work the others' power goes to them.  Measured,
+// pieces (fix-up included) -> whole:
+//   first projection, 128 steps, 3..7 rounds before: 0.06..0.38 of a round 355..683 -> 401..695 us, 0.69 462 -> 482,
+//     0.75..0.97 294 -> 292 (77 tokens), 440 -> 433, 386 -> 331; 9 and more rounds before: 0.19 939 -> 918, 0.31 (4096
+//     tokens) 1488 -> 1446, 0.75 928 -> 866; 64 steps: 0.75 140 -> 135;
+//   second projection: 448 steps, 0.19..0.5 of a round 146..209 -> 281..351, 0.62 279 -> 288 and 328 -> 332, 0.69 313 -> 296,
+//     0.75 402 -> 335, 0.88 469 -> 347; 200 steps: 0.5 258 -> 287.
+#define GG_SPLIT_UP 22          // 32nds of a round up to which the first projection's left-over tiles are cut
+#define GG_SPLIT_DOWN 20        // the second's
+#define GG_SPLIT_MIN_STEPS 36   // steps that cutting has to save (of what it saves at best)
+#define GG_SPLIT_MAX_ROUNDS 8   // ... and rounds of whole tiles from which they stay whole
 struct GgSched {
     int n_full;   // rounds of whole tiles
     int left_lo;  // this XCD's left-over tiles: [left_lo, left_lo + R)
     int R;
+    bool split;   // are they cut in pieces
 };
-__device__ __forceinline__ GgSched gg_sched(int total, int wgs, int xcd) {
+__device__ __forceinline__ GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
     GgSched sc;
     const int W = wgs * 8;
     sc.n_full = total / W;
@@ -221,6 +235,7 @@ __device__ __forceinline__ GgSched gg_sched(int total, int wgs, int xcd) {
     const int lo = left * xcd / 8, hi = left * (xcd + 1) / 8;
     sc.left_lo = sc.n_full * W + lo;
     sc.R = hi - lo;
+    sc.split = left * 32 <= W * split && (W - left) * KS >= W * GG_SPLIT_MIN_STEPS && sc.n_full < GG_SPLIT_MAX_ROUNDS;
     return sc;
 }
 // Workgroup me of an XCD takes a different one of the round's 32 neighbours every round: the
@@ -292,6 +307,38 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t gg_rsrc(const char* p) {
     const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
     return __builtin_amdgcn_make_buffer_rsrc((void*)(((unsigned long long)hi << 32) | lo), 0, (int)GG_RSRC_BYTES,
                                              0x00027000);
+}
+
+// Names the registers of ring slot u of the weight fragments where the slot is about to be used (no
+// instruction).  Left to itself the register allocator gives the copies of the step loop different
+// registers for fragments that are in flight from one copy to the next, and moves or spills them in
+// between, which waits for them: in the 256 x 256 tile's kernels 93 (first projection) and 44 registers
+// were spilled, 17 and 8 are now; 1531 tokens 1009 -> 1001 us, 4096 tokens 2257 -> 2242, both projections.
+template <int I>
+__device__ __forceinline__ void gg_pin(u32x4_t& x) {
+    if constexpr (I == 0) asm volatile("" : "+{v[192:195]}"(x));
+    else if constexpr (I == 1) asm volatile("" : "+{v[196:199]}"(x));
+    else if constexpr (I == 2) asm volatile("" : "+{v[200:203]}"(x));
+    else if constexpr (I == 3) asm volatile("" : "+{v[204:207]}"(x));
+    else if constexpr (I == 4) asm volatile("" : "+{v[208:211]}"(x));
+    else if constexpr (I == 5) asm volatile("" : "+{v[212:215]}"(x));
+    else if constexpr (I == 6) asm volatile("" : "+{v[216:219]}"(x));
+    else if constexpr (I == 7) asm volatile("" : "+{v[220:223]}"(x));
+    else if constexpr (I == 8) asm volatile("" : "+{v[224:227]}"(x));
+    else if constexpr (I == 9) asm volatile("" : "+{v[228:231]}"(x));
+    else if constexpr (I == 10) asm volatile("" : "+{v[232:235]}"(x));
+    else if constexpr (I == 11) asm volatile("" : "+{v[236:239]}"(x));
+    else if constexpr (I == 12) asm volatile("" : "+{v[240:243]}"(x));
+    else if constexpr (I == 13) asm volatile("" : "+{v[244:247]}"(x));
+    else if constexpr (I == 14) asm volatile("" : "+{v[248:251]}"(x));
+    else if constexpr (I == 15) asm volatile("" : "+{v[252:255]}"(x));
+}
+template <int SLOT>
+__device__ __forceinline__ void gg_pin_slot(u32x4_t (&r)[4]) {
+    gg_pin<4 * SLOT>(r[0]);
+    gg_pin<4 * SLOT + 1>(r[1]);
+    gg_pin<4 * SLOT + 2>(r[2]);
+    gg_pin<4 * SLOT + 3>(r[3]);
 }
 
 template <int V>
@@ -370,9 +417,10 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
     const int xcd = blockIdx.x & 7;
     const int wgs = gridDim.x >> 3;
     const int me = blockIdx.x >> 3;
-    const GgSched sc = gg_sched(total, wgs, xcd);
-    const bool split = a.split != 0;
-    const int n_full = sc.n_full + ((!split && gg_round_slot(sc.n_full, wgs, xcd, me) < total) ? 1 : 0);
+    const GgSched sc = gg_sched(total, wgs, xcd, a.KS, a.split);
+    const bool split = sc.split;
+    const int last = (int)((unsigned)(me + sc.n_full) % (unsigned)wgs);  // left-over tile, if it stays whole
+    const int n_full = sc.n_full + (!split && last < sc.R ? 1 : 0);
     // pieces of the left-over tiles for this workgroup
     // (plain scalars, no arrays: an array indexed at run time would live in scratch memory, and
     // every read of it would wait on the counter of the operand loads in flight)
@@ -404,7 +452,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
         if (n >= n_units) return false;
         int L, lo = 0, len = a.KS;
         if (n < n_full) {
-            L = gg_round_slot(n, wgs, xcd, me);
+            L = n < sc.n_full ? gg_round_slot(n, wgs, xcd, me) : sc.left_lo + last;
         } else {
             // first or second piece, selected by arithmetic (a two-way choice on n is turned
             // into a table in scratch memory by the compiler)
@@ -527,6 +575,13 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
                     else GG_WAIT_VMCNT(V0);
                 } else {
                     GG_WAIT_VMCNT((LA - 1) * VMIN);
+                }
+                if constexpr (NBW == 16) {
+                    static_assert(U == 4 && FRW == 4, "four slots of four fragments");
+                    if (u == 0) gg_pin_slot<0>(areg[0]);
+                    else if (u == 1) gg_pin_slot<1>(areg[1]);
+                    else if (u == 2) gg_pin_slot<2>(areg[2]);
+                    else gg_pin_slot<3>(areg[3]);
                 }
                 // One barrier per TWO steps: at an even step every wave has waited for its
                 // shares of stages k+1 and k+2 (see above), so both are published here; and the
@@ -687,13 +742,19 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
     }
 }
 
-template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS>
+// The first projection's whole tiles and pieces are two copies of the loop, one after the other: an
+// epilogue with both the SiLU body and the raw store spills 153-289 registers in the 8 x 8 and 16 x 4 tiles.
+template <bool UP, int NBW, int FRW, int U, int LA, int NS>
 __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
     __shared__ int s_seg[GG_SEG_FIELDS][64];
     const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, threadIdx.x & 63, s_seg,
                                    threadIdx.x < 64);
     __syncthreads();
-    gg_gemm_body<UP, NBW, FRW, MODE, U, LA, NS>(a, total, s_seg);
+    gg_gemm_body<UP, NBW, FRW, UP ? 1 : 0, U, LA, NS>(a, total, s_seg);
+    if (UP) {
+        __syncthreads();  // no wave fills the LDS ring anew while another still reads it
+        gg_gemm_body<UP, NBW, FRW, 2, U, LA, NS>(a, total, s_seg);
+    }
 }
 
 // Adds the pieces of every left-over tile in the order of the workgroups that produced them
@@ -714,6 +775,7 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, lane, s_seg, threadIdx.x < 64);
     const int left = total % (wgs * 8);
+    if (left == 0 || !gg_sched(total, wgs, 0, a.KS, a.split).split) return;
     __syncthreads();
     for (int item = blockIdx.x; item < left * NBW; item += gridDim.x) {
         // (tile fastest: neighbouring workgroups, and not the same ones again, take blocks that exist)
@@ -722,7 +784,7 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
         int xcd = (int)((unsigned)lt * 8u / (unsigned)left);
         while (left * (xcd + 1) / 8 <= lt) xcd++;
         while (left * xcd / 8 > lt) xcd--;
-        const GgSched sc = gg_sched(total, wgs, xcd);
+        const GgSched sc = gg_sched(total, wgs, xcd, a.KS, a.split);
         const int r = sc.n_full * wgs * 8 + lt - sc.left_lo;  // tile number among the XCD's
         TileInfo ti;
         if (!gg_decode_tile_tab(s_seg, lane, a.NT, sc.left_lo + r, ti)) return;
@@ -829,17 +891,16 @@ static GgShape gg_shape(GgVariant v) {
     }
 }
 
-template <bool UP, int MODE>
+template <bool UP>
 static const void* gg_kernel_ptr(GgVariant v) {
     switch (v) {
-        case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, MODE, GG_U, GG_WIDE_LA, GG_NS>;
-        case GG_R192: return (const void*)gg_gemm_kernel<UP, 12, 4, MODE, GG_U, GG_LA, GG_NS>;
-        default: return (const void*)gg_gemm_kernel<UP, 16, 4, MODE, GG_U, GG_LA, GG_NS>;
+        case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, GG_U, GG_WIDE_LA, GG_NS>;
+        case GG_R192: return (const void*)gg_gemm_kernel<UP, 12, 4, GG_U, GG_LA, GG_NS>;
+        default: return (const void*)gg_gemm_kernel<UP, 16, 4, GG_U, GG_LA, GG_NS>;
     }
 }
 
-// One projection: the persistent GEMM (whole tiles; for the first projection the pieces of
-// the left-over tiles are a second launch) and the fix-up of the pieces.
+// One projection: the persistent GEMM and the fix-up of the pieces.
 template <bool UP>
 static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hipStream_t s) {
     const GgShape sh = gg_shape(v);
@@ -849,19 +910,10 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
     a.NT = a.FR / a.FROWS;
     // pieces of >= 32 steps go to scratch and a fix-up kernel adds them; it lists the pieces
     // of a tile with one wave, hence at most 64 workgroups per XCD
-    a.split = (a.KS >= 64 && pgrid / 8 <= 64) ? 1 : 0;
+    a.split = (a.KS >= 64 && pgrid / 8 <= 64) ? (UP ? GG_SPLIT_UP : GG_SPLIT_DOWN) : 0;
     void* params[1] = {(void*)&a};
     const size_t lds_bytes = (size_t)sh.ns * sh.tb * MOE_FRAG_BYTES;
-    if (UP) {
-        MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<true, 1>(v), dim3(pgrid), dim3(GG_THREADS), params,
-                                    lds_bytes, s));
-        if (a.split)
-            MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<true, 2>(v), dim3(pgrid), dim3(GG_THREADS),
-                                        params, lds_bytes, s));
-    } else {
-        MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<false, 0>(v), dim3(pgrid), dim3(GG_THREADS), params,
-                                    lds_bytes, s));
-    }
+    MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<UP>(v), dim3(pgrid), dim3(GG_THREADS), params, lds_bytes, s));
     if (a.split) {
         const dim3 fgrid(GG_FIX_GRID);
         const int wgs = (int)(pgrid / 8);
@@ -942,9 +994,8 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
     if (!attr_set[dev].load(std::memory_order_acquire)) {
         for (int v = 0; v < GG_NVARIANTS; v++) {
             const GgShape sh = gg_shape((GgVariant)v);
-            const void* all[3] = {gg_kernel_ptr<true, 1>((GgVariant)v), gg_kernel_ptr<true, 2>((GgVariant)v),
-                                  gg_kernel_ptr<false, 0>((GgVariant)v)};
-            for (int i = 0; i < 3; i++)
+            const void* all[2] = {gg_kernel_ptr<true>((GgVariant)v), gg_kernel_ptr<false>((GgVariant)v)};
+            for (int i = 0; i < 2; i++)
                 MOE_HIP_TRY(hipFuncSetAttribute(all[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                                                 (int)((size_t)sh.ns * sh.tb * MOE_FRAG_BYTES)));
         }

@@ -25,8 +25,9 @@ EDGES = {
 
 
 # d, f: 512 / 1024 one round of few tiles; 2048 / 512 and 512 / 2304 cut left-over tiles along the
-# reduction of the first and of the second projection
-@pytest.mark.parametrize("d,f", [(512, 1024), (2048, 512), (512, 2304)])
+# reduction of the first and of the second projection; 2048 / 1536 leaves 192 of 256 (256-row tiles: too
+# many to cut); 2048 / 2560 a round of whole tiles and pieces behind it
+@pytest.mark.parametrize("d,f", [(512, 1024), (2048, 512), (512, 2304), (2048, 1536), (2048, 2560)])
 @pytest.mark.parametrize("name", list(EDGES))
 def test_grouped_unit_edges(name, d, f):
     import paper_2402_07033_amd as moe
