@@ -53,10 +53,10 @@
 //     the stores).
 //   * tiles are dealt in rounds of one tile per workgroup, an XCD taking 32 neighbours of the
 //     order expert, group of at most 8 token tiles, feature tile, token tile: about 8 x 4
-//     tiles, which share 12 operand tiles in one L2.  All XCDs work through the same experts at
-//     the same time, so an expert's size does not unbalance them.  One contiguous range of tiles
-//     per XCD, otherwise the same kernel, hits L2 more often and is slower: 4096 tokens 2.308 ->
-//     2.340 ms, 1531 tokens 1.045 -> 1.056, block of 512 0.608 -> 0.615, 16 experts even.
+//     tiles, which share 12 operand tiles in one L2.  Every XCD has its part of every round, so an
+//     expert's size does not unbalance them; where experts of one tile and larger ones are there, they walk
+//     the rounds from different starts (gg_turned).  One contiguous range of tiles per XCD, which hits L2
+//     more often, was slower: 4096 tokens 2.308 -> 2.340 ms, 1531 tokens 1.045 -> 1.056.
 // Measured (kernel with whole 256-row tiles, one tile range per XCD, 64-bit pointers -> this): layer
 // of 4096 tokens, 8 experts, Zipf 2.46 -> 2.35 ms; 1531 tokens 1.19 -> 1.07; 4096 tokens, 16 experts
 // 1.46 -> 1.30; 77 tokens 0.518 -> 0.487; 64 experts of f = 1408, 300 tokens, k = 6 0.276 -> 0.238 (10 us of
@@ -166,6 +166,18 @@ __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets,
         tab[GG_SEG_BB][lane] = inc_b - nb;
     }
     return __builtin_amdgcn_readlane(inc_t, 63) * NT;
+}
+
+// Does every XCD start with a round of its own, an eighth of all rounds behind its neighbour's?  Tiles of
+// an expert that has no other token tile wait for their weights from HBM, tiles of many rows are bound by the
+// matrix cores' power: where both are there, they should be at work at the same time.  First projection, in
+// step -> turned: 16 experts, 4096 tokens Zipf 777 -> 746 us, 1531 tokens 655 -> 627, 1000 tokens 535 -> 501, 64
+// experts, 2000 tokens 211 -> 195.  Not where fewer than 1 of 8 token tiles is its expert's only one (8 x 700 rows
+// 1021 -> 1033, 4096 tokens 1473 -> 1471, its second projection 726 -> 733) and not with fewer than 4
+// rounds (2: 342 -> 357).
+#define GG_TURN_ROUNDS 4
+__device__ __forceinline__ bool gg_turned(const int (*tab)[64], int lane, int total, int NT) {
+    return __popcll(__ballot(tab[GG_SEG_TILES][lane] == 1)) * 8 * NT >= total;
 }
 
 // Logical tile index -> tile, from the table.
@@ -395,7 +407,7 @@ __device__ __forceinline__ unsigned gg_h_off(int lane) {
 // 2 = pieces only.
 // NBW x FRW: token blocks of the tile, at most, x fragment rows of a wave.
 template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS>
-__device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, const int (*s_seg)[64]) {
+__device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bool turned, const int (*s_seg)[64]) {
     static_assert(NBW * FRW <= 64 && NBW % 4 == 0 && FRW % 4 == 0, "at most 64 MFMA tiles (256 accumulators) per wave");
     static_assert(LA < U && U % GG_BARRIER_STEPS == 0, "register ring; a tile starts at a barrier step");
     static_assert(gg_refill_ordered(NS, GG_AHEAD) && gg_arrival_ordered(GG_AHEAD, LA), "stage ring, see moe_gg_ring.h");
@@ -421,6 +433,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
     const bool split = sc.split;
     const int last = (int)((unsigned)(me + sc.n_full) % (unsigned)wgs);  // left-over tile, if it stays whole
     const int n_full = sc.n_full + (!split && last < sc.R ? 1 : 0);
+    const int turn = turned && sc.n_full >= GG_TURN_ROUNDS ? sc.n_full * xcd / 8 : 0;  // the XCD's first round
     // pieces of the left-over tiles for this workgroup
     // (plain scalars, no arrays: an array indexed at run time would live in scratch memory, and
     // every read of it would wait on the counter of the operand loads in flight)
@@ -452,7 +465,8 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, co
         if (n >= n_units) return false;
         int L, lo = 0, len = a.KS;
         if (n < n_full) {
-            L = n < sc.n_full ? gg_round_slot(n, wgs, xcd, me) : sc.left_lo + last;
+            const int r = n + turn;
+            L = n < sc.n_full ? gg_round_slot(r < sc.n_full ? r : r - sc.n_full, wgs, xcd, me) : sc.left_lo + last;
         } else {
             // first or second piece, selected by arithmetic (a two-way choice on n is turned
             // into a table in scratch memory by the compiler)
@@ -750,10 +764,11 @@ __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
     const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, threadIdx.x & 63, s_seg,
                                    threadIdx.x < 64);
     __syncthreads();
-    gg_gemm_body<UP, NBW, FRW, UP ? 1 : 0, U, LA, NS>(a, total, s_seg);
+    const bool turned = gg_turned(s_seg, threadIdx.x & 63, total, a.NT);
+    gg_gemm_body<UP, NBW, FRW, UP ? 1 : 0, U, LA, NS>(a, total, turned, s_seg);
     if (UP) {
         __syncthreads();  // no wave fills the LDS ring anew while another still reads it
-        gg_gemm_body<UP, NBW, FRW, 2, U, LA, NS>(a, total, s_seg);
+        gg_gemm_body<UP, NBW, FRW, 2, U, LA, NS>(a, total, turned, s_seg);
     }
 }
 
