@@ -209,6 +209,17 @@ int moe_expert_ffn_parts(const moe_weights_t* W, const void* xg, moe_dtype_t act
  */
 int moe_combine(const float* yg, const int32_t* inv_perm, const float* weights, int T, int k,
                 int d, float* y, void* stream);
+
+/*
+ * The four calls of the hot path -- moe_route, moe_permute, moe_expert_ffn_path, moe_combine -- one after
+ * the other, for callers to whom a call into the library costs more than a launch.  Arguments, checks,
+ * launches and results are those of the four calls: logits [T,E], x [T,d] of x_dtype, N = T*k rows; the
+ * experts are W's.  *stage: the call that returned the status (0 .. 3).
+ */
+int moe_layer(const moe_weights_t* W, const void* x, moe_dtype_t x_dtype, int d, const float* logits, int T,
+              int E, int k, int path, int32_t* idx, float* weights, int32_t* counts, int32_t* offsets,
+              int32_t* perm, int32_t* inv_perm, void* xg, void* workspace, size_t workspace_bytes, float* yg,
+              float* y, int* stage, void* stream);
 /*
  * The same over unsummed reduction parts (see moe_expert_ffn_parts), in one launch:
  *     v_j    = yg_parts[0][inv_perm[t*k+j], :] + yg_parts[1][...] + ...   (part order)

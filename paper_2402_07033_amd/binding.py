@@ -17,7 +17,7 @@ _LIB_PATH = os.path.join(_PKG, "libmoe_hip.so")
 _lib = None
 
 # entry points of include/moe.h and of include/moe_probe.h
-EXPORTS = ("moe_status_string", "moe_route", "moe_permute", "moe_weights_pack",
+EXPORTS = ("moe_status_string", "moe_route", "moe_permute", "moe_layer", "moe_weights_pack",
            "moe_weights_free", "moe_weights_bytes", "moe_expert_ffn_workspace",
            "moe_expert_ffn", "moe_expert_ffn_path", "moe_expert_ffn_plan",
            "moe_expert_ffn_parts", "moe_expert_ffn_tokens", "moe_expert_ffn_noalloc", "moe_expert_ffn_noalloc_max_bytes",
@@ -79,6 +79,9 @@ def lib():
         L.moe_expert_ffn.argtypes = [vp, vp, i32, vp, i32, vp, C.c_size_t, vp, vp]
         L.moe_expert_ffn_path.argtypes = [vp, vp, i32, vp, i32, vp, C.c_size_t, vp, i32, vp]
         L.moe_combine.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp]
+        L.moe_layer.argtypes = ([vp, vp, i32, i32, vp, i32, i32, i32, i32] + [vp] * 8 +
+                                [C.c_size_t, vp, vp, C.POINTER(C.c_int), vp])
+        L.moe_layer.restype = C.c_int
         L.moe_rmsnorm.argtypes = [vp, i32, i32, f32, vp, vp]
         L.moe_router_logits.argtypes = [vp, vp, i32, i32, i32, vp, vp]
         L.moe_residual_add.argtypes = [vp, vp, i32, i32, vp]
@@ -569,13 +572,39 @@ def moe_hbm_read_probe(data: torch.Tensor, sink: torch.Tensor, stream=None) -> i
     return per_wave * 1024 * 8 * cus
 
 
+_LAYER_CALLS = ("moe_route", "moe_permute", "moe_expert_ffn", "moe_combine")
+
+
 def moe_layer(W: PackedWeights, x: torch.Tensor, logits: torch.Tensor, k: int,
               path: int = MOE_FFN_AUTO, workspace=None, stream=None) -> dict:
-    """The four calls of the hot path in order; returns every intermediate."""
-    idx, w = moe_route(logits, k, stream=stream)
-    counts, offsets, perm, inv_perm, xg = moe_permute(idx, W.E, x, stream=stream)
-    yg = moe_expert_ffn(W, xg, offsets, workspace=workspace, path=path, stream=stream)
-    y = moe_combine(yg, inv_perm, w, stream=stream)
+    """The four calls of the hot path in order; returns every intermediate.  One call into the
+    library (a call costs about as much host time as a launch)."""
+    _dev(logits, torch.float32, "logits")
+    if not x.is_cuda or not x.is_contiguous():
+        raise TypeError("x: expected a contiguous device tensor")
+    T, E = logits.shape
+    d, xdt = x.shape[1], _act_dtype(x)
+    N, dev = T * k, logits.device
+    i32, f32 = torch.int32, torch.float32
+    idx = torch.empty((T, k), dtype=i32, device=dev)
+    w = torch.empty((T, k), dtype=f32, device=dev)
+    counts = torch.empty(W.E, dtype=i32, device=dev)
+    offsets = torch.empty(W.E + 1, dtype=i32, device=dev)
+    perm = torch.empty(N, dtype=i32, device=dev)
+    inv_perm = torch.empty(N, dtype=i32, device=dev)
+    xg = torch.empty((N, d), dtype=x.dtype, device=dev)
+    if workspace is None:
+        need = moe_expert_ffn_workspace(N, W.E, W.d, W.f, xdt)
+        workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
+    yg = torch.empty((N, W.d), dtype=f32, device=dev)
+    y = torch.empty((T, W.d), dtype=f32, device=dev)
+    stage = C.c_int(0)
+    status = lib().moe_layer(W.handle, x.data_ptr(), xdt, d, logits.data_ptr(), T, E, k, path, idx.data_ptr(),
+                             w.data_ptr(), counts.data_ptr(), offsets.data_ptr(), perm.data_ptr(),
+                             inv_perm.data_ptr(), xg.data_ptr(), workspace.data_ptr(), workspace.numel(),
+                             yg.data_ptr(), y.data_ptr(), C.byref(stage), _stream(stream))
+    if status != 0:
+        raise MoeError(status, _LAYER_CALLS[stage.value])
     return dict(idx=idx, w=w, counts=counts, offsets=offsets, perm=perm, inv_perm=inv_perm,
                 xg=xg, yg=yg, y=y)
 

@@ -298,6 +298,26 @@ int moe_combine(const float* yg, const int32_t* inv_perm, const float* weights, 
     return moe_combine_launch(yg, inv_perm, weights, T, k, d, y, (hipStream_t)stream);
 }
 
+int moe_layer(const moe_weights_t* W, const void* x, moe_dtype_t x_dtype, int d, const float* logits, int T,
+              int E, int k, int path, int32_t* idx, float* weights, int32_t* counts, int32_t* offsets,
+              int32_t* perm, int32_t* inv_perm, void* xg, void* workspace, size_t workspace_bytes, float* yg,
+              float* y, int* stage, void* stream) {
+    if (!stage) return MOE_ERR_INVALID_ARG;
+    int rc = moe_route(logits, T, E, k, idx, weights, stream);
+    *stage = 0;
+    if (rc != MOE_OK) return rc;
+    *stage = 2;
+    if (!W) return MOE_ERR_INVALID_ARG;
+    *stage = 1;
+    rc = moe_permute(idx, T, W->E, k, x, d, x_dtype, counts, offsets, perm, inv_perm, xg, stream);
+    if (rc != MOE_OK) return rc;
+    *stage = 2;
+    rc = moe_expert_ffn_path(W, xg, x_dtype, offsets, T * k, workspace, workspace_bytes, yg, path, stream);
+    if (rc != MOE_OK) return rc;
+    *stage = 3;
+    return moe_combine(yg, inv_perm, weights, T, k, W->d, y, stream);
+}
+
 int moe_rmsnorm(const float* x, int T, int d, float eps, float* h, void* stream) {
     if (T < 0 || !dims_ok(d) || !(eps >= 0.f)) return MOE_ERR_INVALID_ARG;
     if (T == 0) return MOE_OK;

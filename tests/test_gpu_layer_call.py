@@ -1,0 +1,46 @@
+"""moe_layer, the four calls in one: the bits of the four calls, and the error of the one that fails."""
+import pytest
+import torch
+
+import moe_inputs as mi
+from gpu_util import pack_layer, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(T, E, k, w, x):
+    cfg = mi.small_config("layer_call", T, 256, 512, E, k, 70 + T, w_dtype=w, x_dtype=x, zipf_s=1.2)
+    li = mi.make_layer(cfg, threads=4)
+    return pack_layer(li), to_dev(li.x), to_dev(li.logits)
+
+
+# all-fp32; decode sized; the grouped kernels with either row type
+@pytest.mark.parametrize("T,E,k,w,x", [(1, 8, 2, mi.F32, mi.F32), (16, 8, 2, mi.F32, mi.F32), (7, 16, 4, mi.BF16, mi.F32),
+                                       (300, 8, 2, mi.BF16, mi.BF16), (301, 3, 1, mi.BF16, mi.F32)])
+def test_layer_is_the_four_calls(T, E, k, w, x):
+    import paper_2402_07033_amd as moe
+    W, xd, lg = _layer(T, E, k, w, x)
+    out = moe.moe_layer(W, xd, lg, k)
+    idx, wt = moe.moe_route(lg, k)
+    counts, offsets, perm, inv_perm, xg = moe.moe_permute(idx, E, xd)
+    yg = moe.moe_expert_ffn(W, xg, offsets)
+    y = moe.moe_combine(yg, inv_perm, wt)
+    want = dict(idx=idx, w=wt, counts=counts, offsets=offsets, perm=perm, inv_perm=inv_perm, xg=xg, yg=yg, y=y)
+    assert set(out) == set(want)
+    for n, v in want.items():
+        assert out[n].dtype == v.dtype and torch.equal(out[n], v), n
+    W.free()
+
+
+def test_layer_names_the_call_that_failed():
+    import paper_2402_07033_amd as moe
+    W, xd, lg = _layer(8, 8, 2, mi.BF16, mi.F32)
+    with pytest.raises(moe.MoeError, match="moe_route"):
+        moe.moe_layer(W, xd, lg, 9)
+    with pytest.raises(moe.MoeError, match="moe_expert_ffn"):
+        moe.moe_layer(W, xd, lg, 2, workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+    with pytest.raises(TypeError):
+        moe.moe_layer(W, xd.t(), lg, 2)
+    W.free()
+    with pytest.raises(moe.MoeError, match="moe_expert_ffn"):
+        moe.moe_layer(W, xd, lg, 2)
