@@ -186,10 +186,16 @@ __device__ void permute_indices(const int32_t* __restrict__ idx, int N, int E,
 static_assert(PM_EARLY_SLOTS >= PM_THREADS * 4, "at least one round of requests");
 
 // A wave's part of a row: 8 KiB of loads in flight, stored to k rows of xg.  pos(j): row of copy j.
+// STREAM: past L2 (the rows are read once).  From two rows per wave on: 8192 tokens of 16 KiB rows 82 -> 66 us; 4096
+// tokens of 8 KiB rows within a program's gating and batching 59.9 -> 55.6, on their own 18.5 either way; with 9 and
+// 12 rows for a workgroup's 8 waves, 16 KiB each, rows that the last-level cache holds 20.2 -> 22.6 and 28.8.
+template <bool STREAM>
 __device__ __forceinline__ void load_row(const u32x4_t* __restrict__ src, int row_chunks, int c0, u32x4_t (&v)[8]) {
 #pragma unroll
-    for (int u = 0; u < 8; u++)  // past the end of the row: its last chunk, not stored
-        v[u] = src[c0 + u * 64 < row_chunks ? c0 + u * 64 : row_chunks - 1];
+    for (int u = 0; u < 8; u++) {  // past the end of the row: its last chunk, not stored
+        const u32x4_t* p = src + (c0 + u * 64 < row_chunks ? c0 + u * 64 : row_chunks - 1);
+        v[u] = STREAM ? __builtin_nontemporal_load(p) : *p;
+    }
 }
 template <class POS>
 __device__ __forceinline__ void store_row_k(const u32x4_t (&v)[8], u32x4_t* __restrict__ xg, int row_chunks, int k,
@@ -202,17 +208,17 @@ __device__ __forceinline__ void store_row_k(const u32x4_t (&v)[8], u32x4_t* __re
     }
 }
 // One row from chunk c0 (of this lane) on, copied by a wave to k rows of xg, the row read once.
-template <class POS>
+template <bool STREAM, class POS>
 __device__ __forceinline__ void copy_row_k(const u32x4_t* __restrict__ src, u32x4_t* __restrict__ xg,
                                            int row_chunks, int k, int c0, POS pos) {
     for (; c0 < row_chunks; c0 += 64 * 8) {
         u32x4_t v[8];
-        load_row(src, row_chunks, c0, v);
+        load_row<STREAM>(src, row_chunks, c0, v);
         store_row_k(v, xg, row_chunks, k, c0, pos);
     }
 }
 
-template <bool GATHER, bool EARLY>
+template <bool GATHER, bool EARLY, bool STREAM>
 __global__ __launch_bounds__(PM_THREADS) void permute_kernel(
     const int32_t* __restrict__ idx, int N, int E, int k, int tpw, const u32x4_t* __restrict__ x,
     int row_chunks /* 16-byte chunks per row */, int32_t* __restrict__ counts,
@@ -262,8 +268,8 @@ __global__ __launch_bounds__(PM_THREADS) void permute_kernel(
 #pragma unroll
         for (int i = 0; i < PM_EARLY; i++)
             if (i < rounds) first[i] = *(const int4*)(idx + p + i * PM_THREADS * 4);
-        if (wave < tokens) load_row(x + (size_t)(t0 + wave) * row_chunks, row_chunks, lane, r0);
-        if (wave + PM_WAVES < tokens) load_row(x + (size_t)(t0 + wave + PM_WAVES) * row_chunks, row_chunks, lane, r1);
+        if (wave < tokens) load_row<STREAM>(x + (size_t)(t0 + wave) * row_chunks, row_chunks, lane, r0);
+        if (wave + PM_WAVES < tokens) load_row<STREAM>(x + (size_t)(t0 + wave + PM_WAVES) * row_chunks, row_chunks, lane, r1);
 #pragma unroll
         for (int i = 0; i < PM_EARLY; i++)
             if (i < rounds) count(p + i * PM_THREADS * 4, first[i]);
@@ -329,7 +335,7 @@ __global__ __launch_bounds__(PM_THREADS) void permute_kernel(
         const bool early = EARLY && t < 2 * PM_WAVES;
         if (early && t < PM_WAVES) store_row_k(r0, xg, row_chunks, k, lane, pos);
         else if (early) store_row_k(r1, xg, row_chunks, k, lane, pos);
-        copy_row_k(src, xg, row_chunks, k, early ? lane + 64 * 8 : lane, pos);
+        copy_row_k<STREAM>(src, xg, row_chunks, k, early ? lane + 64 * 8 : lane, pos);
     }
 }
 
@@ -341,7 +347,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const int32_t* __restr
                                                           u32x4_t* __restrict__ xg) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int t = blockIdx.x * 4 + wave; t < T; t += gridDim.x * 4)
-        copy_row_k(x + (size_t)t * row_chunks, xg, row_chunks, k, lane,
+        copy_row_k<false>(x + (size_t)t * row_chunks, xg, row_chunks, k, lane,
                    [&](int j) { return inv_perm[(size_t)t * k + j]; });
 }
 
@@ -355,14 +361,13 @@ int moe_permute_launch(const int32_t* idx, int T, int E, int k, const void* x, i
     const int tpw = T > cus ? (T + cus - 1) / cus : 1;
     const unsigned grid = T > 0 ? (unsigned)((T + tpw - 1) / tpw) : 1u;
     const bool fused = x != nullptr && (long long)tpw * k <= PM_MAX_SLOTS;
-    if (fused && N >= PM_EARLY_SLOTS)
-        hipLaunchKernelGGL((permute_kernel<true, true>), dim3(grid), dim3(PM_THREADS), 0, s, idx, N, E, k, tpw,
-                           (const u32x4_t*)x, row_chunks, counts, offsets, perm, inv_perm, (u32x4_t*)xg);
-    else if (fused)
-        hipLaunchKernelGGL((permute_kernel<true, false>), dim3(grid), dim3(PM_THREADS), 0, s, idx, N, E, k, tpw,
-                           (const u32x4_t*)x, row_chunks, counts, offsets, perm, inv_perm, (u32x4_t*)xg);
-    else
-        hipLaunchKernelGGL((permute_kernel<false, false>), dim3(grid), dim3(PM_THREADS), 0, s, idx, N, E, k, tpw,
+    if (fused) {
+        auto* kernel = N < PM_EARLY_SLOTS ? permute_kernel<true, false, false>
+                       : tpw < 2 * PM_WAVES ? permute_kernel<true, true, false> : permute_kernel<true, true, true>;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(PM_THREADS), 0, s, idx, N, E, k, tpw, (const u32x4_t*)x, row_chunks,
+                           counts, offsets, perm, inv_perm, (u32x4_t*)xg);
+    } else
+        hipLaunchKernelGGL((permute_kernel<false, false, false>), dim3(grid), dim3(PM_THREADS), 0, s, idx, N, E, k, tpw,
                            (const u32x4_t*)nullptr, 0, counts, offsets, perm, inv_perm, (u32x4_t*)nullptr);
     if (moe_launch_status() != MOE_OK) return MOE_ERR_HIP;
     if (x != nullptr && !fused) {
