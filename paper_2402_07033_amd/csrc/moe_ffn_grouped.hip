@@ -42,8 +42,8 @@
 //   * the requests of a step are spread between the matrix instructions, one barrier per two
 //     steps publishes the next stages (the order of the ring: moe_gg_ring.h).  They are buffer loads:
 //     an address is a descriptor, the lane offset and one scalar, where 64-bit pointers per request
-//     filled the scalar registers (65..229 spills, 26..88 now); 55 other instructions stand beside the
-//     64 matrix instructions of a full step, 61 with pointers.
+//     filled the scalar registers (65..229 spills, 43..63 now); 55 other instructions stand beside the
+//     64 matrix instructions of a full step, 61 with pointers, one between two of them where it can be.
 //   * the workgroup is persistent (one per CU) and the two load streams run across tile
 //     boundaries: while the last steps of a tile are multiplied, the first stages of the next
 //     one are already being requested.  The last groups of U steps of a tile are their own
@@ -403,8 +403,8 @@ __device__ __forceinline__ unsigned gg_h_off(int lane) {
     return (unsigned)(((((lane >> 4) & 1) * 2 + (lane >> 5)) * 16 + (lane & 15)) * 16);
 }
 
-// MODE: which units of work a launch covers: 0 = whole tiles and pieces, 1 = whole tiles only,
-// 2 = pieces only.
+// MODE: which units of work this copy of the loop covers: 0 = whole tiles and pieces, 1 = whole tiles
+// only, 2 = pieces only.
 // NBW x FRW: token blocks of the tile, at most, x fragment rows of a wave.
 template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS>
 __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bool turned, const int (*s_seg)[64]) {

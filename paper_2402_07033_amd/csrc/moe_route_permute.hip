@@ -176,9 +176,8 @@ __device__ void permute_indices(const int32_t* __restrict__ idx, int N, int E,
 // Bound: reading idx from L2 in every workgroup (N * 4 bytes each), then the row copy.  One
 // workgroup for all N slots (and a second launch that read every row k times) took 15 + 21 us at
 // 4096 tokens, k = 2, 8 KiB rows, and 14 us for the indices of 300 tokens, k = 6, 64 experts;
-// this one launch 25 and 5 us.  Routing, batching and combine together, repeated on the same buffers:
-// 4096 tokens, k = 2 75.4 -> 61.7 us (80.7 -> 67.7 with inputs that change); 8192 tokens, k = 6, 64
-// experts, 4 KiB rows 452 -> 173 us.
+// this one launch 18.5 and 5 us.  Routing, batching and combine together, with inputs that change: 4096
+// tokens, k = 2 80.7 -> 55.7 us (of it 8 by the combine); 8192 tokens, k = 6, 64 experts, 4 KiB rows 452 -> 173 us on the same buffers.
 #define PM_THREADS 512
 #define PM_WAVES (PM_THREADS / 64)
 #define PM_MAX_SLOTS 1024  // slots of a workgroup whose positions are kept for the row copy
