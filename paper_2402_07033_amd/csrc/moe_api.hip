@@ -303,6 +303,10 @@ int moe_layer(const moe_weights_t* W, const void* x, moe_dtype_t x_dtype, int d,
               int32_t* perm, int32_t* inv_perm, void* xg, void* workspace, size_t workspace_bytes, float* yg,
               float* y, int* stage, void* stream) {
     if (!stage) return MOE_ERR_INVALID_ARG;
+    // The rows of xg are gathered with length d and read with length W->d, and ids of W->E and above have no
+    // expert.  (Fewer logits than experts: the last experts get no tokens.)
+    *stage = 1;
+    if (W && T > 0 && (d != W->d || E > W->E)) return MOE_ERR_INVALID_ARG;
     int rc = moe_route(logits, T, E, k, idx, weights, stream);
     *stage = 0;
     if (rc != MOE_OK) return rc;

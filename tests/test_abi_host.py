@@ -110,6 +110,38 @@ def test_argument_errors_return_before_any_launch(L):
     assert L.moe_decode_block_supported(4, 8, 2, 4096, 14336, 1) == 0  # eight routed rows
 
 
+class _Weights(C.Structure):
+    """struct moe_weights of csrc/moe_internal.h, for calls that have to fail on their arguments."""
+    _fields_ = [("E", C.c_int), ("d", C.c_int), ("f", C.c_int), ("dtype", C.c_int), ("device", C.c_int),
+                ("w13", C.c_void_p), ("w2", C.c_void_p), ("w1f", C.c_void_p), ("w3f", C.c_void_p),
+                ("w2f", C.c_void_p), ("bytes", C.c_size_t)]
+
+
+def _layer_call(L, **change):
+    """moe_layer with valid arguments (4 tokens, 8 experts of d = 256, f = 512) but for `change`:
+    (status, stage).  Host pointers: every call made here is refused for its arguments."""
+    buf = (C.c_char * 512)()
+    p = (C.addressof(buf) + 255) & ~255
+    W = _Weights(E=8, d=256, f=512, dtype=1)
+    a = dict(W=C.addressof(W), x=p, x_dtype=0, d=256, logits=p, T=4, E=8, k=2, path=0, idx=p, weights=p, counts=p,
+             offsets=p, perm=p, inv_perm=p, xg=p, workspace=p,
+             workspace_bytes=L.moe_expert_ffn_workspace(8, 8, 256, 512, 0), yg=p, y=p)
+    assert set(change) <= set(a)
+    a.update(change)
+    stage = C.c_int(-1)
+    return L.moe_layer(*a.values(), C.byref(stage), None), stage.value
+
+
+def test_layer_sizes_are_the_weights(L):
+    """Rows gathered with another length than the experts' are read out of range or misaligned, and ids
+    beyond the last expert have no weights."""
+    assert L.moe_weights_bytes(C.byref(_Weights(bytes=4711))) == 4711   # the layout above
+    for d in (64, 128, 320, 4096):
+        assert _layer_call(L, d=d) == (-1, 1)
+    assert _layer_call(L, E=9) == (-1, 1)
+    assert _layer_call(L, E=64, d=4096) == (-1, 1)
+
+
 def test_ffn_plan_query(L):
     import paper_2402_07033_amd as m
     pl = m.moe_expert_ffn_plan(32, 8, 4096, 14336)
