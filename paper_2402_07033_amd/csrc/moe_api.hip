@@ -30,16 +30,42 @@ static inline bool ranges_overlap(const void* a, size_t an, const void* b, size_
 //   except that only MID serves f = 128.
 int moe_ffn_auto_path(int N, int E, int d, int f) {
     if (N <= 72 && moe_ffn_stream_supported(d, f)) return MOE_FFN_STREAM;
-    if ((long long)N <= (long long)MOE_MID_MAX_ROWS * E && moe_ffn_mid_supported(N, E, d, f))
+    if ((long long)N <= (long long)MOE_MID_MAX_ROWS * E && moe_ffn_grouped_supported(true, N, E, d, f))
         return MOE_FFN_MID;
     return MOE_FFN_GROUPED;
 }
 
-// moe_expert_ffn and its variants: validation, then the kernel family.  With `perm` the
-// batched row i is read as xg[perm[i] / k] (xg is then the token array).
-static int ffn_dispatch(const moe_weights_t* W, const void* xg, moe_dtype_t act_dtype,
-                        const int32_t* perm, int k, const int32_t* offsets, int N, void* workspace,
-                        size_t workspace_bytes, float* yg, int path, void* stream) {
+// Argument checks of the four calls of the hot path, without a launch: what moe_layer asks of all four
+// before the first of them runs.
+
+static int route_args(const float* logits, int T, int E, int k, const int32_t* idx, const float* weights) {
+    if (!tek_ok(T, E, k)) return MOE_ERR_INVALID_ARG;
+    if (T == 0) return MOE_OK;
+    if (!logits || !idx || !weights) return MOE_ERR_INVALID_ARG;
+    if (!moe_aligned16(logits) || !moe_aligned16(idx) || !moe_aligned16(weights))
+        return MOE_ERR_INVALID_ARG;
+    return MOE_OK;
+}
+
+static int permute_args(const int32_t* idx, int T, int E, int k, const void* x, int d, moe_dtype_t x_dtype,
+                        const int32_t* counts, const int32_t* offsets, const int32_t* perm,
+                        const int32_t* inv_perm, const void* xg) {
+    if (!tek_ok(T, E, k)) return MOE_ERR_INVALID_ARG;
+    if (!counts || !offsets) return MOE_ERR_INVALID_ARG;
+    if (T > 0 && (!idx || !perm || !inv_perm)) return MOE_ERR_INVALID_ARG;
+    if ((x == nullptr) != (xg == nullptr)) return MOE_ERR_INVALID_ARG;
+    if (x) {
+        if (!dims_ok(d) || (x_dtype != MOE_F32 && x_dtype != MOE_BF16)) return MOE_ERR_INVALID_ARG;
+        if (!moe_aligned16(x) || !moe_aligned16(xg)) return MOE_ERR_INVALID_ARG;
+    }
+    if (!moe_aligned16(idx) || !moe_aligned16(perm) || !moe_aligned16(inv_perm))
+        return MOE_ERR_INVALID_ARG;
+    return MOE_OK;
+}
+
+// `path`: the caller's; in its place the kernel family that runs (all-fp32: AUTO).
+static int ffn_args(const moe_weights_t* W, const void* xg, moe_dtype_t act_dtype, const int32_t* offsets,
+                    int N, const void* workspace, size_t workspace_bytes, const float* yg, int& path) {
     if (!W || N < 0 || N >= MOE_MAX_N) return MOE_ERR_INVALID_ARG;
     if (act_dtype != MOE_F32 && act_dtype != MOE_BF16) return MOE_ERR_INVALID_ARG;
     if (path != MOE_FFN_AUTO && path != MOE_FFN_STREAM && path != MOE_FFN_GROUPED &&
@@ -51,16 +77,45 @@ static int ffn_dispatch(const moe_weights_t* W, const void* xg, moe_dtype_t act_
     if (!workspace || (((uintptr_t)workspace) & 255u)) return MOE_ERR_WORKSPACE;
     if (workspace_bytes < moe_expert_ffn_workspace(N, W->E, W->d, W->f, act_dtype))
         return MOE_ERR_WORKSPACE;
-    hipStream_t s = (hipStream_t)stream;
-
+    bool served;
     if (W->dtype == MOE_F32) {
-        if (act_dtype != MOE_F32 || path != MOE_FFN_AUTO) return MOE_ERR_UNSUPPORTED;
-        return moe_ffn_f32_launch(W, (const float*)xg, perm, k, offsets, N, workspace, yg, s);
+        served = act_dtype == MOE_F32 && path == MOE_FFN_AUTO && moe_ffn_f32_supported(N, W->E);
+    } else {
+        if (path == MOE_FFN_AUTO) path = moe_ffn_auto_path(N, W->E, W->d, W->f);
+        served = path == MOE_FFN_STREAM ? moe_ffn_stream_serves(N, W->E, W->d, W->f)
+                                        : moe_ffn_grouped_supported(path == MOE_FFN_MID, N, W->E, W->d, W->f);
     }
-    if (path == MOE_FFN_AUTO) path = moe_ffn_auto_path(N, W->E, W->d, W->f);
+    return served ? MOE_OK : MOE_ERR_UNSUPPORTED;
+}
+
+static int combine_args(const float* yg, const int32_t* inv_perm, const float* weights, int T, int k, int d,
+                        const float* y) {
+    if (T < 0 || k < 1 || k > MOE_MAX_K || (long long)T * k >= MOE_MAX_N || !dims_ok(d))
+        return MOE_ERR_INVALID_ARG;
+    if (T == 0) return MOE_OK;
+    if (!yg || !inv_perm || !weights || !y) return MOE_ERR_INVALID_ARG;
+    if (!moe_aligned16(yg) || !moe_aligned16(y)) return MOE_ERR_INVALID_ARG;
+    return MOE_OK;
+}
+
+// The launches of moe_expert_ffn and its variants, arguments checked, `path` as ffn_args left it.  With
+// `perm` the batched row i is read as xg[perm[i] / k] (xg is then the token array).
+static int ffn_launch(const moe_weights_t* W, const void* xg, moe_dtype_t act_dtype, const int32_t* perm, int k,
+                      const int32_t* offsets, int N, void* workspace, float* yg, int path, hipStream_t s) {
+    if (N == 0) return MOE_OK;
+    if (W->dtype == MOE_F32)
+        return moe_ffn_f32_launch(W, (const float*)xg, perm, k, offsets, N, workspace, yg, s);
     if (path == MOE_FFN_STREAM)
         return moe_ffn_stream_launch(W, xg, act_dtype, perm, k, offsets, N, workspace, yg, nullptr, s);
     return moe_ffn_grouped_launch(path == MOE_FFN_MID, W, xg, act_dtype, perm, k, offsets, N, workspace, yg, s);
+}
+
+static int ffn_dispatch(const moe_weights_t* W, const void* xg, moe_dtype_t act_dtype,
+                        const int32_t* perm, int k, const int32_t* offsets, int N, void* workspace,
+                        size_t workspace_bytes, float* yg, int path, void* stream) {
+    const int rc = ffn_args(W, xg, act_dtype, offsets, N, workspace, workspace_bytes, yg, path);
+    if (rc != MOE_OK) return rc;
+    return ffn_launch(W, xg, act_dtype, perm, k, offsets, N, workspace, yg, path, (hipStream_t)stream);
 }
 
 extern "C" {
@@ -78,27 +133,16 @@ const char* moe_status_string(int status) {
 
 int moe_route(const float* logits, int T, int E, int k, int32_t* idx, float* weights,
               void* stream) {
-    if (!tek_ok(T, E, k)) return MOE_ERR_INVALID_ARG;
-    if (T == 0) return MOE_OK;
-    if (!logits || !idx || !weights) return MOE_ERR_INVALID_ARG;
-    if (!moe_aligned16(logits) || !moe_aligned16(idx) || !moe_aligned16(weights))
-        return MOE_ERR_INVALID_ARG;
+    const int rc = route_args(logits, T, E, k, idx, weights);
+    if (rc != MOE_OK || T == 0) return rc;
     return moe_route_launch(logits, T, E, k, idx, weights, (hipStream_t)stream);
 }
 
 int moe_permute(const int32_t* idx, int T, int E, int k, const void* x, int d,
                 moe_dtype_t x_dtype, int32_t* counts, int32_t* offsets, int32_t* perm,
                 int32_t* inv_perm, void* xg, void* stream) {
-    if (!tek_ok(T, E, k)) return MOE_ERR_INVALID_ARG;
-    if (!counts || !offsets) return MOE_ERR_INVALID_ARG;
-    if (T > 0 && (!idx || !perm || !inv_perm)) return MOE_ERR_INVALID_ARG;
-    if ((x == nullptr) != (xg == nullptr)) return MOE_ERR_INVALID_ARG;
-    if (x) {
-        if (!dims_ok(d) || (x_dtype != MOE_F32 && x_dtype != MOE_BF16)) return MOE_ERR_INVALID_ARG;
-        if (!moe_aligned16(x) || !moe_aligned16(xg)) return MOE_ERR_INVALID_ARG;
-    }
-    if (!moe_aligned16(idx) || !moe_aligned16(perm) || !moe_aligned16(inv_perm))
-        return MOE_ERR_INVALID_ARG;
+    const int rc = permute_args(idx, T, E, k, x, d, x_dtype, counts, offsets, perm, inv_perm, xg);
+    if (rc != MOE_OK) return rc;
     // T == 0 still writes counts = 0 and offsets = 0.
     return moe_permute_launch(idx, T, E, k, T > 0 ? x : nullptr, d, x_dtype, counts, offsets, perm,
                               inv_perm, xg, (hipStream_t)stream);
@@ -290,11 +334,8 @@ int moe_decode_block(const moe_weights_t* W, const float* x_in, const float* gat
 
 int moe_combine(const float* yg, const int32_t* inv_perm, const float* weights, int T, int k,
                 int d, float* y, void* stream) {
-    if (T < 0 || k < 1 || k > MOE_MAX_K || (long long)T * k >= MOE_MAX_N || !dims_ok(d))
-        return MOE_ERR_INVALID_ARG;
-    if (T == 0) return MOE_OK;
-    if (!yg || !inv_perm || !weights || !y) return MOE_ERR_INVALID_ARG;
-    if (!moe_aligned16(yg) || !moe_aligned16(y)) return MOE_ERR_INVALID_ARG;
+    const int rc = combine_args(yg, inv_perm, weights, T, k, d, y);
+    if (rc != MOE_OK || T == 0) return rc;
     return moe_combine_launch(yg, inv_perm, weights, T, k, d, y, (hipStream_t)stream);
 }
 
@@ -303,23 +344,32 @@ int moe_layer(const moe_weights_t* W, const void* x, moe_dtype_t x_dtype, int d,
               int32_t* perm, int32_t* inv_perm, void* xg, void* workspace, size_t workspace_bytes, float* yg,
               float* y, int* stage, void* stream) {
     if (!stage) return MOE_ERR_INVALID_ARG;
-    // The rows of xg are gathered with length d and read with length W->d, and ids of W->E and above have no
-    // expert.  (Fewer logits than experts: the last experts get no tokens.)
-    *stage = 1;
-    if (W && T > 0 && (d != W->d || E > W->E)) return MOE_ERR_INVALID_ARG;
-    int rc = moe_route(logits, T, E, k, idx, weights, stream);
+    int rc;
+    // every call's arguments, before the first launch
     *stage = 0;
-    if (rc != MOE_OK) return rc;
+    if ((rc = route_args(logits, T, E, k, idx, weights)) != MOE_OK) return rc;
     *stage = 2;
     if (!W) return MOE_ERR_INVALID_ARG;
     *stage = 1;
-    rc = moe_permute(idx, T, W->E, k, x, d, x_dtype, counts, offsets, perm, inv_perm, xg, stream);
+    // The rows of xg are gathered with length d and read with length W->d, and ids of W->E and above have no
+    // expert.  (Fewer logits than experts: the last experts get no tokens.)
+    if (T > 0 && (d != W->d || E > W->E)) return MOE_ERR_INVALID_ARG;
+    if ((rc = permute_args(idx, T, W->E, k, x, d, x_dtype, counts, offsets, perm, inv_perm, xg)) != MOE_OK) return rc;
+    *stage = 2;
+    if ((rc = ffn_args(W, xg, x_dtype, offsets, T * k, workspace, workspace_bytes, yg, path)) != MOE_OK) return rc;
+    *stage = 3;
+    if ((rc = combine_args(yg, inv_perm, weights, T, k, W->d, y)) != MOE_OK) return rc;
+
+    hipStream_t s = (hipStream_t)stream;
+    *stage = 0;
+    if (T > 0 && (rc = moe_route_launch(logits, T, E, k, idx, weights, s)) != MOE_OK) return rc;
+    *stage = 1;
+    rc = moe_permute_launch(idx, T, W->E, k, T > 0 ? x : nullptr, d, x_dtype, counts, offsets, perm, inv_perm, xg, s);
     if (rc != MOE_OK) return rc;
     *stage = 2;
-    rc = moe_expert_ffn_path(W, xg, x_dtype, offsets, T * k, workspace, workspace_bytes, yg, path, stream);
-    if (rc != MOE_OK) return rc;
+    if ((rc = ffn_launch(W, xg, x_dtype, nullptr, 1, offsets, T * k, workspace, yg, path, s)) != MOE_OK) return rc;
     *stage = 3;
-    return moe_combine(yg, inv_perm, weights, T, k, W->d, y, stream);
+    return T == 0 ? MOE_OK : moe_combine_launch(yg, inv_perm, weights, T, k, W->d, y, s);
 }
 
 int moe_rmsnorm(const float* x, int T, int d, float eps, float* h, void* stream) {

@@ -180,9 +180,12 @@ static void ffn_f32_projection(const float* act, const int32_t* perm, int perm_k
 #undef F32_CASE
 }
 
+// the largest call served (gridDim.y)
+bool moe_ffn_f32_supported(int N, int E) { return N / 32 + E <= 65535; }
+
 int moe_ffn_f32_launch(const moe_weights* W, const float* xg, const int32_t* perm, int k,
                        const int32_t* offsets, int N, void* ws, float* yg, hipStream_t s) {
-    if (N / 32 + W->E > 65535) return MOE_ERR_UNSUPPORTED;  // the largest call served (gridDim.y)
+    if (!moe_ffn_f32_supported(N, W->E)) return MOE_ERR_UNSUPPORTED;
     float* h = (float*)ws;
     ffn_f32_projection<true>(xg, perm, k, (const float*)W->w1f, (const float*)W->w3f, offsets, W->E, N,
                              W->d, W->f, h, s);

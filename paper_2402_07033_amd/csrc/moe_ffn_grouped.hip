@@ -1078,8 +1078,8 @@ int moe_ffn_grouped_launch(bool mid, const moe_weights* W, const void* xg, moe_d
     return gg_launch(W, xg, act_dtype, perm, k, offsets, N, ws, yg, vu, vd, short_down, s);
 }
 
-bool moe_ffn_mid_supported(int N, int E, int d, int f) {
+bool moe_ffn_grouped_supported(bool mid, int N, int E, int d, int f) {
     GgVariant vu, vd;
     bool short_down;
-    return gg_path_choose(true, N, E, d, f, vu, vd, short_down);
+    return gg_path_choose(mid, N, E, d, f, vu, vd, short_down);
 }

@@ -779,6 +779,11 @@ static bool stream_shape_ok(const StreamPlan& pl, int N, int E, int d, int f) {
     return (long long)ST_MAX_TILES * pl.Pd * ((d > f ? d : f) / 16) < (1ll << 31);
 }
 
+bool moe_ffn_stream_serves(int N, int E, int d, int f) {
+    StreamPlan pl;
+    return stream_plan(d, f, pl) && stream_shape_ok(pl, N, E, d, f);
+}
+
 static StreamArgs stream_args_up(const moe_weights* W, const StreamPlan& pl, const void* act,
                                  const int32_t* offsets, int N, float* h) {
     StreamArgs up = {};

@@ -65,12 +65,14 @@ int moe_ffn_auto_path(int N, int E, int d, int f);
 
 // ---- expert FFN kernel families (each returns a moe_status_t) ----------------
 size_t moe_ffn_f32_workspace(int N, int E, int d, int f);
+bool moe_ffn_f32_supported(int N, int E);
 // All launchers: with `perm` (device, or null) the batched row i of the activations is read
 // as xg[perm[i] / k], i.e. xg is the token array and no gathered copy exists.
 int moe_ffn_f32_launch(const moe_weights* W, const float* xg, const int32_t* perm, int k,
                        const int32_t* offsets, int N, void* ws, float* yg, hipStream_t s);
 
-bool moe_ffn_stream_supported(int d, int f);
+bool moe_ffn_stream_supported(int d, int f);                   // has a plan for the shape ...
+bool moe_ffn_stream_serves(int N, int E, int d, int f);        // ... and tiles for the rows
 size_t moe_ffn_stream_workspace(int N, int E, int d, int f);
 int moe_ffn_stream_parts(int N, int d, int f);  // slabs the second projection leaves (0: unsupported)
 int moe_ffn_stream_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
@@ -97,7 +99,7 @@ int moe_ffn_grouped_plan(bool mid, int N, int E, int d, int f, moe_ffn_plan_t* p
 int moe_ffn_grouped_launch(bool mid, const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
                            const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
                            float* yg, hipStream_t s);
-bool moe_ffn_mid_supported(int N, int E, int d, int f);
+bool moe_ffn_grouped_supported(bool mid, int N, int E, int d, int f);
 
 // ---- small device helpers ------------------------------------------------------
 #ifdef __HIPCC__

@@ -142,6 +142,30 @@ def test_layer_sizes_are_the_weights(L):
     assert _layer_call(L, E=64, d=4096) == (-1, 1)
 
 
+def test_layer_checks_all_four_calls_before_the_first_launch(L):
+    """Without a device a launch ends in MOE_ERR_HIP, so any other status came before it."""
+    buf = (C.c_char * 512)()
+    p = (C.addressof(buf) + 255) & ~255
+    INVALID, UNSUPPORTED, WORKSPACE = -1, -2, -3
+    need = L.moe_expert_ffn_workspace(8, 8, 256, 512, 0)
+    for change, status, stage in [
+            (dict(logits=None), INVALID, 0), (dict(k=9), INVALID, 0), (dict(k=9, d=64), INVALID, 0),
+            (dict(T=1 << 23), INVALID, 0), (dict(weights=p + 4), INVALID, 0),
+            (dict(perm=None), INVALID, 1), (dict(xg=None), INVALID, 1), (dict(x=p + 8), INVALID, 1),
+            (dict(W=None), INVALID, 2), (dict(W=None, d=64), INVALID, 2), (dict(path=4), INVALID, 2),
+            (dict(yg=None), INVALID, 2), (dict(yg=p + 4), INVALID, 2), (dict(workspace=None), WORKSPACE, 2),
+            (dict(workspace=p + 16), WORKSPACE, 2), (dict(workspace_bytes=need - 1), WORKSPACE, 2),
+            (dict(y=None), INVALID, 3), (dict(y=p + 4), INVALID, 3),
+            (dict(y=p + 4, E=3), INVALID, 3)]:     # three logits per token, eight experts: sizes accepted
+        assert _layer_call(L, **change) == (status, stage), change
+    # no kernel family for the sizes: an all-fp32 layer on a forced path, 16-row tiles beyond the decode
+    # kernels' list, f = 128 through GROUPED
+    huge = dict(workspace_bytes=1 << 60)
+    f32, short = _Weights(E=8, d=256, f=512, dtype=0), _Weights(E=8, d=256, f=128, dtype=1)
+    for change in (dict(W=C.addressof(f32), path=2), dict(path=1, T=1 << 20, **huge), dict(W=C.addressof(short), path=2)):
+        assert _layer_call(L, **change) == (UNSUPPORTED, 2), change
+
+
 def test_ffn_plan_query(L):
     import paper_2402_07033_amd as m
     pl = m.moe_expert_ffn_plan(32, 8, 4096, 14336)

@@ -44,3 +44,26 @@ def test_layer_names_the_call_that_failed():
     W.free()
     with pytest.raises(moe.MoeError, match="moe_expert_ffn"):
         moe.moe_layer(W, xd, lg, 2)
+
+
+def test_refused_layer_has_enqueued_nothing():
+    import ctypes as C
+
+    import paper_2402_07033_amd as moe
+    W, xd, lg = _layer(8, 8, 2, mi.BF16, mi.F32)
+    T, E, k, N = 8, 8, 2, 16
+    idx, counts, perm, inv_perm = (torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (N, E, N, N))
+    offsets = torch.full((E + 1,), -7, dtype=torch.int32, device="cuda")
+    w, xg, yg, y = (torch.full(s, -7.0, device="cuda") for s in ((N,), (N, 256), (N, 256), (T, 256)))
+    ws = torch.empty(moe.moe_expert_ffn_workspace(N, E, 256, 512, moe.MOE_F32), dtype=torch.uint8, device="cuda")
+    stage = C.c_int(-1)
+    for ws_bytes, y_ptr, want in ((ws.numel() - 1, y.data_ptr(), (-3, 2)), (ws.numel(), y.data_ptr() + 4, (-1, 3))):
+        rc = moe.lib().moe_layer(W.handle, xd.data_ptr(), moe.MOE_F32, 256, lg.data_ptr(), T, E, k, moe.MOE_FFN_AUTO,
+                                 idx.data_ptr(), w.data_ptr(), counts.data_ptr(), offsets.data_ptr(), perm.data_ptr(),
+                                 inv_perm.data_ptr(), xg.data_ptr(), ws.data_ptr(), ws_bytes, yg.data_ptr(), y_ptr,
+                                 C.byref(stage), None)
+        torch.cuda.synchronize()
+        assert (rc, stage.value) == want
+        for t in (idx, counts, offsets, perm, inv_perm, w, xg, yg, y):
+            assert (t == -7).all()
+    W.free()
