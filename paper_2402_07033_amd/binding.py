@@ -572,6 +572,8 @@ def moe_hbm_read_probe(data: torch.Tensor, sink: torch.Tensor, stream=None) -> i
     return per_wave * 1024 * 8 * cus
 
 
+# the library's domain (include/moe.h)
+_MAX_K, _MAX_E, _MAX_N = 8, 64, 1 << 24
 _LAYER_CALLS = ("moe_route", "moe_permute", "moe_expert_ffn", "moe_combine")
 
 
@@ -585,6 +587,8 @@ def moe_layer(W: PackedWeights, x: torch.Tensor, logits: torch.Tensor, k: int,
     T, E = logits.shape
     d, xdt = x.shape[1], _act_dtype(x)
     N, dev = T * k, logits.device
+    if not 1 <= k <= min(E, _MAX_K) or E > _MAX_E or N >= _MAX_N:
+        moe_route(logits, k, stream=stream)  # refuses them, before N rows are allocated below
     i32, f32 = torch.int32, torch.float32
     idx = torch.empty((T, k), dtype=i32, device=dev)
     w = torch.empty((T, k), dtype=f32, device=dev)

@@ -46,6 +46,20 @@ def test_layer_names_the_call_that_failed():
         moe.moe_layer(W, xd, lg, 2)
 
 
+@pytest.mark.parametrize("k", [9, 300, 0, -1])
+def test_refused_k_allocates_no_rows(k):
+    """The call that refuses is the router's, at the router's price: T*k indices and weights."""
+    import paper_2402_07033_amd as moe
+    W, xd, lg = _layer(64, 8, 2, mi.BF16, mi.F32)
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    with pytest.raises(RuntimeError if k < 0 else moe.MoeError, match=None if k < 0 else "moe_route"):
+        moe.moe_layer(W, xd, lg, k)
+    assert torch.cuda.max_memory_allocated() - before <= 2 * (64 * max(k, 0) * 4 + 512)
+    W.free()
+
+
 def test_refused_layer_has_enqueued_nothing():
     import ctypes as C
 
