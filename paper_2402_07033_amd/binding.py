@@ -572,8 +572,8 @@ def moe_hbm_read_probe(data: torch.Tensor, sink: torch.Tensor, stream=None) -> i
     return per_wave * 1024 * 8 * cus
 
 
-# the library's domain (include/moe.h)
-_MAX_K, _MAX_E, _MAX_N = 8, 64, 1 << 24
+# the library's domain (include/moe.h) and the status of a call outside it
+_MAX_K, _MAX_E, _MAX_N, _INVALID_ARG = 8, 64, 1 << 24, -1
 _LAYER_CALLS = ("moe_route", "moe_permute", "moe_expert_ffn", "moe_combine")
 
 
@@ -589,6 +589,8 @@ def moe_layer(W: PackedWeights, x: torch.Tensor, logits: torch.Tensor, k: int,
     N, dev = T * k, logits.device
     if not 1 <= k <= min(E, _MAX_K) or E > _MAX_E or N >= _MAX_N:
         moe_route(logits, k, stream=stream)  # refuses them, before N rows are allocated below
+    if x.shape[0] < T:
+        raise MoeError(_INVALID_ARG, "moe_permute")
     i32, f32 = torch.int32, torch.float32
     idx = torch.empty((T, k), dtype=i32, device=dev)
     w = torch.empty((T, k), dtype=f32, device=dev)

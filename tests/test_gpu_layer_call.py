@@ -60,6 +60,26 @@ def test_refused_k_allocates_no_rows(k):
     W.free()
 
 
+def test_layer_sizes_that_do_not_fit():
+    """Fewer rows than logits, another row length, more logits than experts: refused.  More rows than
+    logits (the first T are used) and fewer logits than experts are ordinary calls."""
+    import paper_2402_07033_amd as moe
+    W, xd, lg = _layer(64, 8, 2, mi.BF16, mi.F32)
+    for x, logits in ((xd[:63], lg), (xd[:, :192].contiguous(), lg), (torch.cat([xd, xd], dim=1), lg),
+                      (xd, torch.cat([lg, lg[:, :1]], dim=1))):
+        with pytest.raises(moe.MoeError, match="moe_permute"):
+            moe.moe_layer(W, x, logits, 2)
+    five = lg[:37, :5].contiguous()
+    out = moe.moe_layer(W, xd, five, 2)
+    want = moe.moe_layer(W, xd[:37].contiguous(), five, 2)
+    assert all(torch.equal(out[n], want[n]) for n in want)
+    assert (out["counts"][5:] == 0).all() and int(out["offsets"][-1]) == 74
+    idx, w = moe.moe_route(five, 2)
+    _, offsets, _, inv_perm, xg = moe.moe_permute(idx, 8, xd[:37])
+    assert torch.equal(out["y"], moe.moe_combine(moe.moe_expert_ffn(W, xg, offsets), inv_perm, w))
+    W.free()
+
+
 def test_refused_layer_has_enqueued_nothing():
     import ctypes as C
 
