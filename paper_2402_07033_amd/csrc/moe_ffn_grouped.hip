@@ -66,6 +66,7 @@
 #include "moe_internal.h"
 #include "moe_frag_pack.h"
 #include "moe_gg_ring.h"
+#include "moe_gg_sched.h"
 
 // Tile shapes (token rows x weight fragment rows of 16 features per workgroup), by the mean
 // number of rows per expert:
@@ -105,7 +106,7 @@ struct GroupedArgs {
     int NT;      // workgroup tiles along the features = FR / FROWS
     int KS_out;  // up: f/32 (fragment columns of hp); down: unused
     int C;       // down: d (row length of yg)
-    int split;   // left-over tiles are cut in pieces if they are at most split/32 of a round (0: never)
+    int split;   // gg_split_limit
     float* part; // split: partial tiles [8 XCDs][workgroups per XCD][2][256*256] fp32
 };
 
@@ -168,16 +169,9 @@ __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets,
     return __builtin_amdgcn_readlane(inc_t, 63) * NT;
 }
 
-// Does every XCD start with a round of its own, an eighth of all rounds behind its neighbour's?  Tiles of
-// an expert that has no other token tile wait for their weights from HBM, tiles of many rows are bound by the
-// matrix cores' power: where both are there, they should be at work at the same time.  First projection, in
-// step -> turned: 16 experts, 4096 tokens Zipf 777 -> 746 us, 1531 tokens 655 -> 627, 1000 tokens 535 -> 501, 64
-// experts, 2000 tokens 211 -> 195.  Not where fewer than 1 of 8 token tiles is its expert's only one (8 x 700 rows
-// 1021 -> 1033, 4096 tokens 1473 -> 1471, its second projection 726 -> 733) and not with fewer than 4
-// rounds (2: 342 -> 357).
-#define GG_TURN_ROUNDS 4
+// The schedule's turn, decided by one wave from the table (moe_gg_sched.h).
 __device__ __forceinline__ bool gg_turned(const int (*tab)[64], int lane, int total, int NT) {
-    return __popcll(__ballot(tab[GG_SEG_TILES][lane] == 1)) * 8 * NT >= total;
+    return gg_turned(__popcll(__ballot(tab[GG_SEG_TILES][lane] == 1)), total, NT);
 }
 
 // Logical tile index -> tile, from the table.
@@ -216,60 +210,6 @@ __device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lan
     ti.partial = false;
     ti.piece = 0;
     return true;
-}
-
-// Whole tiles go out in n_full rounds of one tile per workgroup.  The tiles of the last, incomplete
-// round are dealt to the XCDs evenly, and cut there along the reduction so that all workgroups
-// take part (see the body below) -- or left whole, one for each of the first workgroups: pieces store and
-// re-read their partial sums, work at different steps of tiles that would otherwise share operands in L2, and a
-// round that is nearly full saves little; with few workgroups at work the others' power goes to them.  Measured,
-// pieces (fix-up included) -> whole:
-//   first projection, 128 steps, 3..7 rounds before: 0.06..0.38 of a round 355..683 -> 401..695 us, 0.69 462 -> 482,
-//     0.75..0.97 294 -> 292 (77 tokens), 440 -> 433, 386 -> 331; 9 and more rounds before: 0.19 939 -> 918, 0.31 (4096
-//     tokens) 1488 -> 1446, 0.75 928 -> 866; 64 steps: 0.75 140 -> 135;
-//   second projection: 448 steps, 0.19..0.5 of a round 146..209 -> 281..351, 0.62 279 -> 288 and 328 -> 332, 0.69 313 -> 296,
-//     0.75 402 -> 335, 0.88 469 -> 347; 200 steps: 0.5 258 -> 287.
-#define GG_SPLIT_UP 22          // 32nds of a round up to which the first projection's left-over tiles are cut
-#define GG_SPLIT_DOWN 20        // the second's
-#define GG_SPLIT_MIN_STEPS 36   // steps that cutting has to save (of what it saves at best)
-#define GG_SPLIT_MAX_ROUNDS 8   // ... and rounds of whole tiles from which they stay whole
-struct GgSched {
-    int n_full;   // rounds of whole tiles
-    int left_lo;  // this XCD's left-over tiles: [left_lo, left_lo + R)
-    int R;
-    bool split;   // are they cut in pieces
-};
-__device__ __forceinline__ GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
-    GgSched sc;
-    const int W = wgs * 8;
-    sc.n_full = total / W;
-    const int left = total - sc.n_full * W;
-    const int lo = left * xcd / 8, hi = left * (xcd + 1) / 8;
-    sc.left_lo = sc.n_full * W + lo;
-    sc.R = hi - lo;
-    sc.split = left * 32 <= W * split && (W - left) * KS >= W * GG_SPLIT_MIN_STEPS && sc.n_full < GG_SPLIT_MAX_ROUNDS;
-    return sc;
-}
-// Workgroup me of an XCD takes a different one of the round's 32 neighbours every round: the
-// token tiles of an expert differ in length, and their period must not pick workgroups.
-__device__ __forceinline__ int gg_round_slot(int n, int wgs, int xcd, int me) {
-    return n * wgs * 8 + xcd * wgs + (int)((unsigned)(me + n) % (unsigned)wgs);
-}
-
-// Cut points of the left-over tiles' joint reduction (S = R tiles x KS steps) for the
-// workgroups of one XCD: workgroup j covers [cut(j), cut(j+1)).  Pieces are multiples of
-// `unit` steps (KS is one too) and no piece is shorter than the smallest multiple of `unit`
-// that covers the `ns` LDS stages of the kernel's pipeline.
-__device__ __forceinline__ int gg_piece_cut(int j, int S, int KS, int wgs, int unit, int ns) {
-    const int minp = (ns + unit - 1) / unit * unit;
-    int per = ((S + wgs - 1) / wgs + unit - 1) / unit * unit;
-    per = per < 32 ? 32 : per;
-    const int c = j * per;
-    if (c >= S) return S;
-    const int r = c % KS;
-    if (r < minp) return c - r;
-    if (KS - r < minp) return c + (KS - r);
-    return c;
 }
 
 // Weight fragment load.  ANT: non-temporal, for a tile whose expert has no other token tile: its
@@ -433,7 +373,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
     const bool split = sc.split;
     const int last = (int)((unsigned)(me + sc.n_full) % (unsigned)wgs);  // left-over tile, if it stays whole
     const int n_full = sc.n_full + (!split && last < sc.R ? 1 : 0);
-    const int turn = turned && sc.n_full >= GG_TURN_ROUNDS ? sc.n_full * xcd / 8 : 0;  // the XCD's first round
+    const int turn = gg_first_round(turned, sc.n_full, xcd);
     // pieces of the left-over tiles for this workgroup
     // (plain scalars, no arrays: an array indexed at run time would live in scratch memory, and
     // every read of it would wait on the counter of the operand loads in flight)
@@ -923,9 +863,7 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
     a.FROWS = sh.frows;
     if (a.FR % a.FROWS != 0) return MOE_ERR_UNSUPPORTED;
     a.NT = a.FR / a.FROWS;
-    // pieces of >= 32 steps go to scratch and a fix-up kernel adds them; it lists the pieces
-    // of a tile with one wave, hence at most 64 workgroups per XCD
-    a.split = (a.KS >= 64 && pgrid / 8 <= 64) ? (UP ? GG_SPLIT_UP : GG_SPLIT_DOWN) : 0;
+    a.split = gg_split_limit(UP, a.KS, (int)(pgrid / 8));
     void* params[1] = {(void*)&a};
     const size_t lds_bytes = (size_t)sh.ns * sh.tb * MOE_FRAG_BYTES;
     MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<UP>(v), dim3(pgrid), dim3(GG_THREADS), params, lds_bytes, s));

@@ -1,0 +1,82 @@
+// How the grouped GEMM (moe_ffn_grouped.hip) deals its tiles to its workgroups: rounds of whole
+// tiles, the tiles of the last, incomplete round, and where these are cut.  Plain functions, so
+// that the schedule can also be replayed on the host.
+//
+// Tiles are numbered 0 .. total-1 (expert, group of token tiles, feature tile, token tile); 8 * wgs
+// workgroups, wgs for each XCD.
+#pragma once
+
+// Whole tiles go out in n_full rounds of one tile per workgroup.  The tiles of the last, incomplete
+// round are dealt to the XCDs evenly, and cut there along the reduction so that all workgroups
+// take part -- or left whole, one for each of the first workgroups: pieces store and
+// re-read their partial sums, work at different steps of tiles that would otherwise share operands in L2, and a
+// round that is nearly full saves little; with few workgroups at work the others' power goes to them.  Measured,
+// pieces (fix-up included) -> whole:
+//   first projection, 128 steps, 3..7 rounds before: 0.06..0.38 of a round 355..683 -> 401..695 us, 0.69 462 -> 482,
+//     0.75..0.97 294 -> 292 (77 tokens), 440 -> 433, 386 -> 331; 9 and more rounds before: 0.19 939 -> 918, 0.31 (4096
+//     tokens) 1488 -> 1446, 0.75 928 -> 866; 64 steps: 0.75 140 -> 135;
+//   second projection: 448 steps, 0.19..0.5 of a round 146..209 -> 281..351, 0.62 279 -> 288 and 328 -> 332, 0.69 313 -> 296,
+//     0.75 402 -> 335, 0.88 469 -> 347; 200 steps: 0.5 258 -> 287.
+#define GG_SPLIT_UP 22          // 32nds of a round up to which the first projection's left-over tiles are cut
+#define GG_SPLIT_DOWN 20        // the second's
+#define GG_SPLIT_MIN_STEPS 36   // steps that cutting has to save (of what it saves at best)
+#define GG_SPLIT_MAX_ROUNDS 8   // ... and rounds of whole tiles from which they stay whole
+// Left-over tiles are cut if they are at most this many 32nds of a round (0: never).  Pieces of >= 32 steps
+// go to scratch and a fix-up kernel adds them; it lists the pieces of a tile with one wave, hence at
+// most 64 workgroups per XCD.
+constexpr int gg_split_limit(bool up, int KS, int wgs) {
+    return KS >= 64 && wgs <= 64 ? (up ? GG_SPLIT_UP : GG_SPLIT_DOWN) : 0;
+}
+struct GgSched {
+    int n_full;   // rounds of whole tiles
+    int left_lo;  // this XCD's left-over tiles: [left_lo, left_lo + R)
+    int R;
+    bool split;   // are they cut in pieces
+};
+constexpr GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
+    GgSched sc{};
+    const int W = wgs * 8;
+    sc.n_full = total / W;
+    const int left = total - sc.n_full * W;
+    const int lo = left * xcd / 8, hi = left * (xcd + 1) / 8;
+    sc.left_lo = sc.n_full * W + lo;
+    sc.R = hi - lo;
+    sc.split = left * 32 <= W * split && (W - left) * KS >= W * GG_SPLIT_MIN_STEPS && sc.n_full < GG_SPLIT_MAX_ROUNDS;
+    return sc;
+}
+// Workgroup me of an XCD takes a different one of the round's 32 neighbours every round: the
+// token tiles of an expert differ in length, and their period must not pick workgroups.
+constexpr int gg_round_slot(int n, int wgs, int xcd, int me) {
+    return n * wgs * 8 + xcd * wgs + (int)((unsigned)(me + n) % (unsigned)wgs);
+}
+
+// Cut points of the left-over tiles' joint reduction (S = R tiles x KS steps) for the
+// workgroups of one XCD: workgroup j covers [cut(j), cut(j+1)).  Pieces are multiples of
+// `unit` steps (KS is one too) and no piece is shorter than the smallest multiple of `unit`
+// that covers the `ns` LDS stages of the kernel's pipeline.
+constexpr int gg_piece_cut(int j, int S, int KS, int wgs, int unit, int ns) {
+    const int minp = (ns + unit - 1) / unit * unit;
+    int per = ((S + wgs - 1) / wgs + unit - 1) / unit * unit;
+    per = per < 32 ? 32 : per;
+    const int c = j * per;
+    if (c >= S) return S;
+    const int r = c % KS;
+    if (r < minp) return c - r;
+    if (KS - r < minp) return c + (KS - r);
+    return c;
+}
+
+// Does every XCD start with a round of its own, an eighth of all rounds behind its neighbour's?  Tiles of
+// an expert that has no other token tile wait for their weights from HBM, tiles of many rows are bound by the
+// matrix cores' power: where both are there, they should be at work at the same time.  First projection, in
+// step -> turned: 16 experts, 4096 tokens Zipf 777 -> 746 us, 1531 tokens 655 -> 627, 1000 tokens 535 -> 501, 64
+// experts, 2000 tokens 211 -> 195.  Not where fewer than 1 of 8 token tiles is its expert's only one (8 x 700 rows
+// 1021 -> 1033, 4096 tokens 1473 -> 1471, its second projection 726 -> 733) and not with fewer than 4
+// rounds (2: 342 -> 357).
+#define GG_TURN_ROUNDS 4
+// ones: experts of one token tile, each NT of the total tiles.
+constexpr bool gg_turned(int ones, int total, int NT) { return ones * 8 * NT >= total; }
+// The XCD's first round.
+constexpr int gg_first_round(bool turned, int n_full, int xcd) {
+    return turned && n_full >= GG_TURN_ROUNDS ? n_full * xcd / 8 : 0;
+}

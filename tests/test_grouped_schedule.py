@@ -1,0 +1,31 @@
+"""The grouped GEMM's schedule, replayed on the CPU with the kernel's own functions
+(csrc/moe_gg_sched.h): every step of every tile is dealt exactly once."""
+import pytest
+
+import gg_schedule as gs
+
+
+@pytest.mark.parametrize("wgs", [32, 5])
+@pytest.mark.parametrize("KS", [8, 64, 128, 448])
+@pytest.mark.parametrize("up", [True, False])
+def test_every_step_is_dealt_once(wgs, KS, up):
+    W = 8 * wgs
+    for rounds in (0, 1, 3, 4, 7, 8, 11):
+        for left in sorted({0, 1, 7, W // 16, W // 4, W // 2 + 3, 5 * W // 8, 11 * W // 16, W - 1}):
+            total = rounds * W + left
+            for turned in (False, True):
+                work = gs.dealt(total, KS, up, turned, wgs)
+                steps = {}
+                for mine in work:
+                    pieces = [m for m in mine if m[2] < KS]
+                    # the kernel has two scratch slots per workgroup; a piece covers its ring's 8 stages
+                    assert len(pieces) <= 2 and all(n >= 8 and n % 4 == 0 for _, _, n in pieces)
+                    for tile, lo, n in mine:
+                        steps.setdefault(tile, []).append((lo, n))
+                assert sorted(steps) == list(range(total))
+                for parts in steps.values():
+                    at = 0
+                    for lo, n in sorted(parts):
+                        assert lo == at
+                        at += n
+                    assert at == KS
