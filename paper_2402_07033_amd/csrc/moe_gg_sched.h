@@ -13,14 +13,17 @@
 // round that is nearly full saves little; with few workgroups at work the others' power goes to them.  Measured,
 // pieces (fix-up included) -> whole:
 //   first projection, 128 steps, 3..7 rounds before: 0.06..0.38 of a round 355..683 -> 401..695 us, 0.69 462 -> 482,
-//     0.75..0.97 294 -> 292 (77 tokens), 440 -> 433, 386 -> 331; 9 and more rounds before: 0.19 939 -> 918, 0.31 (4096
-//     tokens) 1488 -> 1446, 0.75 928 -> 866; 64 steps: 0.75 140 -> 135;
+//     0.75..0.97 294 -> 292 (77 tokens), 440 -> 433, 386 -> 331; 8..15 rounds before, 20 sizes and routings: 0.01..0.2
+//     790..1172 -> 832..1206 (0.3..5 %), 0.25..0.4 0.3..3 % (4096 tokens 1441 -> 1446), 0.5 even, 0.59 749 -> 759 and
+//     792 -> 788, 0.75 887 -> 864; 25 and 56 rounds even; 64 steps: 0.04..0.08 443..456 ->
+//     458..468, 0.46 267 -> 271, 0.75 140 -> 135;
 //   second projection: 448 steps, 0.19..0.5 of a round 146..209 -> 281..351, 0.62 279 -> 288 and 328 -> 332, 0.69 313 -> 296,
-//     0.75 402 -> 335, 0.88 469 -> 347; 200 steps: 0.5 258 -> 287.
+//     0.75 402 -> 335, 0.88 469 -> 347; 200 steps: 0.5 258 -> 287, 0.69 427 -> 437, 0.75 449 -> 450, 460 -> 435; 8 rounds
+//     before and 0.06..0.25 of one: 448 steps 2560..2618 -> 2763..2773, 200 steps 1282..1318 -> 1341..1351, 128 steps
+//     893 -> 918.
 #define GG_SPLIT_UP 22          // 32nds of a round up to which the first projection's left-over tiles are cut
 #define GG_SPLIT_DOWN 20        // the second's
 #define GG_SPLIT_MIN_STEPS 36   // steps that cutting has to save (of what it saves at best)
-#define GG_SPLIT_MAX_ROUNDS 8   // ... and rounds of whole tiles from which they stay whole
 // Left-over tiles are cut if they are at most this many 32nds of a round (0: never).  Pieces of >= 32 steps
 // go to scratch and a fix-up kernel adds them; it lists the pieces of a tile with one wave, hence at
 // most 64 workgroups per XCD.
@@ -41,7 +44,7 @@ constexpr GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
     const int lo = left * xcd / 8, hi = left * (xcd + 1) / 8;
     sc.left_lo = sc.n_full * W + lo;
     sc.R = hi - lo;
-    sc.split = left * 32 <= W * split && (W - left) * KS >= W * GG_SPLIT_MIN_STEPS && sc.n_full < GG_SPLIT_MAX_ROUNDS;
+    sc.split = left * 32 <= W * split && (W - left) * KS >= W * GG_SPLIT_MIN_STEPS;
     return sc;
 }
 // Workgroup me of an XCD takes a different one of the round's 32 neighbours every round: the

@@ -39,6 +39,13 @@ def lib():
     return _lib
 
 
+def schedule(total, wgs, xcd, KS, up):
+    """gg_sched: rounds, the XCD's first left-over tile and their number, are they cut."""
+    out = (C.c_int * 4)()
+    lib().sched(total, wgs, xcd, KS, lib().split_limit(int(up), KS, wgs), out)
+    return tuple(out)
+
+
 @dataclass
 class Branch:
     """Which way one projection of a call goes."""
@@ -63,22 +70,19 @@ def branch(counts, tile_rows, tile_features, weight_rows, KS, up, cus=256):
     NT = weight_rows // tile_features
     per = [tiles_of(n, tile_rows) for n in counts if n]
     total = sum(map(len, per)) * NT
-    out = (C.c_int * 4)()
-    L.sched(total, wgs, 0, KS, L.split_limit(int(up), KS, wgs), out)
+    n_full, _, _, cut = schedule(total, wgs, 0, KS, up)
     ones = sum(len(p) == 1 for p in per)
-    left = total - out[0] * wgs * 8
-    turned = any(L.first_round(L.turned(ones, total, NT), out[0], x) for x in range(8))
-    return Branch(out[0], left, bool(out[3]) and left > 0, turned,
+    left = total - n_full * wgs * 8
+    turned = any(L.first_round(L.turned(ones, total, NT), n_full, x) for x in range(8))
+    return Branch(n_full, left, bool(cut) and left > 0, turned,
                   {u for p in per if len(p) == 1 for u in p}, {u for p in per if len(p) > 1 for u in p})
 
 
 def dealt(total, KS, up, turned, wgs):
     """(tile, first step, steps) of every unit of work, workgroup by workgroup."""
-    L, out, work = lib(), (C.c_int * 4)(), []
-    split_limit = L.split_limit(int(up), KS, wgs)
+    L, work = lib(), []
     for xcd in range(8):
-        L.sched(total, wgs, xcd, KS, split_limit, out)
-        n_full, left_lo, R, split = out
+        n_full, left_lo, R, split = schedule(total, wgs, xcd, KS, up)
         turn = L.first_round(int(turned), n_full, xcd)
         for me in range(wgs):
             mine = [(L.round_slot((n + turn) % n_full, wgs, xcd, me), 0, KS) for n in range(n_full)]

@@ -29,3 +29,13 @@ def test_every_step_is_dealt_once(wgs, KS, up):
                         assert lo == at
                         at += n
                     assert at == KS
+
+
+@pytest.mark.parametrize("up", [True, False])
+@pytest.mark.parametrize("KS", [64, 128, 448])
+def test_a_small_left_over_is_cut_behind_any_number_of_rounds(up, KS):
+    """A tenth of a round left whole costs nearly a tile's time, however many rounds came before."""
+    for rounds in (0, 1, 7, 8, 9, 25, 56):
+        assert gs.schedule(rounds * 256 + 24, 32, 0, KS, up)[3]
+    for rounds in (0, 8):    # and nearly a whole round stays whole
+        assert not gs.schedule(rounds * 256 + 200, 32, 0, KS, up)[3]
