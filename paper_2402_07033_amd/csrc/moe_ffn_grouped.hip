@@ -170,8 +170,8 @@ __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets,
 }
 
 // The schedule's turn, decided by one wave from the table (moe_gg_sched.h).
-__device__ __forceinline__ bool gg_turned(const int (*tab)[64], int lane, int total, int NT) {
-    return gg_turned(__popcll(__ballot(tab[GG_SEG_TILES][lane] == 1)), total, NT);
+__device__ __forceinline__ bool gg_turned(const int (*tab)[64], int lane, int total, int NT, int KS) {
+    return gg_turned(__popcll(__ballot(tab[GG_SEG_TILES][lane] == 1)), total, NT, KS);
 }
 
 // Logical tile index -> tile, from the table.
@@ -704,7 +704,7 @@ __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
     const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, threadIdx.x & 63, s_seg,
                                    threadIdx.x < 64);
     __syncthreads();
-    const bool turned = gg_turned(s_seg, threadIdx.x & 63, total, a.NT);
+    const bool turned = gg_turned(s_seg, threadIdx.x & 63, total, a.NT, a.KS);
     gg_gemm_body<UP, NBW, FRW, UP ? 1 : 0, U, LA, NS>(a, total, turned, s_seg);
     if (UP) {
         __syncthreads();  // no wave fills the LDS ring anew while another still reads it

@@ -72,13 +72,19 @@ constexpr int gg_piece_cut(int j, int S, int KS, int wgs, int unit, int ns) {
 // Does every XCD start with a round of its own, an eighth of all rounds behind its neighbour's?  Tiles of
 // an expert that has no other token tile wait for their weights from HBM, tiles of many rows are bound by the
 // matrix cores' power: where both are there, they should be at work at the same time.  First projection, in
-// step -> turned: 16 experts, 4096 tokens Zipf 777 -> 746 us, 1531 tokens 655 -> 627, 1000 tokens 535 -> 501, 64
-// experts, 2000 tokens 211 -> 195.  Not where fewer than 1 of 8 token tiles is its expert's only one (8 x 700 rows
-// 1021 -> 1033, 4096 tokens 1473 -> 1471, its second projection 726 -> 733) and not with fewer than 4
-// rounds (2: 342 -> 357).
+// step -> turned, at least 1 of 8 token tiles its expert's only one and at least 1 of 4 not: 16 experts, 4096 tokens Zipf
+// 780 -> 734 us, 1531 tokens 429 -> 417, 8 experts, 1531 tokens 661 -> 625, 64 experts, 2000 tokens 210 -> 195; of 34 others,
+// five shapes and three skews, 26 even to 10 % ahead, 8 behind by 1..3 %, most of them where no expert is much larger than another.
+// Fewer only ones: 8 x 700 rows 1021 -> 1033, 4096 tokens 1473 -> 1471, its second projection 726 -> 733.  Fewer others:
+// reductions of 128 and 256 steps, none 947..1014 -> 962..1044, 12 % 923 -> 1004, 17 % 1001 -> 1039, 21 % 1024 -> 1041, 22 %
+// 967 -> 1005; of 64 steps none 465..510 -> 470..502, 9..12 % 507..531 -> 499..512, so there they do not count.  With fewer
+// than 4 rounds: 2 rounds 342 -> 357.
 #define GG_TURN_ROUNDS 4
+#define GG_TURN_SHORT 64  // steps of the reduction
 // ones: experts of one token tile, each NT of the total tiles.
-constexpr bool gg_turned(int ones, int total, int NT) { return ones * 8 * NT >= total; }
+constexpr bool gg_turned(int ones, int total, int NT, int KS) {
+    return ones * 8 * NT >= total && (KS <= GG_TURN_SHORT || (total - ones * NT) * 4 >= total);
+}
 // The XCD's first round.
 constexpr int gg_first_round(bool turned, int n_full, int xcd) {
     return turned && n_full >= GG_TURN_ROUNDS ? n_full * xcd / 8 : 0;

@@ -17,7 +17,7 @@ void sched(int total, int wgs, int xcd, int KS, int split, int* out) {
     const GgSched s = gg_sched(total, wgs, xcd, KS, split);
     out[0] = s.n_full; out[1] = s.left_lo; out[2] = s.R; out[3] = s.split;
 }
-int turned(int ones, int total, int NT) { return gg_turned(ones, total, NT); }
+int turned(int ones, int total, int NT, int KS) { return gg_turned(ones, total, NT, KS); }
 int first_round(int turned, int n_full, int xcd) { return gg_first_round(turned != 0, n_full, xcd); }
 int round_slot(int n, int wgs, int xcd, int me) { return gg_round_slot(n, wgs, xcd, me); }
 int piece_cut(int j, int S, int KS, int wgs) { return gg_piece_cut(j, S, KS, wgs, GG_U, GG_NS); }
@@ -73,7 +73,7 @@ def branch(counts, tile_rows, tile_features, weight_rows, KS, up, cus=256):
     n_full, _, _, cut = schedule(total, wgs, 0, KS, up)
     ones = sum(len(p) == 1 for p in per)
     left = total - n_full * wgs * 8
-    turned = any(L.first_round(L.turned(ones, total, NT), n_full, x) for x in range(8))
+    turned = any(L.first_round(L.turned(ones, total, NT, KS), n_full, x) for x in range(8))
     return Branch(n_full, left, bool(cut) and left > 0, turned,
                   {u for p in per if len(p) == 1 for u in p}, {u for p in per if len(p) > 1 for u in p})
 

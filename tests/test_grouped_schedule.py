@@ -39,3 +39,15 @@ def test_a_small_left_over_is_cut_behind_any_number_of_rounds(up, KS):
         assert gs.schedule(rounds * 256 + 24, 32, 0, KS, up)[3]
     for rounds in (0, 8):    # and nearly a whole round stays whole
         assert not gs.schedule(rounds * 256 + 200, 32, 0, KS, up)[3]
+
+
+@pytest.mark.parametrize("counts,KS,turned", [
+    ([200] * 16, 128, False), ([200] * 16, 64, True),               # every expert has one tile
+    ([600] + [200] * 15, 128, False), ([600] + [200] * 15, 64, True),  # 3 of 18 tiles are a larger expert's
+    ([1500] + [130] * 15, 128, True),                               # 6 of 21
+    ([1800] * 14 + [100], 128, False), ([1800] * 14 + [100], 64, False)])   # 1 of 113 is an only one
+def test_turned_rounds_need_tiles_of_either_kind(counts, KS, turned):
+    got = gs.branch(counts, 256, 256, 32768, KS, True)
+    assert got.rounds >= 4 and got.turned == turned
+    # and never with fewer than four rounds
+    assert not gs.branch(counts[:2], 256, 256, 8192, KS, True).turned
