@@ -379,9 +379,11 @@ int moe_permute_launch(const int32_t* idx, int T, int E, int k, const void* x, i
 
 // ---------------------------------------------------------------- combine ----
 
-// STREAM: y is larger than the L2 caches (32 MiB in all), so the rows, read once, and y go past them.  4096 tokens, d = 4096, k = 2,
-// whose rows a program's own FFN left (gating, batching and combine together) 65.9 -> 62.0 us, of it loads 1.6 and
-// stores 2.0; behind the library's FFN (1531 and 4096 tokens) even.  Smaller y stays where the next kernel finds it.
+// STREAM: y is larger than the L2 caches (32 MiB in all), so the rows, read once, go past them.  A program's pass of
+// gating, batching and combine and the RMSNorm that reads y next, d = 4096, k = 2, buffers that change: 2100 tokens 58.0
+// us either way, 3000 74.5 -> 72.0, 4096 96.4 -> 90.1, 8192 206 -> 173; the same rows combined again and again, which
+// the caches then hold, 50.4 -> 53.7, 63.8 -> 66.4, 91.4 -> 85.5, 206 -> 170.  y itself stays where its next reader finds
+// it: stored past L2 the pass is faster (4096 tokens 59.8 -> 55.7) and the reader slower by more (90.1 -> 99.8 in all).
 #define COMBINE_STREAM_BYTES ((size_t)32 << 20)
 template <bool STREAM>
 __global__ __launch_bounds__(256) void combine_kernel(const float4* __restrict__ yg,
@@ -402,8 +404,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const float4* __restrict__
         acc.z += w * v.z;
         acc.w += w * v.w;
     }
-    if (STREAM) __builtin_nontemporal_store(__builtin_bit_cast(f32x4_t, acc), (f32x4_t*)y + (size_t)t * row_chunks + c);
-    else y[(size_t)t * row_chunks + c] = acc;
+    y[(size_t)t * row_chunks + c] = acc;
 }
 
 int moe_combine_launch(const float* yg, const int32_t* inv_perm, const float* weights, int T, int k,

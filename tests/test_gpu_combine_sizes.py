@@ -1,4 +1,4 @@
-"""moe_combine on either side of the size from which rows and output go past L2 (y of 32 MiB), row
+"""moe_combine on either side of the size from which its rows go past L2 (y of 32 MiB), row
 lengths, against the sum in fp64: k products and sums in fp32, each rounded by 2^-24 of what was added."""
 import pytest
 import torch
