@@ -176,8 +176,9 @@ __device__ void permute_indices(const int32_t* __restrict__ idx, int N, int E,
 // Bound: reading idx from L2 in every workgroup (N * 4 bytes each), then the row copy.  One
 // workgroup for all N slots (and a second launch that read every row k times) took 15 + 21 us at
 // 4096 tokens, k = 2, 8 KiB rows, and 14 us for the indices of 300 tokens, k = 6, 64 experts;
-// this one launch 18.5 and 5 us.  Routing, batching and combine together, with inputs that change: 4096
-// tokens, k = 2 80.7 -> 55.7 us (of it 8 by the combine); 8192 tokens, k = 6, 64 experts, 4 KiB rows 452 -> 173 us on the same buffers.
+// this one launch 18.5 and 5 us.  Routing, batching and combine together: 4096 tokens, k = 2, pass after pass over three
+// sets of buffers 80.7 -> 60 us (a single pass on buffers that were not used before gains less, 70.5 -> 68); 8192 tokens, k
+// = 6, 64 experts, 4 KiB rows 452 -> 173 us on the same buffers.
 #define PM_THREADS 512
 #define PM_WAVES (PM_THREADS / 64)
 #define PM_MAX_SLOTS 1024  // slots of a workgroup whose positions are kept for the row copy
@@ -185,9 +186,13 @@ __device__ void permute_indices(const int32_t* __restrict__ idx, int N, int E,
 static_assert(PM_EARLY_SLOTS >= PM_THREADS * 4, "at least one round of requests");
 
 // A wave's part of a row: 8 KiB of loads in flight, stored to k rows of xg.  pos(j): row of copy j.
-// STREAM: past L2 (the rows are read once).  From two rows per wave on: 8192 tokens of 16 KiB rows 82 -> 66 us; 4096
-// tokens of 8 KiB rows within a program's gating and batching 59.9 -> 55.6, on their own 18.5 either way; with 9 and
-// 12 rows for a workgroup's 8 waves, 16 KiB each, rows that the last-level cache holds 20.2 -> 22.6 and 28.8.
+// STREAM: past L2 (the rows are read once), from 16 rows of a workgroup (two per wave; more than 15 tokens per CU).  No
+// line in the times there: with 9..15 rows the differences are the same.  They lie in where the rows are.  In
+// memory: 8 KiB rows, k = 2, 3841 tokens 21.8 -> 18.7 us, 4096 24.8 -> 19.7, 16 KiB rows 43.2 -> 41.8; just written by another
+// kernel: even (17.5, 32 us), where rows and copies exceed the last-level cache 71 -> 66; read by this call last time, with
+// nothing between: 4096 tokens 18.0 -> 18.2, 8192 34.5 -> 36.9, 16 KiB rows 31.9 -> 34.2, k = 1 21.5 -> 24.8.  128-byte
+// rows even.  Gating, batching and combine with buffers that change, 4096 tokens 64 -> 60 us, with the residual add that
+// reads x and y next 91 -> 87.
 template <bool STREAM>
 __device__ __forceinline__ void load_row(const u32x4_t* __restrict__ src, int row_chunks, int c0, u32x4_t (&v)[8]) {
 #pragma unroll

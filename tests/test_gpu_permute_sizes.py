@@ -1,6 +1,6 @@
 """moe_permute where its launch changes: one token per workgroup and several, groups of 64 slots
-that end inside a token, 4096 slots (from there the first rows are requested before the slots are counted) and 4096 tokens
-(from there the rows go past L2), slots beyond what a workgroup keeps for the row copy (the copy is
+that end inside a token, 4096 slots (from there the first rows are requested before the slots are counted), 15 tokens per CU
+(with more the rows go past L2; 3840 | 3841 on 256 CUs), slots beyond what a workgroup keeps for the row copy (the copy is
 then a launch of its own), rows that are no multiple of the copy's 8 KiB, expert ids out of range."""
 import numpy as np
 import pytest
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,E,k,d,xdt", [
     (1, 1, 1, 64, "bf16"), (255, 8, 2, 4160, "f32"), (256, 64, 8, 64, "bf16"), (257, 64, 7, 2112, "f32"),
-    (2500, 3, 3, 64, "f32"), (2047, 8, 2, 4160, "f32"), (2049, 8, 2, 4160, "f32"), (4099, 5, 1, 64, "bf16"), (4099, 8, 2, 4160, "f32"), (32768, 16, 8, 64, "bf16"), (33000, 16, 8, 64, "f32")])
+    (2500, 3, 3, 64, "f32"), (2047, 8, 2, 4160, "f32"), (2049, 8, 2, 4160, "f32"), (3840, 8, 2, 2112, "bf16"), (3841, 8, 2, 2112, "bf16"), (4099, 5, 1, 64, "bf16"), (4099, 8, 2, 4160, "f32"), (32768, 16, 8, 64, "bf16"), (33000, 16, 8, 64, "f32")])
 def test_permute_at_launch_edges(T, E, k, d, xdt):
     import paper_2402_07033_amd as moe
     rng = np.random.default_rng(T + E)
