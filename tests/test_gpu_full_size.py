@@ -170,8 +170,7 @@ def _tiles_beyond_first(counts, tile_rows):
 
 # The tile shapes that the 32-layer stack at 512 tokens and the sweeps between decode and
 # prefill run, at the Mixtral shape, with balanced routing so that (nearly) every expert has a
-# single token tile and the kernel streams the weights past L2 (its device-side rule: token
-# tiles beyond an expert's first are at most 15 % of all token tiles; 45 % with the 128-row tile).
+# single token tile, whose weights the kernel reads past L2.
 @pytest.mark.parametrize("T,tile_rows,tile_features", [(512, 192, 256), (256, 128, 512),
                                                        (384, 128, 512)])
 def test_grouped_small_tiles_full_size(moe, mixtral, T, tile_rows, tile_features):
@@ -184,7 +183,7 @@ def test_grouped_small_tiles_full_size(moe, mixtral, T, tile_rows, tile_features
     out = _layer_with_nan_canary(moe, mixtral["W"], to_dev(x), to_dev(logits), cfg.k)
     counts = to_host(out["counts"])
     tiles, beyond = _tiles_beyond_first(counts, tile_rows)
-    assert beyond * 100 <= 15 * tiles, "routing does not select the streamed-weight body"
+    assert beyond * 100 <= 15 * tiles, "routing does not give most experts a single tile"
     rows = _sample_rows(to_host(out["offsets"]), cfg.E)
     e_yg, counts, n_tok = _check_sampled(moe, mixtral, cfg, x, logits, out, rows)
     print(f"balanced T={T}: plan={pl} counts={counts.tolist()} sampled rows={len(rows)} "
@@ -193,8 +192,8 @@ def test_grouped_small_tiles_full_size(moe, mixtral, T, tile_rows, tile_features
 
 
 def test_grouped_small_tile_with_weights_through_l2_full_size(moe, mixtral):
-    """Same 192 x 256 tile with skewed routing: hot experts span several token tiles, so the
-    kernel's rule keeps the weights in L2 (the other copy of its loop)."""
+    """Same 192 x 256 tile with skewed routing: hot experts span several token tiles, whose weights
+    stay in L2 (other copies of the step loop, beside those of the single tiles)."""
     cfg = mi.MoEConfig("zipf_t512", 512, 4096, 14336, 8, 2, mi.BF16, mi.BF16, 1177, 1.2, 1002)
     x, logits, _ = mi.make_activations(cfg)
     pl = moe.moe_expert_ffn_plan(cfg.N, cfg.E, cfg.d, cfg.f)

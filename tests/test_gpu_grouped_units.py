@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import gg_schedule
 import moe_inputs as mi
 from gpu_util import max_rel, pack_layer, to_dev, to_host
 from oracle import moe_oracle as orc
@@ -82,45 +83,47 @@ def test_mid_path_shapes(d, f, counts):
 
 # Several rounds of whole tiles per workgroup, then pieces: the operand requests of a tile's last
 # steps are the next tile's, and the waits of its first steps count the stores of the tile before,
-# so neighbours of different numbers of units matter.  Per tile shape one set of counts for each
-# copy of the loop (weights streamed past L2, or kept in it).
+# so neighbours of different numbers of units matter.  The step loop exists per number of units and, for
+# tiles that are their expert's only one, with the weights past L2.
 ROUNDS = {
-    # name: rows per expert (repeated), repeats, tile rows, streamed, features of 2..3 rounds
-    "256 x 256, kept": ([641, 64, 257, 190, 1, 385, 256, 513], 1, 256, False, 10240),
-    "256 x 256, streamed": ([201, 190, 256, 130, 64, 255, 240, 232], 1, 256, True, 18432),
-    "192 x 256, kept": ([385, 193, 64, 128, 17, 130, 192, 65], 1, 192, False, 16384),
-    "192 x 256, streamed": ([200, 190, 128, 65, 17, 130, 192, 64], 1, 192, True, 16384),
-    "128 x 512, kept": ([384, 300, 0, 0, 0, 17, 0, 0], 4, 128, False, 11264),
-    "128 x 512, streamed": ([129, 128, 64, 17, 1, 65, 100, 90], 4, 128, True, 10240),
+    # name: rows per expert (repeated), repeats, tile rows, features of the long projection, its (rounds, cut, turned)
+    "256 x 256, several tiles": ([641, 64, 257, 190, 1, 385, 256, 513], 1, 256, 10240, (2, True, False)),
+    "256 x 256, one tile each": ([201, 190, 256, 130, 64, 255, 240, 232], 1, 256, 18432, (2, True, False)),
+    "256 x 256, turned": ([900, 100, 300, 257, 1, 700, 200, 513], 1, 256, 16384, (4, True, True)),
+    "256 x 256, turned, whole": ([900, 100, 300, 257, 1, 700, 200, 513], 1, 256, 18432, (4, False, True)),
+    "256 x 256, 8 rounds": ([900, 100, 300, 257, 1, 700, 200, 513], 1, 256, 31744, (8, True, True)),
+    "192 x 256, several tiles": ([385, 193, 64, 128, 17, 130, 192, 65], 1, 192, 12800, (2, True, False)),
+    "192 x 256, several tiles, whole": ([385, 193, 64, 128, 17, 130, 192, 65], 1, 192, 16384, (2, False, False)),
+    "192 x 256, nearly one tile each": ([200, 190, 128, 65, 17, 130, 192, 64], 1, 192, 16384, (2, True, False)),
+    "192 x 256, turned": ([385, 193, 64, 128, 17, 130, 192, 65], 1, 192, 24576, (4, True, True)),
+    "192 x 256, 8 rounds": ([385, 193, 64, 128, 17, 130, 192, 65], 2, 192, 24576, (8, True, True)),
+    "128 x 512, several tiles": ([384, 300, 0, 0, 0, 17, 0, 0], 4, 128, 11264, (2, True, False)),
+    "128 x 512, nearly one tile each": ([129, 128, 64, 17, 1, 65, 100, 90], 4, 128, 7680, (2, True, False)),
+    "128 x 512, nearly one tile each, whole": ([129, 128, 64, 17, 1, 65, 100, 90], 4, 128, 10240, (2, False, False)),
+    "128 x 512, turned": ([300, 0, 17, 129, 64, 1, 200, 30], 2, 128, 24576, (4, True, True)),
+    "128 x 512, 8 rounds": ([300, 0, 17, 129, 64, 1, 200, 30], 4, 128, 24576, (8, True, True)),
 }
 
 
-def _streams_weights(counts, tile_rows):
-    """The kernels' rule: token tiles beyond an expert's first, at most 45 % of all with the 128-row
-    tile, 15 % with the others."""
-    tiles = sum(-(-n // tile_rows) for n in counts)
-    beyond = tiles - sum(1 for n in counts if n > 0)
-    return beyond * 100 <= (45 if tile_rows == 128 else 15) * tiles
+def long_branch(name, up, cus=256):
+    counts, repeats, tile_rows, long, _ = ROUNDS[name]
+    return gg_schedule.branch(counts * repeats, tile_rows, 512 if tile_rows == 128 else 256, long, 64, up, cus)
 
 
 @pytest.mark.parametrize("long_side", ["f", "d"])  # many tiles in the first / second projection
 @pytest.mark.parametrize("name", list(ROUNDS))
 def test_rounds_of_whole_tiles_and_pieces(name, long_side):
     import paper_2402_07033_amd as moe
-    counts, repeats, tile_rows, streamed, long = ROUNDS[name]
+    counts, repeats, tile_rows, long, want = ROUNDS[name]
     counts = counts * repeats
     E, N = len(counts), sum(counts)
-    d, f = (2048, long // 2) if long_side == "f" else (long, 2048)   # 64 steps and more: pieces
+    d, f = (2048, long // 2) if long_side == "f" else (long, 2048)   # 64 steps in the long projection
     features = 512 if tile_rows == 128 else 256
     plan = moe.moe_expert_ffn_plan(N, E, d, f, path=moe.MOE_FFN_GROUPED)
     assert (plan["up_tile_rows"], plan["up_tile_features"]) == (tile_rows, features)
     assert (plan["down_tile_rows"], plan["down_tile_features"]) == (tile_rows, features)
-    assert _streams_weights(counts, tile_rows) == streamed
-    units = [-(-n // 64) for n in counts if n]
-    token_tiles = sum(-(-n // tile_rows) for n in counts)
-    workgroups = (torch.cuda.get_device_properties(0).multi_processor_count + 7) // 8 * 8
-    total = token_tiles * ((2 * f if long_side == "f" else d) // features)
-    assert total >= 2 * workgroups and total % workgroups != 0 and len(set(units)) > 2
+    b = long_branch(name, long_side == "f", torch.cuda.get_device_properties(0).multi_processor_count)
+    assert (b.rounds, b.cut, b.turned) == want and b.left > 0 and len(b.once | b.shared) > 1
 
     g = torch.Generator(device="cuda")
     g.manual_seed(4700 + N)
@@ -149,7 +152,7 @@ def test_rounds_of_whole_tiles_and_pieces(name, long_side):
         err = (buf[lo:hi].double() - ref).norm(dim=1) / ref.norm(dim=1)
         assert bool(torch.isfinite(err).all())
         worst = max(worst, float(err.max()))
-    print(f"{name}, long {long_side}: {total / workgroups:.2f} rounds, error {worst:.2e}")
+    print(f"{name}, long {long_side}: {b.rounds} rounds, {b.left} tiles left, error {worst:.2e}")
     # 2-norm of a row.  An h whose fp32 value (relative error about 2^-20: sums of 2048 and more
     # products) lies that close to a rounding boundary of bf16 rounds the other way and moves by 2^-7
     # of itself at most, about one in 2^11.  The largest h of a row of 2048 has about half of the row's

@@ -3,6 +3,7 @@
 import pytest
 
 import gg_schedule as gs
+from test_gpu_grouped_units import ROUNDS, long_branch
 
 
 @pytest.mark.parametrize("wgs", [32, 5])
@@ -51,3 +52,20 @@ def test_turned_rounds_need_tiles_of_either_kind(counts, KS, turned):
     assert got.rounds >= 4 and got.turned == turned
     # and never with fewer than four rounds
     assert not gs.branch(counts[:2], 256, 256, 8192, KS, True).turned
+
+
+@pytest.mark.parametrize("tile_rows", [256, 192, 128])
+@pytest.mark.parametrize("up", [True, False])
+def test_gpu_cases_reach_every_branch(up, tile_rows):
+    """The cases that the GPU runs in rounds, per tile shape and projection: every number of units with either
+    load policy, cut and whole left-over tiles, turned rounds, few and many rounds."""
+    cases = [long_branch(n, up) for n, c in ROUNDS.items() if c[2] == tile_rows]
+    for n, c in ROUNDS.items():
+        b = long_branch(n, up)
+        assert (b.rounds, b.cut, b.turned) == c[4], n
+    units = set(range(1, tile_rows // 64 + 1))
+    assert set().union(*(b.once for b in cases)) == units
+    # (dealt evenly, a tile of one unit among several is there in the two-unit tiles only)
+    assert set().union(*(b.shared for b in cases)) == units - ({1} if tile_rows > 128 else set())
+    assert {b.cut for b in cases} == {b.turned for b in cases} == {True, False}
+    assert min(b.rounds for b in cases) < 4 and max(b.rounds for b in cases) >= 8
