@@ -15,10 +15,10 @@
 //   down  : per (token tile of 256 rows, 256 output features): yg = h.w2, fp32
 //
 // GEMM kernel (one 256 x 256 x 32 step = 1024 matrix-core clocks per SIMD).  What bounds it: a step
-// takes about 0.75 us whatever its number of matrix instructions.  At 4096 tokens nearly all tiles
-// are full, the matrix cores are busy 69-70 % of the clocks, and the board's power holds these at
-// 1.6-1.9 GHz (an earlier loop on 32x32x16 was 1.23 times as fast on all-zero tokens); at 1531 tokens,
-// or with 16 experts, they are busy 52-57 %.  Below ~200 rows per expert the weight stream bounds it
+// takes about 0.7 us, hardly less with fewer matrix instructions.  At 4096 tokens nearly all tiles
+// are full, the matrix cores are busy 72-73 % of the clocks, and the board's power holds these at
+// 1.7-1.9 GHz (an earlier loop on 32x32x16 was 1.23 times as fast on all-zero tokens); at 1531 tokens,
+// or with 16 experts, they are busy 55-62 % at 2.0 GHz.  Below ~200 rows per expert the weight stream bounds it
 // (5.5-6.4 TB/s).
 //   * workgroup tile: up to 256 token rows x 16 weight fragment rows, 4 waves, one per
 //     SIMD; wave w owns fragment rows 4w..4w+3 for all token rows: 64 MFMA tiles = 256
@@ -42,7 +42,7 @@
 //   * the requests of a step are spread between the matrix instructions, one barrier per two
 //     steps publishes the next stages (the order of the ring: moe_gg_ring.h).  They are buffer loads:
 //     an address is a descriptor, the lane offset and one scalar, where 64-bit pointers per request
-//     filled the scalar registers (65..229 spills, 43..63 now); 55 other instructions stand beside the
+//     filled the scalar registers (65..229 spills, 45..64 now); 55 other instructions stand beside the
 //     64 matrix instructions of a full step, 61 with pointers, one between two of them where it can be.
 //   * the workgroup is persistent (one per CU) and the two load streams run across tile
 //     boundaries: while the last steps of a tile are multiplied, the first stages of the next
@@ -55,7 +55,7 @@
 //     order expert, group of at most 8 token tiles, feature tile, token tile: about 8 x 4
 //     tiles, which share 12 operand tiles in one L2.  Every XCD has its part of every round, so an
 //     expert's size does not unbalance them; where experts of one tile and larger ones are there, they walk
-//     the rounds from different starts (gg_turned).  One contiguous range of tiles per XCD, which hits L2
+//     the rounds from different starts (gg_turned in moe_gg_sched.h, with the rest of the schedule).  One contiguous range of tiles per XCD, which hits L2
 //     more often, was slower: 4096 tokens 2.308 -> 2.340 ms, 1531 tokens 1.045 -> 1.056.
 // Measured (kernel with whole 256-row tiles, one tile range per XCD, 64-bit pointers -> this): layer
 // of 4096 tokens, 8 experts, Zipf 2.46 -> 2.35 ms; 1531 tokens 1.19 -> 1.07; 4096 tokens, 16 experts
