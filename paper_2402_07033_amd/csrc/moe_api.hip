@@ -98,6 +98,20 @@ static int combine_args(const float* yg, const int32_t* inv_perm, const float* w
     return MOE_OK;
 }
 
+// Can moe_layer route and batch in one launch?  A few slots; and every workgroup then reads logits and x while others
+// write, so calls in which an output lies over one of them keep the two launches.
+static bool fused_front(const float* logits, int T, int EL, int E, int k, const void* x, size_t x_bytes, const int32_t* idx,
+                        const float* weights, const int32_t* counts, const int32_t* offsets, const int32_t* perm,
+                        const int32_t* inv_perm, const void* xg) {
+    if (T < 1 || !x || !moe_route_permute_rows_supported(T, k)) return false;
+    const size_t n = (size_t)T * k * 4, e = (size_t)E * 4;
+    const struct { const void* p; size_t bytes; } out[7] = {{idx, n}, {weights, n}, {counts, e}, {offsets, e + 4},
+                                                            {perm, n}, {inv_perm, n}, {xg, x_bytes * k}};
+    for (const auto& o : out)
+        if (ranges_overlap(logits, (size_t)T * EL * 4, o.p, o.bytes) || ranges_overlap(x, x_bytes, o.p, o.bytes)) return false;
+    return true;
+}
+
 // The launches of moe_expert_ffn and its variants, arguments checked, `path` as ffn_args left it.  With
 // `perm` the batched row i is read as xg[perm[i] / k] (xg is then the token array).
 static int ffn_launch(const moe_weights_t* W, const void* xg, moe_dtype_t act_dtype, const int32_t* perm, int k,
@@ -362,9 +376,15 @@ int moe_layer(const moe_weights_t* W, const void* x, moe_dtype_t x_dtype, int d,
 
     hipStream_t s = (hipStream_t)stream;
     *stage = 0;
-    if (T > 0 && (rc = moe_route_launch(logits, T, E, k, idx, weights, s)) != MOE_OK) return rc;
-    *stage = 1;
-    rc = moe_permute_launch(idx, T, W->E, k, T > 0 ? x : nullptr, d, x_dtype, counts, offsets, perm, inv_perm, xg, s);
+    if (fused_front(logits, T, E, W->E, k, x, (size_t)T * d * (x_dtype == MOE_BF16 ? 2 : 4), idx, weights, counts, offsets,
+                    perm, inv_perm, xg)) {
+        rc = moe_route_permute_rows_launch(logits, T, E, W->E, k, x, d, x_dtype, idx, weights, counts, offsets, perm,
+                                           inv_perm, xg, s);
+    } else {
+        if (T > 0 && (rc = moe_route_launch(logits, T, E, k, idx, weights, s)) != MOE_OK) return rc;
+        *stage = 1;
+        rc = moe_permute_launch(idx, T, W->E, k, T > 0 ? x : nullptr, d, x_dtype, counts, offsets, perm, inv_perm, xg, s);
+    }
     if (rc != MOE_OK) return rc;
     *stage = 2;
     if ((rc = ffn_launch(W, xg, x_dtype, nullptr, 1, offsets, T * k, workspace, yg, path, s)) != MOE_OK) return rc;

@@ -1,0 +1,69 @@
+"""moe_layer's routing and batching in one launch (up to 512 slots, a workgroup per token): the bits of the two
+calls at the edges of its groups of lanes and slots, on both sides of its limit, and with outputs over its inputs."""
+import ctypes as C
+
+import pytest
+import torch
+
+import moe_inputs as mi
+from gpu_util import pack_layer, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+# one lane per token .. 64; 64 slots and one more, groups that end inside a token, 512 slots and the first beyond (514, 520), as
+# many tokens as CUs and one more; rows of 256 B, and longer than one request of a wave (8 KiB)
+@pytest.mark.parametrize("T,E,EL,k,d,w,x", [
+    (1, 1, 1, 1, 64, mi.F32, mi.F32), (16, 8, 8, 2, 256, mi.F32, mi.F32), (64, 2, 2, 1, 64, mi.F32, mi.F32),
+    (65, 3, 3, 1, 64, mi.F32, mi.F32), (33, 64, 64, 8, 256, mi.BF16, mi.BF16), (64, 64, 33, 8, 256, mi.BF16, mi.F32),
+    (65, 64, 64, 8, 256, mi.BF16, mi.F32), (73, 16, 9, 7, 64, mi.F32, mi.F32), (256, 8, 8, 2, 64, mi.F32, mi.F32),
+    (257, 8, 8, 2, 64, mi.F32, mi.F32), (257, 4, 4, 1, 64, mi.F32, mi.F32), (5, 4, 3, 2, 2112, mi.F32, mi.F32)])
+def test_layer_front(T, E, EL, k, d, w, x):
+    import paper_2402_07033_amd as moe
+    cfg = mi.small_config("front", T, d, 128, E, k, 30 + T + E, w_dtype=w, x_dtype=x, zipf_s=1.2)
+    li = mi.make_layer(cfg, threads=4)
+    W, xd, lg = pack_layer(li), to_dev(li.x), to_dev(li.logits)[:, :EL].contiguous()
+    lg[0].fill_(0.5)  # ties go to the lower expert
+    if EL > 2:
+        lg[T // 2, 1] = float("-inf")
+    path = moe.MOE_FFN_AUTO if w == mi.F32 else moe.MOE_FFN_MID
+    out = moe.moe_layer(W, xd, lg, k, path=path)
+    idx, wt = moe.moe_route(lg, k)
+    counts, offsets, perm, inv_perm, xg = moe.moe_permute(idx, E, xd)
+    y = moe.moe_combine(moe.moe_expert_ffn(W, xg, offsets, path=path), inv_perm, wt)
+    want = dict(idx=idx, w=wt, counts=counts, offsets=offsets, perm=perm, inv_perm=inv_perm, xg=xg, y=y)
+    for n, v in want.items():
+        assert torch.equal(out[n], v), n
+    W.free()
+
+
+@pytest.mark.parametrize("over", ["xg", "perm"])
+def test_outputs_over_the_logits(over):
+    """The logits are dead once the tokens are routed: an output of the batching may lie over them."""
+    import paper_2402_07033_amd as moe
+    T, E, k, d = 16, 8, 2, 256
+    cfg = mi.small_config("front", T, d, 128, E, k, 77)
+    li = mi.make_layer(cfg, threads=4)
+    W, xd, lg = pack_layer(li), to_dev(li.x), to_dev(li.logits)
+    want = moe.moe_layer(W, xd, lg, k)
+    N = T * k
+    i32 = dict(dtype=torch.int32, device="cuda")
+    bufs = dict(idx=torch.empty(N, **i32), w=torch.empty(N, device="cuda"), counts=torch.empty(E, **i32),
+                offsets=torch.empty(E + 1, **i32), perm=torch.empty(T * E, **i32), inv_perm=torch.empty(N, **i32),
+                xg=torch.empty((N, d), device="cuda"), yg=torch.empty((N, d), device="cuda"),
+                y=torch.empty((T, d), device="cuda"))
+    ws = torch.empty(moe.moe_expert_ffn_workspace(N, E, d, 128, moe.MOE_F32), dtype=torch.uint8, device="cuda")
+    logits = bufs[over].reshape(-1).view(torch.float32)[:T * E]
+    logits.copy_(lg.reshape(-1))
+    p = {n: t.data_ptr() for n, t in bufs.items()}
+    stage = C.c_int(-1)
+    torch.cuda.synchronize()
+    rc = moe.lib().moe_layer(W.handle, xd.data_ptr(), moe.MOE_F32, d, logits.data_ptr(), T, E, k, moe.MOE_FFN_AUTO,
+                             p["idx"], p["w"], p["counts"], p["offsets"], p["perm"], p["inv_perm"], p["xg"],
+                             ws.data_ptr(), ws.numel(), p["yg"], p["y"], C.byref(stage), None)
+    torch.cuda.synchronize()
+    assert rc == 0
+    for n in ("idx", "w", "counts", "offsets", "inv_perm", "xg", "yg", "y"):
+        assert torch.equal(bufs[n].reshape(-1), want[n].reshape(-1)), n
+    assert torch.equal(bufs["perm"][:N], want["perm"])
+    W.free()
