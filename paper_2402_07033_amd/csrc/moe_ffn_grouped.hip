@@ -73,8 +73,22 @@
 //   256 x 16 (256 tokens x 256 features): the default;
 //   192 x 16 (192 tokens x 256 features): 97..176 and 233..256 rows;
 //   128 x 32 (128 tokens x 512 features): up to 96 rows -- twice the weight bytes per step,
-//           which is what bounds such experts.
+//           which is what bounds such experts;
+//   160 x 4..32 (up to 160 tokens x 64..512 features; "small experts"): in place of any of them where the offsets show
+//           that no expert has more than 160 rows, decided on the device (gg_flex in moe_gg_sched.h).  The weight stream
+//           bounds such launches.  A step moves a tile's weights W and its token rows t (mostly L2 hits) through one CU, and
+//           its time follows W + t / 2 (KiB: 16 + 8 for 128 rows of the 192 x 256 tile, 32 + 8 here), until HBM is full at
+//           6.5 TB/s; a round that is not full leaves bandwidth unused, so the tiles' width is cut to fill it.  First
+//           projection, 8 experts of f = 14336: 8 x 128 rows 361 -> 328 us (5.2 -> 5.7 TB/s; the fix-up of its pieces, 11 us,
+//           ends at once), 8 x 64 331 -> 311, 2 x 90 120 -> 97, 3 experts of 107 rows 168 -> 150; 16 of f = 6400: 16 x
+//           128 349 -> 326, 16 x 40 300 -> 285, 6 x 90 158 -> 124; 64 of f = 1408: 28 rows each 134 -> 128, 24 x 24 66 -> 57.
+//           Ten blocks of 16 rows are 80 accumulator tiles of a wave, 64 in accumulation registers and 16 in vector
+//           registers.
 #define GG_THREADS 256
+#define GG_SMALL_BLOCKS 10  // token blocks of the small experts' tile
+// The lambdas of the loop have to be inlined: as a call, with its captures in memory, the wave-uniform values
+// among them become per-lane values, and every buffer request a loop over the lanes.
+#define GG_INLINE __attribute__((always_inline))
 #ifndef GG_WIDE_MAX_ROWS
 #define GG_WIDE_MAX_ROWS 96  // mean rows per expert up to which the 128 x 512 tile is used
 #endif
@@ -90,7 +104,10 @@
 #define GG_R192_MIN_ROWS2 233
 #define GG_R192_MAX_ROWS2 256
 #define GG_GROUP 8         // token tiles that are neighbours of one weight tile, see the tile order
-#define GG_UNIT_BLOCKS 4   // 16-row token blocks per unit
+// 16-row token blocks per unit of a tile of NBW blocks: 4, or 2 where the tile is no multiple of 4
+constexpr int gg_unit_blocks(int NBW) { return NBW % 4 == 0 ? 4 : 2; }
+// Blocks of an LDS stage: each wave requests the same number.
+constexpr int gg_stage_blocks(int NBW) { return (NBW + 3) / 4 * 4; }
 
 // ------------------------------------------------------------------- GEMM ----
 struct GroupedArgs {
@@ -101,7 +118,6 @@ struct GroupedArgs {
     int E, N;
     int KS;      // reduction steps of 32
     int FR;      // weight fragment rows per expert (up: 2*f/16, down: d/16)
-    int MU;      // units of 64 token rows per tile, at most
     int FROWS;   // weight fragment rows per tile: 16 or 32
     int NT;      // workgroup tiles along the features = FR / FROWS
     int KS_out;  // up: f/32 (fragment columns of hp); down: unused
@@ -118,6 +134,8 @@ struct GroupedArgs {
 struct TileInfo {
     SegInfo si;
     int nt;     // feature tile
+    int frow;   // its first fragment row, of the expert's
+    int groups; // FLEX: groups of 4 fragment rows in it
     int blk0;   // first block of the tile inside the segment
     int nblk;   // blocks of the tile that exist
     int units;  // units of 4 blocks (the last one may hold fewer blocks)
@@ -138,17 +156,22 @@ struct TileInfo {
 #define GG_SEG_ROWS 1   // rows
 #define GG_SEG_NB 2     // 16-row blocks
 #define GG_SEG_TILES 3  // token tiles
-#define GG_SEG_BASE 4   // first logical tile index
+#define GG_SEG_BASE 4   // first token tile
 #define GG_SEG_BB 5     // first packed block
 #define GG_SEG_FIELDS 6
 
-// One wave fills the table (lane e: expert e); returns the number of logical tiles.
-__device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets, int E, int N,
-                                            int NT, int MU, int lane, int (*tab)[64], bool write) {
+// One wave fills the table (lane e: expert e), for tiles of NBW blocks; returns the number of token tiles.  SMALL:
+// small = feature tiles of an expert where tiles of GG_SMALL_BLOCKS and a width of their own are taken instead (0: they are not).
+template <int NBW, int FRW, bool SMALL>
+__device__ __forceinline__ int gg_seg_table(const GroupedArgs& a, int wgs, int lane, int (*tab)[64], bool write, int& small) {
     int lo, rows;
-    gg_segment_of_lane(offsets, E, N, lane, lo, rows);
+    gg_segment_of_lane(a.offsets, a.E, a.N, lane, lo, rows);
     const int nb = (rows + 15) / 16;
-    const int tiles = (nb + GG_UNIT_BLOCKS * MU - 1) / (GG_UNIT_BLOCKS * MU);
+    small = 0;
+    if (SMALL && __ballot(nb > GG_SMALL_BLOCKS) == 0ull)
+        small = __builtin_amdgcn_readfirstlane(gg_flex(__popcll(__ballot(nb > 0)), a.FR / 4, wgs, a.KS, a.split, FRW == 4));
+    const int tile_blocks = small ? GG_SMALL_BLOCKS : NBW;
+    const int tiles = (nb + tile_blocks - 1) / tile_blocks;
     int inc_t = tiles, inc_b = nb;
 #pragma unroll
     for (int dlt = 1; dlt < 64; dlt <<= 1) {
@@ -163,10 +186,10 @@ __device__ __forceinline__ int gg_seg_table(const int32_t* __restrict__ offsets,
         tab[GG_SEG_ROWS][lane] = rows;
         tab[GG_SEG_NB][lane] = nb;
         tab[GG_SEG_TILES][lane] = tiles;
-        tab[GG_SEG_BASE][lane] = (inc_t - tiles) * NT;
+        tab[GG_SEG_BASE][lane] = inc_t - tiles;
         tab[GG_SEG_BB][lane] = inc_b - nb;
     }
-    return __builtin_amdgcn_readlane(inc_t, 63) * NT;
+    return __builtin_amdgcn_readlane(inc_t, 63);
 }
 
 // The schedule's turn, decided by one wave from the table (moe_gg_sched.h).
@@ -174,16 +197,17 @@ __device__ __forceinline__ bool gg_turned(const int (*tab)[64], int lane, int to
     return gg_turned(__popcll(__ballot(tab[GG_SEG_TILES][lane] == 1)), total, NT, KS);
 }
 
-// Logical tile index -> tile, from the table.
+// Logical tile index -> tile, from the table.  UB: blocks of a unit.
+template <int UB>
 __device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lane, int NT,
                                                    int L, TileInfo& ti) {
-    const int my_tiles = tab[GG_SEG_TILES][lane], my_base = tab[GG_SEG_BASE][lane];
+    const int my_tiles = tab[GG_SEG_TILES][lane], my_base = tab[GG_SEG_BASE][lane] * NT;
     const unsigned long long m = __ballot(my_tiles > 0 && L >= my_base && L < my_base + my_tiles * NT);
     if (m == 0ull) return false;
     const int e = __builtin_amdgcn_readfirstlane((int)__builtin_ctzll(m));
     const int tiles = __builtin_amdgcn_readfirstlane(tab[GG_SEG_TILES][e]);
     const int nb = __builtin_amdgcn_readfirstlane(tab[GG_SEG_NB][e]);
-    const int r = L - __builtin_amdgcn_readfirstlane(tab[GG_SEG_BASE][e]);
+    const int r = L - __builtin_amdgcn_readfirstlane(tab[GG_SEG_BASE][e]) * NT;
     // token tiles in groups of at most GG_GROUP, the feature tile next, the token tile fastest
     const int ng = (tiles + GG_GROUP - 1) / GG_GROUP;
     const int gq = tiles / ng, gmore = tiles % ng;  // the first gmore groups hold one tile more
@@ -200,16 +224,35 @@ __device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lan
     ti.si.bbase = __builtin_amdgcn_readfirstlane(tab[GG_SEG_BB][e]);
     ti.once = tiles == 1;
     // the expert's units, dealt evenly to its tiles
-    const int nu = (nb + GG_UNIT_BLOCKS - 1) / GG_UNIT_BLOCKS;
+    const int nu = (nb + UB - 1) / UB;
     const int per = nu / tiles, more = nu % tiles;  // the first `more` tiles take one more
     ti.units = per + (tis < more ? 1 : 0);
-    ti.blk0 = GG_UNIT_BLOCKS * (tis * per + (tis < more ? tis : more));
-    ti.nblk = (nb - ti.blk0) < GG_UNIT_BLOCKS * ti.units ? (nb - ti.blk0) : GG_UNIT_BLOCKS * ti.units;
+    ti.blk0 = UB * (tis * per + (tis < more ? tis : more));
+    ti.nblk = (nb - ti.blk0) < UB * ti.units ? (nb - ti.blk0) : UB * ti.units;
     ti.k_lo = 0;
     ti.klen = 0;  // filled in by the caller
     ti.partial = false;
     ti.piece = 0;
     return true;
+}
+
+// The tile's fragment rows.  FLEX: the expert's groups of 4 rows dealt evenly to its NT tiles, 1..8 for each; wave w
+// holds groups w and w + 4.
+template <int FRW, bool FLEX>
+__device__ __forceinline__ void gg_feature_rows(int FR, int NT, TileInfo& ti) {
+    if (FLEX) {
+        const int groups = FR / 4, lo = ti.nt * groups / NT, hi = (ti.nt + 1) * groups / NT;
+        ti.frow = lo * 4;
+        ti.groups = hi - lo;
+    } else {
+        ti.frow = ti.nt * (4 * FRW);
+        ti.groups = FRW;
+    }
+}
+// Fragment row j of a wave inside the tile.
+template <int FRW, bool FLEX>
+__device__ __forceinline__ constexpr int gg_wave_row(int wave, int j) {
+    return FLEX ? (j / 4) * 16 + 4 * wave + j % 4 : FRW * wave + j;
 }
 
 // Weight fragment load.  ANT: non-temporal, for a tile whose expert has no other token tile: its
@@ -244,6 +287,13 @@ __device__ __forceinline__ void gg_mfma(f32x4_t& c, const u32x4_t& a, const u32x
 // ... with a zero accumulator going in (the first step of a tile)
 __device__ __forceinline__ void gg_mfma_first(f32x4_t& c, const u32x4_t& a, const u32x4_t& b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+}
+// ... in vector registers: the tiles beyond the 64th of a wave
+__device__ __forceinline__ void gg_mfma_v(f32x4_t& c, const u32x4_t& a, const u32x4_t& b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void gg_mfma_first_v(f32x4_t& c, const u32x4_t& a, const u32x4_t& b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
 }
 
 // Buffer descriptor over the 2 GiB of addresses from p on (p is wave-uniform, which the compiler does not
@@ -346,16 +396,20 @@ __device__ __forceinline__ unsigned gg_h_off(int lane) {
 // MODE: which units of work this copy of the loop covers: 0 = whole tiles and pieces, 1 = whole tiles
 // only, 2 = pieces only.
 // NBW x FRW: token blocks of the tile, at most, x fragment rows of a wave.
-template <bool UP, int NBW, int FRW, int MODE, int U, int LA, int NS>
-__device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bool turned, const int (*s_seg)[64]) {
-    static_assert(NBW * FRW <= 64 && NBW % 4 == 0 && FRW % 4 == 0, "at most 64 MFMA tiles (256 accumulators) per wave");
+// FLEX: feature tiles of 1..8 groups of rows (gg_feature_rows); of a group that is not there a wave requests and
+// stores nothing.
+template <bool UP, int NBW, int FRW, bool FLEX, int MODE, int U, int LA, int NS>
+__device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int NT, int total, int split_limit, bool turned,
+                                             const int (*s_seg)[64]) {
+    static_assert(NBW * FRW <= 80 && NBW % 2 == 0 && FRW % 4 == 0, "at most 256 + 64 accumulators per wave");
     static_assert(LA < U && U % GG_BARRIER_STEPS == 0, "register ring; a tile starts at a barrier step");
     static_assert(gg_refill_ordered(NS, GG_AHEAD) && gg_arrival_ordered(GG_AHEAD, LA), "stage ring, see moe_gg_ring.h");
-    constexpr int FROWS = 4 * FRW;     // fragment rows of the workgroup tile
-    constexpr int NBQ = NBW / 4;       // token blocks each wave requests into LDS per step (= units)
+    constexpr int UB = gg_unit_blocks(NBW);
+    constexpr int NSB = gg_stage_blocks(NBW);
+    constexpr int NBQ = NSB / 4;       // token blocks each wave requests into LDS per step
     constexpr int TG = (GG_AHEAD + U - 1) / U;  // groups at the end of a tile that look into the next
     extern __shared__ __align__(16) unsigned char smem[];
-    u32x4_t* lds = (u32x4_t*)smem;  // [NS stages][NBW fragments][64 lanes]
+    u32x4_t* lds = (u32x4_t*)smem;  // [NS stages][NSB fragments][64 lanes]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // fragment rows [FRW*wave, +FRW)
@@ -369,7 +423,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
     const int xcd = blockIdx.x & 7;
     const int wgs = gridDim.x >> 3;
     const int me = blockIdx.x >> 3;
-    const GgSched sc = gg_sched(total, wgs, xcd, a.KS, a.split);
+    const GgSched sc = gg_sched(total, wgs, xcd, a.KS, split_limit);
     const bool split = sc.split;
     const int last = (int)((unsigned)(me + sc.n_full) % (unsigned)wgs);  // left-over tile, if it stays whole
     const int n_full = sc.n_full + (!split && last < sc.R ? 1 : 0);
@@ -401,7 +455,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
     pc_len1 = __builtin_amdgcn_readfirstlane(pc_len1);
     n_pieces = __builtin_amdgcn_readfirstlane(n_pieces);
     const int n_units = (MODE == 1) ? n_full : n_full + n_pieces;
-    auto unit_at = [&](int n, TileInfo& ti) -> bool {
+    auto unit_at = [&](int n, TileInfo& ti) GG_INLINE -> bool {
         if (n >= n_units) return false;
         int L, lo = 0, len = a.KS;
         if (n < n_full) {
@@ -418,7 +472,8 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
         // (the lane number is recomputed here, opaquely, so that no address derived from it
         // has to stay in a register through the main loop; see the epilogue)
         const int lane_d = gg_lane_opaque();
-        if (!gg_decode_tile_tab(s_seg, lane_d, a.NT, L, ti)) return false;
+        if (!gg_decode_tile_tab<UB>(s_seg, lane_d, NT, L, ti)) return false;
+        gg_feature_rows<FRW, FLEX>(a.FR, NT, ti);
         ti.k_lo = lo;
         ti.klen = len;
         ti.partial = (n >= n_full);  // pieces always go through scratch and the fix-up
@@ -432,14 +487,19 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
     // inside a tile: at most 32 rows of f/32 <= 32768 fragments, 1 GiB.)
     const unsigned row_bytes = (unsigned)a.KS * 1024u;  // one fragment row / token block
     const unsigned voff = (unsigned)lane * 16u;
-    auto a_base = [&](const TileInfo& ti) -> const char* {
+    // the lane's offset of a weight request: behind the descriptor, which returns zeros without a memory access,
+    // for a group of rows that the tile does not have
+    auto has = [&](const TileInfo& ti, int j) GG_INLINE -> bool { return !FLEX || wave + (j / 4) * 4 < ti.groups; };
+    auto a_voff = [&](const TileInfo& ti, int j) GG_INLINE -> unsigned { return has(ti, j) ? voff : GG_RSRC_BYTES; };
+    auto a_row = [&](int j) GG_INLINE -> unsigned { return (unsigned)gg_wave_row<FRW, FLEX>(0, j) * row_bytes; };
+    auto a_base = [&](const TileInfo& ti) GG_INLINE -> const char* {
         return (const char*)a.wfrag +
-               (((size_t)ti.si.e * a.FR + (size_t)ti.nt * FROWS + FRW * wave) * a.KS + ti.k_lo) * 1024;
+               (((size_t)ti.si.e * a.FR + (size_t)ti.frow + gg_wave_row<FRW, FLEX>(wave, 0)) * a.KS + ti.k_lo) * 1024;
     };
-    auto b_base = [&](const TileInfo& ti) -> const char* {
+    auto b_base = [&](const TileInfo& ti) GG_INLINE -> const char* {
         return (const char*)a.bfrag + ((size_t)(ti.si.bbase + ti.blk0) * a.KS + ti.k_lo) * 1024;
     };
-    auto b_off = [&](const TileInfo& ti, unsigned (&vo)[NBQ]) {
+    auto b_off = [&](const TileInfo& ti, unsigned (&vo)[NBQ]) GG_INLINE {
 #pragma unroll
         for (int v = 0; v < NBQ; v++) {
             const int blk = 4 * v + wave;
@@ -447,8 +507,8 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
         }
     };
     // request v of this wave for stage number `gstage`, `soff` bytes along the reduction
-    auto issue_b = [&](__amdgpu_buffer_rsrc_t r, unsigned soff, unsigned gstage, int v) {
-        unsigned char* dst = smem + ((gstage % NS) * (NBW * 1024) + wave * 1024);
+    auto issue_b = [&](__amdgpu_buffer_rsrc_t r, unsigned soff, unsigned gstage, int v) GG_INLINE {
+        unsigned char* dst = smem + ((gstage % NS) * (NSB * 1024) + wave * 1024);
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             r, (__attribute__((address_space(3))) void*)(dst + v * 4096), 16, voff, soff, 0, 0);
     };
@@ -464,6 +524,13 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
     unsigned vo_b[NBQ], vo_bn[NBQ];
     b_off(cur, vo_b);
     b_off(nxt, vo_bn);
+    constexpr int GR = FLEX ? FRW / 4 : 1;
+    unsigned va[GR], va_n[GR];
+#pragma unroll
+    for (int q = 0; q < GR; q++) {
+        va[q] = a_voff(cur, 4 * q);
+        va_n[q] = a_voff(nxt, 4 * q);
+    }
 
     u32x4_t areg[U][FRW];  // [ring slot][fragment row]
 
@@ -476,7 +543,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
 #pragma unroll
         for (int s = 0; s < LA; s++)
 #pragma unroll
-            for (int j = 0; j < FRW; j++) areg[s][j] = gg_ld_a<false>(ra, voff, s * 1024 + j * row_bytes);
+            for (int j = 0; j < FRW; j++) areg[s][j] = gg_ld_a<false>(ra, va[j / 4 % GR], s * 1024 + a_row(j));
     }
     GG_WAIT_VMCNT(0);
     __builtin_amdgcn_s_barrier();
@@ -487,30 +554,34 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
 
     // one tile of B token blocks (B = 4 * units)
     // (its last groups request the next tile's first weights, with this tile's policy)
-    auto tile = [&](auto blocks, auto once) {
+    auto tile = [&](auto blocks, auto once) GG_INLINE {
         constexpr int B = decltype(blocks)::value;
         constexpr bool ANT = decltype(once)::value != 0;
-        constexpr int VMIN = FRW + B / 4;  // requests of a step, at least
+        constexpr int NBB = (B + 3) / 4;
+        constexpr int VMIN = FRW + NBB;  // requests of a step, at least
+        // token fragments in registers: a whole step's, or a ring of half as many where the accumulators
+        // need the registers
+        constexpr int RB = B * FRW > 64 ? B / 2 : B;
         f32x4_t acc[B][FRW];
-        u32x4_t breg[B];
+        u32x4_t breg[RB];
         g = __builtin_amdgcn_readfirstlane(g);
         const __amdgpu_buffer_rsrc_t ra = gg_rsrc(pa), rb = gg_rsrc(pb), ra_n = gg_rsrc(pa_n), rb_n = gg_rsrc(pb_n);
         unsigned kb = 0;  // bytes along the reduction: 1024 * step of the group's first step
         const int klen = __builtin_amdgcn_readfirstlane(cur.klen);
         {
-            const u32x4_t* pl = lds + (g % NS) * NBW * 64 + lane;
+            const u32x4_t* pl = lds + (g % NS) * NSB * 64 + lane;
 #pragma unroll
-            for (int i = 0; i < B; i++) breg[i] = pl[i * 64];
+            for (int i = 0; i < RB; i++) breg[i] = pl[i * 64];
         }
         GG_WAIT_LGKM(0);
 
         // U steps.  Q: how many groups are left in the tile, this one included, or 0: more than
         // TG.  A request for step u + look-ahead of the group lies in the next tile when that is
         // beyond the Q groups.  FIRST: the tile's first group.
-        auto group = [&](auto left, auto first) {
+        auto group = [&](auto left, auto first) GG_INLINE {
             constexpr int Q = decltype(left)::value;
             constexpr bool FIRST = decltype(first)::value != 0;
-            constexpr int NB = Q ? NBQ : B / 4;  // token requests per step (the next tile may need all)
+            constexpr int NB = Q ? NBQ : NBB;  // token requests per step (the next tile may need all)
             constexpr int VREQ = FRW + NB;
 #pragma unroll
             for (int u = 0; u < U; u++) {
@@ -542,8 +613,12 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
                 // slots refilled during steps k and k+1 held stages k-2 and k-1, whose reads
                 // every wave has waited for in its steps k-2 and k-1.
                 if (u % GG_BARRIER_STEPS == 0) __builtin_amdgcn_s_barrier();
-                const u32x4_t* pl = lds + ((g + u + 1) % NS) * NBW * 64 + lane;
-                auto issue = [&](const int v) {
+                const u32x4_t* pc = lds + ((g + u) % NS) * NSB * 64 + lane;
+                const u32x4_t* pl = lds + ((g + u + 1) % NS) * NSB * 64 + lane;
+                auto refill = [&](const int i) GG_INLINE {  // the fragment RB blocks behind block i
+                    breg[i % RB] = i + RB < B ? pc[(i + RB) * 64] : pl[(i + RB - B) * 64];
+                };
+                auto issue = [&](const int v) GG_INLINE {
                     if (v < NB) {
                         const int jb = u + GG_AHEAD;  // step of the group
                         if (Q == 0 || jb < Q * U)
@@ -553,9 +628,9 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
                     } else {
                         const int ja = u + LA, j = v - NB;
                         if (Q == 0 || ja < Q * U)
-                            areg[ja % U][j] = gg_ld_a<ANT>(ra, voff, kb + ja * 1024 + j * row_bytes);
+                            areg[ja % U][j] = gg_ld_a<ANT>(ra, va[j / 4 % GR], kb + ja * 1024 + a_row(j));
                         else
-                            areg[ja % U][j] = gg_ld_a<ANT>(ra_n, voff, (ja - Q * U) * 1024 + j * row_bytes);
+                            areg[ja % U][j] = gg_ld_a<ANT>(ra_n, va_n[j / 4 % GR], (ja - Q * U) * 1024 + a_row(j));
                     }
                 };
                 // One other instruction at most between two matrix instructions where it can be: a
@@ -569,17 +644,22 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
 #pragma unroll
                 for (int i = 0; i < B; i++) {
                     // LDS reads return in order: with at most that many younger ones in flight,
-                    // breg[i] and breg[i+1] (refilled one step ago) have arrived
-                    if (i == 0) GG_WAIT_LGKM(B - 2);
-                    else if ((i & 1) == 0) GG_WAIT_LGKM(B - 3);
+                    // the fragments of blocks i and i + 1 have arrived
+                    if (i == 0) GG_WAIT_LGKM(RB - 2);
+                    else if ((i & 1) == 0) GG_WAIT_LGKM(RB - 3);
 #pragma unroll
                     for (int jj = 0; jj < FRW; jj++) {
                         const int j = (i & 1) ? FRW - 1 - jj : jj;
                         __builtin_amdgcn_sched_barrier(4);
-                        if (FIRST && u == 0) gg_mfma_first(acc[i][j], areg[u][j], breg[i]);
-                        else gg_mfma(acc[i][j], areg[u][j], breg[i]);
+                        if (i * FRW < 64) {
+                            if (FIRST && u == 0) gg_mfma_first(acc[i][j], areg[u][j], breg[i % RB]);
+                            else gg_mfma(acc[i][j], areg[u][j], breg[i % RB]);
+                        } else {
+                            if (FIRST && u == 0) gg_mfma_first_v(acc[i][j], areg[u][j], breg[i % RB]);
+                            else gg_mfma_v(acc[i][j], areg[u][j], breg[i % RB]);
+                        }
                         __builtin_amdgcn_sched_barrier(4);
-                        if (jj == 0 && i > 0) breg[i - 1] = pl[(i - 1) * 64];
+                        if (jj == 0 && i > 0) refill(i - 1);
                         // the vector-memory requests are spread evenly over the blocks, so that the
                         // requests of the four waves never queue up in front of the matrix
                         // instructions
@@ -589,7 +669,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                breg[B - 1] = pl[(B - 1) * 64];
+                refill(B - 1);
             }
             g += U;
             kb += U * 1024;
@@ -614,7 +694,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
         const int lane_e = gg_lane_opaque();
         const int t = lane_e & 15;  // token in block
         // Every store is issued, so that their number is known (see the waits above): those of
-        // rows or blocks that do not exist lie beyond the descriptor and are dropped.
+        // rows, blocks or features that do not exist lie beyond the descriptor and are dropped.
         if (MODE == 2 || (MODE == 0 && cur.partial)) {
             // piece of a tile: raw partial sums to this workgroup's slot, in the order of the
             // accumulators (whole lines); the fix-up kernel adds the pieces
@@ -631,7 +711,7 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
             stores = B * FRW;
         } else if (UP) {
             // fragment rows 4jj..4jj+3 of this wave: w1, w3 of an even and of the next column block
-            const int ks_o = cur.nt * (FROWS / 4) + (FRW / 4) * wave;  // h fragment column of jj = 0
+            const int ks_o = (cur.frow + gg_wave_row<FRW, FLEX>(wave, 0)) / 4;  // h fragment column of jj = 0
             const __amdgpu_buffer_rsrc_t rs = gg_rsrc(
                 (const char*)a.out + ((size_t)(cur.si.bbase + cur.blk0) * a.KS_out + ks_o) * 1024);
             const unsigned vo = gg_h_off(lane_e);
@@ -641,37 +721,46 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
                 for (int jj = 0; jj < FRW / 4; jj++) {
                     const u32x4_t hv = gg_make_h(acc[i][4 * jj], acc[i][4 * jj + 1], acc[i][4 * jj + 2],
                                                  acc[i][4 * jj + 3]);
-                    const unsigned o = vo + (unsigned)i * (unsigned)a.KS_out * 1024u + jj * 1024u;
-                    __builtin_amdgcn_raw_buffer_store_b128(hv, rs, i < cur.nblk ? o : GG_RSRC_BYTES, 0, 0);
+                    const unsigned o = vo + (unsigned)i * (unsigned)a.KS_out * 1024u + gg_wave_row<FRW, FLEX>(0, 4 * jj) * 256u;
+                    __builtin_amdgcn_raw_buffer_store_b128(hv, rs, i < cur.nblk && has(cur, 4 * jj) ? o : GG_RSRC_BYTES, 0, 0);
                 }
             stores = B * (FRW / 4);
         } else {
             const int r0 = cur.blk0 * 16;  // first row of the tile inside the segment
             const __amdgpu_buffer_rsrc_t rs = gg_rsrc(
-                (const char*)((float*)a.out + (size_t)(cur.si.row0 + r0) * a.C + (cur.nt * FROWS + FRW * wave) * 16));
+                (const char*)((float*)a.out + (size_t)(cur.si.row0 + r0) * a.C + (cur.frow + gg_wave_row<FRW, FLEX>(wave, 0)) * 16));
             const int rows = cur.si.rows - r0;
             const unsigned vo = (unsigned)t * (unsigned)a.C * 4u + (unsigned)(lane_e >> 4) * 16u;
 #pragma unroll
-            for (int i = 0; i < B; i++) {
-                const unsigned o = i * 16 + t < rows ? vo + (unsigned)(i * 16) * (unsigned)a.C * 4u : GG_RSRC_BYTES;
+            for (int i = 0; i < B; i++)
 #pragma unroll
-                for (int j = 0; j < FRW; j++)
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs, o + j * 64, 0, 0);
-            }
+                for (int j = 0; j < FRW; j++) {
+                    const unsigned o = i * 16 + t < rows && has(cur, j) ? vo + (unsigned)(i * 16) * (unsigned)a.C * 4u
+                                                                        : GG_RSRC_BYTES;
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, acc[i][j]), rs,
+                                                           o + gg_wave_row<FRW, FLEX>(0, j) * 64, 0, 0);
+                }
             stores = B * FRW;
         }
     };
 
     for (;;) {
         // by the number of units of the tile, 1 .. NBW / 4
-        auto units = [&](auto once) {
-            if (cur.units == 1) tile(GgInt<4>{}, once);
+        auto units = [&](auto once) GG_INLINE {
+            if (NBW == 10) {
+                if (cur.units <= 2) tile(GgInt<4>{}, once);
+                else if (cur.units == 3) tile(GgInt<6>{}, once);
+                else if (cur.units == 4) tile(GgInt<8>{}, once);
+                else tile(GgInt<NBW == 10 ? 10 : 8>{}, once);
+            } else if (cur.units == 1) tile(GgInt<4>{}, once);
             else if (NBW == 8 || cur.units == 2) tile(GgInt<8>{}, once);
             else if constexpr (NBW >= 12) {
                 if (NBW == 12 || cur.units == 3) tile(GgInt<12>{}, once);
                 else if constexpr (NBW >= 16) tile(GgInt<16>{}, once);
             }
         };
+        // (FLEX: no expert has a second token tile, but with one copy of the loop the compiler spills at every tile:
+        // 8 x 128 rows, first projection 325 -> 333 us)
         if (cur.once) units(GgInt<1>{});
         else units(GgInt<0>{});
         if (!has_next) {
@@ -692,23 +781,33 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int total, bo
         pa_n = a_base(nxt);
         pb_n = b_base(nxt);
         b_off(nxt, vo_bn);
+#pragma unroll
+        for (int q = 0; q < GR; q++) {
+            va[q] = va_n[q];
+            va_n[q] = a_voff(nxt, 4 * q);
+        }
         GG_WAIT_LGKM(0);  // the decode's reads must not sit in the LDS read counter
     }
 }
 
 // The first projection's whole tiles and pieces are two copies of the loop, one after the other: an
 // epilogue with both the SiLU body and the raw store spills 153-289 registers in the 8 x 8 and 16 x 4 tiles.
-template <bool UP, int NBW, int FRW, int U, int LA, int NS>
+template <bool UP, int NBW, int FRW, bool SMALL, int U, int LA, int NS>
 __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
     __shared__ int s_seg[GG_SEG_FIELDS][64];
-    const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, threadIdx.x & 63, s_seg,
-                                   threadIdx.x < 64);
+    int small;
+    const int n_tok = gg_seg_table<NBW, FRW, SMALL>(a, (int)(gridDim.x >> 3), threadIdx.x & 63, s_seg, threadIdx.x < 64, small);
     __syncthreads();
-    const bool turned = gg_turned(s_seg, threadIdx.x & 63, total, a.NT, a.KS);
-    gg_gemm_body<UP, NBW, FRW, UP ? 1 : 0, U, LA, NS>(a, total, turned, s_seg);
+    const int NT = SMALL && small ? small : a.NT, total = n_tok * NT;
+    const bool turned = gg_turned(s_seg, threadIdx.x & 63, total, NT, a.KS);
+    if (SMALL && small) {  // whole tiles only
+        gg_gemm_body<UP, GG_SMALL_BLOCKS, 8, true, 1, GG_U, GG_WIDE_LA, GG_NS>(a, NT, total, 0, turned, s_seg);
+        return;
+    }
+    gg_gemm_body<UP, NBW, FRW, false, UP ? 1 : 0, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
     if (UP) {
         __syncthreads();  // no wave fills the LDS ring anew while another still reads it
-        gg_gemm_body<UP, NBW, FRW, 2, U, LA, NS>(a, total, turned, s_seg);
+        gg_gemm_body<UP, NBW, FRW, false, 2, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
     }
 }
 
@@ -720,7 +819,7 @@ __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
 // together: one piece at a time, with a workgroup per item of the largest possible number of
 // tiles, took 40 us instead of 17 for the second projection at 8192 rows.
 #define GG_FIX_GRID 1024
-template <bool UP, int NBW, int FRW>
+template <bool UP, int NBW, int FRW, bool SMALL>
 __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, int unit, int ns) {
     constexpr int FROWS = 4 * FRW;
     // the segment table as in the GEMM: one parallel read of the offsets and two wave scans
@@ -728,9 +827,10 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
     __shared__ int s_seg[GG_SEG_FIELDS][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int total = gg_seg_table(a.offsets, a.E, a.N, a.NT, NBW / 4, lane, s_seg, threadIdx.x < 64);
+    int small;
+    const int total = gg_seg_table<NBW, FRW, SMALL>(a, wgs, lane, s_seg, threadIdx.x < 64, small) * a.NT;
     const int left = total % (wgs * 8);
-    if (left == 0 || !gg_sched(total, wgs, 0, a.KS, a.split).split) return;
+    if (small || left == 0 || !gg_sched(total, wgs, 0, a.KS, a.split).split) return;
     __syncthreads();
     for (int item = blockIdx.x; item < left * NBW; item += gridDim.x) {
         // (tile fastest: neighbouring workgroups, and not the same ones again, take blocks that exist)
@@ -742,7 +842,7 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
         const GgSched sc = gg_sched(total, wgs, xcd, a.KS, a.split);
         const int r = sc.n_full * wgs * 8 + lt - sc.left_lo;  // tile number among the XCD's
         TileInfo ti;
-        if (!gg_decode_tile_tab(s_seg, lane, a.NT, sc.left_lo + r, ti)) return;
+        if (!gg_decode_tile_tab<gg_unit_blocks(NBW)>(s_seg, lane, a.NT, sc.left_lo + r, ti)) return;
         if (i >= ti.nblk) continue;
         // lane w looks at workgroup w's cut: it holds at most one piece of this tile; a ballot
         // keeps the pieces in workgroup order (wgs <= 64)
@@ -836,8 +936,12 @@ size_t moe_ffn_grouped_workspace(int N, int E, int d, int f) {
 
 // Kernel variants by rows per expert (see the tile shapes at the top of the file): token
 // blocks and fragment rows of the tile, unroll / weight look-ahead / LDS stages of the loop.
-enum GgVariant { GG_STD = 0, GG_WIDE = 1, GG_R192 = 2, GG_NVARIANTS = 3 };
+enum GgVariant { GG_STD = 0, GG_WIDE = 1, GG_R192 = 2, GG_STD_S = 3, GG_NVARIANTS = 4 };
 struct GgShape { int tb, frows, u, la, ns; };
+static size_t gg_lds_bytes(const GgShape& sh) {
+    const int nb = gg_stage_blocks(sh.tb), small = gg_stage_blocks(GG_SMALL_BLOCKS);
+    return (size_t)sh.ns * (nb > small ? nb : small) * MOE_FRAG_BYTES;
+}
 static GgShape gg_shape(GgVariant v) {
     switch (v) {
         case GG_WIDE: return {8, 32, GG_U, GG_WIDE_LA, GG_NS};
@@ -849,9 +953,10 @@ static GgShape gg_shape(GgVariant v) {
 template <bool UP>
 static const void* gg_kernel_ptr(GgVariant v) {
     switch (v) {
-        case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, GG_U, GG_WIDE_LA, GG_NS>;
-        case GG_R192: return (const void*)gg_gemm_kernel<UP, 12, 4, GG_U, GG_LA, GG_NS>;
-        default: return (const void*)gg_gemm_kernel<UP, 16, 4, GG_U, GG_LA, GG_NS>;
+        case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, true, GG_U, GG_WIDE_LA, GG_NS>;
+        case GG_R192: return (const void*)gg_gemm_kernel<UP, 12, 4, true, GG_U, GG_LA, GG_NS>;
+        case GG_STD_S: return (const void*)gg_gemm_kernel<UP, 16, 4, true, GG_U, GG_LA, GG_NS>;
+        default: return (const void*)gg_gemm_kernel<UP, 16, 4, false, GG_U, GG_LA, GG_NS>;
     }
 }
 
@@ -859,23 +964,23 @@ static const void* gg_kernel_ptr(GgVariant v) {
 template <bool UP>
 static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hipStream_t s) {
     const GgShape sh = gg_shape(v);
-    a.MU = sh.tb / GG_UNIT_BLOCKS;
     a.FROWS = sh.frows;
     if (a.FR % a.FROWS != 0) return MOE_ERR_UNSUPPORTED;
     a.NT = a.FR / a.FROWS;
     a.split = gg_split_limit(UP, a.KS, (int)(pgrid / 8));
     void* params[1] = {(void*)&a};
-    const size_t lds_bytes = (size_t)sh.ns * sh.tb * MOE_FRAG_BYTES;
+    const size_t lds_bytes = gg_lds_bytes(sh);
     MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<UP>(v), dim3(pgrid), dim3(GG_THREADS), params, lds_bytes, s));
     if (a.split) {
         const dim3 fgrid(GG_FIX_GRID);
         const int wgs = (int)(pgrid / 8);
-        if (v == GG_WIDE)
-            hipLaunchKernelGGL((gg_fixup_kernel<UP, 8, 8>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns);
-        else if (v == GG_R192)
-            hipLaunchKernelGGL((gg_fixup_kernel<UP, 12, 4>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns);
-        else
-            hipLaunchKernelGGL((gg_fixup_kernel<UP, 16, 4>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns);
+#define GG_FIXUP(NBW, FRW, SMALL) \
+    hipLaunchKernelGGL((gg_fixup_kernel<UP, NBW, FRW, SMALL>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns)
+        if (v == GG_WIDE) GG_FIXUP(8, 8, true);
+        else if (v == GG_R192) GG_FIXUP(12, 4, true);
+        else if (v == GG_STD_S) GG_FIXUP(16, 4, true);
+        else GG_FIXUP(16, 4, false);
+#undef GG_FIXUP
     }
     return MOE_OK;
 }
@@ -904,6 +1009,10 @@ static bool gg_choose(int N, int E, int d, int f, GgVariant& vu, GgVariant& vd, 
     } else if (mean_rows <= GG_R192_MAX_ROWS ||
                (mean_rows >= GG_R192_MIN_ROWS2 && mean_rows <= GG_R192_MAX_ROWS2)) {
         vu = vd = GG_R192;
+    }
+    if (mean_rows <= 16 * GG_SMALL_BLOCKS) {  // (above it, some expert has more)
+        if (vu == GG_STD) vu = GG_STD_S;
+        if (vd == GG_STD) vd = GG_STD_S;
     }
     // a variant whose loop does not fit a reduction gives way to the standard one
     if (!gg_fits(vu, d / 32)) vu = GG_STD;
@@ -950,7 +1059,7 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
             const void* all[2] = {gg_kernel_ptr<true>((GgVariant)v), gg_kernel_ptr<false>((GgVariant)v)};
             for (int i = 0; i < 2; i++)
                 MOE_HIP_TRY(hipFuncSetAttribute(all[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                (int)((size_t)sh.ns * sh.tb * MOE_FRAG_BYTES)));
+                                                (int)gg_lds_bytes(sh)));
         }
         attr_set[dev].store(1, std::memory_order_release);
     }

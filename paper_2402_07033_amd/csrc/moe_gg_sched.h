@@ -6,6 +6,9 @@
 // workgroups, wgs for each XCD.
 #pragma once
 
+// (inlined always: what a called function returns is no wave-uniform value)
+#define GG_FN constexpr __attribute__((always_inline)) inline
+
 // Whole tiles go out in n_full rounds of one tile per workgroup.  The tiles of the last, incomplete
 // round are dealt to the XCDs evenly, and cut there along the reduction so that all workgroups
 // take part -- or left whole, one for each of the first workgroups: pieces store and
@@ -27,7 +30,7 @@
 // Left-over tiles are cut if they are at most this many 32nds of a round (0: never).  Pieces of >= 32 steps
 // go to scratch and a fix-up kernel adds them; it lists the pieces of a tile with one wave, hence at
 // most 64 workgroups per XCD.
-constexpr int gg_split_limit(bool up, int KS, int wgs) {
+GG_FN int gg_split_limit(bool up, int KS, int wgs) {
     return KS >= 64 && wgs <= 64 ? (up ? GG_SPLIT_UP : GG_SPLIT_DOWN) : 0;
 }
 struct GgSched {
@@ -36,7 +39,7 @@ struct GgSched {
     int R;
     bool split;   // are they cut in pieces
 };
-constexpr GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
+GG_FN GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
     GgSched sc{};
     const int W = wgs * 8;
     sc.n_full = total / W;
@@ -47,9 +50,35 @@ constexpr GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
     sc.split = left * 32 <= W * split && (W - left) * KS >= W * GG_SPLIT_MIN_STEPS;
     return sc;
 }
+// Feature tiles per expert where each of n_tok experts has one tile of up to 160 rows and 1 .. 8 groups of 4 fragment
+// rows, all left whole: the fewest where they fill their rounds, else as many as the rounds hold, which are narrower, of 3
+// groups and more.  0: the launch's own tiles, where cutting those of the last round is better (split: gg_split_limit).  Pieces of 160
+// x 512 themselves cost more to add up: second projection of 8 x 128 rows 176 + 17 us, 180 + 12 with pieces of 192 x 256; of
+// 8 x 150 198 + 20, 193 + 13.  only_wide: 0 for 4 groups as well, as the launch's own tiles have: these keep more requests
+// in flight (16 x 128 rows 169 -> 159).
+// Narrowed -> cut, GEMM and fix-up: one round, 0.44 of it filled by the fewest tiles, 128 steps 87 -> 101 us, 97 -> 125
+// (24, 90 rows per expert); 0.59 111 -> 134, 124 -> 160; 0.5, 200 steps 142 -> 155; 0.41 129 -> 138, 140 -> 164; 0.34 123 ->
+// 120, 141 -> 146.  Two rounds, 128 steps: 1.09 of them filled 194 -> 200, 229 -> 208; 1.27 236 -> 233, 265 -> 252; 1.31 234 ->
+// 231, 265 -> 256; 1.37 264 -> 256; 1.46 250 -> 260, 283 -> 295; 1.53 269 -> 272, 299 -> 301; 1.56 285 -> 300, 326 -> 349;
+// 64 steps, 1.17 108 -> 115, 124 -> 130.  Narrowed -> whole and not full: 1.75 298 -> 304, 311 -> 331; 0.88 143 -> 139
+// (HBM is full either way), 147 -> 151.
+#define GG_FLEX_CUT_STEPS1 120  // steps that the idle part of the round is worth, one round
+#define GG_FLEX_CUT_STEPS 75    // ... several
+GG_FN int gg_flex(int n_tok, int groups, int wgs, int KS, int split, bool only_wide) {
+    const int least = (groups + 7) / 8, W = wgs * 8, total = n_tok * least;
+    const int slots = (total + W - 1) / W * W;
+    if (n_tok == 0) return 0;
+    const int fill = slots / n_tok, most = fill < groups / 3 ? fill : groups / 3;
+    if (total < slots && gg_sched(total, wgs, 0, KS, split).split &&
+        ((slots - total) * KS >= W * (slots == W ? GG_FLEX_CUT_STEPS1 : GG_FLEX_CUT_STEPS) ||
+         most * n_tok * 4 < slots * 3 || most <= least))
+        return 0;
+    const int NT = most > least ? most : least;
+    return only_wide && groups <= 4 * NT ? 0 : NT;
+}
 // Workgroup me of an XCD takes a different one of the round's 32 neighbours every round: the
 // token tiles of an expert differ in length, and their period must not pick workgroups.
-constexpr int gg_round_slot(int n, int wgs, int xcd, int me) {
+GG_FN int gg_round_slot(int n, int wgs, int xcd, int me) {
     return n * wgs * 8 + xcd * wgs + (int)((unsigned)(me + n) % (unsigned)wgs);
 }
 
@@ -57,7 +86,7 @@ constexpr int gg_round_slot(int n, int wgs, int xcd, int me) {
 // workgroups of one XCD: workgroup j covers [cut(j), cut(j+1)).  Pieces are multiples of
 // `unit` steps (KS is one too) and no piece is shorter than the smallest multiple of `unit`
 // that covers the `ns` LDS stages of the kernel's pipeline.
-constexpr int gg_piece_cut(int j, int S, int KS, int wgs, int unit, int ns) {
+GG_FN int gg_piece_cut(int j, int S, int KS, int wgs, int unit, int ns) {
     const int minp = (ns + unit - 1) / unit * unit;
     int per = ((S + wgs - 1) / wgs + unit - 1) / unit * unit;
     per = per < 32 ? 32 : per;
@@ -82,10 +111,10 @@ constexpr int gg_piece_cut(int j, int S, int KS, int wgs, int unit, int ns) {
 #define GG_TURN_ROUNDS 4
 #define GG_TURN_SHORT 64  // steps of the reduction
 // ones: experts of one token tile, each NT of the total tiles.
-constexpr bool gg_turned(int ones, int total, int NT, int KS) {
+GG_FN bool gg_turned(int ones, int total, int NT, int KS) {
     return ones * 8 * NT >= total && (KS <= GG_TURN_SHORT || (total - ones * NT) * 4 >= total);
 }
 // The XCD's first round.
-constexpr int gg_first_round(bool turned, int n_full, int xcd) {
+GG_FN int gg_first_round(bool turned, int n_full, int xcd) {
     return turned && n_full >= GG_TURN_ROUNDS ? n_full * xcd / 8 : 0;
 }

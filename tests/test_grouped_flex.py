@@ -1,0 +1,76 @@
+"""Feature tiles of the grouped GEMM where no expert has more than 160 rows (gg_flex in csrc/moe_gg_sched.h),
+replayed on the CPU with the kernel's own functions."""
+import ctypes as C
+import os
+import subprocess
+import tempfile
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = r"""
+#include "moe_gg_ring.h"
+#include "moe_gg_sched.h"
+extern "C" {
+int limit(int up, int KS, int wgs) { return gg_split_limit(up != 0, KS, wgs); }
+int flex(int n_tok, int groups, int wgs, int KS, int split, int only_wide) {
+    return gg_flex(n_tok, groups, wgs, KS, split, only_wide != 0);
+}
+int is_cut(int total, int wgs, int KS, int split) { return gg_sched(total, wgs, 0, KS, split).split; }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def L():
+    with tempfile.TemporaryDirectory() as d:
+        with open(os.path.join(d, "s.cpp"), "w") as fh:
+            fh.write(SRC)
+        so = os.path.join(d, "s.so")
+        subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I",
+                        os.path.join(ROOT, "paper_2402_07033_amd", "csrc"), "-o", so, os.path.join(d, "s.cpp")],
+                       check=True)
+        yield C.CDLL(so)
+
+
+def feature_tiles(L, n_tok, groups, wgs, KS, up, only_wide):
+    return L.flex(n_tok, groups, wgs, KS, L.limit(int(up), KS, wgs), int(only_wide))
+
+
+# groups of 4 fragment rows per expert: 448 / 64 (d 4096, f 14336), 200, 44 / 32 (d 2048, f 1408), 8, 4
+@pytest.mark.parametrize("groups", [448, 200, 64, 44, 32, 8, 4])
+@pytest.mark.parametrize("KS", [8, 44, 64, 128, 200, 448])
+@pytest.mark.parametrize("wgs", [32, 5])
+def test_tiles_hold_every_group_once(L, groups, KS, wgs):
+    W = 8 * wgs
+    for n_tok in list(range(0, 17)) + [31, 58, 63, 64]:
+        for up in (0, 1):
+            least = -(-groups // 8)
+            total, rounds = n_tok * least, -(-(n_tok * least) // W)
+            for only_wide in (False, True):
+                NT = feature_tiles(L, n_tok, groups, wgs, KS, up, only_wide)
+                if NT == 0:  # the launch's own tiles: nothing to do, cut, or as wide
+                    assert n_tok == 0 or only_wide or L.is_cut(total, wgs, KS, L.limit(up, KS, wgs))
+                    continue
+                assert least <= NT <= groups
+                edges = [nt * groups // NT for nt in range(NT + 1)]
+                widths = [b - a for a, b in zip(edges, edges[1:])]
+                assert sum(widths) == groups and min(widths) >= 1 and max(widths) <= 8
+                assert n_tok * NT <= rounds * W  # narrower tiles, no more rounds
+                assert not only_wide or groups > 4 * NT
+                if NT > least:
+                    assert groups >= 3 * NT
+
+
+@pytest.mark.parametrize("n_tok,groups,KS,up,only_wide,want", [
+    # 8 experts, d 4096, f 14336: 448 tiles of 8 groups are 1.75 rounds, 512 of 7 are two; the second
+    # projection's 64 are better cut
+    (8, 448, 128, 1, False, 64), (8, 448, 128, 1, True, 64), (8, 64, 448, 0, False, 0), (8, 64, 448, 0, True, 0),
+    # 16 experts, f 6400: 1.56 rounds -> two; half a round of 8 groups -> one of 4, which the 256-feature tiles are
+    (16, 200, 128, 1, False, 32), (16, 64, 200, 0, False, 16), (16, 64, 200, 0, True, 0),
+    # 64 experts, f 1408: 1.5 rounds of 6 tiles -> two of 8; a full round
+    (64, 44, 64, 1, True, 8), (64, 32, 44, 0, False, 4),
+    # a tenth of a second round is cut; one expert cannot fill a round with tiles of 3 groups
+    (5, 448, 128, 1, False, 0), (1, 448, 128, 1, False, 0), (0, 448, 128, 1, False, 0)])
+def test_rule(L, n_tok, groups, KS, up, only_wide, want):
+    assert feature_tiles(L, n_tok, groups, 32, KS, up, only_wide) == want
