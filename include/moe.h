@@ -176,8 +176,9 @@ size_t moe_expert_ffn_noalloc_max_bytes(void);
  *            unsummed (1 unless STREAM)
  *   up_* / down_*  GROUPED, MID: token rows x output features of the workgroup tile of the
  *            first / second projection (0 otherwise).  The first projection's features
- *            count w1 and w3 columns together.  Where the offsets show that no expert has more
- *            than 160 rows, the kernel may take tiles of 160 rows x 64..512 features instead.
+ *            count w1 and w3 columns together.  Up to 96 rows per expert on average, and above
+ *            where the offsets show that no expert has more than 160 rows, the kernel may take
+ *            tiles of 160 rows x 64..512 features instead.
  * Returns MOE_ERR_UNSUPPORTED if a forced family cannot run the shape.
  */
 typedef struct {

@@ -75,13 +75,16 @@
 //   128 x 32 (128 tokens x 512 features): up to 96 rows -- twice the weight bytes per step,
 //           which is what bounds such experts;
 //   160 x 4..32 (up to 160 tokens x 64..512 features; "small experts"): in place of any of them where the offsets show
-//           that no expert has more than 160 rows, decided on the device (gg_flex in moe_gg_sched.h).  The weight stream
+//           that no expert has more than 160 rows, and in place of the 128 x 512 one wherever it fills the rounds better,
+//           decided on the device (gg_flex in moe_gg_sched.h).  The weight stream
 //           bounds such launches.  A step moves a tile's weights W and its token rows t (mostly L2 hits) through one CU, and
 //           its time follows W + t / 2 (KiB: 16 + 8 for 128 rows of the 192 x 256 tile, 32 + 8 here), until HBM is full at
 //           6.5 TB/s; a round that is not full leaves bandwidth unused, so the tiles' width is cut to fill it.  First
 //           projection, 8 experts of f = 14336: 8 x 128 rows 361 -> 328 us (5.2 -> 5.7 TB/s; the fix-up of its pieces, 11 us,
 //           ends at once), 8 x 64 331 -> 311, 2 x 90 120 -> 97, 3 experts of 107 rows 168 -> 150; 16 of f = 6400: 16 x
 //           128 349 -> 326, 16 x 40 300 -> 285, 6 x 90 158 -> 124; 64 of f = 1408: 28 rows each 134 -> 128, 24 x 24 66 -> 57.
+//           With larger experts among them it is ahead up to 96 rows on average (gg_kernel_variant); above, from 1 % ahead to 9
+//           % behind (16 experts, 1100 tokens, Zipf 1.2 613 -> 631; second projections 179 -> 190, 199 -> 215), and not taken.
 //           Ten blocks of 16 rows are 80 accumulator tiles of a wave, 64 in accumulation registers and 16 in vector
 //           registers.
 #define GG_THREADS 256
@@ -168,8 +171,13 @@ __device__ __forceinline__ int gg_seg_table(const GroupedArgs& a, int wgs, int l
     gg_segment_of_lane(a.offsets, a.E, a.N, lane, lo, rows);
     const int nb = (rows + 15) / 16;
     small = 0;
-    if (SMALL && __ballot(nb > GG_SMALL_BLOCKS) == 0ull)
-        small = __builtin_amdgcn_readfirstlane(gg_flex(__popcll(__ballot(nb > 0)), a.FR / 4, wgs, a.KS, a.split, FRW == 4));
+    if (SMALL && (FRW == 8 || __ballot(nb > GG_SMALL_BLOCKS) == 0ull)) {
+        int t = (nb + GG_SMALL_BLOCKS - 1) / GG_SMALL_BLOCKS;
+#pragma unroll
+        for (int dlt = 1; dlt < 64; dlt <<= 1) t += __shfl_xor(t, dlt, 64);
+        small = __builtin_amdgcn_readfirstlane(NBW == GG_SMALL_BLOCKS ? gg_flex_fill(t, a.FR / 4, wgs)
+                                                                      : gg_flex(a.N, t, a.FR / 4, wgs, a.KS, a.split, FRW == 4));
+    }
     const int tile_blocks = small ? GG_SMALL_BLOCKS : NBW;
     const int tiles = (nb + tile_blocks - 1) / tile_blocks;
     int inc_t = tiles, inc_b = nb;
@@ -759,8 +767,6 @@ __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int NT, int t
                 else if constexpr (NBW >= 16) tile(GgInt<16>{}, once);
             }
         };
-        // (FLEX: no expert has a second token tile, but with one copy of the loop the compiler spills at every tile:
-        // 8 x 128 rows, first projection 325 -> 333 us)
         if (cur.once) units(GgInt<1>{});
         else units(GgInt<0>{});
         if (!has_next) {
@@ -800,14 +806,16 @@ __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
     __syncthreads();
     const int NT = SMALL && small ? small : a.NT, total = n_tok * NT;
     const bool turned = gg_turned(s_seg, threadIdx.x & 63, total, NT, a.KS);
-    if (SMALL && small) {  // whole tiles only
+    if (SMALL && (NBW == GG_SMALL_BLOCKS || small)) {  // whole tiles only
         gg_gemm_body<UP, GG_SMALL_BLOCKS, 8, true, 1, GG_U, GG_WIDE_LA, GG_NS>(a, NT, total, 0, turned, s_seg);
         return;
     }
-    gg_gemm_body<UP, NBW, FRW, false, UP ? 1 : 0, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
-    if (UP) {
-        __syncthreads();  // no wave fills the LDS ring anew while another still reads it
-        gg_gemm_body<UP, NBW, FRW, false, 2, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
+    if constexpr (NBW != GG_SMALL_BLOCKS) {
+        gg_gemm_body<UP, NBW, FRW, false, UP ? 1 : 0, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
+        if (UP) {
+            __syncthreads();  // no wave fills the LDS ring anew while another still reads it
+            gg_gemm_body<UP, NBW, FRW, false, 2, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
+        }
     }
 }
 
@@ -936,7 +944,9 @@ size_t moe_ffn_grouped_workspace(int N, int E, int d, int f) {
 
 // Kernel variants by rows per expert (see the tile shapes at the top of the file): token
 // blocks and fragment rows of the tile, unroll / weight look-ahead / LDS stages of the loop.
-enum GgVariant { GG_STD = 0, GG_WIDE = 1, GG_R192 = 2, GG_STD_S = 3, GG_NVARIANTS = 4 };
+// (_S: kernels that hold the small experts' tile as well, of the second projection and, R192, of both.  SLIM: that tile
+// alone, first projection.)
+enum GgVariant { GG_STD = 0, GG_WIDE = 1, GG_R192 = 2, GG_STD_S = 3, GG_WIDE_S = 4, GG_R192_S = 5, GG_SLIM = 6, GG_NVARIANTS = 7 };
 struct GgShape { int tb, frows, u, la, ns; };
 static size_t gg_lds_bytes(const GgShape& sh) {
     const int nb = gg_stage_blocks(sh.tb), small = gg_stage_blocks(GG_SMALL_BLOCKS);
@@ -944,19 +954,29 @@ static size_t gg_lds_bytes(const GgShape& sh) {
 }
 static GgShape gg_shape(GgVariant v) {
     switch (v) {
-        case GG_WIDE: return {8, 32, GG_U, GG_WIDE_LA, GG_NS};
-        case GG_R192: return {12, 16, GG_U, GG_LA, GG_NS};
+        case GG_SLIM: return {GG_SMALL_BLOCKS, 4, GG_U, GG_WIDE_LA, GG_NS};
+        case GG_WIDE:
+        case GG_WIDE_S: return {8, 32, GG_U, GG_WIDE_LA, GG_NS};
+        case GG_R192:
+        case GG_R192_S: return {12, 16, GG_U, GG_LA, GG_NS};
         default: return {16, 16, GG_U, GG_LA, GG_NS};
     }
 }
 
 template <bool UP>
 static const void* gg_kernel_ptr(GgVariant v) {
+    if constexpr (UP) {
+        if (v == GG_SLIM) return (const void*)gg_gemm_kernel<UP, GG_SMALL_BLOCKS, 8, true, GG_U, GG_WIDE_LA, GG_NS>;
+    } else {
+        if (v == GG_WIDE_S) return (const void*)gg_gemm_kernel<UP, 8, 8, true, GG_U, GG_WIDE_LA, GG_NS>;
+        if (v == GG_STD_S) return (const void*)gg_gemm_kernel<UP, 16, 4, true, GG_U, GG_LA, GG_NS>;
+    }
     switch (v) {
-        case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, true, GG_U, GG_WIDE_LA, GG_NS>;
-        case GG_R192: return (const void*)gg_gemm_kernel<UP, 12, 4, true, GG_U, GG_LA, GG_NS>;
-        case GG_STD_S: return (const void*)gg_gemm_kernel<UP, 16, 4, true, GG_U, GG_LA, GG_NS>;
-        default: return (const void*)gg_gemm_kernel<UP, 16, 4, false, GG_U, GG_LA, GG_NS>;
+        case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, false, GG_U, GG_WIDE_LA, GG_NS>;
+        case GG_R192: return (const void*)gg_gemm_kernel<UP, 12, 4, false, GG_U, GG_LA, GG_NS>;
+        case GG_R192_S: return (const void*)gg_gemm_kernel<UP, 12, 4, true, GG_U, GG_LA, GG_NS>;
+        case GG_STD: return (const void*)gg_gemm_kernel<UP, 16, 4, false, GG_U, GG_LA, GG_NS>;
+        default: return nullptr;
     }
 }
 
@@ -967,7 +987,7 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
     a.FROWS = sh.frows;
     if (a.FR % a.FROWS != 0) return MOE_ERR_UNSUPPORTED;
     a.NT = a.FR / a.FROWS;
-    a.split = gg_split_limit(UP, a.KS, (int)(pgrid / 8));
+    a.split = v == GG_SLIM ? 0 : gg_split_limit(UP, a.KS, (int)(pgrid / 8));
     void* params[1] = {(void*)&a};
     const size_t lds_bytes = gg_lds_bytes(sh);
     MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<UP>(v), dim3(pgrid), dim3(GG_THREADS), params, lds_bytes, s));
@@ -976,10 +996,14 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
         const int wgs = (int)(pgrid / 8);
 #define GG_FIXUP(NBW, FRW, SMALL) \
     hipLaunchKernelGGL((gg_fixup_kernel<UP, NBW, FRW, SMALL>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns)
-        if (v == GG_WIDE) GG_FIXUP(8, 8, true);
-        else if (v == GG_R192) GG_FIXUP(12, 4, true);
-        else if (v == GG_STD_S) GG_FIXUP(16, 4, true);
-        else GG_FIXUP(16, 4, false);
+        switch (v) {
+            case GG_WIDE: GG_FIXUP(8, 8, false); break;
+            case GG_WIDE_S: GG_FIXUP(8, 8, true); break;
+            case GG_R192: GG_FIXUP(12, 4, false); break;
+            case GG_R192_S: GG_FIXUP(12, 4, true); break;
+            case GG_STD_S: GG_FIXUP(16, 4, true); break;
+            default: GG_FIXUP(16, 4, false);
+        }
 #undef GG_FIXUP
     }
     return MOE_OK;
@@ -989,6 +1013,28 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
 static bool gg_fits(GgVariant v, int ks) {
     const GgShape sh = gg_shape(v);
     return ks % sh.u == 0 && ks >= sh.ns;
+}
+
+// Up to 96 rows per expert the first projection has the small experts' tile whatever the rows: its rounds are filled by the
+// tiles' width, so nothing is cut and no fix-up is launched (4.6 us where there is nothing to add).  Not where, with all experts in
+// use, cutting is better (5 experts x 90 rows 365 us, 375 without pieces); reductions of more than 128 steps are worth it anyway.
+// Both projections, start -> this: 8 experts, 330 tokens, Zipf 0.6 622 -> 599 us, 220 tokens 526 -> 506; 16 experts, 500 tokens 538 -> 474,
+// Zipf 1.2 554 -> 502, 300 tokens 486 -> 441; 64 experts, 400 tokens, Zipf 1.2 226 -> 201, 200 tokens 167 -> 168; 77 tokens 463 ->
+// 459 and 488 -> 475 on two cards; with fewer experts in use than there are, 3 of 8 x 40 rows 244 -> 209, 6 of 8 x 90 436 -> 431, 5 of
+// 8 x 90 365 -> 375.
+#define GG_SLIM_MAX_STEPS 128
+// The kernel that a projection of variant v is run with: the one with the small experts' tile, too, if that is to
+// be expected (all experts in use); the other's tiles end without spills (77 tokens, second projection 151 us, 153 with the
+// other body beside it).
+static GgVariant gg_kernel_variant(GgVariant v, bool up, int N, int E, int KS, int FR) {
+    const int wgs = (moe_num_cus() + 7) / 8, split = gg_split_limit(up, KS, wgs), most = 16 * GG_SMALL_BLOCKS;
+    if (N > most * E) return v;
+    if (up && N <= GG_WIDE_MAX_ROWS * E)
+        return KS <= GG_SLIM_MAX_STEPS && gg_flex((GG_FLEX_FEW_ROWS + 1) * E, E, FR / 4, wgs, KS, split, false) ? GG_SLIM : v;
+    for (int n = E; n <= E + (v == GG_WIDE ? N / most : 0); n++)  // token tiles
+        if (gg_flex(N, n, FR / 4, wgs, KS, split, v != GG_WIDE))
+            return v == GG_WIDE ? GG_WIDE_S : v == GG_R192 ? GG_R192_S : up ? v : GG_STD_S;
+    return v;
 }
 
 // Variant of each projection by the mean number of rows per expert (the host never sees the
@@ -1009,10 +1055,6 @@ static bool gg_choose(int N, int E, int d, int f, GgVariant& vu, GgVariant& vd, 
     } else if (mean_rows <= GG_R192_MAX_ROWS ||
                (mean_rows >= GG_R192_MIN_ROWS2 && mean_rows <= GG_R192_MAX_ROWS2)) {
         vu = vd = GG_R192;
-    }
-    if (mean_rows <= 16 * GG_SMALL_BLOCKS) {  // (above it, some expert has more)
-        if (vu == GG_STD) vu = GG_STD_S;
-        if (vd == GG_STD) vd = GG_STD_S;
     }
     // a variant whose loop does not fit a reduction gives way to the standard one
     if (!gg_fits(vu, d / 32)) vu = GG_STD;
@@ -1058,7 +1100,7 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
             const GgShape sh = gg_shape((GgVariant)v);
             const void* all[2] = {gg_kernel_ptr<true>((GgVariant)v), gg_kernel_ptr<false>((GgVariant)v)};
             for (int i = 0; i < 2; i++)
-                MOE_HIP_TRY(hipFuncSetAttribute(all[i], hipFuncAttributeMaxDynamicSharedMemorySize,
+                if (all[i]) MOE_HIP_TRY(hipFuncSetAttribute(all[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                                                 (int)gg_lds_bytes(sh)));
         }
         attr_set[dev].store(1, std::memory_order_release);
@@ -1074,6 +1116,9 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
     // scratch of the pieces of left-over tiles, behind the two fragment buffers
     float* part = (float*)((unsigned char*)ws + gg_align256(nb * 16 * d * 2) +
                            gg_align256(nb * 16 * f * 2));
+
+    vu = gg_kernel_variant(vu, true, N, E, d / 32, f / 8);
+    if (!short_down) vd = gg_kernel_variant(vd, false, N, E, f / 32, d / 16);
 
     GroupedArgs up;
     up.wfrag = (const u32x4_t*)W->w13;

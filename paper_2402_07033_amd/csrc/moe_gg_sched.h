@@ -50,30 +50,39 @@ GG_FN GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
     sc.split = left * 32 <= W * split && (W - left) * KS >= W * GG_SPLIT_MIN_STEPS;
     return sc;
 }
-// Feature tiles per expert where each of n_tok experts has one tile of up to 160 rows and 1 .. 8 groups of 4 fragment
+// Feature tiles per expert for n_tok token tiles of up to 160 rows (N rows in all) and 1 .. 8 groups of 4 fragment
 // rows, all left whole: the fewest where they fill their rounds, else as many as the rounds hold, which are narrower, of 3
 // groups and more.  0: the launch's own tiles, where cutting those of the last round is better (split: gg_split_limit).  Pieces of 160
 // x 512 themselves cost more to add up: second projection of 8 x 128 rows 176 + 17 us, 180 + 12 with pieces of 192 x 256; of
 // 8 x 150 198 + 20, 193 + 13.  only_wide: 0 for 4 groups as well, as the launch's own tiles have: these keep more requests
-// in flight (16 x 128 rows 169 -> 159).
+// in flight (16 x 128 rows 169 -> 159).  Otherwise these have 512 features, too, and with few rows nearly full rounds of them fill
+// HBM as they are: 77 tokens 460 -> 462 narrowed, 4 x 24 rows 140 -> 143 (0.88 of a round), 64 experts of f = 1408, second projection
+// 55 -> 55 (0.78), 62 -> 64 (0.9), 58 -> 63 (0.73); 8 x 64 331 -> 311, 4 x 90 151 -> 147.  gg_flex_fill: without these
+// questions.
 // Narrowed -> cut, GEMM and fix-up: one round, 0.44 of it filled by the fewest tiles, 128 steps 87 -> 101 us, 97 -> 125
 // (24, 90 rows per expert); 0.59 111 -> 134, 124 -> 160; 0.5, 200 steps 142 -> 155; 0.41 129 -> 138, 140 -> 164; 0.34 123 ->
 // 120, 141 -> 146.  Two rounds, 128 steps: 1.09 of them filled 194 -> 200, 229 -> 208; 1.27 236 -> 233, 265 -> 252; 1.31 234 ->
 // 231, 265 -> 256; 1.37 264 -> 256; 1.46 250 -> 260, 283 -> 295; 1.53 269 -> 272, 299 -> 301; 1.56 285 -> 300, 326 -> 349;
 // 64 steps, 1.17 108 -> 115, 124 -> 130.  Narrowed -> whole and not full: 1.75 298 -> 304, 311 -> 331; 0.88 143 -> 139
 // (HBM is full either way), 147 -> 151.
+#define GG_FLEX_FEW_ROWS 32
 #define GG_FLEX_CUT_STEPS1 120  // steps that the idle part of the round is worth, one round
 #define GG_FLEX_CUT_STEPS 75    // ... several
-GG_FN int gg_flex(int n_tok, int groups, int wgs, int KS, int split, bool only_wide) {
+GG_FN int gg_flex_fill(int n_tok, int groups, int wgs) {
+    const int least = (groups + 7) / 8, W = wgs * 8, total = n_tok * least;
+    if (n_tok == 0) return least;
+    const int fill = (total + W - 1) / W * W / n_tok, most = fill < groups / 3 ? fill : groups / 3;
+    return most > least ? most : least;
+}
+GG_FN int gg_flex(int N, int n_tok, int groups, int wgs, int KS, int split, bool only_wide) {
     const int least = (groups + 7) / 8, W = wgs * 8, total = n_tok * least;
     const int slots = (total + W - 1) / W * W;
-    if (n_tok == 0) return 0;
-    const int fill = slots / n_tok, most = fill < groups / 3 ? fill : groups / 3;
+    if (n_tok == 0 || (!only_wide && N <= GG_FLEX_FEW_ROWS * n_tok && (slots - total) * 10 <= 3 * W)) return 0;
+    const int NT = gg_flex_fill(n_tok, groups, wgs);
     if (total < slots && gg_sched(total, wgs, 0, KS, split).split &&
-        ((slots - total) * KS >= W * (slots == W ? GG_FLEX_CUT_STEPS1 : GG_FLEX_CUT_STEPS) ||
-         most * n_tok * 4 < slots * 3 || most <= least))
+        ((slots - total) * KS >= W * (slots == W ? GG_FLEX_CUT_STEPS1 : GG_FLEX_CUT_STEPS) || NT * n_tok * 4 < slots * 3 ||
+         NT == least))
         return 0;
-    const int NT = most > least ? most : least;
     return only_wide && groups <= 4 * NT ? 0 : NT;
 }
 // Workgroup me of an XCD takes a different one of the round's 32 neighbours every round: the

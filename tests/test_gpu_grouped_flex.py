@@ -1,5 +1,4 @@
-"""Grouped GEMM where no expert has more than 160 rows: tiles of 160 rows x 4..32 fragment rows (csrc/moe_gg_sched.h,
-gg_flex) at the edges of their token blocks, full and narrowed rounds, both sides of the rule, and the row count beside the line."""
+"""Grouped GEMM's tiles of up to 160 rows x 4..32 fragment rows (csrc/moe_gg_sched.h, gg_flex) at the edges of their token blocks, full and narrowed rounds, both sides of the rule, and the row count beside the line."""
 import pytest
 import torch
 
@@ -21,8 +20,24 @@ CASES = {
     "192 x 256 launch, better cut": ([160, 120, 130, 97], 2048, 2048, 0, 0),
     "256 x 256 launch, 11 half tiles": ([28, 30, 160, 1] * 16, 2048, 1408, 8, 4),
     "256 x 256 launch, second projection": ([28, 30, 160, 1] * 12, 2304, 1280, 5, 5),
-    "161 rows": ([161, 120, 130, 97] * 8, 2048, 1280, None, None),
+    "128 x 512 launch, experts of several tiles": ([161, 320, 16, 17, 90, 0, 0, 100] * 3, 2048, 2560, 10, 10),
+    "128 x 512 launch, 64 experts, skewed": ([480, 170, 40, 20, 9, 3, 1, 0] * 8, 1024, 1536, 6, 3),
+    "161 rows": ([161, 120, 130, 97] * 8, 2048, 1280, 0, 0),
 }
+
+
+def planned(L, counts, d, f, up, only_wide, wgs):  # noqa: F811
+    """Feature tiles of an expert, 0 for the launch's own tiles."""
+    E, N, n_tok = len(counts), sum(counts), sum(-(-n // 160) for n in counts)
+    KS, FR = (d // 32, f // 8) if up else (f // 32, d // 16)
+    if up and N <= 96 * E:
+        slim = KS <= 128 and feature_tiles(L, 33 * E, E, FR // 4, wgs, KS, up, False)
+        return L.fill(n_tok, FR // 4, wgs) if slim else 0
+    if N > 160 * E or (only_wide and max(counts) > 160):
+        return 0
+    tiles = [feature_tiles(L, N, n, FR // 4, wgs, KS, up, only_wide)
+             for n in [n_tok, *range(E, E + (0 if only_wide else N // 160) + 1)]]
+    return tiles[0] if any(tiles[1:]) else 0  # (the host takes the kernel that holds both if it expects them)
 
 
 @pytest.mark.parametrize("name", list(CASES))
@@ -33,13 +48,8 @@ def test_small_experts(L, name):  # noqa: F811
     plan = moe.moe_expert_ffn_plan(N, E, d, f, path=moe.MOE_FFN_GROUPED)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     for up, w in zip((1, 0), want):
-        if w is None:
-            assert max(counts) > 160
-            continue
-        assert max(counts) <= 160
-        KS, FR = (d // 32, f // 8) if up else (f // 32, d // 16)
         only_wide = plan["up_tile_features" if up else "down_tile_features"] == 256
-        NT = feature_tiles(L, sum(n > 0 for n in counts), FR // 4, (cus + 7) // 8, KS, up, only_wide)
+        NT = planned(L, counts, d, f, up, only_wide, (cus + 7) // 8)
         assert cus != 256 or NT == w, (up, NT)
 
     g = torch.Generator(device="cuda")

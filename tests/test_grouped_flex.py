@@ -1,5 +1,4 @@
-"""Feature tiles of the grouped GEMM where no expert has more than 160 rows (gg_flex in csrc/moe_gg_sched.h),
-replayed on the CPU with the kernel's own functions."""
+"""Feature tiles of the grouped GEMM's tiles of up to 160 rows (gg_flex in csrc/moe_gg_sched.h), replayed on the CPU with the kernel's own functions."""
 import ctypes as C
 import os
 import subprocess
@@ -13,9 +12,10 @@ SRC = r"""
 #include "moe_gg_sched.h"
 extern "C" {
 int limit(int up, int KS, int wgs) { return gg_split_limit(up != 0, KS, wgs); }
-int flex(int n_tok, int groups, int wgs, int KS, int split, int only_wide) {
-    return gg_flex(n_tok, groups, wgs, KS, split, only_wide != 0);
+int flex(int N, int n_tok, int groups, int wgs, int KS, int split, int only_wide) {
+    return gg_flex(N, n_tok, groups, wgs, KS, split, only_wide != 0);
 }
+int fill(int n_tok, int groups, int wgs) { return gg_flex_fill(n_tok, groups, wgs); }
 int is_cut(int total, int wgs, int KS, int split) { return gg_sched(total, wgs, 0, KS, split).split; }
 }
 """
@@ -33,8 +33,23 @@ def L():
         yield C.CDLL(so)
 
 
-def feature_tiles(L, n_tok, groups, wgs, KS, up, only_wide):
-    return L.flex(n_tok, groups, wgs, KS, L.limit(int(up), KS, wgs), int(only_wide))
+def feature_tiles(L, N, n_tok, groups, wgs, KS, up, only_wide):
+    return L.flex(N, n_tok, groups, wgs, KS, L.limit(int(up), KS, wgs), int(only_wide))
+
+
+@pytest.mark.parametrize("groups", [2048, 448, 200, 64, 44, 16, 4, 1])
+@pytest.mark.parametrize("wgs", [32, 5, 1])
+def test_tiles_fill_their_rounds(L, groups, wgs):
+    W = 8 * wgs
+    for n_tok in range(0, 170):
+        NT, least = L.fill(n_tok, groups, wgs), -(-groups // 8)
+        assert least <= NT <= max(groups // 3, least)
+        widths = {(nt + 1) * groups // NT - nt * groups // NT for nt in range(NT)}
+        assert min(widths) >= 1 and max(widths) <= 8
+        slots = -(-(n_tok * least) // W) * W
+        assert n_tok * NT <= slots
+        if n_tok:  # one tile more per token tile would not fit, or be of fewer than three groups
+            assert n_tok * (NT + 1) > slots or 3 * (NT + 1) > groups
 
 
 # groups of 4 fragment rows per expert: 448 / 64 (d 4096, f 14336), 200, 44 / 32 (d 2048, f 1408), 8, 4
@@ -47,12 +62,13 @@ def test_tiles_hold_every_group_once(L, groups, KS, wgs):
         for up in (0, 1):
             least = -(-groups // 8)
             total, rounds = n_tok * least, -(-(n_tok * least) // W)
-            for only_wide in (False, True):
-                NT = feature_tiles(L, n_tok, groups, wgs, KS, up, only_wide)
-                if NT == 0:  # the launch's own tiles: nothing to do, cut, or as wide
-                    assert n_tok == 0 or only_wide or L.is_cut(total, wgs, KS, L.limit(up, KS, wgs))
+            for only_wide, rows in ((False, 20), (False, 90), (True, 20), (True, 90)):
+                NT = feature_tiles(L, rows * n_tok, n_tok, groups, wgs, KS, up, only_wide)
+                if NT == 0:  # the launch's own tiles: nothing to do, as wide, full enough, or cut
+                    assert (n_tok == 0 or only_wide or (rows <= 32 and (rounds * W - total) * 10 <= 3 * W)
+                            or L.is_cut(total, wgs, KS, L.limit(up, KS, wgs)))
                     continue
-                assert least <= NT <= groups
+                assert least <= NT <= groups and NT == L.fill(n_tok, groups, wgs)
                 edges = [nt * groups // NT for nt in range(NT + 1)]
                 widths = [b - a for a, b in zip(edges, edges[1:])]
                 assert sum(widths) == groups and min(widths) >= 1 and max(widths) <= 8
@@ -73,4 +89,8 @@ def test_tiles_hold_every_group_once(L, groups, KS, wgs):
     # a tenth of a second round is cut; one expert cannot fill a round with tiles of 3 groups
     (5, 448, 128, 1, False, 0), (1, 448, 128, 1, False, 0), (0, 448, 128, 1, False, 0)])
 def test_rule(L, n_tok, groups, KS, up, only_wide, want):
-    assert feature_tiles(L, n_tok, groups, 32, KS, up, only_wide) == want
+    assert feature_tiles(L, 90 * n_tok, n_tok, groups, 32, KS, up, only_wide) == want
+    # with few rows the 512-feature tiles stay if they fill 0.7 of the last round, the others do not
+    few = feature_tiles(L, 32 * n_tok, n_tok, groups, 32, KS, up, only_wide)
+    full = n_tok * -(-groups // 8) % 256 * 10 >= 7 * 256 or n_tok * -(-groups // 8) % 256 == 0
+    assert few == (0 if full and not only_wide else want)
