@@ -908,40 +908,7 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
     }
 }
 
-// Second projection with fewer reduction steps than the pipelined kernel's stages (f = 128, which
-// MID serves): one wave per (token block, fragment row), straight from the fragments.
-#define GG_SHORT_FEATURES 64
-__global__ __launch_bounds__(256) void gg_down_short_kernel(GroupedArgs a) {
-    SegInfo si;
-    const int lane = threadIdx.x & 63;
-    if (!gg_find_block(a.offsets, a.E, a.N, blockIdx.x, lane, si)) return;
-    const int fr = blockIdx.y * 4 + (threadIdx.x >> 6);  // FR is a multiple of 4
-    const u32x4_t* w = a.wfrag + ((size_t)si.e * a.FR + fr) * a.KS * 64 + lane;
-    const u32x4_t* h = a.bfrag + (size_t)blockIdx.x * a.KS * 64 + lane;
-    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    for (int ks = 0; ks < a.KS; ks++)
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[ks * 64]),
-                                                      __builtin_bit_cast(bf16x8_t, h[ks * 64]), acc, 0, 0, 0);
-    const int row = ((int)blockIdx.x - si.bbase) * 16 + (lane & 15);
-    if (row < si.rows)
-        *(f32x4_t*)((float*)a.out + (size_t)(si.row0 + row) * a.C + fr * 16 + 4 * (lane >> 4)) = acc;
-}
-
 // ---------------------------------------------------------------- host side ----
-static inline size_t gg_align256(size_t v) { return (v + 255) & ~(size_t)255; }
-static inline size_t gg_max_blocks(int N, int E) { return (size_t)N / 16 + E; }
-
-// scratch for the partial tiles of the second projection: 2 slots of 256 x 256 fp32 per
-// persistent workgroup (one workgroup per CU, rounded up to a multiple of 8)
-static inline size_t gg_part_bytes() {
-    return (size_t)((moe_num_cus() + 7) / 8 * 8) * 2 * 256 * 256 * sizeof(float);
-}
-
-size_t moe_ffn_grouped_workspace(int N, int E, int d, int f) {
-    const size_t nb = gg_max_blocks(N, E);
-    return gg_align256(nb * 16 * d * 2) + gg_align256(nb * 16 * f * 2) + gg_part_bytes();
-}
-
 // Kernel variants by rows per expert (see the tile shapes at the top of the file): token
 // blocks and fragment rows of the tile, unroll / weight look-ahead / LDS stages of the loop.
 // (_S: kernels that hold the small experts' tile as well, of the second projection and, R192, of both.  SLIM: that tile
@@ -964,7 +931,7 @@ static GgShape gg_shape(GgVariant v) {
 }
 
 template <bool UP>
-static const void* gg_kernel_ptr(GgVariant v) {
+const void* gg_kernel_ptr(GgVariant v) {
     if constexpr (UP) {
         if (v == GG_SLIM) return (const void*)gg_gemm_kernel<UP, GG_SMALL_BLOCKS, 8, true, GG_U, GG_WIDE_LA, GG_NS>;
     } else {
@@ -982,7 +949,7 @@ static const void* gg_kernel_ptr(GgVariant v) {
 
 // One projection: the persistent GEMM and the fix-up of the pieces.
 template <bool UP>
-static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hipStream_t s) {
+int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hipStream_t s) {
     const GgShape sh = gg_shape(v);
     a.FROWS = sh.frows;
     if (a.FR % a.FROWS != 0) return MOE_ERR_UNSUPPORTED;
@@ -1007,6 +974,47 @@ static int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hip
 #undef GG_FIXUP
     }
     return MOE_OK;
+}
+
+// The second projection's kernels are compiled in a file of their own, beside the first's (a minute and a half each).
+#ifdef GG_SECOND_PROJECTION
+template const void* gg_kernel_ptr<false>(GgVariant);
+template int gg_launch_projection<false>(GroupedArgs&, GgVariant, unsigned, hipStream_t);
+#else
+extern template const void* gg_kernel_ptr<false>(GgVariant);
+extern template int gg_launch_projection<false>(GroupedArgs&, GgVariant, unsigned, hipStream_t);
+
+static inline size_t gg_align256(size_t v) { return (v + 255) & ~(size_t)255; }
+static inline size_t gg_max_blocks(int N, int E) { return (size_t)N / 16 + E; }
+
+// scratch for the partial tiles of the second projection: 2 slots of 256 x 256 fp32 per
+// persistent workgroup (one workgroup per CU, rounded up to a multiple of 8)
+static inline size_t gg_part_bytes() {
+    return (size_t)((moe_num_cus() + 7) / 8 * 8) * 2 * 256 * 256 * sizeof(float);
+}
+
+size_t moe_ffn_grouped_workspace(int N, int E, int d, int f) {
+    const size_t nb = gg_max_blocks(N, E);
+    return gg_align256(nb * 16 * d * 2) + gg_align256(nb * 16 * f * 2) + gg_part_bytes();
+}
+
+// Second projection with fewer reduction steps than the pipelined kernel's stages (f = 128, which
+// MID serves): one wave per (token block, fragment row), straight from the fragments.
+#define GG_SHORT_FEATURES 64
+__global__ __launch_bounds__(256) void gg_down_short_kernel(GroupedArgs a) {
+    SegInfo si;
+    const int lane = threadIdx.x & 63;
+    if (!gg_find_block(a.offsets, a.E, a.N, blockIdx.x, lane, si)) return;
+    const int fr = blockIdx.y * 4 + (threadIdx.x >> 6);  // FR is a multiple of 4
+    const u32x4_t* w = a.wfrag + ((size_t)si.e * a.FR + fr) * a.KS * 64 + lane;
+    const u32x4_t* h = a.bfrag + (size_t)blockIdx.x * a.KS * 64 + lane;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    for (int ks = 0; ks < a.KS; ks++)
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, w[ks * 64]),
+                                                      __builtin_bit_cast(bf16x8_t, h[ks * 64]), acc, 0, 0, 0);
+    const int row = ((int)blockIdx.x - si.bbase) * 16 + (lane & 15);
+    if (row < si.rows)
+        *(f32x4_t*)((float*)a.out + (size_t)(si.row0 + row) * a.C + fr * 16 + 4 * (lane >> 4)) = acc;
 }
 
 // The step loop is unrolled u times and the ring holds ns stages.
@@ -1175,3 +1183,4 @@ bool moe_ffn_grouped_supported(bool mid, int N, int E, int d, int f) {
     bool short_down;
     return gg_path_choose(mid, N, E, d, f, vu, vd, short_down);
 }
+#endif  // GG_SECOND_PROJECTION
