@@ -103,7 +103,7 @@ static int combine_args(const float* yg, const int32_t* inv_perm, const float* w
 static bool fused_front(const float* logits, int T, int EL, int E, int k, const void* x, size_t x_bytes, const int32_t* idx,
                         const float* weights, const int32_t* counts, const int32_t* offsets, const int32_t* perm,
                         const int32_t* inv_perm, const void* xg) {
-    if (T < 1 || !x || !moe_route_permute_rows_supported(T, k)) return false;
+    if (T < 1 || !x || !moe_route_permute_rows_supported(T, EL, k)) return false;
     const size_t n = (size_t)T * k * 4, e = (size_t)E * 4;
     const struct { const void* p; size_t bytes; } out[7] = {{idx, n}, {weights, n}, {counts, e}, {offsets, e + 4},
                                                             {perm, n}, {inv_perm, n}, {xg, x_bytes * k}};

@@ -124,7 +124,7 @@ __device__ __forceinline__ unsigned moe_pack_bf16x2(float lo, float hi) {
 int moe_route_launch(const float* logits, int T, int E, int k, int32_t* idx, float* weights,
                      hipStream_t s);
 // moe_route and moe_permute (with rows) in one launch; EL logits per token, E experts, EL <= E
-bool moe_route_permute_rows_supported(int T, int k);
+bool moe_route_permute_rows_supported(int T, int EL, int k);
 int moe_route_permute_rows_launch(const float* logits, int T, int EL, int E, int k, const void* x, int d,
                                   moe_dtype_t x_dtype, int32_t* idx, float* weights, int32_t* counts, int32_t* offsets,
                                   int32_t* perm, int32_t* inv_perm, void* xg, hipStream_t s);

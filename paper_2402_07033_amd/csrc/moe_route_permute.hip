@@ -489,14 +489,31 @@ __global__ __launch_bounds__(PM_THREADS) void route_permute_kernel(
     copy_row_k<false>(src, xg, row_chunks, k, lane + 64 * 8, pos);
 }
 
-bool moe_route_permute_rows_supported(int T, int k) { return T >= 1 && T * k <= RP_MAX_SLOTS && T <= moe_num_cus(); }
+// Every workgroup routes all tokens, 512 / G at a time, where route_kernel has workgroups of their own for them: the extra
+// passes cost k * log2(G) exchanges between lanes each.
+// Measured, route + permute (and the time between them, about 1 us, and 2-3 us of the host's for the launch) -> this:
+// 16 tokens, 8 experts, k = 2 2.1 + 3.6 -> 4.3 us, 64 tokens 2.4 + 3.6 -> 4.6; 6 exchanges more (128 tokens) 2.6 + 3.6 -> 6.2, 12
+// (192) 3.1 + 3.6 -> 7.8, 18 (256) 3.0 + 3.6 -> 9.9; 20 (32 tokens, 32 experts, k = 4) 3.8 + 3.8 -> 8.7; 36 (16 tokens, 64 experts, k =
+// 6) 5.3 + 4.0 -> 12.3; 252 (64 of them) 5.8 + 4.0 -> 36.
+#define RP_MAX_EXTRA 12
+static int rp_lanes(int EL) {
+    int G = 1;
+    while (G < EL) G <<= 1;
+    return G;
+}
+bool moe_route_permute_rows_supported(int T, int EL, int k) {
+    if (T < 1 || T * k > RP_MAX_SLOTS || T > moe_num_cus()) return false;
+    const int G = rp_lanes(EL), passes = (T * G + PM_THREADS - 1) / PM_THREADS;
+    int log2G = 0;
+    while ((1 << log2G) < G) log2G++;
+    return (passes - 1) * k * log2G <= RP_MAX_EXTRA;
+}
 
 int moe_route_permute_rows_launch(const float* logits, int T, int EL, int E, int k, const void* x, int d,
                                   moe_dtype_t x_dtype, int32_t* idx, float* weights, int32_t* counts, int32_t* offsets,
                                   int32_t* perm, int32_t* inv_perm, void* xg, hipStream_t s) {
     const int row_chunks = (int)(((size_t)d * (x_dtype == MOE_BF16 ? 2 : 4)) / 16);
-    int G = 1;
-    while (G < EL) G <<= 1;
+    const int G = rp_lanes(EL);
 #define RP_CASE(g)                                                                                                   \
     case g:                                                                                                          \
         hipLaunchKernelGGL(route_permute_kernel<g>, dim3((unsigned)T), dim3(PM_THREADS), 0, s, logits, T, EL, E, k,  \

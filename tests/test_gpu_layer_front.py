@@ -1,4 +1,4 @@
-"""moe_layer's routing and batching in one launch (up to 512 slots, a workgroup per token): the bits of the two
+"""moe_layer's routing and batching in one launch (up to 512 slots, a workgroup per token, few passes): the bits of the two
 calls at the edges of its groups of lanes and slots, on both sides of its limit, and with outputs over its inputs."""
 import ctypes as C
 
@@ -11,13 +11,16 @@ from gpu_util import pack_layer, to_dev
 pytestmark = pytest.mark.gpu
 
 
-# one lane per token .. 64; 64 slots and one more, groups that end inside a token, 512 slots and the first beyond (514, 520), as
-# many tokens as CUs and one more; rows of 256 B, and longer than one request of a wave (8 KiB)
+# One launch: 1, 2, 4, 8 and 64 lanes per token; 64 slots and one more, groups that end inside a token, 512 slots, as many tokens
+# as CUs; three passes of the workgroup over the tokens; fewer logits than experts; rows of 256 B, and longer than one request of a
+# wave (8 KiB).  Two: the first slots beyond 512, one token more than CUs, a fourth pass, two passes of 64 lanes.
 @pytest.mark.parametrize("T,E,EL,k,d,w,x", [
     (1, 1, 1, 1, 64, mi.F32, mi.F32), (16, 8, 8, 2, 256, mi.F32, mi.F32), (64, 2, 2, 1, 64, mi.F32, mi.F32),
-    (65, 3, 3, 1, 64, mi.F32, mi.F32), (33, 64, 64, 8, 256, mi.BF16, mi.BF16), (64, 64, 33, 8, 256, mi.BF16, mi.F32),
-    (65, 64, 64, 8, 256, mi.BF16, mi.F32), (73, 16, 9, 7, 64, mi.F32, mi.F32), (256, 8, 8, 2, 64, mi.F32, mi.F32),
-    (257, 8, 8, 2, 64, mi.F32, mi.F32), (257, 4, 4, 1, 64, mi.F32, mi.F32), (5, 4, 3, 2, 2112, mi.F32, mi.F32)])
+    (65, 3, 3, 1, 64, mi.F32, mi.F32), (8, 64, 64, 8, 256, mi.BF16, mi.BF16), (8, 64, 33, 8, 256, mi.BF16, mi.F32),
+    (128, 4, 4, 4, 64, mi.F32, mi.F32), (256, 2, 2, 2, 64, mi.F32, mi.F32), (192, 8, 8, 2, 64, mi.F32, mi.F32),
+    (29, 16, 9, 7, 64, mi.F32, mi.F32), (5, 4, 3, 2, 2112, mi.F32, mi.F32),
+    (129, 4, 4, 4, 64, mi.F32, mi.F32), (257, 4, 4, 1, 64, mi.F32, mi.F32), (193, 8, 8, 2, 64, mi.F32, mi.F32),
+    (9, 64, 64, 8, 256, mi.BF16, mi.BF16)])
 def test_layer_front(T, E, EL, k, d, w, x):
     import paper_2402_07033_amd as moe
     cfg = mi.small_config("front", T, d, 128, E, k, 30 + T + E, w_dtype=w, x_dtype=x, zipf_s=1.2)
