@@ -1026,7 +1026,7 @@ static bool gg_fits(GgVariant v, int ks) {
 // Up to 96 rows per expert the first projection has the small experts' tile whatever the rows: its rounds are filled by the
 // tiles' width, so nothing is cut and no fix-up is launched (4.6 us where there is nothing to add).  Not where, with all experts in
 // use, cutting is better (5 experts x 90 rows 365 us, 375 without pieces); reductions of more than 128 steps are worth it anyway.
-// Both projections, start -> this: 8 experts, 330 tokens, Zipf 0.6 622 -> 599 us, 220 tokens 526 -> 506; 16 experts, 500 tokens 538 -> 474,
+// Both projections, 128 x 512 (256 x 256) tiles -> this: 8 experts, 330 tokens, Zipf 0.6 622 -> 599 us, 220 tokens 526 -> 506; 16 experts, 500 tokens 538 -> 474,
 // Zipf 1.2 554 -> 502, 300 tokens 486 -> 441; 64 experts, 400 tokens, Zipf 1.2 226 -> 201, 200 tokens 167 -> 168; 77 tokens 463 ->
 // 459 and 488 -> 475 on two cards; with fewer experts in use than there are, 3 of 8 x 40 rows 244 -> 209, 6 of 8 x 90 436 -> 431, 5 of
 // 8 x 90 365 -> 375.
