@@ -1031,12 +1031,17 @@ static bool gg_fits(GgVariant v, int ks) {
 // 459 and 488 -> 475 on two cards; with fewer experts in use than there are, 3 of 8 x 40 rows 244 -> 209, 6 of 8 x 90 436 -> 431, 5 of
 // 8 x 90 365 -> 375.
 #define GG_SLIM_MAX_STEPS 128
+// Fragments (KiB) of a projection's weights from which the small experts' tile is considered: smaller ones stay in the
+// last-level cache from call to call, and then a tile's own matrix instructions bound it (all ten blocks of 8 rows of a wave, however
+// narrow the tile): 8 experts of d = 512, f = 1024, skewed 52 -> 61 us, of 1024, 2304 74 -> 79 (balanced 67 -> 63); 4 of 2048, 8192 (268
+// MB) 116..134 -> 99..112.
+#define GG_SMALL_MIN_FRAGS (128u << 10)
 // The kernel that a projection of variant v is run with: the one with the small experts' tile, too, if that is to
 // be expected (all experts in use); the other's tiles end without spills (77 tokens, second projection 151 us, 153 with the
 // other body beside it).
 static GgVariant gg_kernel_variant(GgVariant v, bool up, int N, int E, int KS, int FR) {
     const int wgs = (moe_num_cus() + 7) / 8, split = gg_split_limit(up, KS, wgs), most = 16 * GG_SMALL_BLOCKS;
-    if (N > most * E) return v;
+    if (N > most * E || (size_t)E * FR * KS < GG_SMALL_MIN_FRAGS) return v;
     if (up && N <= GG_WIDE_MAX_ROWS * E)
         return KS <= GG_SLIM_MAX_STEPS && gg_flex((GG_FLEX_FEW_ROWS + 1) * E, E, FR / 4, wgs, KS, split, false) ? GG_SLIM : v;
     for (int n = E; n <= E + (v == GG_WIDE ? N / most : 0); n++)  // token tiles

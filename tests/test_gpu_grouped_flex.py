@@ -12,7 +12,8 @@ CASES = {
     "128 x 512 launch, better cut": (EDGE, 2048, 2048, 0, 0),
     "128 x 512 launch, narrowed": (EDGE * 4, 2048, 1280, 8, 8),
     "128 x 512 launch, two rounds": (EDGE * 8, 2048, 1536, 8, 4),
-    "128 x 512 launch, reductions too short to cut": (EDGE, 512, 1024, 10, 2),
+    "128 x 512 launch, reductions too short to cut": (EDGE * 8, 1024, 1024, 4, 4),
+    "128 x 512 launch, small matrices": (EDGE * 4, 512, 1024, 0, 0),
     "128 x 512 launch, empty experts": ([0, 160, 0, 0, 17, 0, 1, 0] * 8, 2048, 1280, 10, 10),
     "192 x 256 launch, narrowed": ([160, 120, 130, 97] * 8, 2048, 1280, 8, 0),
     "192 x 256 launch, full": ([160, 120, 130, 97] * 8, 2048, 2048, 8, 0),
@@ -30,6 +31,8 @@ def planned(L, counts, d, f, up, only_wide, wgs):  # noqa: F811
     """Feature tiles of an expert, 0 for the launch's own tiles."""
     E, N, n_tok = len(counts), sum(counts), sum(-(-n // 160) for n in counts)
     KS, FR = (d // 32, f // 8) if up else (f // 32, d // 16)
+    if E * FR * KS < 128 << 10:  # the projection's weights in KiB: they stay in the last-level cache
+        return 0
     if up and N <= 96 * E:
         slim = KS <= 128 and feature_tiles(L, 33 * E, E, FR // 4, wgs, KS, up, False)
         return L.fill(n_tok, FR // 4, wgs) if slim else 0
