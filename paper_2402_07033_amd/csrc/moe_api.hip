@@ -113,7 +113,8 @@ static bool fused_front(const float* logits, int T, int EL, int E, int k, const 
 }
 
 // The launches of moe_expert_ffn and its variants, arguments checked, `path` as ffn_args left it.  With
-// `perm` the batched row i is read as xg[perm[i] / k] (xg is then the token array).
+// `perm` the batched row i is read as xg[perm[i] / k] (xg is then the token array).  k: experts of a token (1 if that
+// is not known): so many are in use at least, which rules of a dispatch may go by.
 static int ffn_launch(const moe_weights_t* W, const void* xg, moe_dtype_t act_dtype, const int32_t* perm, int k,
                       const int32_t* offsets, int N, void* workspace, float* yg, int path, hipStream_t s) {
     if (N == 0) return MOE_OK;
@@ -387,7 +388,7 @@ int moe_layer(const moe_weights_t* W, const void* x, moe_dtype_t x_dtype, int d,
     }
     if (rc != MOE_OK) return rc;
     *stage = 2;
-    if ((rc = ffn_launch(W, xg, x_dtype, nullptr, 1, offsets, T * k, workspace, yg, path, s)) != MOE_OK) return rc;
+    if ((rc = ffn_launch(W, xg, x_dtype, nullptr, k, offsets, T * k, workspace, yg, path, s)) != MOE_OK) return rc;
     *stage = 3;
     return T == 0 ? MOE_OK : moe_combine_launch(yg, inv_perm, weights, T, k, W->d, y, s);
 }

@@ -76,26 +76,23 @@
 //           which is what bounds such experts;
 //   160 x 4..32 (up to 160 tokens x 64..512 features; "small experts"): in place of any of them where the offsets show
 //           that no expert has more than 160 rows, and in place of the 128 x 512 one wherever it fills the rounds better,
-//           decided on the device (gg_flex in moe_gg_sched.h).  The weight stream
+//           decided on the device (gg_small_tiles in moe_gg_sched.h).  The weight stream
 //           bounds such launches.  A step moves a tile's weights W and its token rows t (mostly L2 hits) through one CU, and
 //           its time follows W + t / 2 (KiB: 16 + 8 for 128 rows of the 192 x 256 tile, 32 + 8 here), until HBM is full at
 //           6.5 TB/s; a round that is not full leaves bandwidth unused, so the tiles' width is cut to fill it.  First
 //           projection, 8 experts of f = 14336: 8 x 128 rows 361 -> 328 us (5.2 -> 5.7 TB/s; the fix-up of its pieces, 11 us,
 //           ends at once), 8 x 64 331 -> 311, 2 x 90 120 -> 97, 3 experts of 107 rows 168 -> 150; 16 of f = 6400: 16 x
 //           128 349 -> 326, 16 x 40 300 -> 285, 6 x 90 158 -> 124; 64 of f = 1408: 28 rows each 134 -> 128, 24 x 24 66 -> 57.
-//           With larger experts among them it is ahead up to 96 rows on average (gg_kernel_variant); above, from 1 % ahead to 9
+//           With larger experts among them it is ahead up to 96 rows on average (gg_small_tiles); above, from 1 % ahead to 9
 //           % behind (16 experts, 1100 tokens, Zipf 1.2 613 -> 631; second projections 179 -> 190, 199 -> 215), and not taken.
 //           Ten blocks of 16 rows are 80 accumulator tiles of a wave, 64 in accumulation registers and 16 in vector
 //           registers.
 #define GG_THREADS 256
-#define GG_SMALL_BLOCKS 10  // token blocks of the small experts' tile
+#define GG_SMALL_BLOCKS (GG_SMALL_ROWS / 16)  // token blocks of the small experts' tile
 // The lambdas of the loop have to be inlined: as a call, with its captures in memory, the wave-uniform values
 // among them become per-lane values, and every buffer request a loop over the lanes.
 #define GG_INLINE __attribute__((always_inline))
-#ifndef GG_WIDE_MAX_ROWS
-#define GG_WIDE_MAX_ROWS 96  // mean rows per expert up to which the 128 x 512 tile is used
-#endif
-// ... up to which the 192 x 256 tile is used, and the range above it where the 256 x 256 tile comes
+// Mean rows per expert up to which the 192 x 256 tile is used (from GG_WIDE_MAX_ROWS on), and the range above it where the 256 x 256 tile comes
 // first: experts of 177..232 rows on average mostly fit one 256-row tile and need two of 192.  At 36
 // sizes and routings there: balanced 2-33 % ahead (200 rows: 877 -> 671 us over 8 experts, 803 -> 604
 // over 16); Zipf 0.6 and 1.2, where the mean describes no expert, from 1 % behind to 8 % ahead at 23 of
@@ -165,18 +162,21 @@ struct TileInfo {
 
 // One wave fills the table (lane e: expert e), for tiles of NBW blocks; returns the number of token tiles.  SMALL:
 // small = feature tiles of an expert where tiles of GG_SMALL_BLOCKS and a width of their own are taken instead (0: they are not).
-template <int NBW, int FRW, bool SMALL>
+template <bool UP, int NBW, int FRW, bool SMALL>
 __device__ __forceinline__ int gg_seg_table(const GroupedArgs& a, int wgs, int lane, int (*tab)[64], bool write, int& small) {
     int lo, rows;
     gg_segment_of_lane(a.offsets, a.E, a.N, lane, lo, rows);
     const int nb = (rows + 15) / 16;
     small = 0;
-    if (SMALL && (FRW == 8 || __ballot(nb > GG_SMALL_BLOCKS) == 0ull)) {
-        int t = (nb + GG_SMALL_BLOCKS - 1) / GG_SMALL_BLOCKS;
+    if (SMALL && (FRW == 8 || (UP && a.N <= GG_WIDE_MAX_ROWS * a.E) || __ballot(nb > GG_SMALL_BLOCKS) == 0ull)) {
+        int t = (nb + GG_SMALL_BLOCKS - 1) / GG_SMALL_BLOCKS, own = (nb + NBW - 1) / NBW;
 #pragma unroll
-        for (int dlt = 1; dlt < 64; dlt <<= 1) t += __shfl_xor(t, dlt, 64);
-        small = __builtin_amdgcn_readfirstlane(NBW == GG_SMALL_BLOCKS ? gg_flex_fill(t, a.FR / 4, wgs)
-                                                                      : gg_flex(a.N, t, a.FR / 4, wgs, a.KS, a.split, FRW == 4));
+        for (int dlt = 1; dlt < 64; dlt <<= 1) {
+            t += __shfl_xor(t, dlt, 64);
+            own += __shfl_xor(own, dlt, 64);
+        }
+        small = __builtin_amdgcn_readfirstlane(gg_small_tiles(UP, a.N, a.E, __popcll(__ballot(nb > 0)), t, own, a.NT, a.FR, wgs,
+                                                              a.KS, a.split, FRW == 4));
     }
     const int tile_blocks = small ? GG_SMALL_BLOCKS : NBW;
     const int tiles = (nb + tile_blocks - 1) / tile_blocks;
@@ -802,20 +802,18 @@ template <bool UP, int NBW, int FRW, bool SMALL, int U, int LA, int NS>
 __global__ __launch_bounds__(GG_THREADS) void gg_gemm_kernel(GroupedArgs a) {
     __shared__ int s_seg[GG_SEG_FIELDS][64];
     int small;
-    const int n_tok = gg_seg_table<NBW, FRW, SMALL>(a, (int)(gridDim.x >> 3), threadIdx.x & 63, s_seg, threadIdx.x < 64, small);
+    const int n_tok = gg_seg_table<UP, NBW, FRW, SMALL>(a, (int)(gridDim.x >> 3), threadIdx.x & 63, s_seg, threadIdx.x < 64, small);
     __syncthreads();
     const int NT = SMALL && small ? small : a.NT, total = n_tok * NT;
     const bool turned = gg_turned(s_seg, threadIdx.x & 63, total, NT, a.KS);
-    if (SMALL && (NBW == GG_SMALL_BLOCKS || small)) {  // whole tiles only
+    if (SMALL && small) {  // whole tiles only
         gg_gemm_body<UP, GG_SMALL_BLOCKS, 8, true, 1, GG_U, GG_WIDE_LA, GG_NS>(a, NT, total, 0, turned, s_seg);
         return;
     }
-    if constexpr (NBW != GG_SMALL_BLOCKS) {
-        gg_gemm_body<UP, NBW, FRW, false, UP ? 1 : 0, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
-        if (UP) {
-            __syncthreads();  // no wave fills the LDS ring anew while another still reads it
-            gg_gemm_body<UP, NBW, FRW, false, 2, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
-        }
+    gg_gemm_body<UP, NBW, FRW, false, UP ? 1 : 0, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
+    if (UP) {
+        __syncthreads();  // no wave fills the LDS ring anew while another still reads it
+        gg_gemm_body<UP, NBW, FRW, false, 2, U, LA, NS>(a, NT, total, a.split, turned, s_seg);
     }
 }
 
@@ -836,7 +834,7 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int small;
-    const int total = gg_seg_table<NBW, FRW, SMALL>(a, wgs, lane, s_seg, threadIdx.x < 64, small) * a.NT;
+    const int total = gg_seg_table<UP, NBW, FRW, SMALL>(a, wgs, lane, s_seg, threadIdx.x < 64, small) * a.NT;
     const int left = total % (wgs * 8);
     if (small || left == 0 || !gg_sched(total, wgs, 0, a.KS, a.split).split) return;
     __syncthreads();
@@ -911,9 +909,8 @@ __global__ __launch_bounds__(256) void gg_fixup_kernel(GroupedArgs a, int wgs, i
 // ---------------------------------------------------------------- host side ----
 // Kernel variants by rows per expert (see the tile shapes at the top of the file): token
 // blocks and fragment rows of the tile, unroll / weight look-ahead / LDS stages of the loop.
-// (_S: kernels that hold the small experts' tile as well, of the second projection and, R192, of both.  SLIM: that tile
-// alone, first projection.)
-enum GgVariant { GG_STD = 0, GG_WIDE = 1, GG_R192 = 2, GG_STD_S = 3, GG_WIDE_S = 4, GG_R192_S = 5, GG_SLIM = 6, GG_NVARIANTS = 7 };
+// (_S: kernels that hold the small experts' tile as well.)
+enum GgVariant { GG_STD = 0, GG_WIDE = 1, GG_R192 = 2, GG_STD_S = 3, GG_WIDE_S = 4, GG_R192_S = 5, GG_NVARIANTS = 6 };
 struct GgShape { int tb, frows, u, la, ns; };
 static size_t gg_lds_bytes(const GgShape& sh) {
     const int nb = gg_stage_blocks(sh.tb), small = gg_stage_blocks(GG_SMALL_BLOCKS);
@@ -921,7 +918,6 @@ static size_t gg_lds_bytes(const GgShape& sh) {
 }
 static GgShape gg_shape(GgVariant v) {
     switch (v) {
-        case GG_SLIM: return {GG_SMALL_BLOCKS, 4, GG_U, GG_WIDE_LA, GG_NS};
         case GG_WIDE:
         case GG_WIDE_S: return {8, 32, GG_U, GG_WIDE_LA, GG_NS};
         case GG_R192:
@@ -932,35 +928,34 @@ static GgShape gg_shape(GgVariant v) {
 
 template <bool UP>
 const void* gg_kernel_ptr(GgVariant v) {
-    if constexpr (UP) {
-        if (v == GG_SLIM) return (const void*)gg_gemm_kernel<UP, GG_SMALL_BLOCKS, 8, true, GG_U, GG_WIDE_LA, GG_NS>;
-    } else {
-        if (v == GG_WIDE_S) return (const void*)gg_gemm_kernel<UP, 8, 8, true, GG_U, GG_WIDE_LA, GG_NS>;
-        if (v == GG_STD_S) return (const void*)gg_gemm_kernel<UP, 16, 4, true, GG_U, GG_LA, GG_NS>;
-    }
     switch (v) {
         case GG_WIDE: return (const void*)gg_gemm_kernel<UP, 8, 8, false, GG_U, GG_WIDE_LA, GG_NS>;
+        case GG_WIDE_S: return (const void*)gg_gemm_kernel<UP, 8, 8, true, GG_U, GG_WIDE_LA, GG_NS>;
         case GG_R192: return (const void*)gg_gemm_kernel<UP, 12, 4, false, GG_U, GG_LA, GG_NS>;
         case GG_R192_S: return (const void*)gg_gemm_kernel<UP, 12, 4, true, GG_U, GG_LA, GG_NS>;
-        case GG_STD: return (const void*)gg_gemm_kernel<UP, 16, 4, false, GG_U, GG_LA, GG_NS>;
-        default: return nullptr;
+        case GG_STD_S: return (const void*)gg_gemm_kernel<UP, 16, 4, true, GG_U, GG_LA, GG_NS>;
+        default: return (const void*)gg_gemm_kernel<UP, 16, 4, false, GG_U, GG_LA, GG_NS>;
     }
 }
 
-// One projection: the persistent GEMM and the fix-up of the pieces.
+// One projection: the persistent GEMM and the fix-up of the pieces.  least: experts in use, at least (of a different number
+// than that, only the time depends on it).
 template <bool UP>
-int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hipStream_t s) {
+int gg_launch_projection(GroupedArgs& a, GgVariant v, int least, unsigned pgrid, hipStream_t s) {
     const GgShape sh = gg_shape(v);
     a.FROWS = sh.frows;
     if (a.FR % a.FROWS != 0) return MOE_ERR_UNSUPPORTED;
     a.NT = a.FR / a.FROWS;
-    a.split = v == GG_SLIM ? 0 : gg_split_limit(UP, a.KS, (int)(pgrid / 8));
+    const int wgs = (int)(pgrid / 8);
+    a.split = gg_split_limit(UP, a.KS, wgs);
+    if (UP && (v == GG_WIDE_S || v == GG_STD_S) &&
+        !gg_up_may_cut(a.N, a.E, least, 16 * sh.tb, a.NT, a.FR, a.KS, wgs, v == GG_STD_S))
+        a.split = 0;
     void* params[1] = {(void*)&a};
     const size_t lds_bytes = gg_lds_bytes(sh);
     MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<UP>(v), dim3(pgrid), dim3(GG_THREADS), params, lds_bytes, s));
     if (a.split) {
         const dim3 fgrid(GG_FIX_GRID);
-        const int wgs = (int)(pgrid / 8);
 #define GG_FIXUP(NBW, FRW, SMALL) \
     hipLaunchKernelGGL((gg_fixup_kernel<UP, NBW, FRW, SMALL>), fgrid, dim3(256), 0, s, a, wgs, sh.u, sh.ns)
         switch (v) {
@@ -979,10 +974,10 @@ int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hipStream_
 // The second projection's kernels are compiled in a file of their own, beside the first's (a minute and a half each).
 #ifdef GG_SECOND_PROJECTION
 template const void* gg_kernel_ptr<false>(GgVariant);
-template int gg_launch_projection<false>(GroupedArgs&, GgVariant, unsigned, hipStream_t);
+template int gg_launch_projection<false>(GroupedArgs&, GgVariant, int, unsigned, hipStream_t);
 #else
 extern template const void* gg_kernel_ptr<false>(GgVariant);
-extern template int gg_launch_projection<false>(GroupedArgs&, GgVariant, unsigned, hipStream_t);
+extern template int gg_launch_projection<false>(GroupedArgs&, GgVariant, int, unsigned, hipStream_t);
 
 static inline size_t gg_align256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline size_t gg_max_blocks(int N, int E) { return (size_t)N / 16 + E; }
@@ -1023,31 +1018,10 @@ static bool gg_fits(GgVariant v, int ks) {
     return ks % sh.u == 0 && ks >= sh.ns;
 }
 
-// Up to 96 rows per expert the first projection has the small experts' tile whatever the rows: its rounds are filled by the
-// tiles' width, so nothing is cut and no fix-up is launched (4.6 us where there is nothing to add).  Not where, with all experts in
-// use, cutting is better (5 experts x 90 rows 365 us, 375 without pieces); reductions of more than 128 steps are worth it anyway.
-// Both projections, 128 x 512 (256 x 256) tiles -> this: 8 experts, 330 tokens, Zipf 0.6 622 -> 599 us, 220 tokens 526 -> 506; 16 experts, 500 tokens 538 -> 474,
-// Zipf 1.2 554 -> 502, 300 tokens 486 -> 441; 64 experts, 400 tokens, Zipf 1.2 226 -> 201, 200 tokens 167 -> 168; 77 tokens 463 ->
-// 459 and 488 -> 475 on two cards; with fewer experts in use than there are, 3 of 8 x 40 rows 244 -> 209, 6 of 8 x 90 436 -> 431, 5 of
-// 8 x 90 365 -> 375.
-#define GG_SLIM_MAX_STEPS 128
-// Fragments (KiB) of a projection's weights from which the small experts' tile is considered: smaller ones stay in the
-// last-level cache from call to call, and then a tile's own matrix instructions bound it (all ten blocks of 8 rows of a wave, however
-// narrow the tile): 8 experts of d = 512, f = 1024, skewed 52 -> 61 us, of 1024, 2304 74 -> 79 (balanced 67 -> 63); 4 of 2048, 8192 (268
-// MB) 116..134 -> 99..112.
-#define GG_SMALL_MIN_FRAGS (128u << 10)
-// The kernel that a projection of variant v is run with: the one with the small experts' tile, too, if that is to
-// be expected (all experts in use); the other's tiles end without spills (77 tokens, second projection 151 us, 153 with the
-// other body beside it).
+// The kernel that a projection of variant v is run with.
 static GgVariant gg_kernel_variant(GgVariant v, bool up, int N, int E, int KS, int FR) {
-    const int wgs = (moe_num_cus() + 7) / 8, split = gg_split_limit(up, KS, wgs), most = 16 * GG_SMALL_BLOCKS;
-    if (N > most * E || (size_t)E * FR * KS < GG_SMALL_MIN_FRAGS) return v;
-    if (up && N <= GG_WIDE_MAX_ROWS * E)
-        return KS <= GG_SLIM_MAX_STEPS && gg_flex((GG_FLEX_FEW_ROWS + 1) * E, E, FR / 4, wgs, KS, split, false) ? GG_SLIM : v;
-    for (int n = E; n <= E + (v == GG_WIDE ? N / most : 0); n++)  // token tiles
-        if (gg_flex(N, n, FR / 4, wgs, KS, split, v != GG_WIDE))
-            return v == GG_WIDE ? GG_WIDE_S : v == GG_R192 ? GG_R192_S : up ? v : GG_STD_S;
-    return v;
+    if (!gg_small_expected(up, v == GG_WIDE, N, E, FR, KS, (moe_num_cus() + 7) / 8)) return v;
+    return v == GG_WIDE ? GG_WIDE_S : v == GG_R192 ? GG_R192_S : GG_STD_S;
 }
 
 // Variant of each projection by the mean number of rows per expert (the host never sees the
@@ -1113,7 +1087,7 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
             const GgShape sh = gg_shape((GgVariant)v);
             const void* all[2] = {gg_kernel_ptr<true>((GgVariant)v), gg_kernel_ptr<false>((GgVariant)v)};
             for (int i = 0; i < 2; i++)
-                if (all[i]) MOE_HIP_TRY(hipFuncSetAttribute(all[i], hipFuncAttributeMaxDynamicSharedMemorySize,
+                MOE_HIP_TRY(hipFuncSetAttribute(all[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                                                 (int)gg_lds_bytes(sh)));
         }
         attr_set[dev].store(1, std::memory_order_release);
@@ -1144,7 +1118,7 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
     up.KS_out = f / 32;
     up.C = 0;
     up.part = part;
-    int rc = gg_launch_projection<true>(up, vu, pgrid, s);
+    int rc = gg_launch_projection<true>(up, vu, k < E ? k : E, pgrid, s);
     if (rc != MOE_OK) return rc;
     moe_record_mid_event(s);
 
@@ -1163,7 +1137,7 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
         hipLaunchKernelGGL(gg_down_short_kernel, dim3((unsigned)nb, (unsigned)(d / GG_SHORT_FEATURES)), dim3(256), 0, s, dn);
         return moe_launch_status();
     }
-    rc = gg_launch_projection<false>(dn, vd, pgrid, s);
+    rc = gg_launch_projection<false>(dn, vd, 0, pgrid, s);
     if (rc != MOE_OK) return rc;
     return moe_launch_status();
 }

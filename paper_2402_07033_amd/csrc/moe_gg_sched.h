@@ -6,6 +6,16 @@
 // workgroups, wgs for each XCD.
 #pragma once
 
+#ifndef GG_WIDE_MAX_ROWS
+#define GG_WIDE_MAX_ROWS 96  // mean rows per expert up to which the 128 x 512 tile is used
+#endif
+#define GG_SMALL_ROWS 160    // rows of the small experts' tile
+// Fragments (KiB) of a projection's weights from which the small experts' tile is considered: smaller ones stay in the
+// last-level cache from call to call, and then a tile's own matrix instructions bound it (all ten blocks of 8 rows of a wave, however
+// narrow the tile): 8 experts of d = 512, f = 1024, skewed 52 -> 61 us, of 1024, 2304 74 -> 79 (balanced 67 -> 63); 4 of 2048, 8192 (268
+// MB) 116..134 -> 99..112.
+#define GG_SMALL_MIN_FRAGS (128 << 10)
+
 // (inlined always: what a called function returns is no wave-uniform value)
 #define GG_FN constexpr __attribute__((always_inline)) inline
 
@@ -27,11 +37,12 @@
 #define GG_SPLIT_UP 22          // 32nds of a round up to which the first projection's left-over tiles are cut
 #define GG_SPLIT_DOWN 20        // the second's
 #define GG_SPLIT_MIN_STEPS 36   // steps that cutting has to save (of what it saves at best)
+#define GG_SPLIT_KS 64          // steps of the reduction from which tiles are cut
 // Left-over tiles are cut if they are at most this many 32nds of a round (0: never).  Pieces of >= 32 steps
 // go to scratch and a fix-up kernel adds them; it lists the pieces of a tile with one wave, hence at
 // most 64 workgroups per XCD.
 GG_FN int gg_split_limit(bool up, int KS, int wgs) {
-    return KS >= 64 && wgs <= 64 ? (up ? GG_SPLIT_UP : GG_SPLIT_DOWN) : 0;
+    return KS >= GG_SPLIT_KS && wgs <= 64 ? (up ? GG_SPLIT_UP : GG_SPLIT_DOWN) : 0;
 }
 struct GgSched {
     int n_full;   // rounds of whole tiles
@@ -84,6 +95,70 @@ GG_FN int gg_flex(int N, int n_tok, int groups, int wgs, int KS, int split, bool
          NT == least))
         return 0;
     return only_wide && groups <= 4 * NT ? 0 : NT;
+}
+// The same for the first projection up to GG_WIDE_MAX_ROWS rows per expert, where experts of more than 160 rows do not rule
+// these tiles out: always, but for a few cases, all of few experts in use.  only_wide: the launch's own tiles, if these are as wide.
+// Where the tiles leave 48 steps' worth of the one round idle, cutting is better: a step takes 0.47 us however narrow its tile
+// is.  GEMM, narrowed -> cut, fix-up and 1.2 us between them included, 128 steps: 1 expert of f = 6400, 16..128 rows, 60..76 -> 39..50
+// us, 2 of them 66 -> 51, 73 -> 63, 80 -> 66 (62 idle), 3 68 -> 71, 79 -> 93 (29 idle); 1 of f = 14336 66 -> 53, 74 -> 67 (53
+// idle); 64 steps, 1 of f = 8192 37 -> 43 (43 idle).  And in several rounds that the
+// fewest tiles leave idle for GG_FLEX_CUT_STEPS, with more than 64 rows per token tile: 128 steps, 5 experts of f = 14336, 24 rows
+// 188 -> 200, 40 197 -> 200, 56 204 -> 203, 64 203 -> 204, 72 216 -> 209, 90 222 -> 211, 120 233 -> 218; 14 of them 588 -> 579; 11 of
+// f = 6400 186 -> 198, 206 -> 210, 215 -> 217, 227 -> 223, 227 -> 220.
+#define GG_FLEX_IDLE_STEPS 48
+#define GG_FLEX_CUT_ROWS 64
+GG_FN bool gg_up_cut(int N, int n_tok, int groups, int wgs, int KS, int split) {
+    const int W = wgs * 8, total = n_tok * ((groups + 7) / 8), slots = (total + W - 1) / W * W;
+    if (total == slots || !gg_sched(total, wgs, 0, KS, split).split) return false;
+    if (slots == W) return (W - gg_flex_fill(n_tok, groups, wgs) * n_tok) * KS >= W * GG_FLEX_IDLE_STEPS;
+    return (slots - total) * KS >= W * GG_FLEX_CUT_STEPS && N > GG_FLEX_CUT_ROWS * n_tok;
+}
+// Feature tiles per expert of the tiles of up to 160 rows, 0: the launch's own.  `active` experts with rows, in n_tok token tiles of 160
+// rows or own_tok of the launch's, which have own_NT feature tiles per expert.
+// Where an expert has more of the launch's token tiles than of these, these are ahead whatever is idle (cut -> narrowed, 128 steps: 1
+// x 160 rows of f = 14336 112 -> 92, 5 x 150 303 -> 264, 2 x 150 of f = 6400 106 -> 91) unless the last-level cache keeps the matrices of
+// the experts in use and the launch's tiles are one round: two tiles of 5 blocks end before one of 10 does.  64 steps, own -> 160 rows: 2 x
+// 150 rows of f = 8192 (134 MB) 47 -> 57, 4 x 150 (268 MB) 73 -> 66; 4, 8, 10 x 150 of f = 1792 (59, 117, 147 MB) 36, 44, 45 -> 51, 53,
+// 54, 16 (235 MB) 69 -> 64; 128 steps, 1 x 150 of f = 6400 (105 MB) 42 -> 89.
+GG_FN int gg_small_tiles(bool up, int N, int E, int active, int n_tok, int own_tok, int own_NT, int FR, int wgs, int KS, int split,
+                         bool only_wide) {
+    if (!up || N > GG_WIDE_MAX_ROWS * E) return gg_flex(N, n_tok, FR / 4, wgs, KS, split, only_wide);
+    const int NT = gg_flex_fill(n_tok, FR / 4, wgs);
+    if (only_wide && FR / 4 <= 4 * NT) return 0;
+    if (own_tok > n_tok)
+        return own_tok * own_NT <= wgs * 8 && (long long)active * FR * KS <= GG_SMALL_MIN_FRAGS ? 0 : NT;
+    return gg_up_cut(N, n_tok, FR / 4, wgs, KS, split) ? 0 : NT;
+}
+// HOST: is the projection run with the kernel that holds the tiles of 160 rows, too?  If they are to be expected with all experts in
+// use; the other's tiles end without spills (77 tokens, second projection 151 us, 153 with the other body beside it).
+// GG_UP_MAX_STEPS: of the first projection's longer reductions, narrowed -> own: 192 steps, 8 experts of f = 8192 with 20..90 rows 397 -> 394
+// and 445 -> 438 (both projections), 5 of them 349 -> 301, skewed 501 -> 512; 256 steps 896 -> 875, 973 -> 935, skewed 1069 -> 1061:
+// not taken for the skewed ones.
+#define GG_UP_MAX_STEPS 128
+GG_FN bool gg_small_expected(bool up, bool own_wide, int N, int E, int FR, int KS, int wgs) {
+    if (N > GG_SMALL_ROWS * E || (long long)E * FR * KS < GG_SMALL_MIN_FRAGS) return false;
+    const int split = gg_split_limit(up, KS, wgs);
+    if (up && N <= GG_WIDE_MAX_ROWS * E)
+        return KS <= GG_UP_MAX_STEPS && gg_flex((GG_FLEX_FEW_ROWS + 1) * E, E, FR / 4, wgs, KS, split, false) != 0;
+    for (int n = E; n <= E + (own_wide ? N / GG_SMALL_ROWS : 0); n++)  // token tiles
+        if (gg_flex(N, n, FR / 4, wgs, KS, split, !own_wide)) return true;
+    return false;
+}
+// HOST: may such a first projection have pieces?  If not, its tiles are all left whole and no fix-up is launched (4.6 us where
+// there is nothing to add).  least: experts in use, at least.  Cutting the launch's own tiles has to save GG_FIXUP_MIN_STEPS: 64 steps,
+// tiles of 256 x 256, whole -> cut with fix-up: 1..4 experts of f = 1408 with 20..150 rows 25..35 -> 22..28 us, 6 x 24 28 -> 26, 6 x 60 30
+// -> 30, 6 x 200 46 -> 39 (47 steps saved at most), 8 x 100 35 -> 36, 8 x 225 47 -> 45 (42), 10 x 180 45 -> 49; longer ones always.
+#define GG_FIXUP_MIN_STEPS 44
+GG_FN bool gg_up_may_cut(int N, int E, int least, int own_rows, int own_NT, int FR, int KS, int wgs, bool only_wide) {
+    const int W = wgs * 8, split = gg_split_limit(true, KS, wgs);
+    const int own = (N + own_rows - 1) / own_rows, tok = (N + GG_SMALL_ROWS - 1) / GG_SMALL_ROWS;
+    if (!split) return false;
+    if ((only_wide || (long long)least * FR * KS <= GG_SMALL_MIN_FRAGS) &&
+        (KS > GG_SPLIT_KS || (W - (own > least ? own : least) * own_NT) * KS >= W * GG_FIXUP_MIN_STEPS))
+        return true;
+    for (int n = tok > least ? tok : least; n <= E + N / GG_SMALL_ROWS; n++)
+        if (gg_up_cut(N, n, FR / 4, wgs, KS, split)) return true;
+    return false;
 }
 // Workgroup me of an XCD takes a different one of the round's 32 neighbours every round: the
 // token tiles of an expert differ in length, and their period must not pick workgroups.

@@ -2,7 +2,7 @@
 import pytest
 import torch
 
-from test_grouped_flex import L, feature_tiles  # noqa: F401
+import gg_schedule
 
 pytestmark = pytest.mark.gpu
 
@@ -27,43 +27,65 @@ CASES = {
 }
 
 
-def planned(L, counts, d, f, up, only_wide, wgs):  # noqa: F811
-    """Feature tiles of an expert, 0 for the launch's own tiles."""
-    E, N, n_tok = len(counts), sum(counts), sum(-(-n // 160) for n in counts)
-    KS, FR = (d // 32, f // 8) if up else (f // 32, d // 16)
-    if E * FR * KS < 128 << 10:  # the projection's weights in KiB: they stay in the last-level cache
-        return 0
-    if up and N <= 96 * E:
-        slim = KS <= 128 and feature_tiles(L, 33 * E, E, FR // 4, wgs, KS, up, False)
-        return L.fill(n_tok, FR // 4, wgs) if slim else 0
-    if N > 160 * E or (only_wide and max(counts) > 160):
-        return 0
-    tiles = [feature_tiles(L, N, n, FR // 4, wgs, KS, up, only_wide)
-             for n in [n_tok, *range(E, E + (0 if only_wide else N // 160) + 1)]]
-    return tiles[0] if any(tiles[1:]) else 0  # (the host takes the kernel that holds both if it expects them)
+def layer(E, d, f, N, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    normal = lambda *s: torch.randn(s, device="cuda", generator=g)  # noqa: E731
+    w1, w3 = ((normal(E, d, f) * d ** -0.5).to(torch.bfloat16) for _ in range(2))
+    w2 = (normal(E, f, d) * f ** -0.5).to(torch.bfloat16)
+    return w1, w3, w2, normal(N, d).to(torch.bfloat16)
+
+
+def bounds_of(counts):
+    bounds = [0]
+    for n in counts:
+        bounds.append(bounds[-1] + n)
+    return bounds
+
+
+def worst_row(yg, xg, bounds, w1, w3, w2):
+    """Largest error of a row, 2-norm over 2-norm, against 64 bits with h rounded to bf16."""
+    worst = 0.0
+    for e in range(len(bounds) - 1):
+        lo, hi = bounds[e], bounds[e + 1]
+        if lo == hi:
+            continue
+        x = xg[lo:hi].double()
+        h = torch.nn.functional.silu(x @ w1[e].double()) * (x @ w3[e].double())
+        ref = h.to(torch.bfloat16).double() @ w2[e].double()
+        err = (yg[lo:hi].double() - ref).norm(dim=1) / ref.norm(dim=1)
+        assert bool(torch.isfinite(err).all())
+        worst = max(worst, float(err.max()))
+    return worst
+
+
+class Scratch:
+    """A workspace filled with a pattern, whose area for the pieces of tiles shows whether any were stored."""
+
+    def __init__(self, N, E, d, f):
+        import paper_2402_07033_amd as moe
+        align = lambda v: (v + 255) // 256 * 256  # noqa: E731
+        blocks = N // 16 + E  # 16-row blocks of either fragment buffer
+        self.ws = torch.full((moe.moe_expert_ffn_workspace(N, E, d, f, moe.MOE_BF16),), 0xA5, dtype=torch.uint8, device="cuda")
+        self.at = align(blocks * 16 * d * 2) + align(blocks * 16 * f * 2)
+
+    def pieces(self):
+        return bool((self.ws[self.at:] != 0xA5).any())
 
 
 @pytest.mark.parametrize("name", list(CASES))
-def test_small_experts(L, name):  # noqa: F811
+def test_small_experts(name):
     import paper_2402_07033_amd as moe
     counts, d, f, *want = CASES[name]
     E, N = len(counts), sum(counts)
     plan = moe.moe_expert_ffn_plan(N, E, d, f, path=moe.MOE_FFN_GROUPED)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    for up, w in zip((1, 0), want):
-        only_wide = plan["up_tile_features" if up else "down_tile_features"] == 256
-        NT = planned(L, counts, d, f, up, only_wide, (cus + 7) // 8)
-        assert cus != 256 or NT == w, (up, NT)
+    for side, w in zip(("up", "down"), want):
+        tile = plan[side + "_tile_rows"], plan[side + "_tile_features"]
+        assert cus != 256 or gg_schedule.launched(counts, d, f, side == "up", *tile, cus=cus).small == w, side
 
-    g = torch.Generator(device="cuda")
-    g.manual_seed(5100 + N)
-    normal = lambda *s: torch.randn(s, device="cuda", generator=g)  # noqa: E731
-    w1, w3 = ((normal(E, d, f) * d ** -0.5).to(torch.bfloat16) for _ in range(2))
-    w2 = (normal(E, f, d) * f ** -0.5).to(torch.bfloat16)
-    xg = normal(N, d).to(torch.bfloat16)
-    bounds = [0]
-    for n in counts:
-        bounds.append(bounds[-1] + n)
+    w1, w3, w2, xg = layer(E, d, f, N, 5100 + N)
+    bounds = bounds_of(counts)
     off = torch.tensor(bounds, dtype=torch.int32, device="cuda")
     W = moe.moe_weights_pack(w1, w3, w2)
     bufs = []
@@ -74,21 +96,60 @@ def test_small_experts(L, name):  # noqa: F811
         bufs.append(buf)
     assert bool(torch.isnan(bufs[0][N:]).all()), "a store behind the last row"
     assert torch.equal(bufs[0][:N], bufs[1][:N])
-    worst = 0.0
-    for e in range(E):
-        lo, hi = bounds[e], bounds[e + 1]
-        if lo == hi:
-            continue
-        x = xg[lo:hi].double()
-        h = torch.nn.functional.silu(x @ w1[e].double()) * (x @ w3[e].double())
-        ref = h.to(torch.bfloat16).double() @ w2[e].double()
-        err = (bufs[0][lo:hi].double() - ref).norm(dim=1) / ref.norm(dim=1)
-        assert bool(torch.isfinite(err).all())
-        worst = max(worst, float(err.max()))
+    worst = worst_row(bufs[0], xg, bounds, w1, w3, w2)
     print(f"{name}: error {worst:.2e}")
     # 2-norm of a row: an h close to a rounding boundary of bf16 rounds the other way and moves by 2^-7 of itself at
     # most, about one in 2^11; the largest h of a row of 1024 and more has less than 0.6 of the row's norm, so two
     # of that size move yg by less than 1e-2 of its norm.  One step's operands from the wrong tile move it by
     # 1 / sqrt(steps), 0.08 and more.
     assert worst <= 1e-2
+    W.free()
+
+
+# Few experts in use: the second projection (fewer than 64 steps) is never cut, so pieces are the first's.
+FEW = [
+    # rows of the experts in use, f, experts, are there pieces
+    ([90], 1536, 16, True),         # 16 narrow tiles for all CUs
+    ([24] * 8, 1536, 16, True),
+    ([24] * 12, 1536, 16, False),   # 192 of them
+    ([90] * 16, 1536, 16, False),
+    ([150], 1536, 16, True),        # two of the launch's token tiles in place of one
+    ([150] * 8, 1536, 16, False),   # ... and matrices that the last-level cache does not keep
+    ([24] * 6, 1408, 32, True),     # tiles of 256 features, as wide as the narrow ones
+    ([90] * 24, 1408, 32, False),
+]
+
+
+@pytest.mark.parametrize("rows,f,E,pieces", FEW)
+def test_few_experts_in_use(rows, f, E, pieces):
+    import paper_2402_07033_amd as moe
+    d, N, counts = 4096, sum(rows), rows + [0] * (E - len(rows))
+    w1, w3, w2, xg = layer(E, d, f, N, 5300 + N)
+    bounds = bounds_of(counts)
+    W, scratch = moe.moe_weights_pack(w1, w3, w2), Scratch(N, E, d, f)
+    buf = torch.full((N + 16, d), float("nan"), device="cuda")
+    moe.moe_expert_ffn(W, xg, torch.tensor(bounds, dtype=torch.int32, device="cuda"), workspace=scratch.ws, yg=buf[:N],
+                       path=moe.MOE_FFN_GROUPED)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(buf[N:]).all()), "a store behind the last row"
+    assert worst_row(buf, xg, bounds, w1, w3, w2) <= 1e-2  # (as above)
+    assert torch.cuda.get_device_properties(0).multi_processor_count != 256 or scratch.pieces() == pieces
+    W.free()
+
+
+def test_fewer_experts_than_a_token_has():
+    """Without a fix-up launch, since every token has two experts, and then all rows are one expert's: nothing is cut."""
+    import paper_2402_07033_amd as moe
+    E, d, f, T, k = 8, 4096, 8192, 73, 2
+    N = T * k
+    assert not gg_schedule.launched([N] + [0] * 7, d, f, True, 128, 512, least=k).fixup
+    assert gg_schedule.launched([N] + [0] * 7, d, f, True, 128, 512).pieces
+    w1, w3, w2, x = layer(E, d, f, T, 5400)
+    bounds = bounds_of([0, 0, N, 0, 0, 0, 0, 0])
+    W, perm = moe.moe_weights_pack(w1, w3, w2), torch.arange(N, dtype=torch.int32, device="cuda")
+    buf = torch.full((N + 16, d), float("nan"), device="cuda")
+    moe.moe_expert_ffn_tokens(W, x, k, perm, torch.tensor(bounds, dtype=torch.int32, device="cuda"), yg=buf[:N])
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(buf[N:]).all())
+    assert worst_row(buf, x.repeat_interleave(k, dim=0), bounds, w1, w3, w2) <= 1e-2
     W.free()

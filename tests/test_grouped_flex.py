@@ -6,6 +6,8 @@ import tempfile
 
 import pytest
 
+import gg_schedule
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = r"""
 #include "moe_gg_ring.h"
@@ -94,3 +96,52 @@ def test_rule(L, n_tok, groups, KS, up, only_wide, want):
     few = feature_tiles(L, 32 * n_tok, n_tok, groups, 32, KS, up, only_wide)
     full = n_tok * -(-groups // 8) % 256 * 10 >= 7 * 256 or n_tok * -(-groups // 8) % 256 == 0
     assert few == (0 if full and not only_wide else want)
+
+
+# d, f, rows of the experts in use, experts -> feature tiles of 160 rows per expert, 0: the launch's own; each line is a
+# measurement that stands beside the rule
+MIXTRAL, SIXTEEN, SIXTYFOUR = (4096, 14336, 8), (4096, 6400, 16), (2048, 1408, 64)
+FEW = [
+    (MIXTRAL, [90], 0), (MIXTRAL, [160], 149), (MIXTRAL, [300], 128), (MIXTRAL, [24] * 2, 128),
+    (MIXTRAL, [24] * 5, 102), (MIXTRAL, [64] * 5, 102), (MIXTRAL, [72] * 5, 0), (MIXTRAL, [150] * 5, 102),
+    (MIXTRAL, [90] * 8, 64), (MIXTRAL, [20] * 8, 64),
+    (SIXTEEN, [90], 0), (SIXTEEN, [150], 0), (SIXTEEN, [300], 0), (SIXTEEN, [24] * 2, 0), (SIXTEEN, [90] * 2, 0),
+    (SIXTEEN, [150] * 2, 66), (SIXTEEN, [90] * 3, 66), (SIXTEEN, [24] * 11, 46), (SIXTEEN, [90] * 11, 0),
+    (SIXTYFOUR, [90], 0), (SIXTYFOUR, [24] * 6, 0), (SIXTYFOUR, [300] * 6, 0), (SIXTYFOUR, [150] * 12, 0),
+    (SIXTYFOUR, [150] * 20, 0), (SIXTYFOUR, [90] * 24, 10), (SIXTYFOUR, [28] * 64, 8),
+    ((2048, 8192, 16), [150] * 2, 0), ((2048, 8192, 16), [150] * 4, 64),
+    ((2048, 1792, 32), [150] * 8, 0), ((2048, 1792, 32), [150] * 16, 16),
+    ((4096, 1408, 64), [90] * 24, 10), ((4096, 1408, 64), [90] * 47, 0), ((4096, 1408, 64), [40] * 44, 0)]
+
+
+@pytest.mark.parametrize("shape,rows,want", FEW)
+def test_first_projection_of_few_experts(shape, rows, want):
+    d, f, E = shape
+    counts = rows + [0] * (E - len(rows))
+    own = (128, 512) if f % 256 == 0 else (256, 256)
+    got = gg_schedule.launched(counts, d, f, True, *own)
+    assert got.both and got.small == want
+    assert got.fixup or not got.pieces
+    # what the launch's own tiles are cut into needs the fix-up, whatever is known of the experts in use
+    told = gg_schedule.launched(counts, d, f, True, *own, least=len(rows))
+    assert told.small == want and (told.pieces == got.pieces or (own[0] == 256 and d // 32 == 64))
+
+
+@pytest.mark.parametrize("d,f,E", [MIXTRAL, SIXTEEN, SIXTYFOUR, (2048, 1792, 32), (4096, 1408, 64)])
+@pytest.mark.parametrize("least", [1, 2, 6])
+def test_no_fixup_no_verdict_for_it(d, f, E, least):
+    """Where no fix-up is launched, no number of token tiles is one that the rule would rather cut."""
+    L, KS, FR, wgs = gg_schedule.lib(), d // 32, f // 8, 32
+    wide = f % 256 == 0
+    rows, NT, split = (128, FR // 32, L.split_limit(1, KS, wgs)) if wide else (256, FR // 16, L.split_limit(1, KS, wgs))
+    launched = set()
+    for N in list(range(73, 400, 9)) + list(range(400, 96 * E, 97)):
+        may = bool(L.up_may_cut(N, E, least, rows, NT, FR, KS, wgs, int(not wide)))
+        launched.add(may)
+        if may:
+            continue
+        for n in range(max(least, -(-N // 160)), E + N // 160 + 1):
+            assert not L.up_cut(N, n, FR // 4, wgs, KS, split), (N, n)
+        assert wide or KS == 64
+        assert not wide or least * FR * KS > 128 << 10 or (256 - max(least, -(-N // 128)) * NT) * KS < 256 * 44
+    assert True in launched
