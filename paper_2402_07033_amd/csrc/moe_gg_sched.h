@@ -120,8 +120,12 @@ GG_FN bool gg_up_cut(int N, int n_tok, int groups, int wgs, int KS, int split) {
 // the experts in use and the launch's tiles are one round: two tiles of 5 blocks end before one of 10 does.  64 steps, own -> 160 rows: 2 x
 // 150 rows of f = 8192 (134 MB) 47 -> 57, 4 x 150 (268 MB) 73 -> 66; 4, 8, 10 x 150 of f = 1792 (59, 117, 147 MB) 36, 44, 45 -> 51, 53,
 // 54, 16 (235 MB) 69 -> 64; 128 steps, 1 x 150 of f = 6400 (105 MB) 42 -> 89.
+// Reductions too short to cut, whatever the size of the matrices: 44 steps, 64 experts in the layer, own -> 160 rows: 12 x 150 rows 36 -> 43,
+// 28 x 150 42 -> 53, 30 x 150 49 -> 54, 32 x 150 58 -> 56; 4 x 150 and 30 x 20 44 -> 54; 160 and 60 x 30 63 -> 75; in two rounds, 40 x
+// 130 89 -> 70.
 GG_FN int gg_small_tiles(bool up, int N, int E, int active, int n_tok, int own_tok, int own_NT, int FR, int wgs, int KS, int split,
                          bool only_wide) {
+    if (KS < GG_SPLIT_KS && own_tok > n_tok && own_tok * own_NT <= wgs * 8) return 0;
     if (!up || N > GG_WIDE_MAX_ROWS * E) return gg_flex(N, n_tok, FR / 4, wgs, KS, split, only_wide);
     const int NT = gg_flex_fill(n_tok, FR / 4, wgs);
     if (only_wide && FR / 4 <= 4 * NT) return 0;

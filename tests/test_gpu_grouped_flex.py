@@ -10,11 +10,12 @@ EDGE = [160, 129, 1, 96, 65, 33, 16, 128]   # every copy of the step loop: 1..4,
 CASES = {
     # rows per expert, d, f, then per projection: feature tiles of an expert (0: the launch's own tiles)
     "128 x 512 launch, better cut": (EDGE, 2048, 2048, 0, 0),
-    "128 x 512 launch, narrowed": (EDGE * 4, 2048, 1280, 8, 8),
+    "128 x 512 launch, narrowed": (EDGE * 4, 2048, 1280, 8, 0),
+    "128 x 512 launch, narrowed, one tile each": ([128, 97, 1, 96, 65, 33, 16, 17] * 4, 2048, 1280, 8, 8),
     "128 x 512 launch, two rounds": (EDGE * 8, 2048, 1536, 8, 4),
-    "128 x 512 launch, reductions too short to cut": (EDGE * 8, 1024, 1024, 4, 4),
+    "128 x 512 launch, reductions too short to cut": (EDGE * 8, 1024, 1024, 4, 0),
     "128 x 512 launch, small matrices": (EDGE * 4, 512, 1024, 0, 0),
-    "128 x 512 launch, empty experts": ([0, 160, 0, 0, 17, 0, 1, 0] * 8, 2048, 1280, 10, 10),
+    "128 x 512 launch, empty experts": ([0, 160, 0, 0, 17, 0, 1, 0] * 8, 2048, 1280, 10, 0),
     "192 x 256 launch, narrowed": ([160, 120, 130, 97] * 8, 2048, 1280, 8, 0),
     "192 x 256 launch, full": ([160, 120, 130, 97] * 8, 2048, 2048, 8, 0),
     "192 x 256 launch, second projection": ([160, 120, 130, 97] * 12, 2048, 1280, 5, 5),
@@ -22,7 +23,7 @@ CASES = {
     "256 x 256 launch, 11 half tiles": ([28, 30, 160, 1] * 16, 2048, 1408, 8, 4),
     "256 x 256 launch, second projection": ([28, 30, 160, 1] * 12, 2304, 1280, 5, 5),
     "128 x 512 launch, experts of several tiles": ([161, 320, 16, 17, 90, 0, 0, 100] * 3, 2048, 2560, 10, 10),
-    "128 x 512 launch, 64 experts, skewed": ([480, 170, 40, 20, 9, 3, 1, 0] * 8, 1024, 1536, 6, 3),
+    "128 x 512 launch, 64 experts, skewed": ([480, 170, 40, 20, 9, 3, 1, 0] * 8, 1024, 1536, 6, 0),
     "161 rows": ([161, 120, 130, 97] * 8, 2048, 1280, 0, 0),
 }
 

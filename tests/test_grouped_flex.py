@@ -145,3 +145,14 @@ def test_no_fixup_no_verdict_for_it(d, f, E, least):
         assert wide or KS == 64
         assert not wide or least * FR * KS > 128 << 10 or (256 - max(least, -(-N // 128)) * NT) * KS < 256 * 44
     assert True in launched
+
+
+@pytest.mark.parametrize("rows,want", [
+    # 64 experts of f = 1408, second projection (44 steps): one round of the launch's own tiles, of which 150 rows are
+    # two that end before one of 160 rows does; two rounds; no expert with more of them
+    ([150] * 12, 0), ([150] * 28, 0), ([160] + [30] * 60, 0), ([150] * 4 + [20] * 30, 0), ([130] * 40, 6),
+    ([128] * 12, 10), ([90] * 24, 10)])
+def test_second_projection_too_short_to_cut(rows, want):
+    d, f, E = SIXTYFOUR
+    got = gg_schedule.launched(rows + [0] * (E - len(rows)), d, f, False, 128, 512)
+    assert got.both and got.small == want and not got.fixup
