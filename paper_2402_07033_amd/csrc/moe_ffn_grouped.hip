@@ -169,14 +169,13 @@ __device__ __forceinline__ int gg_seg_table(const GroupedArgs& a, int wgs, int l
     const int nb = (rows + 15) / 16;
     small = 0;
     if (SMALL && (FRW == 8 || (UP && a.N <= GG_WIDE_MAX_ROWS * a.E) || __ballot(nb > GG_SMALL_BLOCKS) == 0ull)) {
-        int t = (nb + GG_SMALL_BLOCKS - 1) / GG_SMALL_BLOCKS, own = (nb + NBW - 1) / NBW;
+        // token tiles of 160 rows, and of the launch's own in the upper half (few: gg_small_expected)
+        int t = (nb + GG_SMALL_BLOCKS - 1) / GG_SMALL_BLOCKS + ((nb + NBW - 1) / NBW << 16);
 #pragma unroll
-        for (int dlt = 1; dlt < 64; dlt <<= 1) {
-            t += __shfl_xor(t, dlt, 64);
-            own += __shfl_xor(own, dlt, 64);
-        }
-        small = __builtin_amdgcn_readfirstlane(gg_small_tiles(UP, a.N, a.E, __popcll(__ballot(nb > 0)), t, own, a.NT, a.FR, wgs,
-                                                              a.KS, a.split, FRW == 4));
+        for (int dlt = 1; dlt < 64; dlt <<= 1) t += __shfl_xor(t, dlt, 64);
+        t = __builtin_amdgcn_readfirstlane(t);
+        small = __builtin_amdgcn_readfirstlane(gg_small_tiles(UP, a.N, a.E, __popcll(__ballot(nb > 0)), t & 0xffff, t >> 16, a.NT,
+                                                              a.FR, wgs, a.KS, a.split, FRW == 4));
     }
     const int tile_blocks = small ? GG_SMALL_BLOCKS : NBW;
     const int tiles = (nb + tile_blocks - 1) / tile_blocks;

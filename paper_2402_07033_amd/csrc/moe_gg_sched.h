@@ -97,7 +97,7 @@ GG_FN int gg_flex(int N, int n_tok, int groups, int wgs, int KS, int split, bool
     return only_wide && groups <= 4 * NT ? 0 : NT;
 }
 // The same for the first projection up to GG_WIDE_MAX_ROWS rows per expert, where experts of more than 160 rows do not rule
-// these tiles out: always, but for a few cases, all of few experts in use.  only_wide: the launch's own tiles, if these are as wide.
+// these tiles out: always, but for a few cases, most of them of few experts in use.
 // Where the tiles leave 48 steps' worth of the one round idle, cutting is better: a step takes 0.47 us however narrow its tile
 // is.  GEMM, narrowed -> cut, fix-up and 1.2 us between them included, 128 steps: 1 expert of f = 6400, 16..128 rows, 60..76 -> 39..50
 // us, 2 of them 66 -> 51, 73 -> 63, 80 -> 66 (62 idle), 3 68 -> 71, 79 -> 93 (29 idle); 1 of f = 14336 66 -> 53, 74 -> 67 (53
@@ -115,6 +115,9 @@ GG_FN bool gg_up_cut(int N, int n_tok, int groups, int wgs, int KS, int split) {
 }
 // Feature tiles per expert of the tiles of up to 160 rows, 0: the launch's own.  `active` experts with rows, in n_tok token tiles of 160
 // rows or own_tok of the launch's, which have own_NT feature tiles per expert.
+// only_wide (own tiles of 256 features): only for fewer rounds.  64 experts of f = 1408, own -> 160 rows, both one round 12 x 90 rows 40 ->
+// 44 us, 20 x 90 49 -> 51, 6 x 300 36 -> 54; both two, 200 tokens, Zipf 1.2, 98 -> 100..102, 44 x 40 92 -> 97; two and one 24 x 90 69 + 5 -> 61,
+// 36 x 90 89 + 5 -> 81; three and two 64 x 28 128 + 5 -> 121.
 // Where an expert has more of the launch's token tiles than of these, these are ahead whatever is idle (cut -> narrowed, 128 steps: 1
 // x 160 rows of f = 14336 112 -> 92, 5 x 150 303 -> 264, 2 x 150 of f = 6400 106 -> 91) unless the last-level cache keeps the matrices of
 // the experts in use and the launch's tiles are one round: two tiles of 5 blocks end before one of 10 does.  64 steps, own -> 160 rows: 2 x
@@ -128,9 +131,10 @@ GG_FN int gg_small_tiles(bool up, int N, int E, int active, int n_tok, int own_t
     if (KS < GG_SPLIT_KS && own_tok > n_tok && own_tok * own_NT <= wgs * 8) return 0;
     if (!up || N > GG_WIDE_MAX_ROWS * E) return gg_flex(N, n_tok, FR / 4, wgs, KS, split, only_wide);
     const int NT = gg_flex_fill(n_tok, FR / 4, wgs);
-    if (only_wide && FR / 4 <= 4 * NT) return 0;
+    const int W = wgs * 8;
+    if (only_wide && (own_tok * own_NT + W - 1) / W <= (n_tok * NT + W - 1) / W) return 0;
     if (own_tok > n_tok)
-        return own_tok * own_NT <= wgs * 8 && (long long)active * FR * KS <= GG_SMALL_MIN_FRAGS ? 0 : NT;
+        return own_tok * own_NT <= W && (long long)active * FR * KS <= GG_SMALL_MIN_FRAGS ? 0 : NT;
     return gg_up_cut(N, n_tok, FR / 4, wgs, KS, split) ? 0 : NT;
 }
 // HOST: is the projection run with the kernel that holds the tiles of 160 rows, too?  If they are to be expected with all experts in
@@ -150,9 +154,11 @@ GG_FN bool gg_small_expected(bool up, bool own_wide, int N, int E, int FR, int K
 }
 // HOST: may such a first projection have pieces?  If not, its tiles are all left whole and no fix-up is launched (4.6 us where
 // there is nothing to add).  least: experts in use, at least.  Cutting the launch's own tiles has to save GG_FIXUP_MIN_STEPS: 64 steps,
-// tiles of 256 x 256, whole -> cut with fix-up: 1..4 experts of f = 1408 with 20..150 rows 25..35 -> 22..28 us, 6 x 24 28 -> 26, 6 x 60 30
-// -> 30, 6 x 200 46 -> 39 (47 steps saved at most), 8 x 100 35 -> 36, 8 x 225 47 -> 45 (42), 10 x 180 45 -> 49; longer ones always.
-#define GG_FIXUP_MIN_STEPS 44
+// tiles of 256 x 256, whole -> cut with fix-up: 1..4 experts of f = 1408 with 20..150 rows 25..35 -> 22..28 us; 47 steps saved at most, 6
+// x 24 28 -> 26, 6 x 60 30 -> 30, 6 x 120 36 -> 34, 6 x 200 46 -> 39: not worth 4.6 us of every call with six experts per token (150
+// of them); 8 x 100 35 -> 36, 8 x 225 47 -> 45, 10 x 180 45 -> 49.  Longer reductions always: 128 steps, 1 x 80 53 -> 26, 6 x 24 54 -> 39,
+// 6 x 90 63 -> 49, 26 x 40 148 -> 125.
+#define GG_FIXUP_MIN_STEPS 48
 GG_FN bool gg_up_may_cut(int N, int E, int least, int own_rows, int own_NT, int FR, int KS, int wgs, bool only_wide) {
     const int W = wgs * 8, split = gg_split_limit(true, KS, wgs);
     const int own = (N + own_rows - 1) / own_rows, tok = (N + GG_SMALL_ROWS - 1) / GG_SMALL_ROWS;

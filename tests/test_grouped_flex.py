@@ -127,6 +127,15 @@ def test_first_projection_of_few_experts(shape, rows, want):
     assert told.small == want and (told.pieces == got.pieces or (own[0] == 256 and d // 32 == 64))
 
 
+def test_first_projection_in_as_many_rounds_of_its_own_tiles():
+    # 200 tokens on 64 experts, Zipf 1.2: 46 tiles of 256 rows x 11 fill two rounds, as 48 of 160 x 10 would
+    rows = [194, 169, 147, 108, 95, 81, 50, 49, 45, 32, 34, 21, 21, 16, 14, 9, 14, 10, 13, 6, 5, 6, 6, 6, 2, 5, 6, 6, 4, 4,
+            2, 5, 1, 2, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1]
+    d, f, E = SIXTYFOUR
+    assert gg_schedule.launched(rows + [0] * (E - len(rows)), d, f, True, 256, 256).small == 0
+    assert gg_schedule.launched(rows + [1] * 6 + [0] * 12, d, f, True, 256, 256).small == 9  # three rounds
+
+
 @pytest.mark.parametrize("d,f,E", [MIXTRAL, SIXTEEN, SIXTYFOUR, (2048, 1792, 32), (4096, 1408, 64)])
 @pytest.mark.parametrize("least", [1, 2, 6])
 def test_no_fixup_no_verdict_for_it(d, f, E, least):
@@ -142,9 +151,9 @@ def test_no_fixup_no_verdict_for_it(d, f, E, least):
             continue
         for n in range(max(least, -(-N // 160)), E + N // 160 + 1):
             assert not L.up_cut(N, n, FR // 4, wgs, KS, split), (N, n)
-        assert wide or KS == 64
-        assert not wide or least * FR * KS > 128 << 10 or (256 - max(least, -(-N // 128)) * NT) * KS < 256 * 44
-    assert True in launched
+        assert wide or (KS == 64 and (256 - max(least, -(-N // 256)) * NT) * KS < 256 * 48)
+        assert not wide or least * FR * KS > 128 << 10 or (256 - max(least, -(-N // 128)) * NT) * KS < 256 * 48
+    assert (True in launched) == (wide or KS > 64 or least < 6)
 
 
 @pytest.mark.parametrize("rows,want", [
