@@ -276,14 +276,16 @@ def cpu_baseline(torch, wl, host_w, xs, lgs, budget_s=15.0):
 PATH_NAMES = {0: "fp32", 1: "stream", 2: "grouped", 3: "mid"}
 
 
-def kernel_label(moe, T, forced_path):
-    """Name of the first-projection kernel that runs for T tokens, from the library's plan."""
+def kernel_label(moe, T, forced_path, counts):
+    """Name of the first-projection kernel that runs for T tokens, from the library's plan, and its
+    tiles for `counts` rows per expert."""
     pl = moe.moe_expert_ffn_plan(T * K, E, D, F, moe.MOE_BF16, forced_path)
     fam = PATH_NAMES.get(pl["path"], str(pl["path"]))
     if fam == "stream":
         return "stream_kernel, first projection (x.w1, x.w3, silu*mul)", pl
-    return (f"gg_pack + gg_gemm_kernel<UP> {pl['up_tile_rows']}x{pl['up_tile_features']} tile "
-            "+ fix-up (x.w1, x.w3, silu*mul)"), pl
+    t = moe.moe_expert_ffn_tiles(counts, D, F, pl["path"], K)["up"]
+    return (f"gg_pack + gg_gemm_kernel<UP> {t['rows']}x{t['features']} tile "
+            f"{'+ fix-up ' if t['fixup'] else ''}(x.w1, x.w3, silu*mul)"), pl
 
 
 def run_layer_workload(torch, moe, name, wl, sets, args, steps, warmup, host_w=None):
@@ -346,7 +348,7 @@ def run_layer_workload(torch, moe, name, wl, sets, args, steps, warmup, host_w=N
     # algorithmic work of the dominant kernel (first projection), averaged over the steps
     act_sets = [sum(1 for c in counts_all[i % n_inputs] if c > 0) for i in range(steps)]
     n_active = sum(act_sets) / steps
-    label, plan = kernel_label(moe, T, step.ffn_path)
+    label, plan = kernel_label(moe, T, step.ffn_path, counts_all[0])
     if step.one_call:
         label = "gating + " + label
     traffic = traffic_from_profile(name) if args.tokens is None and args.ffn_path == "auto" else None
@@ -458,7 +460,8 @@ def run_stack_workload(torch, moe, name, wl, layers, args, steps, warmup, host_w
     all_bytes = n_active * 3 * D * F * 2
     whole_gbs = all_bytes / (ms_per_step * 1e-3) / 1e9
     whole_tf = T * K * 6 * D * F * L / (ms_per_step * 1e-3) / 1e12
-    label, plan = kernel_label(moe, T, moe.MOE_FFN_AUTO)
+    first = idx_out[0].cpu().flatten().tolist()
+    label, plan = kernel_label(moe, T, moe.MOE_FFN_AUTO, [first.count(e) for e in range(E)])
     if moe.moe_decode_block_supported(T, E, K, D, F):
         label = "RMSNorm scale + router logits + gating + " + label   # moe_decode_block's first kernel
     roofline = dict(bound="hbm", achieved=achieved, peak=HBM_PEAK_GBS, unit="GB/s",

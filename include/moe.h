@@ -174,11 +174,11 @@ size_t moe_expert_ffn_noalloc_max_bytes(void);
  *            one kernel pair of their own)
  *   n_parts  reduction parts of the second projection that moe_expert_ffn_parts leaves
  *            unsummed (1 unless STREAM)
- *   up_* / down_*  GROUPED, MID: token rows x output features of the workgroup tile of the
- *            first / second projection (0 otherwise).  The first projection's features
- *            count w1 and w3 columns together.  Up to 96 rows per expert on average, and above
- *            where the offsets show that no expert has more than 160 rows, the kernel may take
- *            tiles of 160 rows x 64..512 features instead.
+ *   up_* / down_*  GROUPED, MID: token rows x output features of the launch's workgroup tile
+ *            of the first / second projection (0 otherwise).  The first projection's features
+ *            count w1 and w3 columns together.  By the rows per expert, which only the device
+ *            knows, the kernel may take tiles of 160 rows x 192..512 features instead:
+ *            moe_expert_ffn_tiles says when.
  * Returns MOE_ERR_UNSUPPORTED if a forced family cannot run the shape.
  */
 typedef struct {
@@ -189,6 +189,23 @@ typedef struct {
 } moe_ffn_plan_t;
 int moe_expert_ffn_plan(int N, int E, int d, int f, moe_dtype_t w_dtype, int path,
                         moe_ffn_plan_t* plan);
+
+/*
+ * The workgroup tiles that GROUPED and MID run for these rows per expert (HOST query, by the
+ * same functions as the kernels; nothing is launched).  bf16 weights.
+ *   counts [E] HOST, rows per expert;  path  as moe_expert_ffn_path
+ *   k        experts of a token, as moe_expert_ffn_tokens and moe_layer are told; 1 for the others
+ *   up, down HOST out; all zero where the STREAM family runs
+ */
+typedef struct {
+    int rows, features;  /* of a tile, at most; the first projection's features as in the plan */
+    int feature_tiles;   /* per expert */
+    int tiles;           /* of the launch */
+    int pieces;          /* 1: tiles of the last round are cut along the reduction */
+    int fixup;           /* 1: the kernel that adds such pieces is launched */
+} moe_ffn_tiles_t;
+int moe_expert_ffn_tiles(const int32_t* counts, int E, int d, int f, int path, int k, moe_ffn_tiles_t* up,
+                         moe_ffn_tiles_t* down);
 
 /*
  * moe_expert_ffn for a consumer that adds the second projection's reduction parts itself

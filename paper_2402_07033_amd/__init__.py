@@ -12,7 +12,8 @@ from .binding import (ORCH_CPU, ORCH_GPU_RESIDENT, ORCH_GPU_TRANSFER, ORCH_SKIP,
                       moe_combine, moe_combine_norm_route_permute, moe_combine_parts,
                       moe_combine_residual, moe_decode_block, moe_decode_block_supported, moe_decode_layer, moe_expert_ffn,
                       moe_expert_ffn_noalloc, moe_expert_ffn_noalloc_max_bytes,
-                      moe_expert_ffn_parts, moe_expert_ffn_plan, moe_expert_ffn_tokens, moe_expert_ffn_workspace,
+                      moe_expert_ffn_parts, moe_expert_ffn_plan, moe_expert_ffn_tiles, moe_expert_ffn_tokens,
+                      moe_expert_ffn_workspace,
                       moe_hbm_read_probe, moe_layer, moe_mfma_rate_probe,
                       moe_norm_route_permute, moe_permute, moe_residual_add, moe_rmsnorm,
                       moe_gate_sums, moe_gate_sums_stride, moe_rmsnorm_router_logits, moe_route, moe_route_permute,
@@ -27,6 +28,7 @@ __all__ = [
     "moe_combine_norm_route_permute", "moe_combine_parts", "moe_combine_residual",
     "moe_decode_block", "moe_decode_block_supported", "moe_decode_layer", "moe_expert_ffn", "moe_expert_ffn_noalloc",
     "moe_expert_ffn_noalloc_max_bytes", "moe_expert_ffn_parts", "moe_expert_ffn_tokens", "moe_expert_ffn_plan",
+    "moe_expert_ffn_tiles",
     "moe_expert_ffn_workspace", "moe_hbm_read_probe", "moe_layer", "moe_mfma_rate_probe",
     "moe_norm_route_permute", "moe_permute", "moe_residual_add", "moe_rmsnorm",
     "moe_gate_sums", "moe_gate_sums_stride", "moe_rmsnorm_router_logits", "moe_route", "moe_route_permute", "moe_router_logits",

@@ -19,7 +19,7 @@ _lib = None
 # entry points of include/moe.h and of include/moe_probe.h
 EXPORTS = ("moe_status_string", "moe_route", "moe_permute", "moe_layer", "moe_weights_pack",
            "moe_weights_free", "moe_weights_bytes", "moe_expert_ffn_workspace",
-           "moe_expert_ffn", "moe_expert_ffn_path", "moe_expert_ffn_plan",
+           "moe_expert_ffn", "moe_expert_ffn_path", "moe_expert_ffn_plan", "moe_expert_ffn_tiles",
            "moe_expert_ffn_parts", "moe_expert_ffn_tokens", "moe_expert_ffn_noalloc", "moe_expert_ffn_noalloc_max_bytes",
            "moe_combine", "moe_combine_parts", "moe_decode_layer", "moe_decode_block",
            "moe_rmsnorm", "moe_router_logits", "moe_residual_add", "moe_route_permute",
@@ -44,6 +44,11 @@ class FfnPlan(C.Structure):
     _fields_ = [("path", C.c_int), ("n_parts", C.c_int),
                 ("up_tile_rows", C.c_int), ("up_tile_features", C.c_int),
                 ("down_tile_rows", C.c_int), ("down_tile_features", C.c_int)]
+
+
+class FfnTiles(C.Structure):
+    """moe_ffn_tiles_t."""
+    _fields_ = [(n, C.c_int) for n in ("rows", "features", "feature_tiles", "tiles", "pieces", "fixup")]
 
 
 class MoeError(RuntimeError):
@@ -110,6 +115,8 @@ def lib():
         L.moe_expert_ffn_noalloc_max_bytes.restype = C.c_size_t
         L.moe_expert_ffn_plan.argtypes = [i32] * 6 + [C.POINTER(FfnPlan)]
         L.moe_expert_ffn_plan.restype = C.c_int
+        L.moe_expert_ffn_tiles.argtypes = [vp] + [i32] * 5 + [C.POINTER(FfnTiles)] * 2
+        L.moe_expert_ffn_tiles.restype = C.c_int
         L.moe_expert_ffn_parts.argtypes = [vp, vp, i32, vp, i32, vp, C.c_size_t, vp, i32,
                                            C.POINTER(C.c_int), vp]
         L.moe_expert_ffn_parts.restype = C.c_int
@@ -302,6 +309,15 @@ def moe_expert_ffn_plan(N: int, E: int, d: int, f: int, w_dtype: int = MOE_BF16,
     pl = FfnPlan()
     _check(lib().moe_expert_ffn_plan(N, E, d, f, w_dtype, path, C.byref(pl)), "moe_expert_ffn_plan")
     return {n: getattr(pl, n) for n, _ in FfnPlan._fields_}
+
+
+def moe_expert_ffn_tiles(counts, d: int, f: int, path: int = MOE_FFN_AUTO, k: int = 1) -> dict:
+    """The workgroup tiles of both projections that GROUPED and MID run for these rows per expert
+    (host query; counts: a sequence of E ints; k: experts of a token where the call is told)."""
+    up, down = FfnTiles(), FfnTiles()
+    _check(lib().moe_expert_ffn_tiles((C.c_int32 * len(counts))(*counts), len(counts), d, f, path, k, C.byref(up),
+                                      C.byref(down)), "moe_expert_ffn_tiles")
+    return {side: {n: getattr(t, n) for n, _ in FfnTiles._fields_} for side, t in (("up", up), ("down", down))}
 
 
 def moe_expert_ffn_parts(W: "PackedWeights", xg: torch.Tensor, offsets: torch.Tensor, yg_parts,

@@ -212,6 +212,21 @@ int moe_expert_ffn(const moe_weights_t* W, const void* xg, moe_dtype_t act_dtype
                                MOE_FFN_AUTO, stream);
 }
 
+int moe_expert_ffn_tiles(const int32_t* counts, int E, int d, int f, int path, int k, moe_ffn_tiles_t* up,
+                         moe_ffn_tiles_t* down) {
+    if (!counts || !up || !down || E < 1 || E > MOE_MAX_E || k < 1 || k > MOE_MAX_K || !dims_ok(d) || !dims_ok(f))
+        return MOE_ERR_INVALID_ARG;
+    long long N = 0;
+    for (int e = 0; e < E; e++) {
+        if (counts[e] < 0 || (N += counts[e]) >= MOE_MAX_N) return MOE_ERR_INVALID_ARG;
+    }
+    if (path == MOE_FFN_AUTO) path = moe_ffn_auto_path((int)N, E, d, f);
+    if (path != MOE_FFN_STREAM && path != MOE_FFN_GROUPED && path != MOE_FFN_MID) return MOE_ERR_INVALID_ARG;
+    *up = *down = moe_ffn_tiles_t{};
+    if (path == MOE_FFN_STREAM) return moe_ffn_stream_supported(d, f) ? MOE_OK : MOE_ERR_UNSUPPORTED;
+    return moe_ffn_grouped_tiles(path == MOE_FFN_MID, counts, (int)N, E, d, f, k, up, down);
+}
+
 int moe_expert_ffn_plan(int N, int E, int d, int f, moe_dtype_t w_dtype, int path,
                         moe_ffn_plan_t* plan) {
     if (!plan || N < 0 || N >= MOE_MAX_N || E < 1 || E > MOE_MAX_E || !dims_ok(d) || !dims_ok(f))

@@ -118,11 +118,10 @@ struct GroupedArgs {
     int E, N;
     int KS;      // reduction steps of 32
     int FR;      // weight fragment rows per expert (up: 2*f/16, down: d/16)
-    int FROWS;   // weight fragment rows per tile: 16 or 32
-    int NT;      // workgroup tiles along the features = FR / FROWS
+    int NT;      // the launch's own tiles along the features
     int KS_out;  // up: f/32 (fragment columns of hp); down: unused
     int C;       // down: d (row length of yg)
-    int split;   // gg_split_limit
+    int split;   // gg_split_limit, or 0: nothing is cut
     float* part; // split: partial tiles [8 XCDs][workgroups per XCD][2][256*256] fp32
 };
 
@@ -168,7 +167,7 @@ __device__ __forceinline__ int gg_seg_table(const GroupedArgs& a, int wgs, int l
     gg_segment_of_lane(a.offsets, a.E, a.N, lane, lo, rows);
     const int nb = (rows + 15) / 16;
     small = 0;
-    if (SMALL && (FRW == 8 || (UP && a.N <= GG_WIDE_MAX_ROWS * a.E) || __ballot(nb > GG_SMALL_BLOCKS) == 0ull)) {
+    if (SMALL && gg_small_allowed(UP, FRW == 8, a.N, a.E, __ballot(nb > GG_SMALL_BLOCKS) != 0ull)) {
         // token tiles of 160 rows, and of the launch's own in the upper half (few: gg_small_expected)
         int t = (nb + GG_SMALL_BLOCKS - 1) / GG_SMALL_BLOCKS + ((nb + NBW - 1) / NBW << 16);
 #pragma unroll
@@ -937,19 +936,11 @@ const void* gg_kernel_ptr(GgVariant v) {
     }
 }
 
-// One projection: the persistent GEMM and the fix-up of the pieces.  least: experts in use, at least (of a different number
-// than that, only the time depends on it).
+// One projection: the persistent GEMM and the fix-up of the pieces.
 template <bool UP>
-int gg_launch_projection(GroupedArgs& a, GgVariant v, int least, unsigned pgrid, hipStream_t s) {
+int gg_launch_projection(GroupedArgs& a, GgVariant v, unsigned pgrid, hipStream_t s) {
     const GgShape sh = gg_shape(v);
-    a.FROWS = sh.frows;
-    if (a.FR % a.FROWS != 0) return MOE_ERR_UNSUPPORTED;
-    a.NT = a.FR / a.FROWS;
     const int wgs = (int)(pgrid / 8);
-    a.split = gg_split_limit(UP, a.KS, wgs);
-    if (UP && (v == GG_WIDE_S || v == GG_STD_S) &&
-        !gg_up_may_cut(a.N, a.E, least, 16 * sh.tb, a.NT, a.FR, a.KS, wgs, v == GG_STD_S))
-        a.split = 0;
     void* params[1] = {(void*)&a};
     const size_t lds_bytes = gg_lds_bytes(sh);
     MOE_HIP_TRY(hipLaunchKernel(gg_kernel_ptr<UP>(v), dim3(pgrid), dim3(GG_THREADS), params, lds_bytes, s));
@@ -973,10 +964,10 @@ int gg_launch_projection(GroupedArgs& a, GgVariant v, int least, unsigned pgrid,
 // The second projection's kernels are compiled in a file of their own, beside the first's (a minute and a half each).
 #ifdef GG_SECOND_PROJECTION
 template const void* gg_kernel_ptr<false>(GgVariant);
-template int gg_launch_projection<false>(GroupedArgs&, GgVariant, int, unsigned, hipStream_t);
+template int gg_launch_projection<false>(GroupedArgs&, GgVariant, unsigned, hipStream_t);
 #else
 extern template const void* gg_kernel_ptr<false>(GgVariant);
-extern template int gg_launch_projection<false>(GroupedArgs&, GgVariant, int, unsigned, hipStream_t);
+extern template int gg_launch_projection<false>(GroupedArgs&, GgVariant, unsigned, hipStream_t);
 
 static inline size_t gg_align256(size_t v) { return (v + 255) & ~(size_t)255; }
 static inline size_t gg_max_blocks(int N, int E) { return (size_t)N / 16 + E; }
@@ -1017,10 +1008,20 @@ static bool gg_fits(GgVariant v, int ks) {
     return ks % sh.u == 0 && ks >= sh.ns;
 }
 
-// The kernel that a projection of variant v is run with.
-static GgVariant gg_kernel_variant(GgVariant v, bool up, int N, int E, int KS, int FR) {
-    if (!gg_small_expected(up, v == GG_WIDE, N, E, FR, KS, (moe_num_cus() + 7) / 8)) return v;
-    return v == GG_WIDE ? GG_WIDE_S : v == GG_R192 ? GG_R192_S : GG_STD_S;
+// What a projection of variant v is launched with.
+struct GgProjection {
+    GgVariant v;  // with the tile of 160 rows, too, or not
+    int NT, split;
+};
+// least: experts in use, at least (if there are fewer all the same, only the time depends on it).
+static GgProjection gg_projection(GgVariant v, bool up, int N, int E, int FR, int KS, int least) {
+    const GgShape sh = gg_shape(v);
+    const int wgs = (moe_num_cus() + 7) / 8;
+    GgProjection p = {v, FR / sh.frows, gg_split_limit(up, KS, wgs)};
+    if (!gg_small_expected(up, v == GG_WIDE, N, E, FR, KS, wgs)) return p;
+    p.v = v == GG_WIDE ? GG_WIDE_S : v == GG_R192 ? GG_R192_S : GG_STD_S;
+    if (up && N <= GG_WIDE_MAX_ROWS * E && !gg_up_may_cut(N, E, least, 16 * sh.tb, p.NT, FR, KS, wgs, v != GG_WIDE)) p.split = 0;
+    return p;
 }
 
 // Variant of each projection by the mean number of rows per expert (the host never sees the
@@ -1068,6 +1069,46 @@ int moe_ffn_grouped_plan(bool mid, int N, int E, int d, int f, moe_ffn_plan_t* p
     return MOE_OK;
 }
 
+// The tiles of one projection for these rows per expert, by the functions that the kernels themselves go by.
+static moe_ffn_tiles_t gg_tiles(const GgProjection& p, bool up, const int32_t* counts, int N, int E, int FR, int KS) {
+    const GgShape sh = gg_shape(p.v);
+    const int wgs = (moe_num_cus() + 7) / 8;
+    const bool wide = sh.frows == 32;
+    int active = 0, small_tok = 0, own_tok = 0, most = 0, small = 0;
+    for (int e = 0; e < E; e++) {
+        active += counts[e] > 0;
+        small_tok += (counts[e] + GG_SMALL_ROWS - 1) / GG_SMALL_ROWS;
+        own_tok += (counts[e] + 16 * sh.tb - 1) / (16 * sh.tb);
+        most = counts[e] > most ? counts[e] : most;
+    }
+    if (p.v >= GG_STD_S && gg_small_allowed(up, wide, N, E, most > GG_SMALL_ROWS))
+        small = gg_small_tiles(up, N, E, active, small_tok, own_tok, p.NT, FR, wgs, KS, p.split, !wide);
+    moe_ffn_tiles_t t = {};
+    t.rows = small ? GG_SMALL_ROWS : 16 * sh.tb;
+    t.feature_tiles = small ? small : p.NT;
+    t.features = small ? (FR / 4 + small - 1) / small * 64 : 16 * sh.frows;
+    t.tiles = (small ? small_tok : own_tok) * t.feature_tiles;
+    t.pieces = !small && t.tiles % (8 * wgs) && gg_sched(t.tiles, wgs, 0, KS, p.split).split;
+    t.fixup = p.split != 0;
+    return t;
+}
+
+int moe_ffn_grouped_tiles(bool mid, const int32_t* counts, int N, int E, int d, int f, int k, moe_ffn_tiles_t* up,
+                          moe_ffn_tiles_t* down) {
+    GgVariant vu, vd;
+    bool short_down;
+    if (!gg_path_choose(mid, N, E, d, f, vu, vd, short_down)) return MOE_ERR_UNSUPPORTED;
+    const int fu = f / 8, fd = d / 16;  // fragment rows per expert
+    *up = gg_tiles(gg_projection(vu, true, N, E, fu, d / 32, k < E ? k : E), true, counts, N, E, fu, d / 32);
+    if (!short_down) {
+        *down = gg_tiles(gg_projection(vd, false, N, E, fd, f / 32, 0), false, counts, N, E, fd, f / 32);
+        return MOE_OK;
+    }
+    *down = {16, GG_SHORT_FEATURES, d / GG_SHORT_FEATURES, 0, 0, 0};
+    for (int e = 0; e < E; e++) down->tiles += (counts[e] + 15) / 16 * down->feature_tiles;
+    return MOE_OK;
+}
+
 static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype, const int32_t* perm,
                      int k, const int32_t* offsets, int N, void* ws, float* yg, GgVariant vu, GgVariant vd,
                      bool short_down, hipStream_t s) {
@@ -1103,8 +1144,7 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
     float* part = (float*)((unsigned char*)ws + gg_align256(nb * 16 * d * 2) +
                            gg_align256(nb * 16 * f * 2));
 
-    vu = gg_kernel_variant(vu, true, N, E, d / 32, f / 8);
-    if (!short_down) vd = gg_kernel_variant(vd, false, N, E, f / 32, d / 16);
+    const GgProjection pu = gg_projection(vu, true, N, E, f / 8, d / 32, k < E ? k : E);
 
     GroupedArgs up;
     up.wfrag = (const u32x4_t*)W->w13;
@@ -1114,10 +1154,12 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
     up.E = E; up.N = N;
     up.KS = d / 32;
     up.FR = 2 * (f / 16);
+    up.NT = pu.NT;
+    up.split = pu.split;
     up.KS_out = f / 32;
     up.C = 0;
     up.part = part;
-    int rc = gg_launch_projection<true>(up, vu, k < E ? k : E, pgrid, s);
+    int rc = gg_launch_projection<true>(up, pu.v, pgrid, s);
     if (rc != MOE_OK) return rc;
     moe_record_mid_event(s);
 
@@ -1136,7 +1178,10 @@ static int gg_launch(const moe_weights* W, const void* xg, moe_dtype_t act_dtype
         hipLaunchKernelGGL(gg_down_short_kernel, dim3((unsigned)nb, (unsigned)(d / GG_SHORT_FEATURES)), dim3(256), 0, s, dn);
         return moe_launch_status();
     }
-    rc = gg_launch_projection<false>(dn, vd, 0, pgrid, s);
+    const GgProjection pd = gg_projection(vd, false, N, E, d / 16, f / 32, 0);
+    dn.NT = pd.NT;
+    dn.split = pd.split;
+    rc = gg_launch_projection<false>(dn, pd.v, pgrid, s);
     if (rc != MOE_OK) return rc;
     return moe_launch_status();
 }

@@ -113,6 +113,10 @@ GG_FN bool gg_up_cut(int N, int n_tok, int groups, int wgs, int KS, int split) {
     if (slots == W) return (W - gg_flex_fill(n_tok, groups, wgs) * n_tok) * KS >= W * GG_FLEX_IDLE_STEPS;
     return (slots - total) * KS >= W * GG_FLEX_CUT_STEPS && N > GG_FLEX_CUT_ROWS * n_tok;
 }
+// Do the offsets allow tiles of 160 rows?  larger: an expert has more rows.
+GG_FN bool gg_small_allowed(bool up, bool own_wide, int N, int E, bool larger) {
+    return own_wide || (up && N <= GG_WIDE_MAX_ROWS * E) || !larger;
+}
 // Feature tiles per expert of the tiles of up to 160 rows, 0: the launch's own.  `active` experts with rows, in n_tok token tiles of 160
 // rows or own_tok of the launch's, which have own_NT feature tiles per expert.
 // only_wide (own tiles of 256 features): only for fewer rounds.  64 experts of f = 1408, own -> 160 rows, both one round 12 x 90 rows 40 ->

@@ -96,6 +96,8 @@ int moe_ffn_stream_block_launch(const moe_weights* W, const float* x_in, const f
 size_t moe_ffn_grouped_workspace(int N, int E, int d, int f);
 // GROUPED and MID are one GEMM with the same tiles; `mid` serves f = 128 as well, up to a number of rows.
 int moe_ffn_grouped_plan(bool mid, int N, int E, int d, int f, moe_ffn_plan_t* plan);  // fills the tile fields
+int moe_ffn_grouped_tiles(bool mid, const int32_t* counts, int N, int E, int d, int f, int k, moe_ffn_tiles_t* up,
+                          moe_ffn_tiles_t* down);
 int moe_ffn_grouped_launch(bool mid, const moe_weights* W, const void* xg, moe_dtype_t act_dtype,
                            const int32_t* perm, int k, const int32_t* offsets, int N, void* ws,
                            float* yg, hipStream_t s);

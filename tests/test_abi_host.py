@@ -205,6 +205,35 @@ def test_mid_serves_a_reduction_of_four_steps(L):
             m.moe_expert_ffn_plan(N, 8, 512, 128, path=path)
 
 
+def test_ffn_tiles_query(L):
+    """The tiles that run, where the plan names the launch's own."""
+    import paper_2402_07033_amd as m
+    tiles = lambda counts, *a, **kw: m.moe_expert_ffn_tiles(counts, *a, **kw)  # noqa: E731
+    plan = m.moe_expert_ffn_plan(1024, 8, 4096, 14336)
+    assert (plan["up_tile_rows"], plan["up_tile_features"]) == (192, 256)
+    # 512 tokens, balanced: tiles of 160 rows, 64 per expert fill two rounds; one row too many for them
+    t = tiles([128] * 8, 4096, 14336)
+    assert t["up"] == dict(rows=160, features=448, feature_tiles=64, tiles=512, pieces=0, fixup=1)
+    assert t["down"] == dict(rows=192, features=256, feature_tiles=16, tiles=128, pieces=1, fixup=1)
+    assert tiles([161] + [123] * 7, 4096, 14336)["up"] == dict(rows=192, features=256, feature_tiles=112, tiles=896,
+                                                              pieces=1, fixup=1)
+    # a short prompt, whose tokens have two experts each, and one of whose number of experts nothing is known
+    counts = [45, 30, 24, 18, 15, 10, 8, 4]
+    assert tiles(counts, 4096, 14336, k=2)["up"] == dict(rows=160, features=448, feature_tiles=64, tiles=512, pieces=0, fixup=0)
+    assert tiles(counts, 4096, 14336)["up"]["fixup"] == 1
+    # more rows: no other tiles; decode: none at all
+    assert tiles([1024] * 8, 4096, 14336)["up"]["rows"] == 256
+    assert tiles([9] * 8, 4096, 14336) == dict(up=dict.fromkeys(t["up"], 0), down=dict.fromkeys(t["up"], 0))
+    assert tiles([3, 0, 2], 512, 128, path=m.MOE_FFN_MID)["down"] == dict(rows=16, features=64, feature_tiles=8, tiles=16,
+                                                                         pieces=0, fixup=0)
+    for bad in (([1, -1], 512, 512), ([1 << 25, 1 << 25], 512, 512), ([1] * 65, 512, 512), ([], 512, 512), ([1], 100, 512)):
+        with pytest.raises(m.MoeError):
+            tiles(*bad)
+    for kw in (dict(k=0), dict(path=9), dict(path=m.MOE_FFN_GROUPED)):
+        with pytest.raises(m.MoeError):
+            tiles([100] * 8, 512, 128, **kw)
+
+
 def test_workspace_query(L):
     assert L.moe_expert_ffn_workspace(0, 8, 4096, 14336, 1) >= 256
     assert L.moe_expert_ffn_workspace(-1, 8, 4096, 14336, 1) == 0
