@@ -21,15 +21,6 @@ int turned(int ones, int total, int NT, int KS) { return gg_turned(ones, total, 
 int first_round(int turned, int n_full, int xcd) { return gg_first_round(turned != 0, n_full, xcd); }
 int round_slot(int n, int wgs, int xcd, int me) { return gg_round_slot(n, wgs, xcd, me); }
 int piece_cut(int j, int S, int KS, int wgs) { return gg_piece_cut(j, S, KS, wgs, GG_U, GG_NS); }
-int wide_max_rows() { return GG_WIDE_MAX_ROWS; }
-int small_rows() { return GG_SMALL_ROWS; }
-int small_expected(int up, int own_wide, int N, int E, int FR, int KS, int wgs) {
-    return gg_small_expected(up != 0, own_wide != 0, N, E, FR, KS, wgs);
-}
-int small_tiles(int up, int N, int E, int active, int n_tok, int own_tok, int own_NT, int FR, int wgs, int KS, int split,
-                int only_wide) {
-    return gg_small_tiles(up != 0, N, E, active, n_tok, own_tok, own_NT, FR, wgs, KS, split, only_wide != 0);
-}
 int up_cut(int N, int n_tok, int groups, int wgs, int KS, int split) { return gg_up_cut(N, n_tok, groups, wgs, KS, split); }
 int up_may_cut(int N, int E, int least, int own_rows, int own_NT, int FR, int KS, int wgs, int only_wide) {
     return gg_up_may_cut(N, E, least, own_rows, own_NT, FR, KS, wgs, only_wide != 0);
@@ -89,41 +80,6 @@ def branch(counts, tile_rows, tile_features, weight_rows, KS, up, cus=256):
     turned = any(L.first_round(L.turned(ones, total, NT, KS), n_full, x) for x in range(8))
     return Branch(n_full, left, bool(cut) and left > 0, turned,
                   {u for p in per if len(p) == 1 for u in p}, {u for p in per if len(p) > 1 for u in p})
-
-
-@dataclass
-class Launch:
-    """What one projection of a call launches and what the offsets make of it."""
-    both: bool       # the kernel holds tiles of 160 rows beside the launch's own
-    fixup: bool      # left-over tiles may be cut
-    small: int       # feature tiles of an expert, of 160 rows each; 0: the launch's own tiles
-    pieces: bool     # left-over tiles are cut
-
-
-def launched(counts, d, f, up, own_rows, own_features, least=1, cus=256):
-    """own_*: the launch's own tile, as the plan query names it; least: experts of a token."""
-    L, wgs, E, N = lib(), (cus + 7) // 8, len(counts), sum(counts)
-    KS, FR = (d // 32, f // 8) if up else (f // 32, d // 16)
-    wide, NT = own_features == 512, FR * 16 // own_features
-    up_few = up and N <= L.wide_max_rows() * E
-    both = bool(L.small_expected(int(up), int(wide), N, E, FR, KS, wgs))
-    split = L.split_limit(int(up), KS, wgs)
-    if both and up_few and not L.up_may_cut(N, E, least, own_rows, NT, FR, KS, wgs, int(not wide)):
-        split = 0
-    tiles = lambda rows: sum(-(-n // rows) for n in counts)  # noqa: E731
-    small = 0
-    if both and (wide or up_few or max(counts) <= L.small_rows()):
-        small = L.small_tiles(int(up), N, E, sum(n > 0 for n in counts), tiles(L.small_rows()), tiles(own_rows), NT, FR,
-                              wgs, KS, split, int(not wide))
-    total = tiles(own_rows) * NT
-    pieces = not small and total % (8 * wgs) and schedule_split(total, wgs, KS, split)
-    return Launch(both, split != 0, small, bool(pieces))
-
-
-def schedule_split(total, wgs, KS, split):
-    out = (C.c_int * 4)()
-    lib().sched(total, wgs, 0, KS, split, out)
-    return out[3]
 
 
 def dealt(total, KS, up, turned, wgs):

@@ -31,6 +31,21 @@ def pack_layer(li):
     return W
 
 
+class Scratch:
+    """A workspace of the grouped GEMM filled with a pattern: its area for the pieces of tiles shows whether the kernels
+    stored any, which they do in none of the whole tiles."""
+
+    def __init__(self, N, E, d, f):
+        import paper_2402_07033_amd as moe
+        align = lambda v: (v + 255) // 256 * 256  # noqa: E731
+        blocks = N // 16 + E  # 16-row blocks of either fragment buffer
+        self.ws = torch.full((moe.moe_expert_ffn_workspace(N, E, d, f, moe.MOE_BF16),), 0xA5, dtype=torch.uint8, device="cuda")
+        self.at = align(blocks * 16 * d * 2) + align(blocks * 16 * f * 2)
+
+    def pieces(self):
+        return bool((self.ws[self.at:] != 0xA5).any())
+
+
 def max_rel(gpu: np.ndarray, ref: np.ndarray) -> float:
     """max|gpu - ref| / max|ref| over the whole array."""
     ref = np.asarray(ref, dtype=np.float64)

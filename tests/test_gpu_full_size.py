@@ -8,7 +8,8 @@ every expert segment (so every workgroup tile, every piece of a tile whose
 reduction was split, and every fix-up block is covered) plus the first and last
 row of every segment -- the full fp64 layer at 4096 tokens is ~2.9 TFLOP of CPU
 work.  Which kernel family and tile shape ran is asserted through
-moe_expert_ffn_plan, so that a test cannot silently fall onto another kernel."""
+moe_expert_ffn_plan and, for the rows that the routing gave, moe_expert_ffn_tiles,
+so that a test cannot silently fall onto another kernel."""
 import numpy as np
 import pytest
 import torch
@@ -163,6 +164,12 @@ def _balanced_config(T, seed):
     return mi.MoEConfig(f"bal_t{T}", T, 4096, 14336, 8, 2, mi.BF16, mi.BF16, seed, 0.0, 1002)
 
 
+def _tiles(moe, cfg, out):
+    """Token rows and features of the workgroup tiles that ran, first and second projection."""
+    t = moe.moe_expert_ffn_tiles(to_host(out["counts"]).tolist(), cfg.d, cfg.f)
+    return tuple((t[side]["rows"], t[side]["features"]) for side in ("up", "down"))
+
+
 def _tiles_beyond_first(counts, tile_rows):
     tiles = sum((int(c) + tile_rows - 1) // tile_rows for c in counts)
     return tiles, tiles - sum(1 for c in counts if c > 0)
@@ -171,18 +178,17 @@ def _tiles_beyond_first(counts, tile_rows):
 # The tile shapes that the 32-layer stack at 512 tokens and the sweeps between decode and
 # prefill run, at the Mixtral shape, with balanced routing so that (nearly) every expert has a
 # single token tile, whose weights the kernel reads past L2.
-@pytest.mark.parametrize("T,tile_rows,tile_features", [(512, 192, 256), (256, 128, 512),
-                                                       (384, 128, 512)])
-def test_grouped_small_tiles_full_size(moe, mixtral, T, tile_rows, tile_features):
+@pytest.mark.parametrize("T,up,down", [(512, (160, 448), (192, 256)), (256, (160, 448), (128, 512)),
+                                       (384, (160, 448), (128, 512))])
+def test_grouped_small_tiles_full_size(moe, mixtral, T, up, down):
     cfg = _balanced_config(T, 1100 + T)
     x, logits, _ = mi.make_activations(cfg)
     pl = moe.moe_expert_ffn_plan(cfg.N, cfg.E, cfg.d, cfg.f)
     assert pl["path"] == moe.MOE_FFN_GROUPED
-    assert (pl["up_tile_rows"], pl["up_tile_features"]) == (tile_rows, tile_features)
-    assert (pl["down_tile_rows"], pl["down_tile_features"]) == (tile_rows, tile_features)
     out = _layer_with_nan_canary(moe, mixtral["W"], to_dev(x), to_dev(logits), cfg.k)
+    assert _tiles(moe, cfg, out) == (up, down)
     counts = to_host(out["counts"])
-    tiles, beyond = _tiles_beyond_first(counts, tile_rows)
+    tiles, beyond = _tiles_beyond_first(counts, down[0])
     assert beyond * 100 <= 15 * tiles, "routing does not give most experts a single tile"
     rows = _sample_rows(to_host(out["offsets"]), cfg.E)
     e_yg, counts, n_tok = _check_sampled(moe, mixtral, cfg, x, logits, out, rows)
@@ -196,9 +202,8 @@ def test_grouped_small_tile_with_weights_through_l2_full_size(moe, mixtral):
     stay in L2 (other copies of the step loop, beside those of the single tiles)."""
     cfg = mi.MoEConfig("zipf_t512", 512, 4096, 14336, 8, 2, mi.BF16, mi.BF16, 1177, 1.2, 1002)
     x, logits, _ = mi.make_activations(cfg)
-    pl = moe.moe_expert_ffn_plan(cfg.N, cfg.E, cfg.d, cfg.f)
-    assert (pl["path"], pl["up_tile_rows"]) == (moe.MOE_FFN_GROUPED, 192)
     out = _layer_with_nan_canary(moe, mixtral["W"], to_dev(x), to_dev(logits), cfg.k)
+    assert _tiles(moe, cfg, out) == ((192, 256), (192, 256))
     tiles, beyond = _tiles_beyond_first(to_host(out["counts"]), 192)
     assert beyond * 100 > 15 * tiles
     rows = _sample_rows(to_host(out["offsets"]), cfg.E)
@@ -213,8 +218,9 @@ def test_mid_kernel_full_size(moe, mixtral, T):
     cfg = mi.MoEConfig(f"mid_t{T}", T, 4096, 14336, 8, 2, mi.BF16, mi.F32, 1200 + T, 1.2, 1002)
     x, logits, _ = mi.make_activations(cfg)
     pl = moe.moe_expert_ffn_plan(cfg.N, cfg.E, cfg.d, cfg.f)
-    assert (pl["path"], pl["up_tile_rows"], pl["down_tile_rows"]) == (moe.MOE_FFN_MID, 128, 128)
+    assert pl["path"] == moe.MOE_FFN_MID
     out = _layer_with_nan_canary(moe, mixtral["W"], to_dev(x), to_dev(logits), cfg.k)
+    assert _tiles(moe, cfg, out) == ((160, 448), (128, 512))
     rows = np.arange(cfg.N)  # every row
     e_yg, counts, n_tok = _check_sampled(moe, mixtral, cfg, x, logits, out, rows)
     print(f"mid T={T}: counts={counts.tolist()} err={e_yg:.3e}")

@@ -2,7 +2,7 @@
 import pytest
 import torch
 
-import gg_schedule
+from gpu_util import Scratch
 
 pytestmark = pytest.mark.gpu
 
@@ -25,6 +25,7 @@ CASES = {
     "128 x 512 launch, experts of several tiles": ([161, 320, 16, 17, 90, 0, 0, 100] * 3, 2048, 2560, 10, 10),
     "128 x 512 launch, 64 experts, skewed": ([480, 170, 40, 20, 9, 3, 1, 0] * 8, 1024, 1536, 6, 0),
     "161 rows": ([161, 120, 130, 97] * 8, 2048, 1280, 0, 0),
+    "256 x 256 launch, second projection, 161 rows": ([28, 30, 161, 1] * 10, 2304, 2560, 10, 0),
 }
 
 
@@ -60,43 +61,29 @@ def worst_row(yg, xg, bounds, w1, w3, w2):
     return worst
 
 
-class Scratch:
-    """A workspace filled with a pattern, whose area for the pieces of tiles shows whether any were stored."""
-
-    def __init__(self, N, E, d, f):
-        import paper_2402_07033_amd as moe
-        align = lambda v: (v + 255) // 256 * 256  # noqa: E731
-        blocks = N // 16 + E  # 16-row blocks of either fragment buffer
-        self.ws = torch.full((moe.moe_expert_ffn_workspace(N, E, d, f, moe.MOE_BF16),), 0xA5, dtype=torch.uint8, device="cuda")
-        self.at = align(blocks * 16 * d * 2) + align(blocks * 16 * f * 2)
-
-    def pieces(self):
-        return bool((self.ws[self.at:] != 0xA5).any())
-
-
 @pytest.mark.parametrize("name", list(CASES))
 def test_small_experts(name):
     import paper_2402_07033_amd as moe
     counts, d, f, *want = CASES[name]
     E, N = len(counts), sum(counts)
-    plan = moe.moe_expert_ffn_plan(N, E, d, f, path=moe.MOE_FFN_GROUPED)
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    for side, w in zip(("up", "down"), want):
-        tile = plan[side + "_tile_rows"], plan[side + "_tile_features"]
-        assert cus != 256 or gg_schedule.launched(counts, d, f, side == "up", *tile, cus=cus).small == w, side
+    tiles = moe.moe_expert_ffn_tiles(counts, d, f, path=moe.MOE_FFN_GROUPED)
+    small = [t["feature_tiles"] if t["rows"] == 160 else 0 for t in (tiles["up"], tiles["down"])]
+    assert torch.cuda.get_device_properties(0).multi_processor_count != 256 or small == want
 
     w1, w3, w2, xg = layer(E, d, f, N, 5100 + N)
     bounds = bounds_of(counts)
     off = torch.tensor(bounds, dtype=torch.int32, device="cuda")
-    W = moe.moe_weights_pack(w1, w3, w2)
+    W, scratch = moe.moe_weights_pack(w1, w3, w2), Scratch(N, E, d, f)
     bufs = []
     for _ in range(2):
         buf = torch.full((N + 16, d), float("nan"), device="cuda")
-        moe.moe_expert_ffn(W, xg, off, yg=buf[:N], path=moe.MOE_FFN_GROUPED)
+        moe.moe_expert_ffn(W, xg, off, workspace=scratch.ws, yg=buf[:N], path=moe.MOE_FFN_GROUPED)
         torch.cuda.synchronize()
         bufs.append(buf)
     assert bool(torch.isnan(bufs[0][N:]).all()), "a store behind the last row"
     assert torch.equal(bufs[0][:N], bufs[1][:N])
+    # the device went the way that the host's query says
+    assert scratch.pieces() == bool(tiles["up"]["pieces"] or tiles["down"]["pieces"])
     worst = worst_row(bufs[0], xg, bounds, w1, w3, w2)
     print(f"{name}: error {worst:.2e}")
     # 2-norm of a row: an h close to a rounding boundary of bf16 rounds the other way and moves by 2^-7 of itself at
@@ -118,6 +105,8 @@ FEW = [
     ([150] * 8, 1536, 16, False),   # ... and matrices that the last-level cache does not keep
     ([24] * 6, 1408, 32, True),     # tiles of 256 features, as wide as the narrow ones
     ([90] * 24, 1408, 32, False),
+    ([90] * 37, 1792, 64, True),    # a round of the launch's own tiles, and three of the next
+    ([60] * 37, 1792, 64, False),
 ]
 
 
@@ -129,11 +118,13 @@ def test_few_experts_in_use(rows, f, E, pieces):
     bounds = bounds_of(counts)
     W, scratch = moe.moe_weights_pack(w1, w3, w2), Scratch(N, E, d, f)
     buf = torch.full((N + 16, d), float("nan"), device="cuda")
+    tiles = moe.moe_expert_ffn_tiles(counts, d, f, path=moe.MOE_FFN_GROUPED)
     moe.moe_expert_ffn(W, xg, torch.tensor(bounds, dtype=torch.int32, device="cuda"), workspace=scratch.ws, yg=buf[:N],
                        path=moe.MOE_FFN_GROUPED)
     torch.cuda.synchronize()
     assert bool(torch.isnan(buf[N:]).all()), "a store behind the last row"
     assert worst_row(buf, xg, bounds, w1, w3, w2) <= 1e-2  # (as above)
+    assert scratch.pieces() == bool(tiles["up"]["pieces"]) and not tiles["down"]["pieces"]
     assert torch.cuda.get_device_properties(0).multi_processor_count != 256 or scratch.pieces() == pieces
     W.free()
 
@@ -143,8 +134,8 @@ def test_fewer_experts_than_a_token_has():
     import paper_2402_07033_amd as moe
     E, d, f, T, k = 8, 4096, 8192, 73, 2
     N = T * k
-    assert not gg_schedule.launched([N] + [0] * 7, d, f, True, 128, 512, least=k).fixup
-    assert gg_schedule.launched([N] + [0] * 7, d, f, True, 128, 512).pieces
+    assert not moe.moe_expert_ffn_tiles([N] + [0] * 7, d, f, k=k)["up"]["fixup"]
+    assert moe.moe_expert_ffn_tiles([N] + [0] * 7, d, f)["up"]["pieces"]
     w1, w3, w2, x = layer(E, d, f, T, 5400)
     bounds = bounds_of([0, 0, N, 0, 0, 0, 0, 0])
     W, perm = moe.moe_weights_pack(w1, w3, w2), torch.arange(N, dtype=torch.int32, device="cuda")

@@ -7,7 +7,7 @@ import torch
 
 import gg_schedule
 import moe_inputs as mi
-from gpu_util import max_rel, pack_layer, to_dev, to_host
+from gpu_util import Scratch, max_rel, pack_layer, to_dev, to_host
 from oracle import moe_oracle as orc
 
 pytestmark = pytest.mark.gpu
@@ -34,9 +34,10 @@ def test_grouped_unit_edges(name, d, f):
     import paper_2402_07033_amd as moe
     counts, tile = EDGES[name]
     E, N = len(counts), sum(counts)
-    plan = moe.moe_expert_ffn_plan(N, E, d, f, path=moe.MOE_FFN_GROUPED)
-    assert (plan["up_tile_rows"], plan["up_tile_features"]) == tile
-    assert (plan["down_tile_rows"], plan["down_tile_features"]) == tile
+    if name == "128 x 512" and f == 2560:
+        f = 1792  # (larger matrices have tiles of 160 rows there)
+    tiles = moe.moe_expert_ffn_tiles(counts, d, f, path=moe.MOE_FFN_GROUPED)
+    assert all((t["rows"], t["features"]) == tile for t in tiles.values())
     cfg = mi.small_config("units", 1, d, f, E, 1, 4000 + d + f, w_dtype=mi.BF16, x_dtype=mi.BF16)
     w1, w3, w2 = mi.make_weights(cfg, threads=8)
     xg = mi.f32_to_bf16_bits(mi.normal_f32(cfg.seed, 90, (N, d)))
@@ -44,13 +45,15 @@ def test_grouped_unit_edges(name, d, f):
     W = pack_layer(mi.LayerInputs(cfg, None, None, w1, w3, w2))
     guard = 16  # rows behind yg that no store may reach
     buf = torch.full((N + guard, d), float("nan"), device="cuda")
+    scratch = Scratch(N, E, d, f)
     out = []
     for _ in range(2):
-        moe.moe_expert_ffn(W, to_dev(xg), to_dev(offsets), yg=buf[:N], path=moe.MOE_FFN_GROUPED)
+        moe.moe_expert_ffn(W, to_dev(xg), to_dev(offsets), workspace=scratch.ws, yg=buf[:N], path=moe.MOE_FFN_GROUPED)
         torch.cuda.synchronize()
         out.append(to_host(buf).copy())
     assert np.isnan(out[0][N:]).all(), "a store behind the last row"
     assert (out[0][:N] == out[1][:N]).all()
+    assert scratch.pieces() == any(t["pieces"] for t in tiles.values())
     ref = orc.expert_ffn(mi.to_f64(xg), offsets, w1, w3, w2)
     assert np.isfinite(out[0][:N]).all() and max_rel(out[0][:N], ref) <= TOL_BF16
     W.free()
@@ -84,7 +87,8 @@ def test_mid_path_shapes(d, f, counts):
 # Several rounds of whole tiles per workgroup, then pieces: the operand requests of a tile's last
 # steps are the next tile's, and the waits of its first steps count the stores of the tile before,
 # so neighbours of different numbers of units matter.  The step loop exists per number of units and, for
-# tiles that are their expert's only one, with the weights past L2.
+# tiles that are their expert's only one, with the weights past L2.  64 steps in the long projection, and 136 with 128 x 512
+# tiles, which give way to those of 160 rows in shorter ones.
 ROUNDS = {
     # name: rows per expert (repeated), repeats, tile rows, features of the long projection, its (rounds, cut, turned)
     "256 x 256, several tiles": ([641, 64, 257, 190, 1, 385, 256, 513], 1, 256, 10240, (2, True, False)),
@@ -98,16 +102,21 @@ ROUNDS = {
     "192 x 256, turned": ([385, 193, 64, 128, 17, 130, 192, 65], 1, 192, 24576, (4, True, True)),
     "192 x 256, 8 rounds": ([385, 193, 64, 128, 17, 130, 192, 65], 2, 192, 24576, (8, True, True)),
     "128 x 512, several tiles": ([384, 300, 0, 0, 0, 17, 0, 0], 4, 128, 11264, (2, True, False)),
-    "128 x 512, nearly one tile each": ([129, 128, 64, 17, 1, 65, 100, 90], 4, 128, 7680, (2, True, False)),
-    "128 x 512, nearly one tile each, whole": ([129, 128, 64, 17, 1, 65, 100, 90], 4, 128, 10240, (2, False, False)),
+    "128 x 512, nearly one tile each": ([129, 128, 64, 17, 1, 65, 100, 90], 4, 128, 8704, (2, True, False)),
+    "128 x 512, nearly one tile each, whole": ([129, 128, 64, 17, 1, 65, 100, 90], 4, 128, 13824, (3, False, False)),
     "128 x 512, turned": ([300, 0, 17, 129, 64, 1, 200, 30], 2, 128, 24576, (4, True, True)),
-    "128 x 512, 8 rounds": ([300, 0, 17, 129, 64, 1, 200, 30], 4, 128, 24576, (8, True, True)),
+    "128 x 512, 8 rounds": ([300, 0, 17, 129, 64, 1, 200, 30], 4, 128, 25600, (8, True, True)),
 }
+
+
+def short_side(tile_rows):
+    return 4352 if tile_rows == 128 else 2048
 
 
 def long_branch(name, up, cus=256):
     counts, repeats, tile_rows, long, _ = ROUNDS[name]
-    return gg_schedule.branch(counts * repeats, tile_rows, 512 if tile_rows == 128 else 256, long, 64, up, cus)
+    return gg_schedule.branch(counts * repeats, tile_rows, 512 if tile_rows == 128 else 256, long,
+                              short_side(tile_rows) // 32, up, cus)
 
 
 @pytest.mark.parametrize("long_side", ["f", "d"])  # many tiles in the first / second projection
@@ -117,11 +126,12 @@ def test_rounds_of_whole_tiles_and_pieces(name, long_side):
     counts, repeats, tile_rows, long, want = ROUNDS[name]
     counts = counts * repeats
     E, N = len(counts), sum(counts)
-    d, f = (2048, long // 2) if long_side == "f" else (long, 2048)   # 64 steps in the long projection
+    short = short_side(tile_rows)
+    d, f = (short, long // 2) if long_side == "f" else (long, short)
     features = 512 if tile_rows == 128 else 256
-    plan = moe.moe_expert_ffn_plan(N, E, d, f, path=moe.MOE_FFN_GROUPED)
-    assert (plan["up_tile_rows"], plan["up_tile_features"]) == (tile_rows, features)
-    assert (plan["down_tile_rows"], plan["down_tile_features"]) == (tile_rows, features)
+    tiles = moe.moe_expert_ffn_tiles(counts, d, f, path=moe.MOE_FFN_GROUPED)
+    t = tiles["up" if long_side == "f" else "down"]
+    assert (t["rows"], t["features"], bool(t["pieces"])) == (tile_rows, features, want[1])
     b = long_branch(name, long_side == "f", torch.cuda.get_device_properties(0).multi_processor_count)
     assert (b.rounds, b.cut, b.turned) == want and b.left > 0 and len(b.once | b.shared) > 1
 
@@ -135,11 +145,12 @@ def test_rounds_of_whole_tiles_and_pieces(name, long_side):
     for n in counts:
         bounds.append(bounds[-1] + n)
     off = torch.tensor(bounds, dtype=torch.int32, device="cuda")
-    W = moe.moe_weights_pack(w1, w3, w2)
+    W, scratch = moe.moe_weights_pack(w1, w3, w2), Scratch(N, E, d, f)
     buf = torch.full((N + 16, d), float("nan"), device="cuda")
-    moe.moe_expert_ffn(W, xg, off, yg=buf[:N], path=moe.MOE_FFN_GROUPED)
+    moe.moe_expert_ffn(W, xg, off, workspace=scratch.ws, yg=buf[:N], path=moe.MOE_FFN_GROUPED)
     torch.cuda.synchronize()
     assert bool(torch.isnan(buf[N:]).all()), "a store behind the last row"
+    assert scratch.pieces() == any(t["pieces"] for t in tiles.values())
     # every row in 64 bits, h rounded to bf16 as the kernels do
     worst = 0.0
     for e in range(E):

@@ -7,6 +7,7 @@ import tempfile
 import pytest
 
 import gg_schedule
+import paper_2402_07033_amd as moe
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = r"""
@@ -114,17 +115,24 @@ FEW = [
     ((4096, 1408, 64), [90] * 24, 10), ((4096, 1408, 64), [90] * 47, 0), ((4096, 1408, 64), [40] * 44, 0)]
 
 
+def first(counts, d, f, k=1):
+    return moe.moe_expert_ffn_tiles(counts, d, f, path=moe.MOE_FFN_GROUPED, k=k)["up"]
+
+
+def small(t):
+    return t["feature_tiles"] if t["rows"] == 160 else 0
+
+
 @pytest.mark.parametrize("shape,rows,want", FEW)
 def test_first_projection_of_few_experts(shape, rows, want):
     d, f, E = shape
     counts = rows + [0] * (E - len(rows))
-    own = (128, 512) if f % 256 == 0 else (256, 256)
-    got = gg_schedule.launched(counts, d, f, True, *own)
-    assert got.both and got.small == want
-    assert got.fixup or not got.pieces
+    got = first(counts, d, f)
+    assert small(got) == want
+    assert got["fixup"] or not got["pieces"]
     # what the launch's own tiles are cut into needs the fix-up, whatever is known of the experts in use
-    told = gg_schedule.launched(counts, d, f, True, *own, least=len(rows))
-    assert told.small == want and (told.pieces == got.pieces or (own[0] == 256 and d // 32 == 64))
+    told = first(counts, d, f, k=min(len(rows), 8))
+    assert small(told) == want and (told["pieces"] == got["pieces"] or (f % 256 and d // 32 == 64))
 
 
 def test_first_projection_in_as_many_rounds_of_its_own_tiles():
@@ -132,8 +140,8 @@ def test_first_projection_in_as_many_rounds_of_its_own_tiles():
     rows = [194, 169, 147, 108, 95, 81, 50, 49, 45, 32, 34, 21, 21, 16, 14, 9, 14, 10, 13, 6, 5, 6, 6, 6, 2, 5, 6, 6, 4, 4,
             2, 5, 1, 2, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1]
     d, f, E = SIXTYFOUR
-    assert gg_schedule.launched(rows + [0] * (E - len(rows)), d, f, True, 256, 256).small == 0
-    assert gg_schedule.launched(rows + [1] * 6 + [0] * 12, d, f, True, 256, 256).small == 9  # three rounds
+    assert small(first(rows + [0] * (E - len(rows)), d, f)) == 0
+    assert small(first(rows + [1] * 6 + [0] * 12, d, f)) == 9  # three rounds
 
 
 @pytest.mark.parametrize("d,f,E", [MIXTRAL, SIXTEEN, SIXTYFOUR, (2048, 1792, 32), (4096, 1408, 64)])
@@ -163,5 +171,5 @@ def test_no_fixup_no_verdict_for_it(d, f, E, least):
     ([128] * 12, 10), ([90] * 24, 10)])
 def test_second_projection_too_short_to_cut(rows, want):
     d, f, E = SIXTYFOUR
-    got = gg_schedule.launched(rows + [0] * (E - len(rows)), d, f, False, 128, 512)
-    assert got.both and got.small == want and not got.fixup
+    got = moe.moe_expert_ffn_tiles(rows + [0] * (E - len(rows)), d, f, path=moe.MOE_FFN_GROUPED)["down"]
+    assert small(got) == want and not got["fixup"]
