@@ -231,11 +231,12 @@ int moe_combine(const float* yg, const int32_t* inv_perm, const float* weights, 
 
 /*
  * The four calls of the hot path -- moe_route, moe_permute, moe_expert_ffn_path, moe_combine -- one after
- * the other, for callers to whom a call into the library costs more than a launch.  Arguments, checks,
- * launches and results are those of the four calls: logits [T,E], x [T,d] of x_dtype, N = T*k rows; the
+ * the other, for callers to whom a call into the library costs more than a launch.  Arguments, checks
+ * and results are those of the four calls: logits [T,E], x [T,d] of x_dtype, N = T*k rows; the
  * experts are W's, so d is W's row length and E at most W's number of experts (MOE_ERR_INVALID_ARG
  * otherwise; experts beyond E get no tokens).  The arguments of all four are checked before the first
- * launch.  *stage: HOST out, the call that returned the status (0 .. 3).
+ * launch.  For a few tokens whose logits and rows no output overlaps, routing and batching are one launch.
+ * *stage: HOST out, the call that returned the status (0 .. 3; 0 for that one launch).
  */
 int moe_layer(const moe_weights_t* W, const void* x, moe_dtype_t x_dtype, int d, const float* logits, int T,
               int E, int k, int path, int32_t* idx, float* weights, int32_t* counts, int32_t* offsets,
