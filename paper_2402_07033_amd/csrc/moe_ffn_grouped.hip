@@ -38,11 +38,13 @@
 //   * token fragments (B) are shared by the 4 waves through a ring of NS LDS stages filled by
 //     direct-to-LDS loads (no staging registers, no LDS stores); every wave reads the fragments
 //     of the next step while it issues the matrix instructions of the current one (one register
-//     set, refilled in place right after its last use).
+//     set, refilled in place right after its last use; half a set in tiles of ten blocks, which read
+//     the step's own second half, too).
 //   * the requests of a step are spread between the matrix instructions, one barrier per two
 //     steps publishes the next stages (the order of the ring: moe_gg_ring.h).  They are buffer loads:
 //     an address is a descriptor, the lane offset and one scalar, where 64-bit pointers per request
-//     filled the scalar registers (65..229 spills, 45..64 now); 55 other instructions stand beside the
+//     filled the scalar registers (65..229 spills; 46..61 now and 94..140 in the kernels of two tile shapes, hardly
+//     any of them in a step loop); 55 other instructions stand beside the
 //     64 matrix instructions of a full step, 61 with pointers, one between two of them where it can be.
 //   * the workgroup is persistent (one per CU) and the two load streams run across tile
 //     boundaries: while the last steps of a tile are multiplied, the first stages of the next
@@ -74,9 +76,9 @@
 //   192 x 16 (192 tokens x 256 features): 97..176 and 233..256 rows;
 //   128 x 32 (128 tokens x 512 features): up to 96 rows -- twice the weight bytes per step,
 //           which is what bounds such experts;
-//   160 x 4..32 (up to 160 tokens x 64..512 features; "small experts"): in place of any of them where the offsets show
-//           that no expert has more than 160 rows, and in place of the 128 x 512 one wherever it fills the rounds better,
-//           decided on the device (gg_small_tiles in moe_gg_sched.h).  The weight stream
+//   160 x 12..32 (up to 160 tokens x 192..512 features; "small experts"): in place of any of them where the offsets show
+//           that no expert has more than 160 rows, and up to 96 rows wherever it fills the rounds better, decided on the device
+//           (gg_small_tiles in moe_gg_sched.h).  The weight stream
 //           bounds such launches.  A step moves a tile's weights W and its token rows t (mostly L2 hits) through one CU, and
 //           its time follows W + t / 2 (KiB: 16 + 8 for 128 rows of the 192 x 256 tile, 32 + 8 here), until HBM is full at
 //           6.5 TB/s; a round that is not full leaves bandwidth unused, so the tiles' width is cut to fill it.  First
@@ -242,7 +244,7 @@ __device__ __forceinline__ bool gg_decode_tile_tab(const int (*tab)[64], int lan
     return true;
 }
 
-// The tile's fragment rows.  FLEX: the expert's groups of 4 rows dealt evenly to its NT tiles, 1..8 for each; wave w
+// The tile's fragment rows.  FLEX: the expert's groups of 4 rows dealt evenly to its NT tiles, 3..8 for each; wave w
 // holds groups w and w + 4.
 template <int FRW, bool FLEX>
 __device__ __forceinline__ void gg_feature_rows(int FR, int NT, TileInfo& ti) {
@@ -402,7 +404,7 @@ __device__ __forceinline__ unsigned gg_h_off(int lane) {
 // MODE: which units of work this copy of the loop covers: 0 = whole tiles and pieces, 1 = whole tiles
 // only, 2 = pieces only.
 // NBW x FRW: token blocks of the tile, at most, x fragment rows of a wave.
-// FLEX: feature tiles of 1..8 groups of rows (gg_feature_rows); of a group that is not there a wave requests and
+// FLEX: feature tiles of 3..8 groups of rows (gg_feature_rows); of a group that is not there a wave requests and
 // stores nothing.
 template <bool UP, int NBW, int FRW, bool FLEX, int MODE, int U, int LA, int NS>
 __device__ __forceinline__ void gg_gemm_body(const GroupedArgs& a, int NT, int total, int split_limit, bool turned,

@@ -7,7 +7,9 @@
 //   2. meets the other waves at a barrier, if k is even,
 //   3. requests its shares of stage k + GG_AHEAD into ring slot (k + GG_AHEAD) % NS,
 //   4. multiplies with the fragments of stage k and reads those of stage k + 1; the reads are
-//      waited for in step k + 1, fragment by fragment.
+//      waited for in step k + 1, fragment by fragment.  A tile of ten blocks has registers for
+//      half a step's fragments: in step k it reads the second half of stage k and the first of
+//      stage k + 1.
 // So a wave's reads of stage s have returned when it ends step s, and no earlier.
 #pragma once
 

@@ -61,7 +61,7 @@ GG_FN GgSched gg_sched(int total, int wgs, int xcd, int KS, int split) {
     sc.split = left * 32 <= W * split && (W - left) * KS >= W * GG_SPLIT_MIN_STEPS;
     return sc;
 }
-// Feature tiles per expert for n_tok token tiles of up to 160 rows (N rows in all) and 1 .. 8 groups of 4 fragment
+// Feature tiles per expert for n_tok token tiles of up to 160 rows (N rows in all) and 3 .. 8 groups of 4 fragment
 // rows, all left whole: the fewest where they fill their rounds, else as many as the rounds hold, which are narrower, of 3
 // groups and more.  0: the launch's own tiles, where cutting those of the last round is better (split: gg_split_limit).  Pieces of 160
 // x 512 themselves cost more to add up: second projection of 8 x 128 rows 176 + 17 us, 180 + 12 with pieces of 192 x 256; of
@@ -119,17 +119,17 @@ GG_FN bool gg_small_allowed(bool up, bool own_wide, int N, int E, bool larger) {
 }
 // Feature tiles per expert of the tiles of up to 160 rows, 0: the launch's own.  `active` experts with rows, in n_tok token tiles of 160
 // rows or own_tok of the launch's, which have own_NT feature tiles per expert.
-// only_wide (own tiles of 256 features): only for fewer rounds.  64 experts of f = 1408, own -> 160 rows, both one round 12 x 90 rows 40 ->
-// 44 us, 20 x 90 49 -> 51, 6 x 300 36 -> 54; both two, 200 tokens, Zipf 1.2, 98 -> 100..102, 44 x 40 92 -> 97; two and one 24 x 90 69 + 5 -> 61,
-// 36 x 90 89 + 5 -> 81; three and two 64 x 28 128 + 5 -> 121.
+// only_wide (own tiles of 256 features): only for fewer rounds.  64 experts of f = 1408, own -> 160 rows, both one round 12 x 90
+// rows 40 -> 44 us, 20 x 90 49 -> 51, 6 x 300 36 -> 54; both two, 200 tokens, Zipf 1.2, 98 -> 100..102, 44 x 40 92 -> 97; two and
+// one 24 x 90 69 + 5 -> 61, 36 x 90 89 + 5 -> 81; three and two 64 x 28 128 + 5 -> 121.
 // Where an expert has more of the launch's token tiles than of these, these are ahead whatever is idle (cut -> narrowed, 128 steps: 1
 // x 160 rows of f = 14336 112 -> 92, 5 x 150 303 -> 264, 2 x 150 of f = 6400 106 -> 91) unless the last-level cache keeps the matrices of
 // the experts in use and the launch's tiles are one round: two tiles of 5 blocks end before one of 10 does.  64 steps, own -> 160 rows: 2 x
 // 150 rows of f = 8192 (134 MB) 47 -> 57, 4 x 150 (268 MB) 73 -> 66; 4, 8, 10 x 150 of f = 1792 (59, 117, 147 MB) 36, 44, 45 -> 51, 53,
 // 54, 16 (235 MB) 69 -> 64; 128 steps, 1 x 150 of f = 6400 (105 MB) 42 -> 89.
-// Reductions too short to cut, whatever the size of the matrices: 44 steps, 64 experts in the layer, own -> 160 rows: 12 x 150 rows 36 -> 43,
-// 28 x 150 42 -> 53, 30 x 150 49 -> 54, 32 x 150 58 -> 56; 4 x 150 and 30 x 20 44 -> 54; 160 and 60 x 30 63 -> 75; in two rounds, 40 x
-// 130 89 -> 70.
+// Reductions too short to cut, whatever the size of the matrices: 44 steps, 64 experts in the layer, own -> 160 rows: 12 x 150 rows
+// 36 -> 43, 28 x 150 42 -> 53, 30 x 150 49 -> 54, 32 x 150 58 -> 56; 4 x 150 and 30 x 20 44 -> 54; 160 and 60 x 30 63 -> 75; in two
+// rounds, 40 x 130 89 -> 70.
 GG_FN int gg_small_tiles(bool up, int N, int E, int active, int n_tok, int own_tok, int own_NT, int FR, int wgs, int KS, int split,
                          bool only_wide) {
     if (KS < GG_SPLIT_KS && own_tok > n_tok && own_tok * own_NT <= wgs * 8) return 0;
@@ -143,9 +143,9 @@ GG_FN int gg_small_tiles(bool up, int N, int E, int active, int n_tok, int own_t
 }
 // HOST: is the projection run with the kernel that holds the tiles of 160 rows, too?  If they are to be expected with all experts in
 // use; the other's tiles end without spills (77 tokens, second projection 151 us, 153 with the other body beside it).
-// GG_UP_MAX_STEPS: of the first projection's longer reductions, narrowed -> own: 192 steps, 8 experts of f = 8192 with 20..90 rows 397 -> 394
-// and 445 -> 438 (both projections), 5 of them 349 -> 301, skewed 501 -> 512; 256 steps 896 -> 875, 973 -> 935, skewed 1069 -> 1061:
-// not taken for the skewed ones.
+// GG_UP_MAX_STEPS: both projections, own -> 160 rows in the first one with more steps: 192 steps, 8 experts of f = 8192 with 20 and 90
+// rows 397 -> 394, 445 -> 438, 5 of them with 90 349 -> 301, skewed 501 -> 512; 256 steps, f = 14336 896 -> 875, 973 -> 935, skewed
+// 1069 -> 1061.  Not taken for the skewed ones of 192 steps.
 #define GG_UP_MAX_STEPS 128
 GG_FN bool gg_small_expected(bool up, bool own_wide, int N, int E, int FR, int KS, int wgs) {
     if (N > GG_SMALL_ROWS * E || (long long)E * FR * KS < GG_SMALL_MIN_FRAGS) return false;

@@ -394,8 +394,9 @@ int moe_permute_launch(const int32_t* idx, int T, int E, int k, const void* x, i
 // Routing and batching of a few slots in one launch, for moe_layer: every workgroup routes all tokens (G lanes each) and
 // places all slots for itself, writes its own tokens' idx and weights and copies their rows; workgroup 0 writes the
 // batch's indices.  Same values as the two calls.  Launches and latency are everything at these sizes (the host
-// issues them more slowly than they run): all-fp32 layer of 16 tokens, d = 256, f = 512, 8 experts, call after call 38.6 -> 30.2
-// us with four launches for five.  The limit is what one wave can place (8 groups of 64 slots), a token per CU.
+// issues them more slowly than they run): all-fp32 layer of 16 tokens, d = 256, f = 512, 8 experts, call after call 36.2..37.1
+// -> 31.4..34.1 us by the host's speed, with four launches for five.  The limit is what one wave can place (8 groups of 64
+// slots), a token per CU.
 #define RP_MAX_SLOTS 512
 template <int G>
 __global__ __launch_bounds__(PM_THREADS) void route_permute_kernel(

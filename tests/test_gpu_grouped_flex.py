@@ -1,4 +1,5 @@
-"""Grouped GEMM's tiles of up to 160 rows x 4..32 fragment rows (csrc/moe_gg_sched.h, gg_flex) at the edges of their token blocks, full and narrowed rounds, both sides of the rule, and the row count beside the line."""
+"""Grouped GEMM's tiles of up to 160 rows x 12..32 fragment rows (csrc/moe_gg_sched.h, gg_small_tiles) at the edges of their token
+blocks, full and narrowed rounds, both sides of the rule, and the row count beside the line."""
 import pytest
 import torch
 
