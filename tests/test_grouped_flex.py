@@ -146,7 +146,7 @@ def test_first_projection_in_as_many_rounds_of_its_own_tiles():
 
 @pytest.mark.parametrize("d,f,E", [MIXTRAL, SIXTEEN, SIXTYFOUR, (2048, 1792, 32), (4096, 1408, 64)])
 @pytest.mark.parametrize("least", [1, 2, 6])
-def test_no_fixup_no_verdict_for_it(d, f, E, least):
+def test_no_fixup_where_pieces_are_ruled_out(d, f, E, least):
     """Where no fix-up is launched, no number of token tiles is one that the rule would rather cut."""
     L, KS, FR, wgs = gg_schedule.lib(), d // 32, f // 8, 32
     wide = f % 256 == 0
